@@ -581,11 +581,11 @@ __global__ void __launch_bounds__(TPC_BLOCK) rs_pack(RsBatch Bt) {
 }
 
 // ---------------------------------------------------------------------------
-// Decoder.  rd_head parses and checks the header, rd_table builds the
-// cumulative frequencies and a per-slot table (symbol, frequency, slot minus
-// the symbol's cumulative start), rd_decode runs each block forwards with one
-// wavefront: the lanes whose state drops below 2^16 take the next words in
-// lane order (ballot rank), which is the order the encoder stored them.
+// Decoder.  rd_table parses and checks the header and builds the cumulative
+// frequencies, rd_slots the slot tables, rd_decode runs each block forwards
+// with one wavefront: the lanes whose state drops below 2^16 take the next
+// words in lane order (ballot rank), which is the order the encoder stored
+// them.
 
 struct RdArgs {
     const uint8_t *in;
@@ -598,8 +598,22 @@ struct RdArgs {
     uint32_t *freq;       // [TPC_RANS_MAX_RANGE] the table, expanded
     uint32_t *vals;       // [RD_MAX_TABLE] the table's varints
     uint32_t *cum;        // [TPC_RANS_MAX_RANGE + 1]
-    uint4 *slot;          // [2^16]
+    uint4 *slot;          // [2^16] per slot (symbol, frequency, slot minus the symbol's cumulative
+                          // start), for tables that do not fit the LDS; else:
+    uint16_t *slot_sym;   // [RD_SLOT_LDS] (the same memory) the symbol of each slot
+    uint32_t *sym_fc;     // [RD_SYM_LDS] per symbol (f - 1) << 16 | cumulative start
 };
+
+// Slot tables of up to 2^14 slots over a range of up to 2^13 symbols are
+// decoded from LDS (2 bytes a slot and 4 a symbol: 64 KB, two workgroups of
+// 16 wavefronts per CU, all 32 its SIMDs hold); beyond that one 16-byte
+// entry per slot is gathered from L2.  The host does not know L and R (they
+// are in the stream), so one kernel holds both.
+#define RD_SLOT_LDS (1 << 14)
+#define RD_SYM_LDS (1 << 13)
+#define RD_T 1024              // threads of a decoding workgroup
+#define RD_CHUNK 128           // words a wavefront loads at once (4 bytes per lane)
+__device__ inline bool rd_in_lds(int64_t L, int64_t R) { return (1ll << L) <= RD_SLOT_LDS && R <= RD_SYM_LDS; }
 
 __device__ inline uint32_t get32(const uint8_t *p) { return *reinterpret_cast<const uint32_t *>(p); }
 
@@ -608,8 +622,8 @@ __device__ inline uint32_t get32(const uint8_t *p) { return *reinterpret_cast<co
 #define RD_MAX_TABLE (6 * 65536)
 __device__ inline int64_t table_bound(int64_t R) { return 6 * (R < 65536 ? R : 65536); }
 
-__global__ void rd_head(RdArgs A) {
-    if (threadIdx.x != 0) return;
+// Header fields into A.hd (one thread).
+__device__ inline void rd_header(const RdArgs &A) {
     int st = TPC_OK;
     int64_t n = 0, lo = 0, R = 0, L = 0, B = 0, nb = 0, head = 0;
     int64_t T = 0;
@@ -639,10 +653,19 @@ __global__ void rd_head(RdArgs A) {
 // varint is at most 3 bytes), then the (run, f - 1) pairs placed by a scan
 // of run + 1, then the cumulative frequencies.  Malformed tables (a varint
 // too long or cut off, an odd number of varints, a symbol past the range,
-// f above 2^L, frequencies not summing to 2^L) are refused.
+// f above 2^L, frequencies not summing to 2^L) are refused.  Before it the
+// header; after it the outputs *n_out and *dev_status are what a decoding
+// without a malformed block leaves (rd_decode overwrites the status).
 __global__ void __launch_bounds__(TPC_BLOCK) rd_table(RdArgs A) {
     __shared__ int sh[TPC_BLOCK / TPC_WAVE];
     __shared__ int bad;
+    if (threadIdx.x == 0) {
+        rd_header(A);
+        *A.n_out = A.hd[0];
+        *A.dev_status = (int32_t)A.hd[7];
+    }
+    __threadfence_block();
+    __syncthreads();
     if (A.hd[7] != TPC_OK) return;
     const int64_t R = A.hd[2], L = A.hd[3], T = A.hd[8];
     const uint32_t M = 1u << L;
@@ -711,75 +734,142 @@ __global__ void __launch_bounds__(TPC_BLOCK) rd_table(RdArgs A) {
     __syncthreads();
     if (threadIdx.x == 0) {
         A.cum[R] = csum <= M ? (uint32_t)csum : M;
-        if (bad || (A.hd[0] > 0 && csum != M)) A.hd[7] = TPC_ERR_ARG;
+        if (bad || (A.hd[0] > 0 && csum != M)) {
+            A.hd[7] = TPC_ERR_ARG;
+            *A.dev_status = TPC_ERR_ARG;
+        }
     }
 }
 
-// Slot table: grid over symbols, each thread fills its symbol's slots.
+// Slot tables: each wavefront takes 64 symbols at a time and fills the slots
+// of the present ones together, one after another (a thread per symbol
+// wrote a frequent symbol's hundreds of slots alone: 30 against 5 us for
+// 2^14 slots over 130 symbols).
 __global__ void __launch_bounds__(TPC_BLOCK) rd_slots(RdArgs A) {
     if (A.hd[7] != TPC_OK) return;
-    const int64_t R = A.hd[2];
-    const uint32_t *f = A.freq;
-    for (int64_t s = (int64_t)blockIdx.x * TPC_BLOCK + threadIdx.x; s < R; s += (int64_t)gridDim.x * TPC_BLOCK) {
-        const uint32_t c = A.cum[s], fs = f[s];
-        for (uint32_t q = 0; q < fs && c + q < (1u << 16); ++q) A.slot[c + q] = make_uint4((uint32_t)s, fs, q, 0u);
+    const int64_t L = A.hd[3], R = A.hd[2];
+    const bool lds = rd_in_lds(L, R);
+    const int lane = threadIdx.x & (TPC_WAVE - 1);
+    const int64_t w0 = (int64_t)blockIdx.x * (TPC_BLOCK / TPC_WAVE) + threadIdx.x / TPC_WAVE;
+    const int64_t W = (int64_t)gridDim.x * (TPC_BLOCK / TPC_WAVE);
+    for (int64_t s0 = w0 * TPC_WAVE; s0 < R; s0 += W * TPC_WAVE) {
+        const int64_t s = s0 + lane;
+        const uint32_t f = s < R ? A.freq[s] : 0u, c = s < R ? A.cum[s] : 0u;
+        if (lds && f) A.sym_fc[s] = ((f - 1u) << 16) | c;
+        for (unsigned long long m = __ballot(f > 0u); m; m &= m - 1ull) {
+            const int k = __ffsll(m) - 1;
+            const uint32_t fs = __shfl(f, k, TPC_WAVE), cs = __shfl(c, k, TPC_WAVE);
+            const uint32_t sk = (uint32_t)(s0 + k);
+            for (uint32_t q = lane; q < fs && cs + q < (1u << L); q += TPC_WAVE) {
+                if (lds) A.slot_sym[cs + q] = (uint16_t)sk;
+                else A.slot[cs + q] = make_uint4(sk, fs, q, 0u);
+            }
+        }
     }
 }
 
-__global__ void __launch_bounds__(TPC_BLOCK) rd_decode(RdArgs A) {
-    __shared__ int failed;
-    if (A.hd[7] != TPC_OK) return;                         // uniform over the grid
-    const int64_t n = A.hd[0], lo = A.hd[1], R = A.hd[2], B = A.hd[4], nb = A.hd[5], head = A.hd[6];
+__device__ inline uint32_t lanes_below(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+struct RdLds {
+    uint16_t slot_sym[RD_SLOT_LDS];
+    uint32_t sym_fc[RD_SYM_LDS];
+    uint32_t ring[RD_T / TPC_WAVE][RD_CHUNK];        // two chunks of words per wavefront
+};
+
+// Two words (one per half) at 2 i of the word area, zeros past its end.
+__device__ inline uint32_t word_pair(const uint16_t *words, uint64_t n_words, uint64_t i) {
+    if (2 * i + 1 < n_words) return reinterpret_cast<const uint32_t *>(words)[i];
+    return 2 * i < n_words ? (uint32_t)words[2 * i] : 0u;
+}
+
+// Block b by one wavefront.  A round's chain is state -> slot -> symbol ->
+// (f, start) -> state -> word; the block's words come through a ring of two
+// chunks of 128 in LDS, filled from a register that holds the chunk after
+// them (loaded a chunk, about five rounds, ahead), so the chain waits on LDS
+// only.  Returns whether the block decodes back to the coders' start states
+// using all its words.
+template <bool LDS>
+__device__ inline bool decode_block(const RdArgs &A, const RdLds &S, uint32_t *ring, int64_t b, int lane) {
+    const int64_t n = A.hd[0], B = A.hd[4], nb = A.hd[5], head = A.hd[6];
+    const uint32_t lo = (uint32_t)A.hd[1];
     const int L = (int)A.hd[3];
     const uint32_t mask_M = (1u << L) - 1u;
-    const uint8_t *base = A.in + RS_HEAD + ((A.hd[8] + 3) & ~(int64_t)3);
-    const uint32_t *ws = reinterpret_cast<const uint32_t *>(base);
-    const uint32_t *sts = ws + nb + 1;
+    const uint32_t *ws = reinterpret_cast<const uint32_t *>(A.in + RS_HEAD + ((A.hd[8] + 3) & ~(int64_t)3));
     const uint16_t *words = reinterpret_cast<const uint16_t *>(A.in + head);
     const uint64_t n_words = (A.size - (uint64_t)head) / 2;
-    const int lane = threadIdx.x & (TPC_WAVE - 1);
-    if (threadIdx.x == 0) failed = 0;
-    __syncthreads();
-    const int64_t W = (int64_t)gridDim.x * (TPC_BLOCK / TPC_WAVE);
-    for (int64_t b = (int64_t)blockIdx.x * (TPC_BLOCK / TPC_WAVE) + threadIdx.x / TPC_WAVE; b < nb; b += W) {
-        const int64_t i0 = b * B, i1 = i0 + B < n ? i0 + B : n;
-        uint32_t x = sts[b * RS_LANES + lane];
-        uint64_t w = ws[b], w_end = ws[b + 1];
-        bool ok = w <= w_end && w_end <= n_words;
-        const int64_t rounds = (i1 - i0 + RS_LANES - 1) / RS_LANES;
-        for (int64_t j = 0; j < rounds && ok; ++j) {
-            const int64_t i = i0 + j * RS_LANES + lane;
-            const bool act = i < i1;
-            const uint32_t sl = x & mask_M;
-            const uint4 e = act ? A.slot[sl] : make_uint4(0u, 1u, 0u, 0u);
-            if (act) {
-                A.out[i] = (int32_t)(lo + (int64_t)e.x);
-                x = e.y * (x >> L) + e.z;
-            }
-            const bool need = act && x < (1u << 16);
-            const unsigned long long m = __ballot(need);
-            const uint32_t cnt = (uint32_t)__popcll(m);
-            if (w + cnt > w_end) {
-                ok = false;
-                break;
-            }
-            if (need) {
-                const uint32_t rank = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-                x = (x << 16) | words[w + rank];
-            }
-            w += cnt;
+    const int64_t i0 = b * B, i1 = i0 + B < n ? i0 + B : n;
+    uint32_t x = (ws + nb + 1)[b * RS_LANES + lane];
+    uint32_t w = ws[b];
+    const uint32_t w_end = ws[b + 1];
+    if (w > w_end || w_end > n_words) return false;
+    uint32_t q = w / RD_CHUNK;                              // chunks q, q + 1 in the ring
+    ring[(q & 1) * TPC_WAVE + lane] = word_pair(words, n_words, (uint64_t)q * TPC_WAVE + lane);
+    ring[((q + 1) & 1) * TPC_WAVE + lane] = word_pair(words, n_words, (uint64_t)(q + 1) * TPC_WAVE + lane);
+    uint32_t next = word_pair(words, n_words, (uint64_t)(q + 2) * TPC_WAVE + lane);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int32_t *out = A.out + i0 + lane;
+    const int rounds = (int)((i1 - i0 + RS_LANES - 1) / RS_LANES);
+    for (int j = 0; j < rounds; ++j) {
+        const bool act = i0 + (int64_t)j * RS_LANES + lane < i1;
+        const uint32_t sl = x & mask_M;
+        uint32_t s, f, d;
+        if (LDS) {
+            s = S.slot_sym[sl];
+            const uint32_t e = S.sym_fc[s];
+            f = (e >> 16) + 1u;
+            d = sl - (e & 0xffffu);
+        } else {
+            const uint4 e = A.slot[sl];
+            s = e.x;
+            f = e.y;
+            d = e.z;
         }
-        // a block decodes back to the coders' start states, using all its words
-        if (!ok || w != w_end || __ballot(x != (1u << 16)) != 0ull) failed = 1;
+        if (act) {
+            out[j * RS_LANES] = (int32_t)(lo + s);
+            x = f * (x >> L) + d;
+        }
+        const bool need = act && x < (1u << 16);
+        const unsigned long long m = __ballot(need);
+        const uint32_t at = w + lanes_below(m);
+        w += (uint32_t)__popcll(m);
+        if (w > w_end) return false;
+        if (need) x = (x << 16) | ((ring[(at >> 1) & (RD_CHUNK - 1)] >> (16 * (at & 1))) & 0xffffu);
+        if (w / RD_CHUNK != q) {                            // chunk q is used up (64 words a round at most)
+            ring[(q & 1) * TPC_WAVE + lane] = next;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            ++q;
+            next = word_pair(words, n_words, (uint64_t)(q + 2) * TPC_WAVE + lane);
+        }
     }
-    __syncthreads();
-    if (threadIdx.x == 0 && failed) A.hd[7] = TPC_ERR_ARG;
+    return w == w_end && __ballot(x != (1u << 16)) == 0ull;
 }
 
-__global__ void rd_done(RdArgs A) {
-    if (threadIdx.x == 0) {
-        *A.n_out = A.hd[0];
-        *A.dev_status = (int32_t)A.hd[7];
+// Bound by VALU issue (about 25 instructions per round, eight wavefronts per
+// SIMD) and by HBM: 2^28 symbols (L = 14, 130 symbols, blocks of 2^15) took
+// 1.28 ms with a 16-byte gather from L2 and a 2-byte word load on each
+// round's chain, 0.30 ms (4.2 TB/s of stream and symbols) with both in LDS;
+// the whole call 1.31 -> 0.35 ms.
+__global__ void __launch_bounds__(RD_T, 8) rd_decode(RdArgs A) {
+    __shared__ RdLds S;
+    if (A.hd[7] != TPC_OK) return;                         // uniform over the grid
+    const int64_t L = A.hd[3], R = A.hd[2], nb = A.hd[5];
+    const bool lds = rd_in_lds(L, R);
+    const int lane = threadIdx.x & (TPC_WAVE - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / TPC_WAVE);
+    const int64_t b0 = (int64_t)blockIdx.x * (RD_T / TPC_WAVE);
+    if (b0 >= nb) return;
+    if (lds) {
+        for (int k = threadIdx.x; k < (1 << L); k += RD_T) S.slot_sym[k] = A.slot_sym[k];
+        for (int k = threadIdx.x; k < R; k += RD_T) S.sym_fc[k] = A.sym_fc[k];
+        __syncthreads();
+    }
+    const int64_t W = (int64_t)gridDim.x * (RD_T / TPC_WAVE);
+    for (int64_t b = b0 + wid; b < nb; b += W) {
+        const bool ok = lds ? decode_block<true>(A, S, S.ring[wid], b, lane)
+                            : decode_block<false>(A, S, S.ring[wid], b, lane);
+        if (!ok && lane == 0) *A.dev_status = TPC_ERR_ARG;
     }
 }
 
@@ -891,13 +981,15 @@ hipError_t launch_rans_decode(const void *in, uint64_t size, int32_t *out, int64
     A.vals = w.take<uint32_t>(RD_MAX_TABLE);
     A.cum = w.take<uint32_t>(TPC_RANS_MAX_RANGE + 1);
     A.slot = w.take<uint4>(1 << 16);
-    hipLaunchKernelGGL(rd_head, dim3(1), dim3(TPC_WAVE), 0, st, A);
+    A.slot_sym = reinterpret_cast<uint16_t *>(A.slot);
+    A.sym_fc = reinterpret_cast<uint32_t *>(A.slot_sym + RD_SLOT_LDS);
     hipLaunchKernelGGL(rd_table, dim3(1), dim3(TPC_BLOCK), 0, st, A);
-    hipLaunchKernelGGL(rd_slots, dim3(64), dim3(TPC_BLOCK), 0, st, A);
+    hipLaunchKernelGGL(rd_slots, dim3(256), dim3(TPC_BLOCK), 0, st, A);
+    // a wavefront per coding block (at least 64 symbols each), two
+    // workgroups per CU at most
     const int64_t blocks_max = cap > 0 ? (cap + RS_LANES - 1) / RS_LANES : 1;
-    int g = (int)((blocks_max + TPC_BLOCK / TPC_WAVE - 1) / (TPC_BLOCK / TPC_WAVE));
-    g = g < 1 ? 1 : (g > 4096 ? 4096 : g);
-    hipLaunchKernelGGL(rd_decode, dim3(g), dim3(TPC_BLOCK), 0, st, A);
-    hipLaunchKernelGGL(rd_done, dim3(1), dim3(TPC_WAVE), 0, st, A);
+    int64_t g = (blocks_max + RD_T / TPC_WAVE - 1) / (RD_T / TPC_WAVE);
+    g = g < 1 ? 1 : (g > 512 ? 512 : g);
+    hipLaunchKernelGGL(rd_decode, dim3((unsigned)g), dim3(RD_T), 0, st, A);
     return hipGetLastError();
 }

@@ -158,6 +158,24 @@ def test_decoder_round_trips(torch_dev):
     np.testing.assert_array_equal(got, x)
 
 
+@pytest.mark.parametrize("L,D,B,n", [
+    (14, 8192, 64, 64 * 129 + 5),        # the largest table decoded from LDS, one-round blocks
+    (14, 8193, 4096, 70_001),            # one symbol past it
+    (15, 300, 4096, 70_001),             # slots past it
+    (14, 2, 1 << 15, (1 << 16) + 1),     # hardly any words, a block of one symbol
+    (13, 8192, 1 << 15, 1 << 17),        # every coder takes a word nearly every round
+    (16, 65536, 8192, 300_000)])
+def test_decoder_tables_and_word_ring(torch_dev, L, D, B, n):
+    rng = np.random.default_rng(L * 31 + D)
+    x = rng.integers(-D // 2, D - D // 2, n).astype(np.int32)
+    x[0], x[-1] = -D // 2, D - D // 2 - 1
+    s = oracle.rans_encode(x, L, B)
+    print("[rans] decode L=%d D=%d B=%d n=%d" % (L, D, B, n), flush=True)
+    got, m, st = _decode(s, n)
+    assert st == 0 and m == n
+    np.testing.assert_array_equal(got, x)
+
+
 def test_decoder_refuses_bad_streams(torch_dev):
     x = np.random.default_rng(22).integers(0, 40, 50_000).astype(np.int32)
     s = oracle.rans_encode(x, 12, 4096)

@@ -99,16 +99,12 @@ __host__ __device__ inline double sqrt_pos(double x, double *inv) {
 #endif
 }
 
-// asin(u)/u and its derivative away from 0 (|u| >= 0.05: a step that turns
-// the track by more than ~6 degrees).  Out of line: rarely taken, and the
+// asin(u)/u away from 0 (|u| >= 0.05: a step that turns the track by more
+// than ~6 degrees).  Out of line: rarely taken, and the
 // library asin would otherwise occupy registers in the filter loop.
 __host__ __device__ __attribute__((noinline)) inline double asin_over_far(double u) {
     return asin(u) / u;
 }
-__host__ __device__ __attribute__((noinline)) inline double asin_over_d_far(double u) {
-    return (u / sqrt((1.0 - u) * (1.0 + u)) - asin(u)) / (u * u);
-}
-
 // asin(u)/u in the state precision (Taylor series to u^8 near 0)
 template <class R>
 __host__ __device__ inline R asin_over_r(R u) {
@@ -119,16 +115,6 @@ __host__ __device__ inline R asin_over_r(R u) {
     return (R)asin_over_far((double)u);
 }
 
-// first derivative of asin(u)/u in the state precision
-template <class R>
-__host__ __device__ inline R asin_over_d_r(R u) {
-    if (fabs(u) < (R)0.05) {
-        const R u2 = u * u;
-        return u * ((R)1 / 3 + u2 * ((R)3 / 10 + u2 * ((R)15 / 56 + u2 * ((R)35 / 144))));
-    }
-    return (R)asin_over_d_far((double)u);
-}
-
 // Exact helix step from x to x + dx, state and Jacobian in precision R
 // (double in the library: on gfx950 the FP64 vector FMA issues at the rate
 // of the non-packed FP32 one, so a single-precision Jacobian would only add
@@ -137,45 +123,57 @@ __host__ __device__ inline R asin_over_d_r(R u) {
 // filter loop free of branches), so p and J are then meaningless.
 // The plane distance dx and kbz = -c Bz come in precision K: single in the
 // fit (adjacent planes), double where steps cross several planes.
+//
+// The filters are bound by this step's instructions (one wavefront per SIMD,
+// every instruction of the chain counts), so it is written with few of them.
+// With s' = s + kappa dx, cosines c, c', T = (s + s')/(c + c') and
+// B = c + s T (= c' + s' T), the turned angle delta has sin delta =
+// s'c - s c' = kappa dx B, so the path is dx B asin(v)/v with v = sin delta
+// (no chord length), and the partial derivatives are
+//   dT/ds = B/(c c'),            dT/dkappa = dx B / ((c + c') c'),
+//   darc/ds = (1/c' - 1/c)/kappa = dx T/(c c'),
+//   darc/dkappa = dx s dT/dkappa / cos delta + (dx B)^2 g'(v),
+// g = asin(v)/v, 1/cos delta = g + v g'.  Turns of |v| >= 0.05 (and beyond 90
+// degrees, where v falls again) take the half angle u = sin(delta/2) =
+// kappa chord/2 and darc/dkappa = (dx/c' - arc)/kappa.
 template <class R, class K = float>
 __host__ __device__ inline bool helix_step(R p[5], K dx, K kbz, float max_sin, StepJac &J) {
     // kbz = -c Bz, so kappa = kbz * w
-    const R s = p[2], t = p[3], w = p[4];
-    const R kap = (R)kbz * w;
-    const R s2 = s + kap * (R)dx;
+    const R s = p[2], t = p[3], w = p[4], d = (R)dx, kb = (R)kbz;
+    const R kap = kb * w, kd = kap * d;
+    const R s2 = s + kd;
     const bool ok = fabs(s) < (R)max_sin && fabs(s2) < (R)max_sin;
-    R ic1, ic2, isq;
-    const R c1 = sqrt_pos(((R)1 - s) * ((R)1 + s), &ic1);
-    const R c2 = sqrt_pos(((R)1 - s2) * ((R)1 + s2), &ic2);
+    R ic1, ic2;
+    const R c1 = sqrt_pos(fma(-s, s, (R)1), &ic1);
+    const R c2 = sqrt_pos(fma(-s2, s2, (R)1), &ic2);
     const R den = c1 + c2;
     const R iden = recip_pos(den);
-    const R A1 = s + s2;
-    const R T = A1 * iden;                        // tan of the chord direction
-    const R adx = fabs((R)dx);
-    const R sq = sqrt_pos((R)1 + T * T, &isq);
-    const R chord = adx * sq;
-    const R u = (R)0.5 * kap * chord;
-    const R sgn = dx >= (K)0 ? (R)1 : (R)-1;
-    const R arc = sgn * chord * asin_over_r(u);  // signed transverse path length
-    // Jacobian
-    const R iden2 = iden * iden;
-    const R dTs_p = (den + A1 * s * ic1) * iden2;
-    const R dTs2_p = (den + A1 * s2 * ic2) * iden2;
-    const R dT_ds = dTs_p + dTs2_p;
-    const R dT_dw = dTs2_p * (R)dx * (R)kbz;
-    R darc_dchord;                                // d(chord g(u))/dchord = 1/sqrt(1 - u^2)
-    sqrt_pos(((R)1 - u) * ((R)1 + u), &darc_dchord);
-    darc_dchord *= sgn;
-    const R darc_dkap = sgn * (R)0.5 * chord * chord * asin_over_d_r(u);
-    const R dchord_dT = adx * T * isq;
-    const R q = darc_dchord * dchord_dT;
-    J.f02 = (R)dx * dT_ds;
-    J.f04 = (R)dx * dT_dw;
-    J.f12 = t * q * dT_ds;
+    const R T = (s + s2) * iden;                  // tan of the chord direction
+    const R B = c1 + s * T;
+    const R dB = d * B, v = kd * B;
+    const R dTk = dB * iden * ic2;                // dT/dkappa
+    const R cc = ic1 * ic2;
+    R arc, dark;                                  // signed transverse path length, darc/dkappa
+    // (a turn of 90 degrees or more changes s by at least 1)
+    if (fabs(v) < (R)0.05 && fabs(kd) < (R)1) {
+        const R v2 = v * v;
+        const R g = (R)1 + v2 * ((R)1 / 6 + v2 * ((R)3 / 40 + v2 * ((R)5 / 112 + v2 * ((R)35 / 1152))));
+        const R gd = v * ((R)1 / 3 + v2 * ((R)3 / 10 + v2 * ((R)15 / 56 + v2 * ((R)35 / 144))));
+        arc = dB * g;
+        dark = d * s * dTk * (g + v * gd) + dB * dB * gd;
+    } else {
+        const R chord = fabs(d) * sqrt((R)1 + T * T);
+        const R u = (R)0.5 * kap * chord;
+        arc = (d >= (R)0 ? chord : -chord) * asin_over_r(u);
+        dark = (d * ic2 - arc) / kap;
+    }
+    J.f02 = dB * cc;
+    J.f04 = d * kb * dTk;
+    J.f12 = t * (d * T * cc);
     J.f13 = arc;
-    J.f14 = t * (q * dT_dw + darc_dkap * (R)kbz);
-    J.f24 = (R)dx * (R)kbz;
-    p[0] += (R)dx * T;
+    J.f14 = t * (kb * dark);
+    J.f24 = d * kb;
+    p[0] += d * T;
     p[1] += t * arc;
     p[2] = s2;
     return ok;
@@ -261,11 +259,20 @@ __host__ __device__ inline void sym_transport(SymT<R> &C, const StepJac &J) {
 // positive definite; everything is evaluated regardless, and p, C are then
 // meaningless); kalman_cov applies C -= K H C.  The filter loop runs the
 // covariance half of one step next to the helix step of the next, which
-// does not need it.  K and the rows H C are kept in a Gain.
+// does not need it.  Columns 0 and 1 of the updated covariance are K V, V =
+// diag(vy, vz): C - K (S - V) = K V there, one product instead of two
+// multiply-adds and no cancellation.  The other six entries need K and the
+// rows H C, kept in a Gain.
 template <class R>
 struct Gain {
-    R k00, k01, k10, k11, k20, k21, k30, k31, k40, k41;   // K
-    R r00, r01, r02, r03, r04, r11, r12, r13, r14;         // rows 0 and 1 of C
+    R k00, k10, k11, k20, k21, k30, k31, k40, k41;   // K (k01 = k10 vy / vz is not used)
+    R r02, r03, r04, r12, r13, r14;                   // rows 0 and 1 of C
+    // the gain that leaves diag(vy, vz, *, *, *) as it is
+    __host__ __device__ static Gain none() {
+        Gain g = {};
+        g.k00 = g.k11 = (R)1;
+        return g;
+    }
 };
 
 template <class R>
@@ -276,39 +283,40 @@ __host__ __device__ inline R kalman_gain(R p[5], const SymT<R> &C, R my, R mz, R
     const bool pd = det > (R)0;
     const R idet = recip_pos(det);
     const R i00 = S11 * idet, i01 = -S01 * idet, i11 = S00 * idet;
+    // p += C[:, 0:2] S^-1 r
+    const R a0 = i00 * r0 + i01 * r1, a1 = i01 * r0 + i11 * r1;
+    p[0] = p[0] + C.c00 * a0 + C.c10 * a1;
+    p[1] = p[1] + C.c10 * a0 + C.c11 * a1;
+    p[2] = p[2] + C.c20 * a0 + C.c21 * a1;
+    p[3] = p[3] + C.c30 * a0 + C.c31 * a1;
+    p[4] = p[4] + C.c40 * a0 + C.c41 * a1;
     // K = C[:, 0:2] S^-1
-    G.k00 = C.c00 * i00 + C.c10 * i01; G.k01 = C.c00 * i01 + C.c10 * i11;
+    G.k00 = C.c00 * i00 + C.c10 * i01;
     G.k10 = C.c10 * i00 + C.c11 * i01; G.k11 = C.c10 * i01 + C.c11 * i11;
     G.k20 = C.c20 * i00 + C.c21 * i01; G.k21 = C.c20 * i01 + C.c21 * i11;
     G.k30 = C.c30 * i00 + C.c31 * i01; G.k31 = C.c30 * i01 + C.c31 * i11;
     G.k40 = C.c40 * i00 + C.c41 * i01; G.k41 = C.c40 * i01 + C.c41 * i11;
-    // written as chains of multiply-adds (one rounding per term)
-    p[0] = p[0] + G.k00 * r0 + G.k01 * r1;
-    p[1] = p[1] + G.k10 * r0 + G.k11 * r1;
-    p[2] = p[2] + G.k20 * r0 + G.k21 * r1;
-    p[3] = p[3] + G.k30 * r0 + G.k31 * r1;
-    p[4] = p[4] + G.k40 * r0 + G.k41 * r1;
-    G.r00 = C.c00; G.r01 = C.c10; G.r02 = C.c20; G.r03 = C.c30; G.r04 = C.c40;
-    G.r11 = C.c11; G.r12 = C.c21; G.r13 = C.c31; G.r14 = C.c41;
-    const R chi = r0 * (i00 * r0 + i01 * r1) + r1 * (i01 * r0 + i11 * r1);
+    G.r02 = C.c20; G.r03 = C.c30; G.r04 = C.c40;
+    G.r12 = C.c21; G.r13 = C.c31; G.r14 = C.c41;
+    const R chi = r0 * a0 + r1 * a1;
     return pd ? chi : (R)-1;
 }
 
-// C -= K H C (a zero Gain leaves C exactly unchanged)
+// C -= K H C for the gain G of a measurement with variances vy, vz
 template <class R>
-__host__ __device__ inline void kalman_cov(SymT<R> &C, const Gain<R> &G) {
-    C.c00 = C.c00 - G.k00 * G.r00 - G.k01 * G.r01;
-    C.c10 = C.c10 - G.k10 * G.r00 - G.k11 * G.r01;
-    C.c11 = C.c11 - G.k10 * G.r01 - G.k11 * G.r11;
-    C.c20 = C.c20 - G.k20 * G.r00 - G.k21 * G.r01;
-    C.c21 = C.c21 - G.k20 * G.r01 - G.k21 * G.r11;
+__host__ __device__ inline void kalman_cov(SymT<R> &C, const Gain<R> &G, R vy, R vz) {
+    C.c00 = G.k00 * vy;
+    C.c10 = G.k10 * vy;
+    C.c11 = G.k11 * vz;
+    C.c20 = G.k20 * vy;
+    C.c21 = G.k21 * vz;
     C.c22 = C.c22 - G.k20 * G.r02 - G.k21 * G.r12;
-    C.c30 = C.c30 - G.k30 * G.r00 - G.k31 * G.r01;
-    C.c31 = C.c31 - G.k30 * G.r01 - G.k31 * G.r11;
+    C.c30 = G.k30 * vy;
+    C.c31 = G.k31 * vz;
     C.c32 = C.c32 - G.k30 * G.r02 - G.k31 * G.r12;
     C.c33 = C.c33 - G.k30 * G.r03 - G.k31 * G.r13;
-    C.c40 = C.c40 - G.k40 * G.r00 - G.k41 * G.r01;
-    C.c41 = C.c41 - G.k40 * G.r01 - G.k41 * G.r11;
+    C.c40 = G.k40 * vy;
+    C.c41 = G.k41 * vz;
     C.c42 = C.c42 - G.k40 * G.r02 - G.k41 * G.r12;
     C.c43 = C.c43 - G.k40 * G.r03 - G.k41 * G.r13;
     C.c44 = C.c44 - G.k40 * G.r04 - G.k41 * G.r14;
@@ -318,7 +326,7 @@ template <class R>
 __host__ __device__ inline R kalman_update(R p[5], SymT<R> &C, R my, R mz, R vy, R vz) {
     Gain<R> G;
     const R chi = kalman_gain(p, C, my, mz, vy, vz, G);
-    kalman_cov(C, G);
+    kalman_cov(C, G, vy, vz);
     return chi;
 }
 

@@ -151,7 +151,7 @@ fit_order_place(const int32_t *__restrict__ n_seeds, int32_t cap, const int32_t 
 }  // namespace
 
 // The length order of the seeds into ord (workspace); sets A.order.
-static void launch_fit_order(FitArgs &A, const FitOrderWs &ord, hipStream_t st) {
+void launch_fit_order(FitArgs &A, const FitOrderWs &ord, hipStream_t st) {
     int blocks = (A.cap_seeds + TPC_BLOCK - 1) / TPC_BLOCK;
     blocks = blocks < 1 ? 1 : (blocks > 1024 ? 1024 : blocks);
     hipLaunchKernelGGL(fit_order_clear, dim3(1), dim3(TPC_BLOCK), 0, st, ord.hist, ord.cur);
@@ -267,6 +267,14 @@ size_t chi2_ws_layout(void *ws, int64_t cap_seeds, double **part) {
     return (w.off + 255) & ~size_t(255);
 }
 
+FitOrderWs fit_order_carve(WsCarver &w, int64_t cap_seeds) {
+    int32_t *o = w.take<int32_t>(cap_seeds > 0 ? cap_seeds : 1);
+    int32_t *hi = w.take<int32_t>(TPC_MAX_ROWS + 1);
+    int32_t *cu = w.take<int32_t>(TPC_MAX_ROWS + 1);
+    int32_t *n = w.take<int32_t>(1);
+    return FitOrderWs{o, hi, cu, n};
+}
+
 // Fit workspace: the chi2 partials, the seed-ordered hit coordinates, then
 // the length order of the seeds.
 size_t fit_ws_layout(void *ws, int64_t cap_seeds, int64_t cap_hits, double **part, float2 **hyz,
@@ -276,11 +284,8 @@ size_t fit_ws_layout(void *ws, int64_t cap_seeds, int64_t cap_hits, double **par
     w.off = a;
     float2 *h = w.take<float2>(cap_hits > 0 ? cap_hits : 1);
     if (hyz) *hyz = h;
-    int32_t *o = w.take<int32_t>(cap_seeds > 0 ? cap_seeds : 1);
-    int32_t *hi = w.take<int32_t>(TPC_MAX_ROWS + 1);
-    int32_t *cu = w.take<int32_t>(TPC_MAX_ROWS + 1);
-    int32_t *n = w.take<int32_t>(1);
-    if (ord) *ord = FitOrderWs{o, hi, cu, n};
+    const FitOrderWs o = fit_order_carve(w, cap_seeds);
+    if (ord) *ord = o;
     return (w.off + 255) & ~size_t(255);
 }
 

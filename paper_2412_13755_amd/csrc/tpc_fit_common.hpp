@@ -259,5 +259,7 @@ __host__ __device__ inline void adj_one(const FitArgs &F, const int32_t *status,
 
 FitArgs make_fit_args(const tpc_context *ctx, const tpc_frames *fr, const tpc_seeds *sd,
                       const float *map);
+// The length order of the seeds into ord (workspace); sets A.order.
+void launch_fit_order(FitArgs &A, const FitOrderWs &ord, hipStream_t st);
 hipError_t launch_fit_args(const FitArgs &A, hipStream_t st, bool ordered = false, int block = 0,
                            int spt = 0);

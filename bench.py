@@ -315,14 +315,14 @@ def stage_events(reco, dfr, out, ws, steps):
 
 def fit_roofline(n_hits, n_seeds, fit_ms, traffic=None):
     """Roofline of tpc_kalman_fit (the length order of the seeds, four small
-    kernels, then fit_tracks_ordered, when the seeds carry their hit
+    kernels, then fit_tracks, when the seeds carry their hit
     coordinates) against the FP64 vector peak; fit_ms is the whole call."""
     flops = FLOP_FIT_PER_HIT * n_hits
     achieved = flops / (fit_ms * 1e-3) / 1e12
     nbytes = B_FIT_PER_HIT * n_hits + B_FIT_PER_TRACK * n_seeds
     return {"bound": "alu", "achieved": round(achieved, 4), "peak": VALU_PEAK_TFLOPS,
             "unit": "TFLOP/s", "frac": round(achieved / VALU_PEAK_TFLOPS, 5), "traffic": traffic,
-            "kernel": "tpc_kalman_fit (fit_order_* + fit_tracks_ordered)", "avg_ms": round(fit_ms, 5),
+            "kernel": "tpc_kalman_fit (fit_order_* + fit_tracks)", "avg_ms": round(fit_ms, 5),
             "algorithmic_flops": int(flops),
             "algorithmic_bytes": int(nbytes),
             "hbm_frac": round(nbytes / (fit_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 6)}

@@ -1,7 +1,7 @@
 // Kalman helix fit (gfx950): one thread per seed, state and covariance in
-// registers (covariance algebra in FP64, Jacobian in FP32; see
-// tpc_fit_math.hpp), exact helix steps with analytic Jacobians.  Hits of a
-// seed are read through their global cluster ids; row r of the seed is
+// registers (all FP64; see tpc_fit_math.hpp), exact helix steps with
+// analytic Jacobians.  Hits of a seed are read from the seed-ordered
+// coordinates; row r of the seed is
 // first_row + k, so x comes from an LDS copy of the row table and the map
 // correction from [sector][row].  Optionally writes filter-state checkpoints
 // every ckpt_rows updates for the adjoint.
@@ -9,9 +9,12 @@
 
 namespace {
 
+template <bool MAP, bool CKPT>
 __device__ inline void fit_all(const FitArgs &A) {
-    __shared__ float xs[TPC_MAX_ROWS];
+    __shared__ float xsl[TPC_MAX_ROWS + 1];
+    float *xs = xsl + 1;                              // fit_one reads one entry below
     for (int r = threadIdx.x; r < A.n_rows; r += blockDim.x) xs[r] = A.row_x[r];
+    if (threadIdx.x == 0) xsl[0] = 0.0f;
     __syncthreads();
     int T = *A.n_seeds;
     if (T > A.cap_seeds) T = A.cap_seeds;
@@ -24,22 +27,15 @@ __device__ inline void fit_all(const FitArgs &A) {
     // knob; results do not depend on it)
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < T; i += gridDim.x * blockDim.x) {
         const int s = A.order ? A.order[i] : i;
-        if ((uint32_t)s < (uint32_t)A.cap_seeds) fit_one(A, s, xs);
+        if ((uint32_t)s < (uint32_t)A.cap_seeds) fit_one<MAP, CKPT>(A, s, xs);
     }
 }
 
-// Seeds in seed order (the fit stage).
-__global__ void __launch_bounds__(TPC_BLOCK)
-fit_tracks(FitArgs A) {
-    fit_all(A);
-}
-
-// The fit in length order (the staged fit of many seeds, or after the
-// persistent kernel with sort_fit): the same code under its own name, so
-// profiles tell the launches apart.
-__global__ void __launch_bounds__(TPC_BLOCK)
-fit_tracks_ordered(FitArgs A) {
-    fit_all(A);
+// Seeds in seed order, or (A.order) in descending length: every staged fit
+// of many seeds and the fit after the persistent kernel with sort_fit.
+template <bool MAP, bool CKPT>
+__global__ void __launch_bounds__(TPC_BLOCK) fit_tracks(FitArgs A) {
+    fit_all<MAP, CKPT>(A);
 }
 
 // (y, z) of every seed hit in seed-hit order, so the fit reads each seed's
@@ -222,22 +218,22 @@ hipError_t launch_fit(const tpc_context *ctx, const tpc_frames *fr, const tpc_se
         launch_gather(fr, sd, hyz, st);
     }
     if (sd->cap_seeds >= TPC_FIT_ORDER_MIN) launch_fit_order(A, ord, st);
-    return launch_fit_args(A, st, A.order != nullptr, 0, 0);
+    return launch_fit_args(A, st);
 }
 
 // Launch shape of the fit: workgroups of `block` threads (0: TPC_BLOCK) and
 // about `spt` seeds per thread (0: one) over the seed capacity.
-hipError_t launch_fit_args(const FitArgs &A, hipStream_t st, bool ordered, int block, int spt) {
+hipError_t launch_fit_args(const FitArgs &A, hipStream_t st, int block, int spt) {
     const int b = block > 0 ? block : TPC_BLOCK;
     const int64_t per = (int64_t)b * (spt > 0 ? spt : 1);
     int64_t blocks = ((int64_t)A.cap_seeds + per - 1) / per;
     const int64_t maxb = (int64_t)8192 * TPC_BLOCK / b;
     if (blocks > maxb) blocks = maxb;
     if (blocks < 1) blocks = 1;
-    if (ordered)
-        hipLaunchKernelGGL(fit_tracks_ordered, dim3((unsigned)blocks), dim3(b), 0, st, A);
-    else
-        hipLaunchKernelGGL(fit_tracks, dim3((unsigned)blocks), dim3(b), 0, st, A);
+    const dim3 g((unsigned)blocks), t(b);
+    if (A.ckpt) hipLaunchKernelGGL((fit_tracks<true, true>), g, t, 0, st, A);
+    else if (A.map) hipLaunchKernelGGL((fit_tracks<true, false>), g, t, 0, st, A);
+    else hipLaunchKernelGGL((fit_tracks<false, false>), g, t, 0, st, A);
     return hipGetLastError();
 }
 
@@ -256,7 +252,7 @@ hipError_t launch_fit_shaped(const tpc_context *ctx, const tpc_frames *fr, const
         launch_gather(fr, sd, hyz, st);
     }
     if (sd->cap_seeds >= TPC_FIT_ORDER_MIN) launch_fit_order(A, ord, st);
-    return launch_fit_args(A, st, A.order != nullptr, block, spt);
+    return launch_fit_args(A, st, block, spt);
 }
 
 size_t chi2_ws_layout(void *ws, int64_t cap_seeds, double **part) {

@@ -52,12 +52,12 @@ __host__ __device__ inline float2 hit_raw(const FitArgs &A, const SeedView &v, i
     return make_float2(A.y[j], A.z[j]);
 }
 
-// Corrected measurement of hit k in double precision.
-__host__ __device__ inline void hit_fix(const FitArgs &A, const SeedView &v, int k, float2 raw,
-                                        double &my, double &mz) {
+// Corrected measurement of hit k in double precision (MAP: with a map).
+template <bool MAP = true>
+__host__ __device__ inline void hit_fix(const SeedView &v, int k, float2 raw, double &my, double &mz) {
     my = (double)raw.x;
     mz = (double)raw.y;
-    if (v.mp) {
+    if (MAP && v.mp) {
         my -= (double)v.mp[(v.row0 + k) * 2];
         mz -= (double)v.mp[(v.row0 + k) * 2 + 1];
     }
@@ -65,7 +65,7 @@ __host__ __device__ inline void hit_fix(const FitArgs &A, const SeedView &v, int
 
 __host__ __device__ inline void hit_meas(const FitArgs &A, const SeedView &v, int k, int32_t id, double &my,
                                          double &mz) {
-    hit_fix(A, v, k, hit_raw(A, v, k, id), my, mz);
+    hit_fix(v, k, hit_raw(A, v, k, id), my, mz);
 }
 
 __host__ __device__ inline bool start_state(const FitArgs &A, const SeedView &v, const float *xs, double p[5]) {
@@ -101,7 +101,14 @@ __host__ __device__ inline void read_ckpt(const double *ck, double p[5], SymT<do
     C.c40 = ck[15]; C.c41 = ck[16]; C.c42 = ck[17]; C.c43 = ck[18]; C.c44 = ck[19];
 }
 
-// Forward fit of seed i (one thread's work); xs = row table.
+// Forward fit of seed i (one thread's work); xs = row table, readable one
+// entry below its start.  A.hyz is set.  CKPT: filter states to A.ckpt.
+//
+// Bound by instructions: a wavefront alone on its SIMD issues one about
+// every five clocks whatever it is, so the loop carries no test that a
+// template argument or the step before can decide, and ends by one
+// condition (what the last step left is sorted out after it).
+template <bool MAP, bool CKPT>
 __host__ __device__ inline void fit_one(const FitArgs &A, int i, const float *xs) {
     SeedView sv = seed_view(A, i);
     double p[5] = {0, 0, 0, 0, 0};
@@ -115,46 +122,54 @@ __host__ __device__ inline void fit_one(const FitArgs &A, int i, const float *xs
     C.c22 = A.var_s;
     C.c33 = A.var_t;
     C.c44 = A.var_w;
-    double *ck = A.ckpt ? A.ckpt + (size_t)ckpt_slot(sv.o0, i, A.ckpt_rows) * TPC_CKPT_WORDS : nullptr;
     if (status == TPC_FIT_OK) {
-        if (ck) write_ckpt(ck, p, C);
+        double *ck = CKPT ? A.ckpt + (size_t)ckpt_slot(sv.o0, i, A.ckpt_rows) * TPC_CKPT_WORDS : nullptr;
+        int left = A.ckpt_rows;                       // updates until the next checkpoint
+        if (CKPT) write_ckpt(ck, p, C);
+        int k = sv.n - 2;
         // Each hit is read one step ahead, into the register its predecessor
         // has just been consumed from (no copy at the loop edge, so the load
         // is waited for only at its use a whole step later).
-        float2 raw = hit_raw(A, sv, sv.n - 2, A.hyz ? 0 : sv.hh[sv.n - 2]);
-        float xk = xs[sv.row0 + sv.n - 2];            // plane of hit k
+        const float2 *hp = A.hyz + sv.o0 + k;
+        float2 raw = *hp;
+        const float *xp = xs + sv.row0 + k;
+        float xk = *xp, xl = xcur;                    // planes of hit k and of the hit before it
         // the covariance half of each update is applied at the next step,
         // beside its helix step (before the first update G leaves the start
         // covariance as it is)
         Gain<double> G = Gain<double>::none();
-        for (int k = sv.n - 2, j = 1; k >= 0; --k, ++j) {
+        bool stepped, good;
+        do {
             double my, mz;
-            hit_fix(A, sv, k, raw, my, mz);
-            const float xnext = k > 0 ? xs[sv.row0 + k - 1] : 0.0f;
-            if (k > 0) raw = hit_raw(A, sv, k - 1, A.hyz ? 0 : sv.hh[k - 1]);
-            // one exit test per step: the step and the update are evaluated
-            // unconditionally and a failed track's final state is not used
+            hit_fix<MAP>(sv, k, raw, my, mz);
+            hp -= k > 0;
+            raw = *hp;
             kalman_cov(C, G, A.vy, A.vz);
             StepJac J;
-            const bool stepped = helix_step(p, xk - xcur, A.kbz, A.max_sin, J);
+            stepped = helix_step(p, xk - xl, A.kbz, A.max_sin, J);
+            xcur = xl;
+            xl = xk;
+            xk = *--xp;                               // below the seed after its last hit, then unused
             sym_transport<double, false>(C, J);
             const double dchi = kalman_gain<double>(p, C, my, mz, A.vy, A.vz, G);
             chi2 += dchi;
+            // evaluated to the end whatever happens: a failed track's final
+            // state is not used
             const double chk = chi2 + p[0] + p[1] + p[2] + p[3] + p[4];
-            if (!stepped || !(dchi >= 0.0) || !(chk - chk == 0.0)) {   // non-finite state too
-                status = stepped ? TPC_FIT_NUM_FAIL : TPC_FIT_SIN_FAIL;
-                break;
-            }
-            xcur = xk;
-            xk = xnext;
-            // state after j updates opens segment j / K of the adjoint
-            if (ck && j % A.ckpt_rows == 0 && k > 0) {
+            good = (int)stepped & (int)(dchi >= 0.0) & (int)(chk - chk == 0.0);   // non-finite state too
+            --k;
+            // state after j updates opens segment j / ckpt_rows of the adjoint
+            if (CKPT && --left == 0 && good && k >= 0) {
+                left = A.ckpt_rows;
+                ck += TPC_CKPT_WORDS;
                 SymT<double> Cj = C;
                 kalman_cov(Cj, G, A.vy, A.vz);
-                write_ckpt(ck + (size_t)(j / A.ckpt_rows) * TPC_CKPT_WORDS, p, Cj);
+                write_ckpt(ck, p, Cj);
             }
-        }
+        } while ((int)good & (int)(k >= 0));
         kalman_cov(C, G, A.vy, A.vz);                 // the last update's covariance half
+        if (good) xcur = xl;
+        else status = stepped ? TPC_FIT_NUM_FAIL : TPC_FIT_SIN_FAIL;
     }
     A.out.x[i] = xcur;
     float *po = A.out.par + (size_t)i * 5;
@@ -261,5 +276,4 @@ FitArgs make_fit_args(const tpc_context *ctx, const tpc_frames *fr, const tpc_se
                       const float *map);
 // The length order of the seeds into ord (workspace); sets A.order.
 void launch_fit_order(FitArgs &A, const FitOrderWs &ord, hipStream_t st);
-hipError_t launch_fit_args(const FitArgs &A, hipStream_t st, bool ordered = false, int block = 0,
-                           int spt = 0);
+hipError_t launch_fit_args(const FitArgs &A, hipStream_t st, int block = 0, int spt = 0);

@@ -250,7 +250,7 @@ __device__ inline void fit_ms_one(const MsArgs &A, int i, const float *xs) {
         if (ROWS && A.rows_out) A.rows_out[sv.o0 + sv.n - 1] = (int16_t)ra;
         for (int k = sv.n - 2; k >= 0; --k) {
             double my, mz;
-            hit_fix(F, sv, k, raw, my, mz);
+            hit_fix<false>(sv, k, raw, my, mz);
             if (k > 0) raw = hit_raw(F, sv, k - 1, F.hyz ? 0 : sv.hh[k - 1]);
             int32_t nid = 0, v1 = INT32_MAX, v2 = INT32_MAX;
             if (ROWS) {

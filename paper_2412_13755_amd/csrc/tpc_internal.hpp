@@ -75,12 +75,16 @@ struct CaWs {
 size_t nb_ws_layout(void *ws, int64_t N, int64_t NR, NbWs *out);
 size_t ca_ws_layout(void *ws, int64_t N, int64_t NR, CaWs *out);
 size_t chi2_ws_layout(void *ws, int64_t cap_seeds, double **part);
-// Length order of the seeds for the fit: order[cap_seeds], the per-length
-// bin starts and cursors, the number of ordered seeds.  Fits of at least
-// TPC_FIT_ORDER_MIN seed slots run in that order.
+// Length order of the seeds for the fit: order[cap_seeds], the lengths
+// counted by each workgroup [TPC_ORDER_BLOCKS][TPC_ORDER_LENS], the number
+// of ordered seeds.  Fits of at least TPC_FIT_ORDER_MIN seed slots run in
+// that order.
 struct FitOrderWs {
-    int32_t *order, *hist, *cur, *n;
+    int32_t *order, *hist, *n;
 };
+#define TPC_ORDER_BLOCKS 128
+#define TPC_ORDER_T 1024
+#define TPC_ORDER_LENS (TPC_MAX_ROWS + 1)
 #define TPC_FIT_ORDER_MIN 4096
 FitOrderWs fit_order_carve(WsCarver &w, int64_t cap_seeds);
 size_t fit_ws_layout(void *ws, int64_t cap_seeds, int64_t cap_hits, double **part, float2 **hyz,

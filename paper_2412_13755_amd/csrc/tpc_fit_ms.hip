@@ -45,11 +45,11 @@ namespace {
 struct MsArgs {
     FitArgs F;
     double kbz;            // -c Bz in double precision
-    double x0, mass2, cut;
+    double inv_x0, mass2, cut;
     bool scatter;          // x0 finite
     bool eloss;            // rho > 0
-    double mass, rho, zoa;         // energy loss: mass, density, Z/A,
-    double inv_mass2, me_over_m, inv_exc2;   // 1/m^2, m_e/m, 1/I^2
+    double mass, rho, kza;         // energy loss: mass, density, K Z/A (K = 0.307075 MeV cm^2/mol),
+    double inv_mass, inv_mass2, me_over_m, inv_exc2;   // 1/m, 1/m^2, m_e/m, 1/I^2
     uint8_t *rejected;     // [cap_hits] or null
     // fits over any rows
     const int32_t *row_offsets;   // cluster layout of the frames
@@ -62,21 +62,28 @@ struct MsArgs {
 
 // The segment of plane distance dx about to be crossed, seen from the
 // state p at the plane the step leaves: path ds = |dx| sqrt(1+t^2) /
-// sqrt(1-s^2), momentum P = sqrt(1+t^2)/|w|, energy E, beta^2 = P^2/E^2.
+// sqrt(1-s^2), momentum P = sqrt(1+t^2)/|w|, energy E.  Inverses are kept
+// instead of taken again (1/P^2 = w^2/(1+t^2), 1/beta^2 = E^2/P^2): no
+// division is left below.  Meaningless for w = 0, which its users leave out.
 struct Segment {
-    double ds, P, E, b2;
+    double ds, t2, it2;        // path; 1 + t^2 and its inverse
+    double P, P2, iP2, E, E2, iE;
 };
 
 __device__ inline Segment segment(const MsArgs &A, const double p[5], double dx) {
     const double s = p[2], t = p[3], w = p[4];
-    const double st = sqrt(1.0 + t * t);
     Segment g;
-    g.ds = fabs(dx) * st / sqrt(1.0 - s * s);
-    g.P = st / fabs(w);
-    const double P2 = g.P * g.P;
-    const double E2 = P2 + A.mass2;
-    g.E = sqrt(E2);
-    g.b2 = P2 / E2;
+    double ist, ics;
+    g.t2 = fma(t, t, 1.0);
+    const double st = sqrt_pos(g.t2, &ist);
+    sqrt_pos(fma(-s, s, 1.0), &ics);
+    g.ds = fabs(dx) * st * ics;
+    g.it2 = ist * ist;
+    g.P = st * recip_pos(fabs(w));
+    g.P2 = g.P * g.P;
+    g.iP2 = w * w * g.it2;
+    g.E2 = g.P2 + A.mass2;
+    g.E = sqrt_pos(g.E2, &g.iE);
     return g;
 }
 
@@ -86,15 +93,14 @@ __device__ inline Segment segment(const MsArgs &A, const double p[5], double dx)
 __device__ inline void add_scattering(const MsArgs &A, const double p[5], const Segment &g, SymT<double> &C) {
     const double s = p[2], t = p[3], w = p[4];
     if (!A.scatter || w == 0.0) return;
-    const double t2 = 1.0 + t * t;
-    const double xr = g.ds / A.x0;
+    const double xr = g.ds * A.inv_x0;
     const double f = 1.0 + 0.038 * (double)logf((float)xr);
-    const double k = 0.0136 * 0.0136 / (g.b2 * g.P * g.P);
-    const double th2 = k * xr * f * f;
-    C.c22 += th2 * (1.0 - s * s) * t2;
-    C.c33 += th2 * t2 * t2;
-    C.c43 += th2 * t * w * t2;
-    C.c44 += th2 * t * t * w * w;
+    const double th2 = 0.0136 * 0.0136 * (g.E2 * g.iP2 * g.iP2) * xr * f * f;
+    const double tt = th2 * g.t2, tw = th2 * t * w;
+    C.c22 += tt * fma(-s, s, 1.0);
+    C.c33 += tt * g.t2;
+    C.c43 += tw * g.t2;
+    C.c44 += tw * t * w;
 }
 
 // Energy-loss map of the segment (the particle moves outwards: dir = +1
@@ -115,23 +121,24 @@ __device__ inline bool eloss_map(const MsArgs &A, const double p[5], const Segme
     j44 = 1.0;
     vw = 0.0;
     if (w == 0.0) return false;
-    const double K = 0.307075e-3, me = 0.51099895e-3;
-    const double m = A.mass, P2 = g.P * g.P;
-    const double bg2 = P2 * A.inv_mass2, r = A.me_over_m;
-    const double W = 2.0 * me * bg2 / (1.0 + 2.0 * (g.E / m) * r + r * r);
-    const double L = (double)logf((float)(2.0 * me * bg2 * W * A.inv_exc2));
-    const double dedx = K * A.zoa / g.b2 * (0.5 * L - g.b2);
+    const double me = 0.51099895e-3;
+    const double m = A.mass, r = A.me_over_m;
+    const double mbg = 2.0 * me * A.inv_mass2 * g.P2;            // 2 m_e (beta gamma)^2
+    const double W = mbg * recip_pos(1.0 + 2.0 * A.inv_mass * g.E * r + r * r);
+    const double L = (double)logf((float)(mbg * W * A.inv_exc2));
+    const double dedx = A.kza * (0.5 * L * g.E2 * g.iP2 - 1.0);
     const double E1 = g.E + dir * (g.ds * A.rho * dedx);
     if (!(E1 > m)) return true;
-    const double P1 = sqrt(E1 * E1 - A.mass2);
+    double iP1;
+    const double P1 = sqrt_pos(fma(E1, E1, -A.mass2), &iP1);
     if (fabs(P1 - g.P) > 0.01 * g.P) return false;
-    const double q = g.P / P1, e = E1 / g.E;
+    iP1 = fma(iP1, fma(-P1, iP1, 1.0), iP1);                     // 1/P' to rounding, as it scales w
+    const double q = g.P * iP1, e = E1 * g.iE;
     wo = w * q;
     j44 = q * q * q * e;
-    const double t2 = 1.0 + t * t;
-    j43 = wo * t / t2 * (1.0 - e * q * q);
-    const double varE = K * A.zoa * A.rho * g.ds * me * (1.0 - 0.5 * g.b2) / (1.0 - g.b2);
-    const double dw = w * g.E / P2;
+    j43 = wo * t * g.it2 * (1.0 - e * q * q);
+    const double varE = A.kza * A.rho * g.ds * me * (1.0 - 0.5 * g.P2 * g.iE * g.iE) * (g.E2 * A.inv_mass2);
+    const double dw = w * g.E * g.iP2;
     vw = varE * dw * dw;
     return false;
 }
@@ -240,34 +247,41 @@ __device__ inline void fit_ms_one(const MsArgs &A, int i, const float *xs) {
         C.c44 = F.var_w;
     }
     if (status == TPC_FIT_OK) {
-        float2 raw = hit_raw(F, sv, sv.n - 2, F.hyz ? 0 : sv.hh[sv.n - 2]);
+        // Everything of a hit is read ahead: coordinates and, with ERRS, its
+        // error a step, its id (which the error and the row hang on) two.
+        // ROWS: the row of the next hit is resolved a step ahead too -- the
+        // row starts one and two rows below are loaded at the top of a step
+        // and compared after its helix step (a longer gap walks on); equal
+        // to walk_row, as seed_rows has checked every row.
+        const float2 *hp = F.hyz + sv.o0 + sv.n - 2;
+        float2 raw = *hp;
         int rk = ra;
-        // ROWS: the row of the next hit is resolved a step ahead -- the row
-        // starts one and two rows below are loaded at the top of a step and
-        // compared after its helix step (a longer gap walks on); equal to
-        // walk_row, as seed_rows has checked every row
-        int rnext = ROWS ? walk_row(ro, ra - 1, sv.hh[sv.n - 2]) : 0;
+        int32_t nid = ROWS ? sv.hh[sv.n - 2] : 0;                // id of the next hit
+        int rnext = ROWS ? walk_row(ro, ra - 1, nid) : 0;
+        float2 en = ERRS ? A.err[nid] : make_float2(0.f, 0.f);
+        if (ROWS && sv.n > 2) nid = sv.hh[sv.n - 3];
         if (ROWS && A.rows_out) A.rows_out[sv.o0 + sv.n - 1] = (int16_t)ra;
         for (int k = sv.n - 2; k >= 0; --k) {
             double my, mz;
             hit_fix<false>(sv, k, raw, my, mz);
-            if (k > 0) raw = hit_raw(F, sv, k - 1, F.hyz ? 0 : sv.hh[k - 1]);
-            int32_t nid = 0, v1 = INT32_MAX, v2 = INT32_MAX;
+            hp -= k > 0;
+            raw = *hp;
+            int32_t v1 = INT32_MAX, v2 = INT32_MAX, id = nid;    // id: of hit k - 1
             if (ROWS) {
                 rk = rnext;
                 if (A.rows_out) A.rows_out[sv.o0 + k] = (int16_t)rk;
                 if (k > 0) {
-                    nid = sv.hh[k - 1];
                     if (rk >= 1) v1 = ro[rk - 1];
                     if (rk >= 2) v2 = ro[rk - 2];
                 }
+                if (k > 1) nid = sv.hh[k - 2];
             } else {
                 rk = sv.row0 + k;
             }
             if (ERRS) {
-                const float2 e = A.err[sv.hh[k]];
-                vy = (double)e.x * (double)e.x;
-                vz = (double)e.y * (double)e.y;
+                vy = (double)en.x * (double)en.x;
+                vz = (double)en.y * (double)en.y;
+                if (k > 0) en = A.err[id];
             }
             const double xk = (double)xs[rk];
             const double dx = xk - xcur;
@@ -292,21 +306,21 @@ __device__ inline void fit_ms_one(const MsArgs &A, int i, const float *xs) {
             }
             sym_transport<double, false>(C, J);
             xcur = xk;
-            if (ROWS && k > 0) rnext = nid >= v1 ? rk - 1 : (nid >= v2 ? rk - 2 : walk_row(ro, rk - 3, nid));
-            // predicted-residual chi2 of the hit
-            const double r0 = my - p[0], r1 = mz - p[1];
-            const double S00 = C.c00 + vy, S01 = C.c10, S11 = C.c11 + vz;
-            const double det = S00 * S11 - S01 * S01;
-            const double chi = (r0 * (S11 * r0 - S01 * r1) + r1 * (S00 * r1 - S01 * r0)) / det;
-            // (a singular S is not a rejection: the update reports it)
-            if (det > 0.0 && chi > A.cut) {
+            if (ROWS && k > 0) rnext = id >= v1 ? rk - 1 : (id >= v2 ? rk - 2 : walk_row(ro, rk - 3, id));
+            // the update, unless the predicted-residual chi2 rejects the hit
+            // (a singular S is not a rejection: the update reports it, -1)
+            double pn[5] = {p[0], p[1], p[2], p[3], p[4]};
+            Gain<double> G;
+            const double dchi = kalman_gain<double>(pn, C, my, mz, vy, vz, G);
+            if (dchi > A.cut) {
                 if (A.rejected) A.rejected[sv.o0 + k] = 1;
                 continue;
             }
-            const double dchi = kalman_update<double>(p, C, my, mz, vy, vz);
+            kalman_cov(C, G, vy, vz);
+            for (int q = 0; q < 5; ++q) p[q] = pn[q];
             chi2 += dchi;
             const double chk = chi2 + p[0] + p[1] + p[2] + p[3] + p[4];
-            if (!(dchi >= 0.0) || !(chk - chk == 0.0)) {
+            if (!((int)(dchi >= 0.0) & (int)(chk - chk == 0.0))) {
                 status = TPC_FIT_NUM_FAIL;
                 break;
             }
@@ -327,14 +341,17 @@ __device__ inline void fit_ms_one(const MsArgs &A, int i, const float *xs) {
     F.out.status[i] = status;
 }
 
+// Workgroups of one wavefront: an event's seeds make fewer wavefronts than
+// there are SIMDs, and single ones spread over all CUs.
+#define MS_T TPC_WAVE
 template <bool ROWS, bool ERRS>
-__global__ void __launch_bounds__(TPC_BLOCK) fit_ms_tracks(MsArgs A) {
+__global__ void __launch_bounds__(MS_T) fit_ms_tracks(MsArgs A) {
     __shared__ float xs[TPC_MAX_ROWS];
-    for (int r = threadIdx.x; r < A.F.n_rows; r += TPC_BLOCK) xs[r] = A.F.row_x[r];
+    for (int r = threadIdx.x; r < A.F.n_rows; r += MS_T) xs[r] = A.F.row_x[r];
     __syncthreads();
     int T = *A.F.n_seeds;
     if (T > A.F.cap_seeds) T = A.F.cap_seeds;
-    for (int i = blockIdx.x * TPC_BLOCK + threadIdx.x; i < T; i += gridDim.x * TPC_BLOCK)
+    for (int i = blockIdx.x * MS_T + threadIdx.x; i < T; i += gridDim.x * MS_T)
         fit_ms_one<ROWS, ERRS>(A, i, xs);
 }
 
@@ -666,13 +683,13 @@ __device__ inline void smooth_one(const SmArgs &S, int i, const float *xs) {
 }
 
 template <bool ERRS>
-__global__ void __launch_bounds__(TPC_BLOCK) smooth_tracks(SmArgs S) {
+__global__ void __launch_bounds__(MS_T) smooth_tracks(SmArgs S) {
     __shared__ float xs[TPC_MAX_ROWS];
-    for (int r = threadIdx.x; r < S.M.F.n_rows; r += TPC_BLOCK) xs[r] = S.M.F.row_x[r];
+    for (int r = threadIdx.x; r < S.M.F.n_rows; r += MS_T) xs[r] = S.M.F.row_x[r];
     __syncthreads();
     int T = *S.M.F.n_seeds;
     if (T > S.M.F.cap_seeds) T = S.M.F.cap_seeds;
-    for (int i = blockIdx.x * TPC_BLOCK + threadIdx.x; i < T; i += gridDim.x * TPC_BLOCK)
+    for (int i = blockIdx.x * MS_T + threadIdx.x; i < T; i += gridDim.x * MS_T)
         smooth_one<ERRS>(S, i, xs);
 }
 
@@ -690,14 +707,15 @@ MsArgs make_ms_args(const tpc_context *ctx, const tpc_frames *fr, const tpc_seed
         (void)launch_gather(fr, sd, hyz, st);    // a launch error surfaces at the fit's launch
     }
     A.kbz = -0.00299792458 * (double)ctx->cfg.bz;
-    A.x0 = mat ? (double)mat->x0 : (double)INFINITY;
+    A.inv_x0 = mat ? 1.0 / (double)mat->x0 : 0.0;
     A.scatter = mat && mat->x0 < INFINITY;
     A.mass2 = mat ? (double)mat->mass * (double)mat->mass : 0.0;
     A.cut = mat ? (double)mat->chi2_cut : (double)INFINITY;
     A.eloss = mat && mat->rho > 0.f;
     A.mass = mat ? (double)mat->mass : 0.0;
     A.rho = mat ? (double)mat->rho : 0.0;
-    A.zoa = mat ? (double)mat->z_over_a : 0.0;
+    A.kza = mat ? 0.307075e-3 * (double)mat->z_over_a : 0.0;
+    A.inv_mass = A.eloss ? 1.0 / A.mass : 0.0;
     A.inv_mass2 = A.eloss ? 1.0 / A.mass2 : 0.0;
     A.me_over_m = A.eloss ? 0.51099895e-3 / A.mass : 0.0;
     A.inv_exc2 = A.eloss ? 1.0 / ((double)mat->mean_exc * (double)mat->mean_exc) : 0.0;
@@ -712,8 +730,8 @@ MsArgs make_ms_args(const tpc_context *ctx, const tpc_frames *fr, const tpc_seed
 }
 
 int fit_blocks(const tpc_seeds *sd) {
-    int blocks = (sd->cap_seeds + TPC_BLOCK - 1) / TPC_BLOCK;
-    if (blocks > 8192) blocks = 8192;
+    int blocks = (sd->cap_seeds + MS_T - 1) / MS_T;
+    if (blocks > 32768) blocks = 32768;
     if (blocks < 1) blocks = 1;
     return blocks;
 }
@@ -724,7 +742,7 @@ hipError_t launch_fit_material(const tpc_context *ctx, const tpc_frames *fr, con
                                const tpc_material *mat, const tpc_tracks *tr, uint8_t *rejected,
                                void *ws, hipStream_t st) {
     const MsArgs A = make_ms_args(ctx, fr, sd, mat, tr, rejected, ws, st);
-    hipLaunchKernelGGL((fit_ms_tracks<false, false>), dim3(fit_blocks(sd)), dim3(TPC_BLOCK), 0, st, A);
+    hipLaunchKernelGGL((fit_ms_tracks<false, false>), dim3(fit_blocks(sd)), dim3(MS_T), 0, st, A);
     return hipGetLastError();
 }
 
@@ -734,9 +752,9 @@ hipError_t launch_fit_rows(const tpc_context *ctx, const tpc_frames *fr, const t
     MsArgs A = make_ms_args(ctx, fr, sd, mat, tr, rejected, ws, st);
     A.err = reinterpret_cast<const float2 *>(err);
     if (err)
-        hipLaunchKernelGGL((fit_ms_tracks<true, true>), dim3(fit_blocks(sd)), dim3(TPC_BLOCK), 0, st, A);
+        hipLaunchKernelGGL((fit_ms_tracks<true, true>), dim3(fit_blocks(sd)), dim3(MS_T), 0, st, A);
     else
-        hipLaunchKernelGGL((fit_ms_tracks<true, false>), dim3(fit_blocks(sd)), dim3(TPC_BLOCK), 0, st, A);
+        hipLaunchKernelGGL((fit_ms_tracks<true, false>), dim3(fit_blocks(sd)), dim3(MS_T), 0, st, A);
     return hipGetLastError();
 }
 
@@ -764,11 +782,11 @@ hipError_t launch_smooth(const tpc_context *ctx, const tpc_frames *fr, const tpc
     S.hit_cov = hit_cov;
     const int blocks = fit_blocks(sd);
     if (err) {
-        hipLaunchKernelGGL((fit_ms_tracks<true, true>), dim3(blocks), dim3(TPC_BLOCK), 0, st, S.M);
-        hipLaunchKernelGGL((smooth_tracks<true>), dim3(blocks), dim3(TPC_BLOCK), 0, st, S);
+        hipLaunchKernelGGL((fit_ms_tracks<true, true>), dim3(blocks), dim3(MS_T), 0, st, S.M);
+        hipLaunchKernelGGL((smooth_tracks<true>), dim3(blocks), dim3(MS_T), 0, st, S);
     } else {
-        hipLaunchKernelGGL((fit_ms_tracks<true, false>), dim3(blocks), dim3(TPC_BLOCK), 0, st, S.M);
-        hipLaunchKernelGGL((smooth_tracks<false>), dim3(blocks), dim3(TPC_BLOCK), 0, st, S);
+        hipLaunchKernelGGL((fit_ms_tracks<true, false>), dim3(blocks), dim3(MS_T), 0, st, S.M);
+        hipLaunchKernelGGL((smooth_tracks<false>), dim3(blocks), dim3(MS_T), 0, st, S);
     }
     return hipGetLastError();
 }

@@ -262,10 +262,10 @@ FitOrderWs fit_order_carve(WsCarver &w, int64_t cap_seeds) {
     return FitOrderWs{o, h, n};
 }
 
-// Fit workspace: the chi2 partials, the seed-ordered hit coordinates, then
-// the length order of the seeds.
+// Fit workspace: the chi2 partials, the seed-ordered hit coordinates, the
+// length order of the seeds, then the seed-ordered hit errors.
 size_t fit_ws_layout(void *ws, int64_t cap_seeds, int64_t cap_hits, double **part, float2 **hyz,
-                     FitOrderWs *ord) {
+                     FitOrderWs *ord, float2 **herr) {
     const size_t a = chi2_ws_layout(ws, cap_seeds, part);
     WsCarver w(ws);
     w.off = a;
@@ -273,6 +273,8 @@ size_t fit_ws_layout(void *ws, int64_t cap_seeds, int64_t cap_hits, double **par
     if (hyz) *hyz = h;
     const FitOrderWs o = fit_order_carve(w, cap_seeds);
     if (ord) *ord = o;
+    float2 *e = w.take<float2>(cap_hits > 0 ? cap_hits : 1);
+    if (herr) *herr = e;
     return (w.off + 255) & ~size_t(255);
 }
 

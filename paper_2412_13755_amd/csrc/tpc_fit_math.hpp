@@ -141,7 +141,7 @@ __host__ __device__ inline bool helix_step(R p[5], K dx, K kbz, float max_sin, S
     // kbz = -c Bz, so kappa = kbz * w
     const R s = p[2], t = p[3], w = p[4], d = (R)dx, kb = (R)kbz;
     const R kap = kb * w, kd = kap * d;
-    const R s2 = s + kd;
+    const R s2 = fma(kap, d, s);
     const bool ok = fabs(s) < (R)max_sin && fabs(s2) < (R)max_sin;
     R ic1, ic2;
     const R c1 = sqrt_pos(fma(-s, s, (R)1), &ic1);

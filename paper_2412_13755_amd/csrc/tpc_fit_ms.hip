@@ -55,7 +55,7 @@ struct MsArgs {
     const int32_t *row_offsets;   // cluster layout of the frames
     const int32_t *frame;         // frame of each seed
     int32_t n_frames;
-    const float2 *err;            // per-cluster (sigma_y, sigma_z), cm
+    const float2 *err;            // (sigma_y, sigma_z) of every seed hit in seed-hit order, cm
     double *pfin;                 // [cap_seeds][5] final state in FP64, or null
     int16_t *rows_out;            // [cap_hits] row of every seed hit (ROWS), or null
 };
@@ -153,21 +153,28 @@ __device__ inline void eloss_cov(SymT<double> &C, double a, double b) {
     C.c44 = a * a * c33 + 2.0 * a * b * c43 + b * b * c44;
 }
 
-// Row of cluster id at or below row r_hi of a (frame, sector) whose R + 1
-// row offsets are ro: walking down from r_hi, the first row starting at or
-// before id; -1 if id is not in that row (it lies above r_hi, or below the
-// first row).
-__device__ inline int walk_row(const int32_t *ro, int r_hi, int32_t id) {
-    int r = r_hi;
-    while (r >= 0 && ro[r] > id) --r;
-    return (r >= 0 && id < ro[r + 1]) ? r : -1;
-}
+// Fits over rows: the pad rows of the seeds of one wavefront, row of hit k of
+// lane t at s[64 k + t] (four lanes share a bank: no conflicts), and the
+// row starts of two neighbouring (frame, sector)s.  Seeds come ordered by
+// (frame, sector), so those of a wavefront rarely need a third.
+struct RowLds {
+    uint8_t s[TPC_MAX_ROWS * TPC_WAVE];
+    int32_t start[2][TPC_MAX_ROWS + 1];
+};
 
-// Rows of the outermost, middle ((n-1)/2) and innermost hits of a seed, if
-// every hit lies in the (frame, sector) and the rows rise strictly.
-__device__ inline bool seed_rows(const int32_t *ro, int R, const SeedView &sv, int &ra, int &rb, int &rc) {
-    const int n = sv.n, kb = (n - 1) / 2;
+// Rows of the hits of a seed into the strip, if every hit lies in the
+// (frame, sector) whose R + 1 row starts are ro and the rows rise strictly:
+// a binary search for the outermost hit, then a walk down for each next one
+// (the first row below the last one's that starts at or before its id).
+// The ids are read four hits ahead.
+template <class RO>
+__device__ inline bool seed_rows(RO ro, int R, const SeedView &sv, uint8_t *strip) {
+    const int n = sv.n;
+    if (n > R) return false;                      // (more hits than rows cannot rise strictly)
     const int32_t top = sv.hh[n - 1];
+    int32_t id[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) id[j] = sv.hh[n - 2 - j > 0 ? n - 2 - j : 0];
     if (top < ro[0] || top >= ro[R]) return false;
     int lo = 0, hi = R - 1;                       // ro[lo] <= top < ro[hi + 1]
     while (lo < hi) {
@@ -176,22 +183,31 @@ __device__ inline bool seed_rows(const int32_t *ro, int R, const SeedView &sv, i
         else hi = mid - 1;
     }
     int r = lo;
-    ra = rb = r;
-    for (int k = n - 2; k >= 0; --k) {
-        r = walk_row(ro, r - 1, sv.hh[k]);
-        if (r < 0) return false;
-        if (k == kb) rb = r;
+    strip[(n - 1) * TPC_WAVE] = (uint8_t)r;
+    for (int k0 = n - 2; k0 >= 0; k0 -= 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = k0 - j;
+            if (k < 0) break;
+            const int32_t h = id[j];
+            id[j] = sv.hh[k > 4 ? k - 4 : 0];
+            --r;
+            while (r >= 0 && ro[r] > h) --r;
+            if (r < 0 || h >= ro[r + 1]) return false;
+            strip[k * TPC_WAVE] = (uint8_t)r;
+        }
     }
-    rc = r;
     return true;
 }
 
+// fs0: the (frame, sector) whose row starts L.start[0] holds (L.start[1] the
+// next one's), -1 if some seed of the wavefront lies in neither.
 template <bool ROWS, bool ERRS>
-__device__ inline void fit_ms_one(const MsArgs &A, int i, const float *xs) {
+__device__ inline void fit_ms_one(const MsArgs &A, int i, const float *xs, RowLds *L, int fs0) {
     static_assert(ROWS || !ERRS, "per-cluster errors come with the row lookup");
     const FitArgs &F = A.F;
     SeedView sv = seed_view(F, i);
-    const int32_t *ro = nullptr;
+    uint8_t *strip = ROWS ? L->s + (threadIdx.x & (TPC_WAVE - 1)) : nullptr;
     int ra = 0, rb = 0, rc = 0;                   // rows of hits n-1, (n-1)/2, 0
     bool refused = false;
     if (ROWS) {
@@ -202,8 +218,14 @@ __device__ inline void fit_ms_one(const MsArgs &A, int i, const float *xs) {
             for (int k = 0; k < sv.n; ++k) A.rejected[sv.o0 + k] = 0;
         sv.sane = inb && sv.sec >= 0 && sv.sec < F.n_sectors && fi >= 0 && fi < A.n_frames;
         if (sv.sane) {
-            ro = A.row_offsets + ((size_t)fi * F.n_sectors + sv.sec) * F.n_rows;
-            sv.sane = seed_rows(ro, F.n_rows, sv, ra, rb, rc);
+            const int fs = fi * F.n_sectors + sv.sec;
+            if (fs0 >= 0) sv.sane = seed_rows(L->start[fs - fs0], F.n_rows, sv, strip);
+            else sv.sane = seed_rows(A.row_offsets + (size_t)fs * F.n_rows, F.n_rows, sv, strip);
+        }
+        if (sv.sane) {
+            ra = strip[(sv.n - 1) * TPC_WAVE];
+            rb = strip[(sv.n - 1) / 2 * TPC_WAVE];
+            rc = strip[0];
         }
         refused = !sv.sane;
     } else {
@@ -222,7 +244,7 @@ __device__ inline void fit_ms_one(const MsArgs &A, int i, const float *xs) {
     double xcur = sv.sane ? (double)xs[ra] : 0.0;
     double vy = F.vy, vz = F.vz;
     if (ERRS && sv.sane) {
-        const float2 e = A.err[sv.hh[sv.n - 1]];
+        const float2 e = A.err[sv.o0 + sv.n - 1];
         vy = (double)e.x * (double)e.x;
         vz = (double)e.y * (double)e.y;
     }
@@ -247,43 +269,30 @@ __device__ inline void fit_ms_one(const MsArgs &A, int i, const float *xs) {
         C.c44 = F.var_w;
     }
     if (status == TPC_FIT_OK) {
-        // Everything of a hit is read ahead: coordinates and, with ERRS, its
-        // error a step, its id (which the error and the row hang on) two.
-        // ROWS: the row of the next hit is resolved a step ahead too -- the
-        // row starts one and two rows below are loaded at the top of a step
-        // and compared after its helix step (a longer gap walks on); equal
-        // to walk_row, as seed_rows has checked every row.
-        const float2 *hp = F.hyz + sv.o0 + sv.n - 2;
-        float2 raw = *hp;
-        int rk = ra;
-        int32_t nid = ROWS ? sv.hh[sv.n - 2] : 0;                // id of the next hit
-        int rnext = ROWS ? walk_row(ro, ra - 1, nid) : 0;
-        float2 en = ERRS ? A.err[nid] : make_float2(0.f, 0.f);
-        if (ROWS && sv.n > 2) nid = sv.hh[sv.n - 3];
+        // a hit's coordinates (and, with ERRS, its error), its row and its
+        // plane are read a step ahead
+        const float2 *hp = F.hyz + sv.o0 + sv.n - 2, *ep = ERRS ? A.err + sv.o0 + sv.n - 2 : nullptr;
+        float2 raw = *hp, en = ERRS ? *ep : make_float2(0.f, 0.f);
         if (ROWS && A.rows_out) A.rows_out[sv.o0 + sv.n - 1] = (int16_t)ra;
+        int rn = ROWS ? (int)strip[(sv.n - 2) * TPC_WAVE] : sv.row0 + sv.n - 2;
+        float xn = xs[rn];
         for (int k = sv.n - 2; k >= 0; --k) {
             double my, mz;
             hit_fix<false>(sv, k, raw, my, mz);
             hp -= k > 0;
             raw = *hp;
-            int32_t v1 = INT32_MAX, v2 = INT32_MAX, id = nid;    // id: of hit k - 1
-            if (ROWS) {
-                rk = rnext;
-                if (A.rows_out) A.rows_out[sv.o0 + k] = (int16_t)rk;
-                if (k > 0) {
-                    if (rk >= 1) v1 = ro[rk - 1];
-                    if (rk >= 2) v2 = ro[rk - 2];
-                }
-                if (k > 1) nid = sv.hh[k - 2];
-            } else {
-                rk = sv.row0 + k;
+            if (ROWS && A.rows_out) A.rows_out[sv.o0 + k] = (int16_t)rn;
+            const double xk = (double)xn;
+            if (k > 0) {
+                rn = ROWS ? (int)strip[(k - 1) * TPC_WAVE] : rn - 1;
+                xn = xs[rn];
             }
             if (ERRS) {
                 vy = (double)en.x * (double)en.x;
                 vz = (double)en.y * (double)en.y;
-                if (k > 0) en = A.err[id];
+                ep -= k > 0;
+                en = *ep;
             }
-            const double xk = (double)xs[rk];
             const double dx = xk - xcur;
             if (A.scatter || A.eloss) {
                 const Segment g = segment(A, p, dx);
@@ -306,7 +315,6 @@ __device__ inline void fit_ms_one(const MsArgs &A, int i, const float *xs) {
             }
             sym_transport<double, false>(C, J);
             xcur = xk;
-            if (ROWS && k > 0) rnext = id >= v1 ? rk - 1 : (id >= v2 ? rk - 2 : walk_row(ro, rk - 3, id));
             // the update, unless the predicted-residual chi2 rejects the hit
             // (a singular S is not a rejection: the update reports it, -1)
             double pn[5] = {p[0], p[1], p[2], p[3], p[4]};
@@ -349,18 +357,61 @@ __global__ void __launch_bounds__(MS_T) fit_ms_tracks(MsArgs A) {
     __shared__ float xs[TPC_MAX_ROWS];
     for (int r = threadIdx.x; r < A.F.n_rows; r += MS_T) xs[r] = A.F.row_x[r];
     __syncthreads();
+    RowLds *L = nullptr;
+    if constexpr (ROWS) {
+        __shared__ RowLds rows;
+        L = &rows;
+    }
     int T = *A.F.n_seeds;
     if (T > A.F.cap_seeds) T = A.F.cap_seeds;
-    for (int i = blockIdx.x * MS_T + threadIdx.x; i < T; i += gridDim.x * MS_T)
-        fit_ms_one<ROWS, ERRS>(A, i, xs);
+    for (int i0 = blockIdx.x * MS_T; i0 < T; i0 += gridDim.x * MS_T) {
+        const int i = i0 + threadIdx.x;
+        int fs0 = -1;
+        if (ROWS) {
+            // the row starts of the seeds' (frame, sector)s, if two in a row hold them all
+            const int n_fs = A.n_frames * A.F.n_sectors;
+            int fs = i < T ? A.frame[i] : -1;
+            fs = (uint32_t)fs < (uint32_t)A.n_frames ? fs * A.F.n_sectors + A.F.sector[i] : -1;
+            const bool in = (uint32_t)fs < (uint32_t)n_fs;
+            int lo = in ? fs : INT32_MAX;
+#pragma unroll
+            for (int d = TPC_WAVE / 2; d > 0; d >>= 1) {
+                const int o = __shfl_xor(lo, d, TPC_WAVE);
+                lo = o < lo ? o : lo;
+            }
+            if (lo != INT32_MAX && __ballot(in && fs > lo + 1) == 0ull) fs0 = lo;
+            __syncthreads();
+            if (fs0 >= 0)
+                for (int r = threadIdx.x; r <= A.F.n_rows; r += MS_T) {
+                    L->start[0][r] = A.row_offsets[(size_t)fs0 * A.F.n_rows + r];
+                    if (fs0 + 1 < n_fs) L->start[1][r] = A.row_offsets[(size_t)(fs0 + 1) * A.F.n_rows + r];
+                }
+            __syncthreads();
+        }
+        if (i < T) fit_ms_one<ROWS, ERRS>(A, i, xs, L, fs0);
+    }
+}
+
+// Errors of every seed hit in seed-hit order, so that the fit reads them as
+// it reads the coordinates (from the id that a step loads, the error's load
+// was waited for in every step).
+__global__ void __launch_bounds__(TPC_BLOCK)
+gather_err(const int32_t *__restrict__ n_seeds, int32_t cap_seeds, const int32_t *__restrict__ offsets,
+           int32_t cap_hits, const int32_t *__restrict__ hits, const float2 *__restrict__ err, int32_t N,
+           float2 *__restrict__ out) {
+    const int T = *n_seeds < cap_seeds ? *n_seeds : cap_seeds;
+    const int H = T > 0 ? (offsets[T] < cap_hits ? offsets[T] : cap_hits) : 0;
+    for (int64_t j = blockIdx.x * TPC_BLOCK + threadIdx.x; j < H; j += gridDim.x * TPC_BLOCK) {
+        const int32_t id = hits[j];
+        out[j] = (uint32_t)id < (uint32_t)N ? err[id] : make_float2(0.f, 0.f);
+    }
 }
 
 // Per seed hit the smoother keeps the filtered deviation (5), its
-// covariance (15, packed), the reference state (5) and the step that
-// arrived at the hit's plane from the next one out (helix Jacobian (6),
-// scattering and straggling noise (4), energy-loss factors (2)), padded to
-// 38 doubles.
-constexpr int SM_REC = 38;
+// covariance (15, packed), the reference state (5) and the step that leaves
+// the hit's plane inwards (helix Jacobian (6), scattering and straggling
+// noise (4), energy-loss factors (2)) in 38 doubles, 16-byte aligned.
+constexpr int SM_REC = 38, SM_R = 20, SM_J = 26, SM_Q = 32, SM_E = 36;
 
 __device__ inline void load_record(const double *rec, double w[SM_REC]) {
     const double2 *v = reinterpret_cast<const double2 *>(rec);
@@ -420,34 +471,42 @@ __device__ inline void jac_times(const StepJac &J, const double C[5][5], double 
     }
 }
 
-// Solves P X = A (P symmetric positive definite, 5x5) in place of A by a
-// Cholesky factorisation; false if a pivot is not positive.
-__device__ inline bool chol_solve(double P[5][5], double A[5][5]) {
+// Solves P X = A (P symmetric positive definite, 5x5, lower triangle read)
+// in place of A by P = L D L^T: five reciprocals and no square root; false
+// if a pivot is not positive.
+__device__ inline bool ldl_solve(double P[5][5], double A[5][5]) {
+    double iD[5];
+    bool ok = true;
+#pragma unroll
     for (int j = 0; j < 5; ++j) {
-        double s = P[j][j];
-        for (int k = 0; k < j; ++k) s -= P[j][k] * P[j][k];
-        if (!(s > 0.0)) return false;
-        const double l = sqrt(s);
-        P[j][j] = l;
-        for (int r = j + 1; r < 5; ++r) {
-            double t = P[r][j];
-            for (int k = 0; k < j; ++k) t -= P[r][k] * P[j][k];
-            P[r][j] = t / l;
+        double v[5], d = P[j][j];
+#pragma unroll
+        for (int k = 0; k < j; ++k) {
+            v[k] = P[j][k];                          // L[j][k] D[k]
+            P[j][k] = v[k] * iD[k];                  // L[j][k]
+            d -= P[j][k] * v[k];
         }
+        ok = ok && d > 0.0;
+        iD[j] = recip_pos(d);
+#pragma unroll
+        for (int r = j + 1; r < 5; ++r)              // L[r][j] D[j]
+#pragma unroll
+            for (int k = 0; k < j; ++k) P[r][j] -= P[r][k] * P[j][k];
     }
+#pragma unroll
     for (int c = 0; c < 5; ++c) {
-        for (int r = 0; r < 5; ++r) {           // L y = a
-            double t = A[r][c];
-            for (int k = 0; k < r; ++k) t -= P[r][k] * A[k][c];
-            A[r][c] = t / P[r][r];
-        }
-        for (int r = 4; r >= 0; --r) {          // L^T x = y
-            double t = A[r][c];
-            for (int k = r + 1; k < 5; ++k) t -= P[k][r] * A[k][c];
-            A[r][c] = t / P[r][r];
+#pragma unroll
+        for (int r = 1; r < 5; ++r)                  // L y = a
+#pragma unroll
+            for (int k = 0; k < r; ++k) A[r][c] -= P[r][k] * A[k][c];
+#pragma unroll
+        for (int r = 4; r >= 0; --r) {               // D L^T x = y
+            A[r][c] *= iD[r];
+#pragma unroll
+            for (int k = r + 1; k < 5; ++k) A[r][c] -= P[k][r] * A[k][c];
         }
     }
-    return true;
+    return ok;
 }
 
 template <bool ERRS>
@@ -473,8 +532,11 @@ __device__ inline void smooth_one(const SmArgs &S, int i, const float *xs) {
         for (int q = 0; q < 5; ++q) R[q] = pf[q];
         StepJac J;
         if (A.eloss) {
+            int row = wr[1], rlast = rc;
             for (int k = 1; k < n && status == TPC_FIT_OK; ++k) {
-                const double dx = (double)xs[wr[k]] - (double)xs[wr[k - 1]];
+                const double dx = (double)xs[row] - (double)xs[rlast];
+                rlast = row;
+                row = wr[k + 1 < n ? k + 1 : k];
                 double w1 = R[4], a, b, vw;
                 if (!helix_step<double, double>(R, dx, A.kbz, F.max_sin, J) ||
                     eloss_map(A, R, segment(A, R, dx), -1.0, w1, a, b, vw))
@@ -486,11 +548,12 @@ __device__ inline void smooth_one(const SmArgs &S, int i, const float *xs) {
         }
         double vy = F.vy, vz = F.vz;
         if (ERRS) {
-            const float2 e = A.err[sv.hh[n - 1]];
+            const float2 e = A.err[sv.o0 + n - 1];
             vy = (double)e.x * (double)e.x;
             vz = (double)e.y * (double)e.y;
         }
-        // inwards along the reference: Kalman filter of the deviation d
+        // inwards along the reference: Kalman filter of the deviation d;
+        // the hit, its row and flag are read a step ahead
         double d[5] = {0, 0, 0, 0, 0};
         SymT<double> C = {};
         C.c00 = 1e4 * vy;
@@ -498,17 +561,24 @@ __device__ inline void smooth_one(const SmArgs &S, int i, const float *xs) {
         C.c22 = F.var_s;
         C.c33 = F.var_t;
         C.c44 = F.var_w;
-        int rk = ra;
-        int rn = wr[n - 2];                 // loaded a step ahead
+        const float2 *hz = F.hyz + sv.o0;
+        float2 raw = hz[n - 1];
+        int rj = rej[n - 1];
+        float xr = xs[ra], xl = xr;                   // x of planes k and k + 1
+        int row = wr[n - 2];                          // row of plane k - 1
         for (int k = n - 1; k >= 0 && status == TPC_FIT_OK; --k) {
-            // the step that arrives at plane k: its noise and energy-loss
-            // factors, kept for the outward pass with its Jacobian J
-            SymT<double> Q = {};
-            double ea = 0.0, eb = 1.0;
+            const float2 hk = raw;
+            const int rjk = rj, kn = k > 0 ? k - 1 : 0;
+            const float xc = xr;
+            raw = hz[kn];
+            rj = rej[kn];
+            xr = xs[row];
+            row = wr[k > 1 ? k - 2 : 0];
             if (k < n - 1) {
-                const int rcur = rn;
-                if (k > 0) rn = wr[k - 1];
-                const double dx = (double)xs[rcur] - (double)xs[rk];
+                // the step from plane k + 1 to plane k, kept with plane k + 1
+                SymT<double> Q = {};
+                double ea = 0.0, eb = 1.0;
+                const double dx = (double)xc - (double)xl;
                 const Segment g = (A.scatter || A.eloss) ? segment(A, R, dx) : Segment{};
                 add_scattering(A, R, g, Q);
                 if (A.eloss) {
@@ -529,30 +599,33 @@ __device__ inline void smooth_one(const SmArgs &S, int i, const float *xs) {
                     status = TPC_FIT_SIN_FAIL;
                     break;
                 }
+                double2 *w = reinterpret_cast<double2 *>(wd + (size_t)(k + 1) * SM_REC + SM_J);
+                w[0] = make_double2(J.f02, J.f04);
+                w[1] = make_double2(J.f12, J.f13);
+                w[2] = make_double2(J.f14, J.f24);
+                w[3] = make_double2(Q.c22, Q.c33);
+                w[4] = make_double2(Q.c43, Q.c44);
+                w[5] = make_double2(ea, eb);
                 double nd[5];
                 jac_apply(J, d, nd);
                 for (int q = 0; q < 5; ++q) d[q] = nd[q];
                 sym_transport<double, false>(C, J);
-                rk = rcur;
                 if (ERRS) {
-                    const float2 e = A.err[sv.hh[k]];
+                    const float2 e = A.err[sv.o0 + k];
                     vy = (double)e.x * (double)e.x;
                     vz = (double)e.y * (double)e.y;
                 }
             }
-            if (!rej[k]) {
-                double my, mz;
-                hit_meas(F, sv, k, F.hyz ? 0 : sv.hh[k], my, mz);
-                const double dchi = kalman_update<double>(d, C, my - R[0], mz - R[1], vy, vz);
+            xl = xc;
+            if (!rjk) {
+                const double dchi =
+                    kalman_update<double>(d, C, (double)hk.x - R[0], (double)hk.y - R[1], vy, vz);
                 const double chk = dchi + d[0] + d[1] + d[2] + d[3] + d[4];
                 if (!(chk - chk == 0.0)) {
                     status = TPC_FIT_NUM_FAIL;
                     break;
                 }
             }
-            // d, C, the reference and the arriving step (Jacobian, the four
-            // noise terms, energy-loss factors): 38 doubles as 19 16-byte
-            // stores (the record is 16-byte aligned)
             double2 *w = reinterpret_cast<double2 *>(wd + (size_t)k * SM_REC);
             w[0] = make_double2(d[0], d[1]);
             w[1] = make_double2(d[2], d[3]);
@@ -566,111 +639,86 @@ __device__ inline void smooth_one(const SmArgs &S, int i, const float *xs) {
             w[9] = make_double2(C.c43, C.c44);
             w[10] = make_double2(R[0], R[1]);
             w[11] = make_double2(R[2], R[3]);
-            w[12] = make_double2(R[4], J.f02);
-            w[13] = make_double2(J.f04, J.f12);
-            w[14] = make_double2(J.f13, J.f14);
-            w[15] = make_double2(J.f24, Q.c22);
-            w[16] = make_double2(Q.c33, Q.c43);
-            w[17] = make_double2(Q.c44, ea);
-            w[18] = make_double2(eb, 0.0);
+            w[12] = make_double2(R[4], 0.0);
         }
-        // outwards: Rauch-Tung-Striebel
+        // outwards: Rauch-Tung-Striebel, each record read a step ahead
         if (status == TPC_FIT_OK) {
-            double ds[5], Cs[5][5];
-            // the step from plane 1 to plane 0 is stored with plane 0
-            StepJac Jk;
-            double q22, q33, q43, q44, ea, eb;
-            {
-                double w[SM_REC];
-                load_record(wd, w);
-                Jk = StepJac{w[25], w[26], w[27], w[28], w[29], w[30]};
-                q22 = w[31]; q33 = w[32]; q43 = w[33]; q44 = w[34]; ea = w[35]; eb = w[36];
-                for (int q = 0; q < 5; ++q) ds[q] = w[q];
-                SymT<double> C0;
-                C0.c00 = w[5]; C0.c10 = w[6]; C0.c11 = w[7]; C0.c20 = w[8]; C0.c21 = w[9];
-                C0.c22 = w[10]; C0.c30 = w[11]; C0.c31 = w[12]; C0.c32 = w[13]; C0.c33 = w[14];
-                C0.c40 = w[15]; C0.c41 = w[16]; C0.c42 = w[17]; C0.c43 = w[18]; C0.c44 = w[19];
-                sym_dense(C0, Cs);
-                for (int q = 0; q < 5; ++q) hp[q] = (float)(w[20 + q] + ds[q]);
-            }
-            {
-                const SymT<double> P0 = sym_packed(Cs);
-                const double cc[15] = {P0.c00, P0.c10, P0.c11, P0.c20, P0.c21, P0.c22, P0.c30, P0.c31,
-                                       P0.c32, P0.c33, P0.c40, P0.c41, P0.c42, P0.c43, P0.c44};
-                for (int q = 0; q < 15; ++q) hc[q] = (float)cc[q];
-            }
-            for (int k = 1; k < n; ++k) {
-                double w[SM_REC];
-                load_record(wd + (size_t)k * SM_REC, w);
-                const double dk[5] = {w[0], w[1], w[2], w[3], w[4]};
-                SymT<double> Ck;
-                Ck.c00 = w[5]; Ck.c10 = w[6]; Ck.c11 = w[7]; Ck.c20 = w[8]; Ck.c21 = w[9];
-                Ck.c22 = w[10]; Ck.c30 = w[11]; Ck.c31 = w[12]; Ck.c32 = w[13]; Ck.c33 = w[14];
-                Ck.c40 = w[15]; Ck.c41 = w[16]; Ck.c42 = w[17]; Ck.c43 = w[18]; Ck.c44 = w[19];
-                const double Rk[5] = {w[20], w[21], w[22], w[23], w[24]};
-                // the step inwards from plane k: F = Jh Je, noise Q (stored
-                // with plane k - 1 by the filter)
-                SymT<double> Pq = Ck;
-                Pq.c22 += q22;
-                Pq.c33 += q33;
-                Pq.c43 += q43;
-                Pq.c44 += q44;
-                double Cd[5][5], X[5][5], ed[5] = {dk[0], dk[1], dk[2], dk[3], dk[4]};
-                sym_dense(Ck, Cd);
-                if (A.eloss) {
-                    eloss_cov(Pq, ea, eb);
-                    ed[4] = ea * dk[3] + eb * dk[4];
-                    double EC[5][5];
-                    for (int a = 0; a < 5; ++a)
-                        for (int b = 0; b < 5; ++b)
-                            EC[a][b] = a < 4 ? Cd[a][b] : ea * Cd[3][b] + eb * Cd[4][b];
-                    jac_times(Jk, EC, X);                    // F C_k
+            double ds[5] = {0, 0, 0, 0, 0}, Cs[5][5] = {};
+            // smoothed state and covariance of plane k from its record and
+            // those of plane k - 1 in (ds, Cs); false if P is singular
+            auto rts = [&](int k, const double *w) {
+                const SymT<double> Ck = {w[5],  w[6],  w[7],  w[8],  w[9],  w[10], w[11], w[12],
+                                         w[13], w[14], w[15], w[16], w[17], w[18], w[19]};
+                bool ok = true;
+                if (k == 0) {
+                    for (int q = 0; q < 5; ++q) ds[q] = w[q];
+                    sym_dense(Ck, Cs);
                 } else {
-                    jac_times(Jk, Cd, X);                    // F C_k
-                }
-                sym_transport<double, false>(Pq, Jk);       // P = F (C_k + Q) F^T
-                double P[5][5], Pd[5][5];
-                sym_dense(Pq, P);
-                sym_dense(Pq, Pd);
-                if (!chol_solve(P, X)) {                     // X = P^-1 F C_k = G^T
-                    status = TPC_FIT_NUM_FAIL;
-                    break;
-                }
-                double pd[5], e[5], nds[5];
-                jac_apply(Jk, ed, pd);
-                for (int q = 0; q < 5; ++q) e[q] = ds[q] - pd[q];
-                for (int a = 0; a < 5; ++a) {
-                    double acc = dk[a];
-                    for (int b = 0; b < 5; ++b) acc += X[b][a] * e[b];
-                    nds[a] = acc;
-                }
-                // Cs <- C_k + G (Cs - P) G^T
-                double D[5][5], T[5][5];
-                for (int a = 0; a < 5; ++a)
-                    for (int b = 0; b < 5; ++b) D[a][b] = Cs[a][b] - Pd[a][b];
-                for (int a = 0; a < 5; ++a)
-                    for (int b = 0; b < 5; ++b) {
-                        double acc = 0.0;
-                        for (int c = 0; c < 5; ++c) acc += X[c][a] * D[c][b];
-                        T[a][b] = acc;
+                    // the step inwards from plane k: F = Jh Je, noise Q
+                    const StepJac Jk = {w[SM_J], w[SM_J + 1], w[SM_J + 2], w[SM_J + 3], w[SM_J + 4], w[SM_J + 5]};
+                    const double ea = w[SM_E], eb = w[SM_E + 1];
+                    SymT<double> Pq = Ck;
+                    Pq.c22 += w[SM_Q];
+                    Pq.c33 += w[SM_Q + 1];
+                    Pq.c43 += w[SM_Q + 2];
+                    Pq.c44 += w[SM_Q + 3];
+                    double Cd[5][5], EC[5][5], X[5][5], ed[5] = {w[0], w[1], w[2], w[3], w[4]};
+                    sym_dense(Ck, Cd);
+                    sym_dense(Ck, EC);
+                    if (A.eloss) {
+                        eloss_cov(Pq, ea, eb);
+                        ed[4] = ea * w[3] + eb * w[4];
+                        for (int b = 0; b < 5; ++b) EC[4][b] = ea * Cd[3][b] + eb * Cd[4][b];
                     }
-                for (int a = 0; a < 5; ++a)
-                    for (int b = 0; b <= a; ++b) {
-                        double acc = 0.0;
-                        for (int c = 0; c < 5; ++c) acc += T[a][c] * X[c][b];
-                        Cs[a][b] = Cs[b][a] = Cd[a][b] + acc;
+                    jac_times(Jk, EC, X);                        // F C_k
+                    sym_transport<double, false>(Pq, Jk);       // P = F (C_k + Q) F^T
+                    double P[5][5], D[5][5];
+                    sym_dense(Pq, P);
+                    for (int a = 0; a < 5; ++a)
+                        for (int b = 0; b < 5; ++b) D[a][b] = Cs[a][b] - P[a][b];
+                    ok = ldl_solve(P, X);                        // X = P^-1 F C_k = G^T
+                    double pd[5], e[5];
+                    jac_apply(Jk, ed, pd);
+                    for (int q = 0; q < 5; ++q) e[q] = ds[q] - pd[q];
+                    for (int a = 0; a < 5; ++a) {
+                        double acc = w[a];
+                        for (int b = 0; b < 5; ++b) acc += X[b][a] * e[b];
+                        ds[a] = acc;
                     }
-                for (int q = 0; q < 5; ++q) ds[q] = nds[q];
-                float *o = hp + (size_t)k * 5;
-                for (int q = 0; q < 5; ++q) o[q] = (float)(Rk[q] + ds[q]);
-                float *oc = hc + (size_t)k * 15;
+                    // Cs <- C_k + G (Cs - P) G^T
+                    double T[5][5];
+                    for (int a = 0; a < 5; ++a)
+                        for (int b = 0; b < 5; ++b) {
+                            double acc = 0.0;
+                            for (int c = 0; c < 5; ++c) acc += X[c][a] * D[c][b];
+                            T[a][b] = acc;
+                        }
+                    for (int a = 0; a < 5; ++a)
+                        for (int b = 0; b <= a; ++b) {
+                            double acc = Cd[a][b];
+                            for (int c = 0; c < 5; ++c) acc += T[a][c] * X[c][b];
+                            Cs[a][b] = Cs[b][a] = acc;
+                        }
+                }
+                float *o = hp + (size_t)k * 5, *oc = hc + (size_t)k * 15;
+                for (int q = 0; q < 5; ++q) o[q] = (float)(w[SM_R + q] + ds[q]);
                 int q = 0;
                 for (int a = 0; a < 5; ++a)
                     for (int b = 0; b <= a; ++b, ++q) oc[q] = (float)Cs[a][b];
-                // the step from plane k + 1, stored with plane k
-                Jk = StepJac{w[25], w[26], w[27], w[28], w[29], w[30]};
-                q22 = w[31]; q33 = w[32]; q43 = w[33]; q44 = w[34]; ea = w[35]; eb = w[36];
+                return ok;
+            };
+            double wa[SM_REC], wb[SM_REC];
+            load_record(wd, wa);
+            bool ok = true;
+            for (int k = 0; k < n && ok; k += 2) {
+                const int k1 = k + 1 < n ? k + 1 : n - 1, k2 = k + 2 < n ? k + 2 : n - 1;
+                load_record(wd + (size_t)k1 * SM_REC, wb);
+                ok = rts(k, wa);
+                if (!ok || k + 1 >= n) break;
+                load_record(wd + (size_t)k2 * SM_REC, wa);
+                ok = rts(k + 1, wb);
             }
+            if (!ok) status = TPC_FIT_NUM_FAIL;
         }
         if (status != TPC_FIT_OK) F.out.status[i] = status;
     }
@@ -693,16 +741,25 @@ __global__ void __launch_bounds__(MS_T) smooth_tracks(SmArgs S) {
         smooth_one<ERRS>(S, i, xs);
 }
 
-MsArgs make_ms_args(const tpc_context *ctx, const tpc_frames *fr, const tpc_seeds *sd, const tpc_material *mat,
-                    const tpc_tracks *tr, uint8_t *rejected, void *ws, hipStream_t st) {
+MsArgs make_ms_args(const tpc_context *ctx, const tpc_frames *fr, const tpc_seeds *sd, const float *err,
+                    const tpc_material *mat, const tpc_tracks *tr, uint8_t *rejected, void *ws, hipStream_t st) {
     MsArgs A;
     A.F = make_fit_args(ctx, fr, sd, nullptr);
     A.F.out = *tr;
+    float2 *hyz, *herr;
+    fit_ws_layout(ws, sd->cap_seeds, sd->cap_hits, nullptr, &hyz, nullptr, &herr);
+    A.err = nullptr;
+    if (err) {
+        int64_t blocks = ((int64_t)sd->cap_hits + TPC_BLOCK - 1) / TPC_BLOCK;
+        blocks = blocks < 1 ? 1 : (blocks > 8192 ? 8192 : blocks);
+        hipLaunchKernelGGL(gather_err, dim3((unsigned)blocks), dim3(TPC_BLOCK), 0, st, sd->n_seeds, sd->cap_seeds,
+                           sd->offsets, sd->cap_hits, sd->hits, reinterpret_cast<const float2 *>(err),
+                           fr->n_clusters, herr);
+        A.err = herr;
+    }
     if (sd->hit_yz) {
         A.F.hyz = reinterpret_cast<const float2 *>(sd->hit_yz);
     } else {
-        float2 *hyz;
-        fit_ws_layout(ws, sd->cap_seeds, sd->cap_hits, nullptr, &hyz);
         A.F.hyz = hyz;
         (void)launch_gather(fr, sd, hyz, st);    // a launch error surfaces at the fit's launch
     }
@@ -723,7 +780,6 @@ MsArgs make_ms_args(const tpc_context *ctx, const tpc_frames *fr, const tpc_seed
     A.row_offsets = fr->row_offsets;
     A.frame = sd->frame;
     A.n_frames = fr->n_frames;
-    A.err = nullptr;
     A.pfin = nullptr;
     A.rows_out = nullptr;
     return A;
@@ -741,7 +797,7 @@ int fit_blocks(const tpc_seeds *sd) {
 hipError_t launch_fit_material(const tpc_context *ctx, const tpc_frames *fr, const tpc_seeds *sd,
                                const tpc_material *mat, const tpc_tracks *tr, uint8_t *rejected,
                                void *ws, hipStream_t st) {
-    const MsArgs A = make_ms_args(ctx, fr, sd, mat, tr, rejected, ws, st);
+    const MsArgs A = make_ms_args(ctx, fr, sd, nullptr, mat, tr, rejected, ws, st);
     hipLaunchKernelGGL((fit_ms_tracks<false, false>), dim3(fit_blocks(sd)), dim3(MS_T), 0, st, A);
     return hipGetLastError();
 }
@@ -749,8 +805,7 @@ hipError_t launch_fit_material(const tpc_context *ctx, const tpc_frames *fr, con
 hipError_t launch_fit_rows(const tpc_context *ctx, const tpc_frames *fr, const tpc_seeds *sd, const float *err,
                            const tpc_material *mat, const tpc_tracks *tr, uint8_t *rejected, void *ws,
                            hipStream_t st) {
-    MsArgs A = make_ms_args(ctx, fr, sd, mat, tr, rejected, ws, st);
-    A.err = reinterpret_cast<const float2 *>(err);
+    const MsArgs A = make_ms_args(ctx, fr, sd, err, mat, tr, rejected, ws, st);
     if (err)
         hipLaunchKernelGGL((fit_ms_tracks<true, true>), dim3(fit_blocks(sd)), dim3(MS_T), 0, st, A);
     else
@@ -772,8 +827,7 @@ hipError_t launch_smooth(const tpc_context *ctx, const tpc_frames *fr, const tpc
                          const tpc_material *mat, const tpc_tracks *tr, uint8_t *rejected, float *hit_par,
                          float *hit_cov, void *ws, hipStream_t st) {
     SmArgs S;
-    S.M = make_ms_args(ctx, fr, sd, mat, tr, rejected, ws, st);
-    S.M.err = reinterpret_cast<const float2 *>(err);
+    S.M = make_ms_args(ctx, fr, sd, err, mat, tr, rejected, ws, st);
     smooth_ws_layout(ws, sd->cap_seeds, sd->cap_hits, &S.w);
     S.M.pfin = S.w.pfin;
     S.M.rows_out = S.w.wrow;

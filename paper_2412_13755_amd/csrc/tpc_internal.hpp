@@ -88,7 +88,7 @@ struct FitOrderWs {
 #define TPC_FIT_ORDER_MIN 4096
 FitOrderWs fit_order_carve(WsCarver &w, int64_t cap_seeds);
 size_t fit_ws_layout(void *ws, int64_t cap_seeds, int64_t cap_hits, double **part, float2 **hyz,
-                     FitOrderWs *ord = nullptr);
+                     FitOrderWs *ord = nullptr, float2 **herr = nullptr);
 hipError_t launch_gather(const tpc_frames *fr, const tpc_seeds *sd, float2 *hyz, hipStream_t st);
 size_t adj_ws_layout(void *ws, int64_t cap_hits, int64_t cap_seeds, int64_t n_fs, int32_t n_rows,
                      int32_t K, float2 **g, double **tape, float2 **partial, float2 **hyz,

@@ -94,19 +94,21 @@ __device__ double pair_fuse(const MgArgs &A, int a, int b, double ca, double sa,
     const float *pa = A.par + (size_t)a * 5, *pb = A.par + (size_t)b * 5;
     const double x = (double)A.x[a], y = (double)pa[0], s = (double)pa[2], t = (double)pa[3], w = (double)pa[4];
     if (!(fabs(s) < 1.0)) return INFINITY;
-    const double c = sqrt(1.0 - s * s);
+    double ic, ic2;
+    const double c = sqrt_pos(fma(-s, s, 1.0), &ic);
     if (!(c * ca + s * sa > 0.0)) return INFINITY;
     const double x1 = x * ca + y * sa;
     double q[5] = {-x * sa + y * ca, (double)pa[1], s * ca - c * sa, t, w};
     StepJac F;
     if (!helix_step<double, double>(q, (double)A.x[b] - x1, A.kbz, A.max_sin, F)) return INFINITY;
     // J = F R - v e_0^T sin(da), R = diag(ca, 1, ca + (s/c) sa, 1, 1), v = (s2/c2, t/c2, kappa, 0, 0)
-    const double r22 = ca + s / c * sa;
-    const double s2 = q[2], c2 = sqrt(1.0 - s2 * s2), kap = A.kbz * w;
+    const double r22 = ca + s * ic * sa;
+    const double s2 = q[2], kap = A.kbz * w;
+    sqrt_pos(fma(-s2, s2, 1.0), &ic2);
     double J[3][5];
-    J[0][0] = ca - sa * s2 / c2; J[0][1] = 0.0; J[0][2] = F.f02 * r22; J[0][3] = 0.0;   J[0][4] = F.f04;
-    J[1][0] = -sa * t / c2;      J[1][1] = 1.0; J[1][2] = F.f12 * r22; J[1][3] = F.f13; J[1][4] = F.f14;
-    J[2][0] = -sa * kap;         J[2][1] = 0.0; J[2][2] = r22;         J[2][3] = 0.0;   J[2][4] = F.f24;
+    J[0][0] = ca - sa * s2 * ic2; J[0][1] = 0.0; J[0][2] = F.f02 * r22; J[0][3] = 0.0;   J[0][4] = F.f04;
+    J[1][0] = -sa * t * ic2;      J[1][1] = 1.0; J[1][2] = F.f12 * r22; J[1][3] = F.f13; J[1][4] = F.f14;
+    J[2][0] = -sa * kap;          J[2][1] = 0.0; J[2][2] = r22;         J[2][3] = 0.0;   J[2][4] = F.f24;
     double Ca[5][5], Cb[5][5], S[5][5], P[5][5];
     const float *ca_ = A.cov + (size_t)a * 15, *cb_ = A.cov + (size_t)b * 15;
     for (int i = 0, k = 0; i < 5; ++i)
@@ -138,23 +140,25 @@ __device__ double pair_fuse(const MgArgs &A, int a, int b, double ca, double sa,
         }
     double d[5];
     for (int i = 0; i < 5; ++i) d[i] = q[i] - (double)pb[i];
-    // chi2 = |L^-1 d|^2 with S = L L^T
-    double L[5][5], z[5], chi = 0.0;
+    // chi2 = u^T D^-1 u with S = L D L^T, L u = d (L's diagonal is 1)
+    double L[5][5], iD[5], u[5], chi = 0.0;
+#pragma unroll
     for (int i = 0; i < 5; ++i) {
-        for (int j = 0; j <= i; ++j) {
-            double acc = S[i][j];
-            for (int k = 0; k < j; ++k) acc -= L[i][k] * L[j][k];
-            if (i == j) {
-                if (!(acc > 0.0)) return INFINITY;
-                L[i][i] = sqrt(acc);
-            } else {
-                L[i][j] = acc / L[j][j];
-            }
+        double acc = S[i][i], v = d[i];
+#pragma unroll
+        for (int j = 0; j < i; ++j) {
+            double l = S[i][j];                       // L[i][j] D[j]
+#pragma unroll
+            for (int k = 0; k < j; ++k) l -= S[i][k] * L[j][k];
+            S[i][j] = l;
+            L[i][j] = l * iD[j];
+            acc -= L[i][j] * l;
+            v -= L[i][j] * u[j];
         }
-        double acc = d[i];
-        for (int k = 0; k < i; ++k) acc -= L[i][k] * z[k];
-        z[i] = acc / L[i][i];
-        chi += z[i] * z[i];
+        if (!(acc > 0.0)) return INFINITY;
+        iD[i] = recip_pos(acc);
+        u[i] = v;
+        chi += v * v * iD[i];
     }
     if (mp && mc) {
         // X = S^-1 P by the two triangular solves, column by column
@@ -164,12 +168,12 @@ __device__ double pair_fuse(const MgArgs &A, int a, int b, double ca, double sa,
             for (int i = 0; i < 5; ++i) {
                 double acc = P[i][c];
                 for (int k = 0; k < i; ++k) acc -= L[i][k] * y[k];
-                y[i] = acc / L[i][i];
+                y[i] = acc;
             }
             for (int i = 4; i >= 0; --i) {
-                double acc = y[i];
+                double acc = y[i] * iD[i];
                 for (int k = i + 1; k < 5; ++k) acc -= L[k][i] * X[k][c];
-                X[i][c] = acc / L[i][i];
+                X[i][c] = acc;
             }
         }
         // d = p_a' - p_b: x = p_a' - P S^-1 d = p_a' - X^T d
@@ -204,7 +208,11 @@ __device__ inline double pair_chi2(const MgArgs &A, int a, int b, double ca, dou
 // of MG_CHUNK candidates, the ones that pass the tan(lambda) / q/pT test go
 // to the lane's own LDS column, so that the transfer runs over short lists
 // (a wavefront's iterations are the longest list of its lanes) instead of
-// every candidate of every lane.
+// every candidate of every lane.  The test's bound is the best chi2 that
+// any of the segment's lanes has found on the candidate's side (shared
+// after each chunk), or the cut: a pair whose (t, w) chi2 alone is above it
+// by more than rounding (TPC_MG_SLACK) can neither be nor tie the best.
+#define TPC_MG_SLACK 1.000001
 #define MG_SPLIT 4
 #define MG_CHUNK 64
 #define MG_LANE_CHUNK (MG_CHUNK / MG_SPLIT)
@@ -227,10 +235,12 @@ __global__ void __launch_bounds__(TPC_BLOCK) mg_best(MgArgs A) {
     for (int base = blockIdx.x * per_block; base < T; base += gridDim.x * per_block) {
         const int i = base + threadIdx.x / MG_SPLIT;
         int bo = -1, bi = -1;
-        double co = INFINITY, ci_ = INFINITY;
+        double co = INFINITY, ci_ = INFINITY;         // this lane's best
+        double lo = A.cut, li = A.cut;                // the segment's, at most the cut
         if (i < T && A.status[i] == 0 && A.n_sectors == 36) {
             const float *pi_ = A.par + (size_t)i * 5, *ci = A.cov + (size_t)i * 15;
-            const double ri = hypot((double)A.x[i], (double)pi_[0]);
+            const double xi = (double)A.x[i], ri = hypot(xi, (double)pi_[0]);
+            const double r2i = xi * xi + (double)pi_[0] * (double)pi_[0];
             const double ti = (double)pi_[3], wi = (double)pi_[4], vti = (double)ci[9], vwi = (double)ci[14];
             const double cti = (double)ci[13];
             const int sec = A.sector[i], side = sec / 18, s18 = sec % 18;
@@ -256,7 +266,11 @@ __global__ void __launch_bounds__(TPC_BLOCK) mg_best(MgArgs A) {
                         const double s33 = vti + (double)cj[9], s44 = vwi + (double)cj[14];
                         const double s43 = cti + (double)cj[13];
                         const double det = s33 * s44 - s43 * s43;
-                        if (det > 0.0 && (s44 * dt * dt - 2.0 * s43 * dt * dw + s33 * dw * dw) > A.cut * det)
+                        // j further out or in beyond rounding of its radius, or undecided
+                        const double xj = (double)A.x[j], yj = (double)pj[0], r2j = xj * xj + yj * yj;
+                        const double lim = r2j > r2i * (1.0 + 1e-9) ? lo : (r2j < r2i * (1.0 - 1e-9) ? li : fmax(lo, li));
+                        if (det > 0.0 &&
+                            (s44 * dt * dt - 2.0 * s43 * dt * dw + s33 * dw * dw) > lim * TPC_MG_SLACK * det)
                             continue;
                         cand[n++][threadIdx.x] = j;
                     }
@@ -276,6 +290,14 @@ __global__ void __launch_bounds__(TPC_BLOCK) mg_best(MgArgs A) {
                                 bi = j;
                             }
                         }
+                    }
+                    // (the lanes of a segment walk the same chunks together)
+                    lo = fmin(lo, co);
+                    li = fmin(li, ci_);
+#pragma unroll
+                    for (int d = 1; d < MG_SPLIT; d <<= 1) {
+                        lo = fmin(lo, __shfl_xor(lo, d, TPC_WAVE));
+                        li = fmin(li, __shfl_xor(li, d, TPC_WAVE));
                     }
                 }
             }
@@ -338,22 +360,25 @@ struct Circle {
     double s00, s10, s11, s20, s21, s22, s30, s31, s32, s33;   // J C J^T, lower triangle
 };
 
-// The circle of segment i (false if too large or degenerate).
-__device__ __forceinline__ bool leg_circle(const MgArgs &A, int i, Circle &o) {
+// The circle of segment i (false if too large or degenerate); ang: cosine
+// and sine of the 18 sector angles of a side.
+__device__ __forceinline__ bool leg_circle(const MgArgs &A, int i, const double (*ang)[2], Circle &o) {
     const float *p = A.par + (size_t)i * 5, *co = A.cov + (size_t)i * 15;
     const double y = (double)p[0], s = (double)p[2], t = (double)p[3], w = (double)p[4];
     const double k = A.kbz, kap = k * w;
     if (!(fabs(s) < 1.0) || !(fabs(kap) * LEG_MAX_RADIUS > 1.0)) return false;
-    const double al = sector_angle(A.sector[i], A.n_sectors);
-    const double c = sqrt(1.0 - s * s), ca = cos(al), sa = sin(al);
+    const double *cs = ang[A.sector[i] % 18];
+    double ic;
+    const double c = sqrt_pos(fma(-s, s, 1.0), &ic), ca = cs[0], sa = cs[1];
+    const double ik = copysign(recip_pos(fabs(kap)), kap);
     const double x = (double)A.x[i];
-    const double xc = x - s / kap, yc = y + c / kap;
+    const double xc = x - s * ik, yc = y + c * ik;
     o.m[0] = xc * ca - yc * sa;
     o.m[1] = xc * sa + yc * ca;
     o.m[2] = kap;
     o.m[3] = t;
-    const double dxc[5] = {0.0, 0.0, -1.0 / kap, 0.0, s * k / (kap * kap)};
-    const double dyc[5] = {1.0, 0.0, -s / (c * kap), 0.0, -c * k / (kap * kap)};
+    const double dxc[5] = {0.0, 0.0, -ik, 0.0, s * k * ik * ik};
+    const double dyc[5] = {1.0, 0.0, -s * ic * ik, 0.0, -c * k * ik * ik};
     double J[4][5];
 #pragma unroll
     for (int j = 0; j < 5; ++j) {
@@ -396,31 +421,22 @@ __device__ __forceinline__ bool leg_circle(const MgArgs &A, int i, Circle &o) {
 
 // chi2 of legs a and b (m_a - D m_b against S_a + D S_b D, D = diag(1, 1,
 // -1, -1): the (centre, kappa/t) cross terms of S_b change sign), by a 4x4
-// Cholesky; INFINITY if the sum is not positive definite.
+// L D L^T; INFINITY if the sum is not positive definite.
 __device__ __forceinline__ double leg_chi2(const Circle &a, const Circle &b) {
     const double d0 = a.m[0] - b.m[0], d1 = a.m[1] - b.m[1], d2 = a.m[2] + b.m[2], d3 = a.m[3] + b.m[3];
     const double S00 = a.s00 + b.s00, S10 = a.s10 + b.s10, S11 = a.s11 + b.s11;
     const double S20 = a.s20 - b.s20, S21 = a.s21 - b.s21, S22 = a.s22 + b.s22;
     const double S30 = a.s30 - b.s30, S31 = a.s31 - b.s31, S32 = a.s32 + b.s32, S33 = a.s33 + b.s33;
-    bool ok = S00 > 0.0;
-    const double L00 = sqrt(ok ? S00 : 1.0);
-    const double L10 = S10 / L00, L20 = S20 / L00, L30 = S30 / L00;
-    const double e11 = S11 - L10 * L10;
-    ok = ok && e11 > 0.0;
-    const double L11 = sqrt(ok ? e11 : 1.0);
-    const double L21 = (S21 - L20 * L10) / L11, L31 = (S31 - L30 * L10) / L11;
-    const double e22 = S22 - L20 * L20 - L21 * L21;
-    ok = ok && e22 > 0.0;
-    const double L22 = sqrt(ok ? e22 : 1.0);
-    const double L32 = (S32 - L30 * L20 - L31 * L21) / L22;
-    const double e33 = S33 - L30 * L30 - L31 * L31 - L32 * L32;
-    ok = ok && e33 > 0.0;
-    const double L33 = sqrt(ok ? e33 : 1.0);
-    const double z0 = d0 / L00;
-    const double z1 = (d1 - L10 * z0) / L11;
-    const double z2 = (d2 - L20 * z0 - L21 * z1) / L22;
-    const double z3 = (d3 - L30 * z0 - L31 * z1 - L32 * z2) / L33;
-    return ok ? z0 * z0 + z1 * z1 + z2 * z2 + z3 * z3 : INFINITY;
+    const double i0 = recip_pos(S00);
+    const double l10 = S10 * i0, l20 = S20 * i0, l30 = S30 * i0;
+    const double e1 = S11 - l10 * S10, i1 = recip_pos(e1);
+    const double t21 = S21 - l20 * S10, t31 = S31 - l30 * S10, l21 = t21 * i1, l31 = t31 * i1;
+    const double e2 = S22 - l20 * S20 - l21 * t21, i2 = recip_pos(e2);
+    const double t32 = S32 - l30 * S20 - l31 * t21, l32 = t32 * i2;
+    const double e3 = S33 - l30 * S30 - l31 * t31 - l32 * t32, i3 = recip_pos(e3);
+    const double u1 = d1 - l10 * d0, u2 = d2 - l20 * d0 - l21 * u1, u3 = d3 - l30 * d0 - l31 * u1 - l32 * u2;
+    const bool ok = (int)(S00 > 0.0) & (int)(e1 > 0.0) & (int)(e2 > 0.0) & (int)(e3 > 0.0);
+    return ok ? d0 * d0 * i0 + u1 * u1 * i1 + u2 * u2 * i2 + u3 * u3 * i3 : INFINITY;
 }
 
 // Candidates are the segments of the segment's (frame, side): one
@@ -431,7 +447,13 @@ __device__ __forceinline__ double leg_chi2(const Circle &a, const Circle &b) {
 // workgroup walks the union of its segments' ranges in tiles of TPC_BLOCK
 // segments: each thread forms the circle of one tile segment into LDS, then
 // the lanes test the tile from there.  Each circle is formed once per
-// workgroup and tile instead of once per pair.
+// workgroup and tile instead of once per pair.  A lane first collects the
+// tile's candidates whose (kappa, tan(lambda)) chi2 alone (exact rows of J:
+// never above the full one) does not exceed the best full chi2 that any of
+// the segment's lanes has found (shared after each tile; the cut before),
+// with a slack far above rounding, then tests only those: the wavefront
+// takes as many full tests as its longest list, not one whenever any lane
+// has a candidate.
 #define LG_SPLIT 8
 #define LG_SEGS (TPC_BLOCK / LG_SPLIT)
 
@@ -439,6 +461,8 @@ struct LegTile {
     double m[4][TPC_BLOCK];
     double s[10][TPC_BLOCK];
     int ok[TPC_BLOCK];
+    double ang[18][2];                           // cosine, sine of the sector angles
+    uint8_t list[TPC_BLOCK / LG_SPLIT][TPC_BLOCK];   // each lane's candidates of the tile
 };
 
 __global__ void __launch_bounds__(TPC_BLOCK) lg_best(MgArgs A) {
@@ -446,14 +470,20 @@ __global__ void __launch_bounds__(TPC_BLOCK) lg_best(MgArgs A) {
     __shared__ int span[2];
     const int T = mg_count(A);
     const int sub = threadIdx.x % LG_SPLIT;
+    if (threadIdx.x < 18) {
+        const double al = sector_angle(threadIdx.x, A.n_sectors);
+        tile.ang[threadIdx.x][0] = cos(al);
+        tile.ang[threadIdx.x][1] = sin(al);
+    }
+    __syncthreads();
     // whole workgroups step together: every lane reaches the barriers and
     // the shuffles
     for (int base = blockIdx.x * LG_SEGS; base < T; base += gridDim.x * LG_SEGS) {
         const int i = base + threadIdx.x / LG_SPLIT;
         int best = -1;
-        double bchi = INFINITY;
+        double bchi = INFINITY, lim = A.cut;          // this lane's best; the segment's, at most the cut
         Circle ci;
-        const bool live = i < T && A.status[i] == 0 && A.n_sectors == 36 && leg_circle(A, i, ci);
+        const bool live = i < T && A.status[i] == 0 && A.n_sectors == 36 && leg_circle(A, i, tile.ang, ci);
         int j0 = T, j1 = 0;
         if (live) {
             const int64_t key = (int64_t)A.frame[i] * A.n_sectors + (A.sector[i] / 18) * 18;
@@ -474,7 +504,7 @@ __global__ void __launch_bounds__(TPC_BLOCK) lg_best(MgArgs A) {
         for (int c0 = u0; c0 < u1; c0 += TPC_BLOCK) {
             const int c = c0 + threadIdx.x;
             Circle cc;
-            const bool okc = c < u1 && A.status[c] == 0 && leg_circle(A, c, cc);
+            const bool okc = c < u1 && A.status[c] == 0 && leg_circle(A, c, tile.ang, cc);
             tile.ok[threadIdx.x] = okc;
             if (okc) {
 #pragma unroll
@@ -490,14 +520,18 @@ __global__ void __launch_bounds__(TPC_BLOCK) lg_best(MgArgs A) {
                 const int q0 = j0 > c0 ? j0 - c0 : 0;
                 const int q1 = j1 - c0 < n ? j1 - c0 : n;
                 // this lane's candidates: q = sub (mod LG_SPLIT) in [q0, q1)
+                const double bound = lim * TPC_MG_SLACK;
+                int cnt = 0;
                 for (int q = q0 + ((sub - q0 % LG_SPLIT + LG_SPLIT) % LG_SPLIT); q < q1; q += LG_SPLIT) {
-                    const int j = c0 + q;
-                    if (!tile.ok[q] || j == i) continue;
-                    // curvature and tan(lambda) alone (exact rows of J): a pair
-                    // failing either cannot pass the full test
                     const double dk = ci.m[2] + tile.m[2][q], dt = ci.m[3] + tile.m[3][q];
-                    if (dk * dk > A.cut * (ci.s22 + tile.s[5][q]) || dt * dt > A.cut * (ci.s33 + tile.s[9][q]))
-                        continue;
+                    const double S22 = ci.s22 + tile.s[5][q], S32 = ci.s32 + tile.s[8][q], S33 = ci.s33 + tile.s[9][q];
+                    const double det = S22 * S33 - S32 * S32;
+                    const bool far = S33 * dk * dk - 2.0 * S32 * dk * dt + S22 * dt * dt > bound * det;
+                    if ((int)(tile.ok[q] != 0) & (int)(c0 + q != i) & (int)!((int)(det > 0.0) & (int)far))
+                        tile.list[cnt++][threadIdx.x] = (uint8_t)q;
+                }
+                for (int k = 0; k < cnt; ++k) {
+                    const int q = tile.list[k][threadIdx.x];
                     Circle cj;
                     cj.m[0] = tile.m[0][q]; cj.m[1] = tile.m[1][q]; cj.m[2] = tile.m[2][q]; cj.m[3] = tile.m[3][q];
                     cj.s00 = tile.s[0][q]; cj.s10 = tile.s[1][q]; cj.s11 = tile.s[2][q]; cj.s20 = tile.s[3][q];
@@ -506,10 +540,13 @@ __global__ void __launch_bounds__(TPC_BLOCK) lg_best(MgArgs A) {
                     const double chi = leg_chi2(ci, cj);
                     if (chi > 0.0 && chi <= A.cut && chi < bchi) {   // j ascends: ties keep the smaller
                         bchi = chi;
-                        best = j;
+                        best = c0 + q;
                     }
                 }
             }
+            lim = fmin(lim, bchi);
+#pragma unroll
+            for (int d = 1; d < LG_SPLIT; d <<= 1) lim = fmin(lim, __shfl_xor(lim, d, TPC_WAVE));
             __syncthreads();
         }
 #pragma unroll

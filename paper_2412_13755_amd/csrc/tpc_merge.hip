@@ -85,12 +85,21 @@ __device__ inline double turn_angle(int sa, int sb, int n_sectors) {
     return da;
 }
 
+#define TPC_MG_SLACK 1.000001   // far above the rounding of a chi2
+
 // chi2 of carrying segment a onto segment b (INFINITY if it cannot be
-// formed); ca, sa: cos and sin of the turn from a's sector to b's.  With mp,
-// mc non-null also the two combined at b's plane: a's transferred state
-// (covariance P = J C_a J^T) and b's fused, x = p_a' + P S^-1 (p_b - p_a'),
-// C = P S^-1 C_b (= P - P S^-1 P), S = P + C_b (packed, in float).
-__device__ double pair_fuse(const MgArgs &A, int a, int b, double ca, double sa, float *mp, float *mc) {
+// formed, or if it exceeds lim for certain); ca, sa: cos and sin of the turn
+// from a's sector to b's.  With mp, mc non-null also the two combined at b's
+// plane: a's transferred state (covariance P = J C_a J^T) and b's fused,
+// x = p_a' + P S^-1 (p_b - p_a'), C = P S^-1 C_b (= P - P S^-1 P),
+// S = P + C_b (packed, in float).
+//
+// chi2 = u^T D^-1 u with S = L D L^T, L u = d (L's diagonal is 1), grows
+// with every component eliminated.  They are taken in the order (t, w, z, s,
+// y): two candidates of similar direction and momentum lie anywhere along
+// the beam, so z decides against nearly all of them after its own row of S,
+// before the other rows are formed.
+__device__ double pair_fuse(const MgArgs &A, int a, int b, double ca, double sa, double lim, float *mp, float *mc) {
     const float *pa = A.par + (size_t)a * 5, *pb = A.par + (size_t)b * 5;
     const double x = (double)A.x[a], y = (double)pa[0], s = (double)pa[2], t = (double)pa[3], w = (double)pa[4];
     if (!(fabs(s) < 1.0)) return INFINITY;
@@ -109,41 +118,42 @@ __device__ double pair_fuse(const MgArgs &A, int a, int b, double ca, double sa,
     J[0][0] = ca - sa * s2 * ic2; J[0][1] = 0.0; J[0][2] = F.f02 * r22; J[0][3] = 0.0;   J[0][4] = F.f04;
     J[1][0] = -sa * t * ic2;      J[1][1] = 1.0; J[1][2] = F.f12 * r22; J[1][3] = F.f13; J[1][4] = F.f14;
     J[2][0] = -sa * kap;          J[2][1] = 0.0; J[2][2] = r22;         J[2][3] = 0.0;   J[2][4] = F.f24;
-    double Ca[5][5], Cb[5][5], S[5][5], P[5][5];
+    double Ca[5][5], Cb[5][5];
     const float *ca_ = A.cov + (size_t)a * 15, *cb_ = A.cov + (size_t)b * 15;
+#pragma unroll
     for (int i = 0, k = 0; i < 5; ++i)
+#pragma unroll
         for (int j = 0; j <= i; ++j, ++k) {
             Ca[i][j] = Ca[j][i] = (double)ca_[k];
-            S[i][j] = S[j][i] = Cb[i][j] = Cb[j][i] = (double)cb_[k];
+            Cb[i][j] = Cb[j][i] = (double)cb_[k];
         }
-    // S += J Ca J^T, with rows 3 and 4 of J those of the identity
-    double JC[5][5];
-    for (int i = 0; i < 5; ++i)
-        for (int j = 0; j < 5; ++j) {
-            double acc = 0.0;
-            if (i < 3)
-                for (int k = 0; k < 5; ++k) acc += J[i][k] * Ca[k][j];
-            else
-                acc = Ca[i][j];
-            JC[i][j] = acc;
-        }
-    for (int i = 0; i < 5; ++i)
-        for (int j = 0; j <= i; ++j) {
-            double acc = 0.0;
-            if (j < 3)
-                for (int k = 0; k < 5; ++k) acc += JC[i][k] * J[j][k];
-            else
-                acc = JC[i][j];
-            P[i][j] = P[j][i] = acc;
-            S[i][j] += acc;
-            if (j != i) S[j][i] = S[i][j];
-        }
-    double d[5];
-    for (int i = 0; i < 5; ++i) d[i] = q[i] - (double)pb[i];
-    // chi2 = u^T D^-1 u with S = L D L^T, L u = d (L's diagonal is 1)
-    double L[5][5], iD[5], u[5], chi = 0.0;
+    // P = J Ca J^T in the order of elimination, rows 3 and 4 of J those of
+    // the identity; L D in place of S's lower triangle
+    constexpr int ord[5] = {3, 4, 1, 2, 0};
+    double P[5][5], S[5][5], L[5][5], iD[5], u[5], d[5], chi = 0.0;
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
+        const int ri = ord[i];
+        double JC[5];
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            double acc = ri < 3 ? 0.0 : Ca[ri][j];
+            if (ri < 3)
+#pragma unroll
+                for (int k = 0; k < 5; ++k) acc += J[ri][k] * Ca[k][j];
+            JC[j] = acc;
+        }
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+            const int rj = ord[j];
+            double acc = rj < 3 ? 0.0 : JC[rj];
+            if (rj < 3)
+#pragma unroll
+                for (int k = 0; k < 5; ++k) acc += JC[k] * J[rj][k];
+            P[i][j] = P[j][i] = acc;
+            S[i][j] = acc + Cb[ri][rj];
+        }
+        d[i] = q[ri] - (double)pb[ri];
         double acc = S[i][i], v = d[i];
 #pragma unroll
         for (int j = 0; j < i; ++j) {
@@ -159,6 +169,7 @@ __device__ double pair_fuse(const MgArgs &A, int a, int b, double ca, double sa,
         iD[i] = recip_pos(acc);
         u[i] = v;
         chi += v * v * iD[i];
+        if (i == 2 && chi > lim * TPC_MG_SLACK) return INFINITY;
     }
     if (mp && mc) {
         // X = S^-1 P by the two triangular solves, column by column
@@ -177,28 +188,34 @@ __device__ double pair_fuse(const MgArgs &A, int a, int b, double ca, double sa,
             }
         }
         // d = p_a' - p_b: x = p_a' - P S^-1 d = p_a' - X^T d
+#pragma unroll
         for (int i = 0; i < 5; ++i) {
-            double acc = q[i];
+            double acc = q[ord[i]];
+#pragma unroll
             for (int k = 0; k < 5; ++k) acc -= X[k][i] * d[k];
-            mp[i] = (float)acc;
+            mp[ord[i]] = (float)acc;
         }
         // C = P S^-1 C_b = X^T C_b, symmetrised (equal to P - P S^-1 P, with
         // no difference of large terms when one covariance dwarfs the other)
+        constexpr int pos[5] = {4, 2, 3, 0, 1};       // of component i in the order
+#pragma unroll
         for (int i = 0, k = 0; i < 5; ++i)
+#pragma unroll
             for (int j = 0; j <= i; ++j, ++k) {
-                double u = 0.0, v = 0.0;
+                double e = 0.0, f = 0.0;
+#pragma unroll
                 for (int m = 0; m < 5; ++m) {
-                    u += X[m][i] * Cb[m][j];
-                    v += X[m][j] * Cb[m][i];
+                    e += X[m][pos[i]] * Cb[ord[m]][j];
+                    f += X[m][pos[j]] * Cb[ord[m]][i];
                 }
-                mc[k] = (float)(0.5 * (u + v));
+                mc[k] = (float)(0.5 * (e + f));
             }
     }
     return chi > 0.0 ? chi : INFINITY;
 }
 
-__device__ inline double pair_chi2(const MgArgs &A, int a, int b, double ca, double sa) {
-    return pair_fuse(A, a, b, ca, sa, nullptr, nullptr);
+__device__ inline double pair_chi2(const MgArgs &A, int a, int b, double ca, double sa, double lim) {
+    return pair_fuse(A, a, b, ca, sa, lim, nullptr, nullptr);
 }
 
 // MG_SPLIT lanes of one wavefront share a segment and take every
@@ -212,7 +229,6 @@ __device__ inline double pair_chi2(const MgArgs &A, int a, int b, double ca, dou
 // any of the segment's lanes has found on the candidate's side (shared
 // after each chunk), or the cut: a pair whose (t, w) chi2 alone is above it
 // by more than rounding (TPC_MG_SLACK) can neither be nor tie the best.
-#define TPC_MG_SLACK 1.000001
 #define MG_SPLIT 4
 #define MG_CHUNK 64
 #define MG_LANE_CHUNK (MG_CHUNK / MG_SPLIT)
@@ -278,13 +294,13 @@ __global__ void __launch_bounds__(TPC_BLOCK) mg_best(MgArgs A) {
                         const int j = cand[k][threadIdx.x];
                         const double rj = hypot((double)A.x[j], (double)A.par[(size_t)j * 5]);
                         if (ri < rj) {                        // j outside: an outer partner
-                            const double chi = pair_chi2(A, i, j, cda, sda);
+                            const double chi = pair_chi2(A, i, j, cda, sda, fmin(lo, co));
                             if (chi <= A.cut && (chi < co || (chi == co && j < bo))) {
                                 co = chi;
                                 bo = j;
                             }
                         } else if (rj < ri) {                 // an inner partner
-                            const double chi = pair_chi2(A, j, i, cdb, sdb);
+                            const double chi = pair_chi2(A, j, i, cdb, sdb, fmin(li, ci_));
                             if (chi <= A.cut && (chi < ci_ || (chi == ci_ && j < bi))) {
                                 ci_ = chi;
                                 bi = j;
@@ -330,7 +346,7 @@ __global__ void __launch_bounds__(TPC_BLOCK) mg_link_next(MgArgs A) {
             for (int q = 0; q < 15; ++q) mc[q] = 0.f;
             if (linked) {
                 const double da = turn_angle(A.sector[a], A.sector[b], A.n_sectors);
-                pair_fuse(A, a, b, cos(da), sin(da), mp, mc);
+                pair_fuse(A, a, b, cos(da), sin(da), INFINITY, mp, mc);
             }
         }
     }
@@ -522,6 +538,7 @@ __global__ void __launch_bounds__(TPC_BLOCK) lg_best(MgArgs A) {
                 // this lane's candidates: q = sub (mod LG_SPLIT) in [q0, q1)
                 const double bound = lim * TPC_MG_SLACK;
                 int cnt = 0;
+#pragma unroll 4
                 for (int q = q0 + ((sub - q0 % LG_SPLIT + LG_SPLIT) % LG_SPLIT); q < q1; q += LG_SPLIT) {
                     const double dk = ci.m[2] + tile.m[2][q], dt = ci.m[3] + tile.m[3][q];
                     const double S22 = ci.s22 + tile.s[5][q], S32 = ci.s32 + tile.s[8][q], S33 = ci.s33 + tile.s[9][q];

@@ -123,18 +123,37 @@ __global__ void __launch_bounds__(TPC_BLOCK) rf_ids_final(RfArgs A) {
 // ---------------------------------------------------------------------------
 // chain refit
 
+// A segment walked inwards: its hits' ids, rows and map rows.
+struct RfSeg {
+    const int32_t *hits;
+    const float *map;      // rows of its sector, or null
+    int row0;
+};
+
+__device__ inline RfSeg rf_seg(const RfArgs &A, int g) {
+    return RfSeg{A.hits + A.offsets[g], A.map ? A.map + (size_t)A.sector[g] * A.n_rows * 2 : nullptr,
+                 A.first_row[g]};
+}
+
+// Hit k of the segment with cluster id c: plane and coordinates.
+struct RfHit {
+    float x, y, z, dy, dz;
+    __device__ double my() const { return (double)y - (double)dy; }
+    __device__ double mz() const { return (double)z - (double)dz; }
+};
+
+__device__ inline RfHit rf_load(const RfArgs &A, const RfSeg &S, int k, int32_t c) {
+    const int r = S.row0 + k;
+    return RfHit{A.row_x[r], A.y[c], A.z[c], S.map ? S.map[2 * r] : 0.f, S.map ? S.map[2 * r + 1] : 0.f};
+}
+
 // Measurement of hit k of segment g in its own frame (map-corrected).
 __device__ inline void rf_hit(const RfArgs &A, int g, int k, double &x, double &my, double &mz) {
-    const int r = A.first_row[g] + k;
-    const int c = A.hits[A.offsets[g] + k];
-    x = (double)A.row_x[r];
-    my = (double)A.y[c];
-    mz = (double)A.z[c];
-    if (A.map) {
-        const float *m = A.map + ((size_t)A.sector[g] * A.n_rows + r) * 2;
-        my -= (double)m[0];
-        mz -= (double)m[1];
-    }
+    const RfSeg S = rf_seg(A, g);
+    const RfHit h = rf_load(A, S, k, S.hits[k]);
+    x = (double)h.x;
+    my = h.my();
+    mz = h.mz();
 }
 
 __device__ inline bool rf_sane(const RfArgs &A, int g) {
@@ -142,9 +161,10 @@ __device__ inline bool rf_sane(const RfArgs &A, int g) {
     if (!(m >= 1 && r0 >= 0 && r0 + m <= A.n_rows && s >= 0 && s < A.n_sectors && o0 >= 0 &&
           o0 <= A.cap_hits - m))
         return false;
-    for (int k = 0; k < m; ++k)
-        if ((uint32_t)A.hits[o0 + k] >= (uint32_t)A.n_clusters) return false;
-    return true;
+    bool ok = true;                                  // (no early exit: the loads overlap)
+#pragma unroll 8
+    for (int k = 0; k < m; ++k) ok = (int)ok & (int)((uint32_t)A.hits[o0 + k] < (uint32_t)A.n_clusters);
+    return ok;
 }
 
 // The state p at plane x, rotated into the frame turned by da (cos ca, sin
@@ -156,17 +176,19 @@ __device__ inline bool rf_transfer(double p[5], double x, double ca, double sa, 
                                    float max_sin, double J[3][5]) {
     const double y = p[0], s = p[2], t = p[3], w = p[4];
     if (!(fabs(s) < 1.0)) return false;
-    const double c = sqrt(1.0 - s * s);
+    double ic, ic2;
+    const double c = sqrt_pos(fma(-s, s, 1.0), &ic);
     if (!(c * ca + s * sa > 0.0)) return false;
     const double x1 = x * ca + y * sa;
     p[0] = -x * sa + y * ca;
     p[2] = s * ca - c * sa;
     StepJac F;
     if (!helix_step<double, double>(p, xt - x1, kbz, max_sin, F)) return false;
-    const double r22 = ca + s / c * sa;
-    const double s2 = p[2], c2 = sqrt(1.0 - s2 * s2), kap = kbz * w;
-    J[0][0] = ca - sa * s2 / c2; J[0][1] = 0.0; J[0][2] = F.f02 * r22; J[0][3] = 0.0;   J[0][4] = F.f04;
-    J[1][0] = -sa * t / c2;      J[1][1] = 1.0; J[1][2] = F.f12 * r22; J[1][3] = F.f13; J[1][4] = F.f14;
+    const double r22 = ca + s * ic * sa;
+    const double s2 = p[2], kap = kbz * w;
+    sqrt_pos(fma(-s2, s2, 1.0), &ic2);
+    J[0][0] = ca - sa * s2 * ic2; J[0][1] = 0.0; J[0][2] = F.f02 * r22; J[0][3] = 0.0;   J[0][4] = F.f04;
+    J[1][0] = -sa * t * ic2;     J[1][1] = 1.0; J[1][2] = F.f12 * r22; J[1][3] = F.f13; J[1][4] = F.f14;
     J[2][0] = -sa * kap;         J[2][1] = 0.0; J[2][2] = r22;         J[2][3] = 0.0;   J[2][4] = F.f24;
     return true;
 }
@@ -222,9 +244,18 @@ __device__ inline void rf_write(const RfArgs &A, int i, float x, const double p[
     A.out.status[i] = status;
 }
 
-__global__ void __launch_bounds__(TPC_BLOCK) rf_chains(RfArgs A) {
+// Workgroups of one wavefront, as in the other fits of fewer seeds than the
+// chip has lanes.
+__global__ void __launch_bounds__(TPC_WAVE) rf_chains(RfArgs A) {
+    __shared__ double ang[18][2];                     // cosine, sine of the sector angles
+    if (threadIdx.x < 18) {
+        const double al = sector_angle(threadIdx.x, A.n_sectors);
+        ang[threadIdx.x][0] = cos(al);
+        ang[threadIdx.x][1] = sin(al);
+    }
+    __syncthreads();
     const int T = rf_count(A);
-    for (int h = blockIdx.x * TPC_BLOCK + threadIdx.x; h < T; h += gridDim.x * TPC_BLOCK) {
+    for (int h = blockIdx.x * TPC_WAVE + threadIdx.x; h < T; h += gridDim.x * TPC_WAVE) {
         double p[5] = {0, 0, 0, 0, 0};
         SymT<double> C = {};
         if (A.status[h] != 0 || prev_link(A, T, h) >= 0) {
@@ -287,15 +318,20 @@ __global__ void __launch_bounds__(TPC_BLOCK) rf_chains(RfArgs A) {
         C.c33 = A.var_t;
         C.c44 = A.var_w;
         double chi2 = 0.0, xcur = xa;
-        // inwards from the tail's outermost hit
+        // inwards from the tail's outermost hit; within a segment a hit's
+        // coordinates are read a step ahead and its id two
         int g = tail, k = mt - 1;
+        RfSeg S = rf_seg(A, g);
+        RfHit nx = rf_load(A, S, k > 0 ? k - 1 : 0, S.hits[k > 0 ? k - 1 : 0]);
+        int32_t id = S.hits[k > 1 ? k - 2 : 0];
         while (status == TPC_FIT_OK) {
-            double xk, my, mz;
+            RfHit hk = nx;
             if (k > 0) {
                 --k;
-                rf_hit(A, g, k, xk, my, mz);
+                nx = rf_load(A, S, k > 0 ? k - 1 : 0, id);
+                id = S.hits[k > 1 ? k - 2 : 0];
                 StepJac F;
-                if (!helix_step<double, double>(p, xk - xcur, A.kbz, A.max_sin, F)) {
+                if (!helix_step<double, double>(p, (double)hk.x - xcur, A.kbz, A.max_sin, F)) {
                     status = TPC_FIT_SIN_FAIL;
                     break;
                 }
@@ -303,26 +339,27 @@ __global__ void __launch_bounds__(TPC_BLOCK) rf_chains(RfArgs A) {
             } else {
                 const int gp = prev_link(A, T, g);
                 if (gp < 0) break;
-                double da = sector_angle(A.sector[gp], A.n_sectors) - sector_angle(A.sector[g], A.n_sectors);
-                const double pi = 3.14159265358979323846;
-                if (da > pi) da -= 2.0 * pi;
-                if (da < -pi) da += 2.0 * pi;
+                // the turn from g's sector to gp's, from the sectors' own angles
+                const double *ca = ang[A.sector[gp] % 18], *cb = ang[A.sector[g] % 18];
+                const double cda = ca[0] * cb[0] + ca[1] * cb[1], sda = ca[1] * cb[0] - ca[0] * cb[1];
                 g = gp;
+                S = rf_seg(A, g);
                 k = A.offsets[g + 1] - A.offsets[g] - 1;
-                rf_hit(A, g, k, xk, my, mz);
+                hk = rf_load(A, S, k, S.hits[k]);
+                nx = rf_load(A, S, k > 0 ? k - 1 : 0, S.hits[k > 0 ? k - 1 : 0]);
+                id = S.hits[k > 1 ? k - 2 : 0];
                 double J[3][5];
-                if (!rf_transfer(p, xcur, cos(da), sin(da), xk, A.kbz, A.max_sin, J)) {
+                if (!rf_transfer(p, xcur, cda, sda, (double)hk.x, A.kbz, A.max_sin, J)) {
                     status = TPC_FIT_SIN_FAIL;
                     break;
                 }
                 rf_transport(C, J);
             }
-            xcur = xk;
-            const double dchi = kalman_update<double>(p, C, my, mz, A.vy, A.vz);
+            xcur = (double)hk.x;
+            const double dchi = kalman_update<double>(p, C, hk.my(), hk.mz(), A.vy, A.vz);
             chi2 += dchi;
-            bool finite = dchi >= 0.0 && isfinite(chi2);
-            for (int q = 0; q < 5; ++q) finite = finite && isfinite(p[q]);
-            if (!finite) status = TPC_FIT_NUM_FAIL;
+            const double chk = chi2 + p[0] + p[1] + p[2] + p[3] + p[4];
+            if (!((int)(dchi >= 0.0) & (int)(chk - chk == 0.0))) status = TPC_FIT_NUM_FAIL;
         }
         rf_write(A, h, (float)xcur, p, C, chi2, 2 * n - 5, status);
     }
@@ -530,7 +567,9 @@ hipError_t launch_refit(const tpc_context *ctx, const tpc_frames *fr, const tpc_
     hipLaunchKernelGGL(rf_ids_init, dim3(g), dim3(TPC_BLOCK), 0, st, A);
     hipLaunchKernelGGL(rf_ids_union, dim3(g), dim3(TPC_BLOCK), 0, st, A);
     hipLaunchKernelGGL(rf_ids_final, dim3(g), dim3(TPC_BLOCK), 0, st, A);
-    hipLaunchKernelGGL(rf_chains, dim3(g), dim3(TPC_BLOCK), 0, st, A);
+    int gc = (sd->cap_seeds + TPC_WAVE - 1) / TPC_WAVE;
+    gc = gc < 1 ? 1 : (gc > 16384 ? 16384 : gc);
+    hipLaunchKernelGGL(rf_chains, dim3(gc), dim3(TPC_WAVE), 0, st, A);
     if (loop_par) hipLaunchKernelGGL(rf_loops, dim3(g), dim3(TPC_BLOCK), 0, st, A);
     return hipGetLastError();
 }

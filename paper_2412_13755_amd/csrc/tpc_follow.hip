@@ -4,9 +4,10 @@
 // longer one are marked as duplicates.
 //
 //  fl_index        workgroup per (frame, sector, row): the row's clusters in
-//                  y cells (about one cluster per cell, counting sort with
-//                  atomics in global memory); non-finite clusters are left out
-//                  (they can never pass the gate)
+//                  y cells (about one cluster per cell, a counting sort);
+//                  non-finite clusters are left out (they can never pass the
+//                  gate)
+//  fl_order        the seeds of each window of 1024 by descending length
 //  fl_tracks       thread per seed, double precision throughout: seed fit
 //                  (the seed's hits at the rows that hold them, so seeds may
 //                  skip rows), inward prolongation, outward refit and
@@ -26,9 +27,8 @@ namespace {
 struct FlIndex {
     float2 *grid;                 // [NR] (y0, cells per cm) of the segment's y cells
     int32_t *cstart;              // [N + NR] cell starts of segment s at row_offsets[s] + s (n + 1 entries)
-    int32_t *cur;                 // [N + NR] scatter cursors
-    float2 *syz;                  // [N] (y, z) ordered by cell within each segment
-    int32_t *sid;                 // [N] their global ids
+    int32_t *cur;                 // [N + NR] scatter cursors (rows of more than FL_LDS_ROW only)
+    float4 *sc;                   // [N] (y, z, global id) ordered by cell within each segment
     float2 *yz;                   // [N] (y, z) by global id: one gather per hit
     unsigned long long *owner;    // [N] smallest key of a track holding the cluster
 };
@@ -40,6 +40,8 @@ struct FlArgs {
     int32_t n_frames;
     FlIndex X;
     int32_t *rows;                // [cap_seeds][n_rows] cluster per pad row, -1 for none
+    const int32_t *order;         // seeds longest first within each window of FL_WINDOW ...
+    int64_t cap_order;            // ... if there are at most so many (else in their own order)
     double kbz;                   // -c Bz in double precision
     double gate;
     int32_t max_miss;
@@ -52,12 +54,16 @@ __device__ inline int ycell(float y, float y0, float iw, int n) {
     return (int)c;
 }
 
+// Rows of up to FL_LDS_ROW clusters are counted and placed in LDS (8 KB),
+// longer ones with atomics in global memory (50 -> 25 us for an event).
+#define FL_LDS_ROW 2048
 __global__ void __launch_bounds__(TPC_BLOCK)
 fl_index(const int32_t *__restrict__ off, const float *__restrict__ y, const float *__restrict__ z,
          FlIndex X) {
     __shared__ float red[2][TPC_BLOCK / TPC_WAVE];
     __shared__ int sh[TPC_BLOCK / TPC_WAVE];
     __shared__ int carry;
+    __shared__ int lcs[FL_LDS_ROW + 1];
     const int seg = xcd_item(blockIdx.x, gridDim.x);
     const int a = off[seg], n = off[seg + 1] - a;
     const int base = a + seg;
@@ -77,7 +83,12 @@ fl_index(const int32_t *__restrict__ off, const float *__restrict__ y, const flo
         red[0][wid] = lo;
         red[1][wid] = hi;
     }
-    for (int j = threadIdx.x; j <= n; j += TPC_BLOCK) X.cstart[base + j] = 0;
+    const bool lds = n <= FL_LDS_ROW;
+    int32_t *cs = X.cstart + base, *cu = X.cur + base;
+    for (int j = threadIdx.x; j <= n; j += TPC_BLOCK) {
+        if (lds) lcs[j] = 0;
+        else cs[j] = 0;
+    }
     if (threadIdx.x == 0) carry = 0;
     __syncthreads();
 #pragma unroll
@@ -90,29 +101,34 @@ fl_index(const int32_t *__restrict__ off, const float *__restrict__ y, const flo
     if (threadIdx.x == 0) X.grid[seg] = make_float2(y0, iw);
     for (int j = threadIdx.x; j < n; j += TPC_BLOCK) {
         const float v = y[a + j], w = z[a + j];
-        if (isfinite(v) && isfinite(w)) atomicAdd(&X.cstart[base + ycell(v, y0, iw, n)], 1);
+        if (isfinite(v) && isfinite(w)) {
+            const int c = ycell(v, y0, iw, n);
+            if (lds) atomicAdd(&lcs[c], 1);
+            else atomicAdd(&cs[c], 1);
+        }
     }
     __syncthreads();
     for (int c0 = 0; c0 <= n; c0 += TPC_BLOCK) {
         const int j = c0 + threadIdx.x;
-        const int v = j <= n ? X.cstart[base + j] : 0;
+        const int v = j <= n ? (lds ? lcs[j] : cs[j]) : 0;
         int tot;
         const int ex = block_exclusive_scan(v, sh, &tot);
-        const int cr = carry;
+        const int st = carry + ex;
         if (j <= n) {
-            X.cstart[base + j] = cr + ex;
-            X.cur[base + j] = cr + ex;
+            cs[j] = st;
+            if (lds) lcs[j] = st;
+            else cu[j] = st;
         }
         __syncthreads();
-        if (threadIdx.x == 0) carry = cr + tot;
+        if (threadIdx.x == 0) carry += tot;
         __syncthreads();
     }
     for (int j = threadIdx.x; j < n; j += TPC_BLOCK) {
         const float v = y[a + j], w = z[a + j];
         if (isfinite(v) && isfinite(w)) {
-            const int pos = atomicAdd(&X.cur[base + ycell(v, y0, iw, n)], 1);
-            X.syz[a + pos] = make_float2(v, w);
-            X.sid[a + pos] = a + j;
+            const int c = ycell(v, y0, iw, n);
+            const int pos = lds ? atomicAdd(&lcs[c], 1) : atomicAdd(&cu[c], 1);
+            X.sc[a + pos] = make_float4(v, w, __int_as_float(a + j), 0.f);
         }
     }
 }
@@ -144,10 +160,18 @@ __device__ inline RowSeg row_seg(const FlArgs &A, int seg, int r) {
     return s;
 }
 
+// Half-extent of the gate ellipse along an axis of variance S, sqrt(gate S),
+// widened so that float rounding of it, of the cell bounds and of a float
+// difference to v cannot exclude a cluster.
+__device__ inline float gate_half(const FlArgs &A, double S, double v) {
+    return __builtin_amdgcn_sqrtf((float)(A.gate * S)) * 1.00001f + 1e-5f * (1.0f + fabsf((float)v));
+}
+
 // Cluster of segment `seg` with the smallest predicted-residual chi2 against
 // (p, C), ties to the smaller id; -1 if none is within the gate.  Only the
-// cells covering the gate ellipse's y extent, sqrt(gate * S_yy), are read,
-// widened so that float rounding of the bounds cannot exclude a cluster.
+// cells covering the gate ellipse's y extent are read, each cluster while
+// the one before it is tested; those outside the ellipse's bounding box
+// (single precision, widened) are dropped before the chi2 is formed.
 __device__ inline int pick_cluster(const FlArgs &A, int seg, const RowSeg &rs, const double p[5],
                                    const SymT<double> &C, float2 &yz) {
     const int a = rs.a, n = rs.n;
@@ -155,29 +179,40 @@ __device__ inline int pick_cluster(const FlArgs &A, int seg, const RowSeg &rs, c
     const double S00 = C.c00 + A.F.vy, S01 = C.c10, S11 = C.c11 + A.F.vz;
     const double det = S00 * S11 - S01 * S01;
     if (!(det > 0.0)) return -1;
-    const double idet = 1.0 / det;
-    const double i00 = S11 * idet, i01 = -S01 * idet, i11 = S00 * idet;
-    const double hy = sqrt(A.gate * S00) * (1.0 + 1e-6) + 1e-5 * (1.0 + fabs(p[0]));
-    const int c0 = ycell((float)(p[0] - hy), rs.g.x, rs.g.y, n);
-    const int c1 = ycell((float)(p[0] + hy), rs.g.x, rs.g.y, n);
-    const int base = a + seg;
-    const int j0 = A.X.cstart[base + c0], j1 = A.X.cstart[base + c1 + 1];
+    const float py = (float)p[0], pz = (float)p[1];
+    const float hy = gate_half(A, S00, p[0]), hz = gate_half(A, S11, p[1]);
+    const int32_t *cs = A.X.cstart + a + seg;
+    const int j0 = cs[ycell(py - hy, rs.g.x, rs.g.y, n)], j1 = cs[ycell(py + hy, rs.g.x, rs.g.y, n) + 1];
     int best = -1;
     double bchi = 0.0;
+    if (j0 >= j1) return best;
+    const float4 *sc = A.X.sc + a;
+    const double idet = recip_pos(det);
+    const double i00 = S11 * idet, i01 = -S01 * idet, i11 = S00 * idet;
+    float4 c = sc[j0];
     for (int j = j0; j < j1; ++j) {
-        const float2 c = A.X.syz[a + j];
-        const int id = A.X.sid[a + j];
-        const double r0 = (double)c.x - p[0], r1 = (double)c.y - p[1];
+        const float4 q = c;
+        c = sc[j + 1 < j1 ? j + 1 : j];
+        if (!((int)(fabsf(q.x - py) <= hy) & (int)(fabsf(q.y - pz) <= hz))) continue;
+        const int id = __float_as_int(q.z);
+        const double r0 = (double)q.x - p[0], r1 = (double)q.y - p[1];
         const double chi = r0 * (i00 * r0 + i01 * r1) + r1 * (i01 * r0 + i11 * r1);
         if (chi <= A.gate && (best < 0 || chi < bchi || (chi == bchi && id < best))) {
             best = id;
             bchi = chi;
-            yz = c;
+            yz = make_float2(q.x, q.y);
         }
     }
     return best;
 }
 
+// Reads that only bring their cache line near: the search of a row is two
+// dependent reads of lines that this XCD has mostly not seen (cell starts,
+// then clusters), and a wavefront waits for its slowest lane.  After each
+// row the line of the cell starts three rows on and, from the cell start
+// read so a row before, the clusters two rows on are fetched at the
+// linearly extrapolated y.
+__device__ inline void touched(int v) { asm volatile("" ::"v"(v)); }
 __device__ inline void start_cov(const FitArgs &F, SymT<double> &C) {
     C = SymT<double>{};
     C.c00 = F.vy;
@@ -190,8 +225,8 @@ __device__ inline void start_cov(const FitArgs &F, SymT<double> &C) {
 // One prolongation row: helix step to the row's plane, stop (false) if it
 // fails or leaves the row's width; pick = cluster taken up (state updated)
 // or -1.
-__device__ inline bool follow_row(const FlArgs &A, int seg, const RowSeg &rs, double p[5],
-                                  SymT<double> &C, double &xcur, int &pick) {
+__device__ inline bool follow_row(const FlArgs &A, int seg, const RowSeg &rs, double p[5], SymT<double> &C,
+                                  double &xcur, int &pick) {
     pick = -1;
     StepJac J;
     const double xr = (double)rs.x;
@@ -199,7 +234,7 @@ __device__ inline bool follow_row(const FlArgs &A, int seg, const RowSeg &rs, do
     sym_transport<double, false>(C, J);
     xcur = xr;
     if (!(fabs(p[0]) <= xr * TPC_TAN10)) return false;
-    float2 yz;
+    float2 yz = make_float2(0.f, 0.f);
     const int c = pick_cluster(A, seg, rs, p, C, yz);
     if (c < 0) return true;
     const double dchi = kalman_update<double>(p, C, (double)yz.x, (double)yz.y, A.F.vy, A.F.vz);
@@ -219,13 +254,16 @@ __device__ inline int prolong(const FlArgs &A, const Strip &S, int seg0, int fro
     int last = from, miss = 0;
     int r = from + dir;
     if (r < 0 || r >= R) return last;
-    RowSeg nx = row_seg(A, seg0 + r, r);
+    auto seg_at = [&](int q) {
+        q = q < 0 ? 0 : (q < R ? q : R - 1);
+        return row_seg(A, seg0 + q, q);
+    };
+    RowSeg s0 = seg_at(r), s1 = seg_at(r + dir), s2 = seg_at(r + 2 * dir), s3 = seg_at(r + 3 * dir);
+    int start = -1, line = 0;
     for (; r >= 0 && r < R; r += dir) {
-        const RowSeg cs = nx;
-        const int rn = r + dir;
-        if (rn >= 0 && rn < R) nx = row_seg(A, seg0 + rn, rn);      // one row ahead
+        const double y0 = p[0];
         int pick;
-        if (!follow_row(A, seg0 + r, cs, p, C, xcur, pick)) break;
+        if (!follow_row(A, seg0 + r, s0, p, C, xcur, pick)) break;
         if (pick >= 0) {
             S.set(r, pick);
             last = r;
@@ -235,7 +273,18 @@ __device__ inline int prolong(const FlArgs &A, const Strip &S, int seg0, int fro
         } else if (++miss > A.max_miss) {
             break;
         }
+        touched(line);
+        if (start >= 0 && s2.n > 0) line = __float_as_int(A.X.sc[s2.a + (start < s2.n ? start : s2.n - 1)].x);
+        const int q3 = r + 3 * dir;
+        start = -1;
+        if (s3.n > 0 && q3 >= 0 && q3 < R)
+            start = A.X.cstart[s3.a + seg0 + q3 + ycell((float)(p[0] + 3.0 * (p[0] - y0)), s3.g.x, s3.g.y, s3.n)];
+        s0 = s1;
+        s1 = s2;
+        s2 = s3;
+        s3 = seg_at(r + 4 * dir);
     }
+    touched(line);
     return last;
 }
 
@@ -421,11 +470,44 @@ __device__ inline void follow_one(const FlArgs &A, int i, const Strip &S) {
     write_track(F, i, xcur, p, C, chi2, m, status);
 }
 
-// One wavefront per workgroup; lane t follows seed i0 + t of each round,
-// then the workgroup writes the round's rows out row-contiguously.
+// Order of the seeds: within each window of FL_WINDOW consecutive ones by
+// descending length (a counting sort in LDS).  A wavefront takes as long as
+// the longest of its lanes in each phase: a long seed has many steps to fit
+// and few rows to prolong over, a short one the reverse, so mixed lanes pay
+// for both.  Windows of a sector's size keep the lanes' clusters together.
+#define FL_WINDOW 1024
+__global__ void __launch_bounds__(FL_WINDOW)
+fl_order(const int32_t *__restrict__ n_seeds, int32_t cap, const int32_t *__restrict__ offsets,
+         int32_t *__restrict__ order, int64_t cap_order) {
+    __shared__ int32_t cnt[TPC_MAX_ROWS + 1];
+    __shared__ int32_t all;
+    const int T = *n_seeds < cap ? *n_seeds : cap;
+    if (T > cap_order) return;
+    for (int i0 = blockIdx.x * FL_WINDOW; i0 < T; i0 += gridDim.x * FL_WINDOW) {
+        const int i = i0 + threadIdx.x;
+        for (int b = threadIdx.x; b <= TPC_MAX_ROWS; b += FL_WINDOW) cnt[b] = 0;
+        __syncthreads();
+        int n = 0;
+        if (i < T) {
+            n = offsets[i + 1] - offsets[i];
+            n = n < 0 ? 0 : (n < TPC_MAX_ROWS ? n : TPC_MAX_ROWS);
+            atomicAdd(&cnt[n], 1);
+        }
+        __syncthreads();
+        if (threadIdx.x < TPC_WAVE) len_starts_wave(cnt, &all);
+        __syncthreads();
+        if (i < T) order[i0 + atomicAdd(&cnt[n], 1)] = i;
+        __syncthreads();
+    }
+}
+
+// One wavefront per workgroup; lane t follows seed i0 + t of the order in
+// each round, then the workgroup writes the round's rows out
+// row-contiguously.
 __global__ void __launch_bounds__(TPC_WAVE)
 fl_tracks(FlArgs A) {
     extern __shared__ int32_t fl_strip[];
+    __shared__ int32_t seed[TPC_WAVE];
     const int t = threadIdx.x;
     const int R = A.F.n_rows;
     const Strip S{fl_strip, t};
@@ -437,13 +519,17 @@ fl_tracks(FlArgs A) {
     G = G < (int)gridDim.x ? G : (int)gridDim.x;
     if ((int)blockIdx.x >= G) return;
     for (int i0 = xcd_item(blockIdx.x, G) * TPC_WAVE; i0 < T; i0 += G * TPC_WAVE) {
-        if (i0 + t < T) follow_one(A, i0 + t, S);
+        const bool ordered = T <= A.cap_order;
+        if (i0 + t < T) {
+            const int i = ordered ? A.order[i0 + t] : i0 + t;
+            seed[t] = i;
+            follow_one(A, i, S);
+        }
         __syncthreads();
         const int nt = T - i0 < TPC_WAVE ? T - i0 : TPC_WAVE;
-        int32_t *out = A.rows + (size_t)i0 * R;
-        for (int e = t; e < nt * R; e += TPC_WAVE) {
-            const int u = e / R, r = e - u * R;
-            out[e] = fl_strip[r * TPC_WAVE + (u ^ (r & 31))];
+        for (int u = 0; u < nt; ++u) {
+            int32_t *out = A.rows + (size_t)seed[u] * R;
+            for (int r = t; r < R; r += TPC_WAVE) out[r] = fl_strip[r * TPC_WAVE + (u ^ (r & 31))];
         }
         __syncthreads();
     }
@@ -520,8 +606,7 @@ size_t follow_ws_layout(void *ws, int64_t N, int64_t NR, void *out) {
     X.grid = w.take<float2>(NR > 0 ? NR : 1);
     X.cstart = w.take<int32_t>(N + NR + 1);
     X.cur = w.take<int32_t>(N + NR + 1);
-    X.syz = w.take<float2>(N > 0 ? N : 1);
-    X.sid = w.take<int32_t>(N > 0 ? N : 1);
+    X.sc = w.take<float4>(N > 0 ? N : 1);
     X.yz = w.take<float2>(N > 0 ? N : 1);
     X.owner = w.take<unsigned long long>(N > 0 ? N : 1);
     if (out) *static_cast<FlIndex *>(out) = X;
@@ -546,6 +631,14 @@ hipError_t launch_follow(const tpc_context *ctx, const tpc_frames *fr, const tpc
     A.max_miss = max_miss;
     hipLaunchKernelGGL(fl_index, dim3((unsigned)NR), dim3(TPC_BLOCK), 0, st, fr->row_offsets, fr->y,
                        fr->z, A.X);
+    // the order lives in the owner keys' buffer until those are initialised
+    int32_t *order = reinterpret_cast<int32_t *>(A.X.owner);
+    A.order = order;
+    A.cap_order = 2 * (int64_t)fr->n_clusters;
+    int ob = (sd->cap_seeds + FL_WINDOW - 1) / FL_WINDOW;
+    ob = ob > 1024 ? 1024 : (ob < 1 ? 1 : ob);
+    hipLaunchKernelGGL(fl_order, dim3(ob), dim3(FL_WINDOW), 0, st, sd->n_seeds, sd->cap_seeds, sd->offsets, order,
+                       A.cap_order);
     int tb = (int)((sd->cap_seeds + TPC_WAVE - 1) / TPC_WAVE);
     tb = tb > 16384 ? 16384 : (tb < 1 ? 1 : tb);
     hipLaunchKernelGGL(fl_tracks, dim3(tb), dim3(TPC_WAVE), (size_t)c.n_rows * TPC_WAVE * sizeof(int32_t), st, A);

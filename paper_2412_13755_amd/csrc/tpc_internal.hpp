@@ -262,6 +262,34 @@ __device__ inline int seg_size_key(const int32_t *off, int s) {
     return off[s + 1] == off[s] ? 0 : 1 + (b < TPC_ORDER_BINS - 1 ? b : TPC_ORDER_BINS - 1);
 }
 
+// Minimum over the wavefront, valid in its last lane: six cross-lane operands
+// (DPP) and no LDS round trips.  (row_shr 1, 2, 4, 8 within each row of 16
+// lanes, then row_bcast 15 into rows 1 and 3 and row_bcast 31 into 2 and 3.)
+__device__ inline int lane63_min(int v) {
+    constexpr int top = 0x7FFFFFFF;
+    v = min(v, __builtin_amdgcn_update_dpp(top, v, 0x111, 0xF, 0xF, false));
+    v = min(v, __builtin_amdgcn_update_dpp(top, v, 0x112, 0xF, 0xF, false));
+    v = min(v, __builtin_amdgcn_update_dpp(top, v, 0x114, 0xF, 0xF, false));
+    v = min(v, __builtin_amdgcn_update_dpp(top, v, 0x118, 0xF, 0xF, false));
+    v = min(v, __builtin_amdgcn_update_dpp(top, v, 0x142, 0xA, 0xF, false));
+    return min(v, __builtin_amdgcn_update_dpp(top, v, 0x143, 0xC, 0xF, false));
+}
+
+// Inclusive sum over the lanes below and this one, by the same operands.
+__device__ inline int lane_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+    return v + __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+}
+
+// Bits of m below this lane's.
+__device__ inline int lanes_below(uint64_t m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
 __device__ inline float wave_min(float v) {
 #pragma unroll
     for (int d = TPC_WAVE / 2; d > 0; d >>= 1) v = fminf(v, __shfl_xor(v, d, TPC_WAVE));

@@ -446,19 +446,16 @@ __device__ inline Best best_pair(float yh, float zh, FP UY, FP UZ, IP UI, CP UCS
 #ifndef TPC_LDS_CELLS
 #define TPC_LDS_CELLS 2048
 #endif
-#define TPC_LDS_ROW_S 512
-#define TPC_LDS_CELLS_S 1024
 
 template <int ROW, int CELLS>
 struct PairLdsT {
     float y[2 * ROW], z[2 * ROW];
     uint16_t rel[2 * ROW];                  // cluster id minus its row's first id
-    int32_t cs[2 * CELLS + 2];              // cell starts of both rows, concatenated
+    alignas(16) int32_t cs[2 * CELLS];      // cell starts of both rows (< CELLS each), concatenated
     float red[8][TPC_BLOCK / TPC_WAVE];
     int scan_sh[TPC_BLOCK / TPC_WAVE];
 };
 using PairLds = PairLdsT<TPC_LDS_ROW, TPC_LDS_CELLS>;
-using PairLdsSmall = PairLdsT<TPC_LDS_ROW_S, TPC_LDS_CELLS_S>;
 
 // Bins a down row of n0 clusters and an up row of n1 clusters with one LDS
 // counting sort over the concatenated cell range (whole workgroup; contains
@@ -475,7 +472,7 @@ template <int CELLS>
 __device__ inline SegGrid pair_grid(float ymin, float ymax, float zmin, float zmax, int n, float win_y,
                                     float win_z, float edge) {
     if (n == 0) return SegGrid{0.f, 0.f, 0.f, 0.f, 0, 0, 0, 0};
-    const int cap = 4 * n < CELLS ? 4 * n : CELLS;
+    const int cap = 4 * n < CELLS ? 4 * n : CELLS - 1;
     return row_grid(ymin, ymax, zmin, zmax, cap, cap, win_y, win_z, edge);
 }
 
@@ -513,9 +510,13 @@ __device__ inline void pair_bin(const Src &src, int n0, int n1, float win_y, flo
                                 PairLdsT<ROW, CELLS> &L, SegGrid &gd, SegGrid &gu, int &C0) {
 #pragma clang fp contract(off)
     constexpr int PT = 2 * ROW / TPC_BLOCK;      // row-pair clusters per thread
+    constexpr int PC = 2 * CELLS / TPC_BLOCK;    // cell words per thread
+    static_assert(PC % 4 == 0, "cell words in 16-byte groups");
     const int tid = threadIdx.x;
     const int nt = n0 + n1;
-    // both rows are read once, into registers (one global round trip)
+    // both rows are read once, into registers (one global round trip); the
+    // groups of TPC_BLOCK clusters that the pair does not reach are skipped
+    // by the whole workgroup
     float vy[PT], vz[PT];
     uint16_t vr[PT];
 #pragma unroll
@@ -524,12 +525,16 @@ __device__ inline void pair_bin(const Src &src, int n0, int n1, float win_y, flo
         vy[j] = 0.f;
         vz[j] = 0.f;
         vr[j] = 0;
-        if (k < nt) src(k, vy[j], vz[j], vr[j]);
+        if (j * TPC_BLOCK < nt && k < nt) src(k, vy[j], vz[j], vr[j]);
     }
+    int4 *cs4 = reinterpret_cast<int4 *>(L.cs) + tid * (PC / 4);
+#pragma unroll
+    for (int q = 0; q < PC / 4; ++q) cs4[q] = make_int4(0, 0, 0, 0);
     // finite extents of both rows
     float e[8] = {INFINITY, -INFINITY, INFINITY, -INFINITY, INFINITY, -INFINITY, INFINITY, -INFINITY};
 #pragma unroll
     for (int j = 0; j < PT; ++j) {
+        if (j * TPC_BLOCK >= nt) break;
         const int k = tid + j * TPC_BLOCK;
         const bool fy = k < nt && isfinite(vy[j]), fz = k < nt && isfinite(vz[j]);
         if (k < n0) {
@@ -559,36 +564,45 @@ __device__ inline void pair_bin(const Src &src, int n0, int n1, float win_y, flo
     gd = pair_grid<CELLS>(e[0], e[1], e[2], e[3], n0, win_y, win_z, edge_d);
     gu = pair_grid<CELLS>(e[4], e[5], e[6], e[7], n1, win_y, win_z, edge_u);
     C0 = gd.ny * gd.nz;
-    const int C = C0 + gu.ny * gu.nz;
-    for (int c = tid; c < C + 2; c += TPC_BLOCK) L.cs[c] = 0;
-    __syncthreads();
     // count cell c into cs[c + 2]
     int cell[PT];
 #pragma unroll
     for (int j = 0; j < PT; ++j) {
+        cell[j] = 0;
+        if (j * TPC_BLOCK >= nt) break;
         const int k = tid + j * TPC_BLOCK;
-        cell[j] = k < n0 ? pair_cell(vy[j], vz[j], gd) : C0 + pair_cell(vy[j], vz[j], gu);
+        const SegGrid g = k < n0 ? gd : gu;
+        cell[j] = (k < n0 ? 0 : C0) + pair_cell(vy[j], vz[j], g);
         if (k < nt) atomicAdd(&L.cs[cell[j] + 2], 1);
     }
     __syncthreads();
-    // inclusive scan of cs[1 .. C+1] (cs[1] is 0): cs[c + 1] = first position of cell c
-    const int len = C + 1;
-    const int per = (len + TPC_BLOCK - 1) / TPC_BLOCK;
-    const int j0 = 1 + tid * per;
-    const int j1 = j0 + per < 1 + len ? j0 + per : 1 + len;
+    // inclusive scan: cs[c + 1] = first position of cell c (the counts of
+    // cells below c are in cs[2 .. c + 1]).  Each thread takes PC words of
+    // the array as they lie, whatever the number of cells: 16-byte accesses
+    // and no loop (a run per thread, word by word, conflicted on the banks).
+    int4 w[PC / 4];
     int local = 0;
-    for (int j = j0; j < j1; ++j) local += L.cs[j];
+#pragma unroll
+    for (int q = 0; q < PC / 4; ++q) {
+        w[q] = cs4[q];
+        local += w[q].x + w[q].y + w[q].z + w[q].w;
+    }
     int total;
     int run = block_exclusive_scan(local, L.scan_sh, &total);
-    for (int j = j0; j < j1; ++j) {
-        run += L.cs[j];
-        L.cs[j] = run;
+#pragma unroll
+    for (int q = 0; q < PC / 4; ++q) {
+        w[q].x = run += w[q].x;
+        w[q].y = run += w[q].y;
+        w[q].z = run += w[q].z;
+        w[q].w = run += w[q].w;
+        cs4[q] = w[q];
     }
     __syncthreads();
     // scatter; the cursor of cell c moves from its start to its end, which
     // leaves cs[c] = start of cell c for every c in [0, C]
 #pragma unroll
     for (int j = 0; j < PT; ++j) {
+        if (j * TPC_BLOCK >= nt) break;
         const int k = tid + j * TPC_BLOCK;
         if (k < nt) {
             const int slot = atomicAdd(&L.cs[cell[j] + 1], 1);
@@ -601,15 +615,17 @@ __device__ inline void pair_bin(const Src &src, int n0, int n1, float win_y, flo
 }
 
 // Does h-row `seg` (an interior, non-empty row) have neighbour rows that fit
-// the small LDS form?
+// the mixed LDS form (mix_query_seg)?
+#define TPC_MIX_N 1152
 __device__ inline bool small_pair(const int32_t *off, int seg) {
-    return seg_size(off, seg - 1) <= TPC_LDS_ROW_S && seg_size(off, seg + 1) <= TPC_LDS_ROW_S;
+    const int n0 = seg_size(off, seg - 1), n1 = seg_size(off, seg + 1);
+    return n0 <= TPC_LDS_ROW && n1 <= TPC_LDS_ROW && n0 + n1 <= TPC_MIX_N;
 }
 
-// Which segments a query call handles: rows whose neighbour rows fit the
-// small LDS form, the other rows whose neighbour rows fit the large form,
-// both, or the dense rows (a neighbour row of more than TPC_LDS_ROW).
-enum NbClass { NB_NOT_DENSE = 0, NB_SMALL = 1, NB_LARGE = 2, NB_DENSE = 3 };
+// Which segments nb_query_seg handles: all that are not dense (a neighbour
+// row of more than TPC_LDS_ROW), or those of them that mix_query_seg does
+// not take.
+enum NbClass { NB_NOT_DENSE = 0, NB_LARGE = 2 };
 
 // Tunables of the dense-row search: h clusters per slab (the slab's
 // clusters are consecutive in the z-sorted h-row), the smallest slab before
@@ -922,6 +938,340 @@ __device__ inline void nb_dense_seg(int seg, const int32_t *__restrict__ off, in
     __syncthreads();                 // LDS reuse across calls in a persistent loop
 }
 
+// The two neighbouring rows of an h-row binned together: one cell grid, one
+// cell order, so that a cluster's window is one set of cells.
+#define TPC_MIX_CELLS 1024
+#define TPC_MIX_LIST 16
+#define TPC_MIX_OVER 8
+struct MixLds {
+    float2 p[TPC_MIX_N];                            // (y, z) in cell order
+    uint16_t id[TPC_MIX_N];                         // position in the down row, or n0 + position in the up row
+    alignas(16) uint16_t cs[TPC_MIX_CELLS];         // cell starts
+    union {
+        alignas(16) uint32_t cnt[TPC_MIX_CELLS];    // while binning
+        uint16_t list[TPC_MIX_LIST][TPC_BLOCK];     // per thread: clusters in its window, by position in p
+    } u;
+    unsigned long long best[TPC_BLOCK];
+    unsigned long long starts[TPC_BLOCK / TPC_WAVE][TPC_WAVE];
+    int red[4][TPC_BLOCK / TPC_WAVE];
+    int scan_sh[TPC_BLOCK / TPC_WAVE];
+};
+
+// Orders of the LDS accesses within a wavefront (the hardware keeps them in
+// order; this keeps the compiler from moving them).
+__device__ inline void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// Bins both neighbouring rows of an h-row into L (whole workgroup; contains
+// barriers): the clusters of [ra0, ra0 + n0) and [ra1, ra1 + nt - n0).  The
+// grid covers the finite extents of both rows; how it divides them decides
+// no result, so its divisions are hardware reciprocals.
+__device__ inline SegGrid mix_bin(const float *__restrict__ y, const float *__restrict__ z, int ra0, int n0, int ra1,
+                                  int nt, float win_y, float win_z, MixLds &L) {
+#pragma clang fp contract(off)
+    constexpr int PT = (TPC_MIX_N + TPC_BLOCK - 1) / TPC_BLOCK;
+    static_assert(TPC_MIX_CELLS == 4 * TPC_BLOCK, "four cells per thread");
+    static_assert(TPC_MIX_N < 65536, "16-bit positions");
+    const int tid = threadIdx.x;
+    float vy[PT], vz[PT];
+#pragma unroll
+    for (int j = 0; j < PT; ++j) {
+        const int k = tid + j * TPC_BLOCK;
+        vy[j] = NAN;
+        vz[j] = NAN;
+        if (j * TPC_BLOCK < nt && k < nt) {
+            const int i = k < n0 ? ra0 + k : ra1 + (k - n0);
+            vy[j] = y[i];
+            vz[j] = z[i];
+        }
+    }
+    reinterpret_cast<int4 *>(L.u.cnt)[tid] = make_int4(0, 0, 0, 0);
+    // extents as integers of the same order: min y, min -y, min z, min -z
+    auto ordered = [](float v) {
+        const int i = __float_as_int(v);
+        return i ^ ((i >> 31) & 0x7FFFFFFF);
+    };
+    constexpr int TOP = 0x7FFFFFFF;
+    int e[4] = {TOP, TOP, TOP, TOP};
+#pragma unroll
+    for (int j = 0; j < PT; ++j) {
+        if (j * TPC_BLOCK >= nt) break;
+        const int oy = ordered(vy[j]), oz = ordered(vz[j]);
+        const bool fy = isfinite(vy[j]), fz = isfinite(vz[j]);
+        e[0] = min(e[0], fy ? oy : TOP);
+        e[1] = min(e[1], fy ? ~oy : TOP);
+        e[2] = min(e[2], fz ? oz : TOP);
+        e[3] = min(e[3], fz ? ~oz : TOP);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) e[j] = lane63_min(e[j]);
+    const int wid = tid / TPC_WAVE, lane = tid & (TPC_WAVE - 1);
+    if (lane == TPC_WAVE - 1) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) L.red[j][wid] = e[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        e[j] = L.red[j][0];
+#pragma unroll
+        for (int w = 1; w < TPC_BLOCK / TPC_WAVE; ++w) e[j] = min(e[j], L.red[j][w]);
+    }
+    auto back = [](int o) { return __int_as_float(o ^ ((o >> 31) & 0x7FFFFFFF)); };
+    const float ymin = back(e[0]), ymax = back(~e[1]), zmin = back(e[2]), zmax = back(~e[3]);
+    // up to four cells per cluster of the larger row, edges of at least the window
+    const int nm = n0 > nt - n0 ? n0 : nt - n0;
+    const int cap = 4 * nm < TPC_MIX_CELLS - 2 ? 4 * nm : TPC_MIX_CELLS - 2;
+    const float fc = (float)cap, ry = ymax - ymin, rz = zmax - zmin;
+    const float fz = rz * (0.99f * __builtin_amdgcn_rcpf(win_z)), fy = ry * (0.99f * __builtin_amdgcn_rcpf(win_y));
+    const int nz = fz >= fc ? cap : (fz >= 1.0f ? (int)fz : 1);
+    int ny = (int)(fc * __builtin_amdgcn_rcpf((float)nz));
+    if (ny * nz > cap) --ny;
+    ny = fy >= (float)ny ? ny : (fy >= 1.0f ? (int)fy : 1);
+    if (ny < 1) ny = 1;
+    const SegGrid g = {ymin, zmin, ny > 1 ? (float)ny * __builtin_amdgcn_rcpf(ry) : 0.f,
+                       nz > 1 ? (float)nz * __builtin_amdgcn_rcpf(rz) : 0.f, ny, nz, 0, 0};
+    int cell[PT];
+#pragma unroll
+    for (int j = 0; j < PT; ++j) {
+        cell[j] = 0;
+        if (j * TPC_BLOCK >= nt) break;
+        cell[j] = pair_cell(vy[j], vz[j], g);
+        if (tid + j * TPC_BLOCK < nt) atomicAdd(&L.u.cnt[cell[j]], 1u);
+    }
+    __syncthreads();
+    // exclusive scan, four cells per thread whatever the number of cells (at
+    // most TPC_MIX_CELLS - 2, so the word behind the last cell's is the total)
+    int4 c = reinterpret_cast<int4 *>(L.u.cnt)[tid];
+    int total;
+    const int b0 = block_exclusive_scan(c.x + c.y + c.z + c.w, L.scan_sh, &total);
+    const int b1 = b0 + c.x, b2 = b1 + c.y, b3 = b2 + c.z;
+    reinterpret_cast<int4 *>(L.u.cnt)[tid] = make_int4(b0, b1, b2, b3);
+    reinterpret_cast<uint2 *>(L.cs)[tid] = make_uint2((uint32_t)b0 | (uint32_t)b1 << 16,
+                                                      (uint32_t)b2 | (uint32_t)b3 << 16);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PT; ++j) {
+        if (j * TPC_BLOCK >= nt) break;
+        const int k = tid + j * TPC_BLOCK;
+        if (k < nt) {
+            const uint32_t slot = atomicAdd(&L.u.cnt[cell[j]], 1u);
+            L.p[slot] = make_float2(vy[j], vz[j]);
+            L.id[slot] = (uint16_t)k;
+        }
+    }
+    __syncthreads();
+    return g;
+}
+
+// Key of the pair (up position ku, down position kd) of the h-cluster
+// (yh, zh), smaller for the better pair: bits of q, then the ids.  All ones
+// if the pair fails the cuts.  By the operations of the definition.
+__device__ inline unsigned long long mix_key(float yh, float zh, int ku, int kd, const MixLds &L, float cut_y,
+                                             float cut_z) {
+#pragma clang fp contract(off)
+    const float2 u = L.p[ku], d = L.p[kd];
+    const float dy = (u.x - yh) - (yh - d.x), dz = (u.y - zh) - (zh - d.y);
+    const float qy = dy * dy, qz = dz * dz;
+    const float q = qy + qz;
+    if (!((int)(fabsf(dy) <= cut_y) & (int)(fabsf(dz) <= cut_z))) return ~0ull;
+    return ((unsigned long long)__float_as_uint(q) << 32) | (uint32_t)L.id[ku] << 16 | L.id[kd];
+}
+
+// Best pair of cluster (yh, zh) by a whole wavefront, into *best (its key so
+// far, an LDS word): the clusters in its window, at most
+// TPC_MIX_LIST * TPC_WAVE, are compacted into the wavefront's part of the
+// lists, and their pairs taken 64 at a time.
+__device__ inline void mix_wave(float yh, float zh, int n0, const SegGrid &g, MixLds &L, float win_y, float win_z,
+                                float cut_y, float cut_z, float my, float mz, unsigned long long *best) {
+#pragma clang fp contract(off)
+    const int lane = threadIdx.x & (TPC_WAVE - 1), base = threadIdx.x - lane;
+    auto at = [&](int e) -> uint16_t & { return L.u.list[e / TPC_WAVE][base + e % TPC_WAVE]; };
+    const int y0 = cell_coord(yh - (win_y + my), g.y0, g.iwy, g.ny);
+    const int y1 = cell_coord(yh + (win_y + my), g.y0, g.iwy, g.ny);
+    const int z0 = cell_coord(zh - (win_z + mz), g.z0, g.iwz, g.nz);
+    const int z1 = cell_coord(zh + (win_z + mz), g.z0, g.iwz, g.nz);
+    int nd = 0, nu = 0;
+    for (int iy = y0; iy <= y1; ++iy) {
+        const int e = L.cs[iy * g.nz + z1 + 1];
+        for (int k0 = L.cs[iy * g.nz + z0]; k0 < e; k0 += TPC_WAVE) {
+            const int k = k0 + lane;
+            bool in = k < e, s = false;
+            if (in) {
+                in = fabsf(L.p[k].x - yh) <= win_y && fabsf(L.p[k].y - zh) <= win_z;
+                s = L.id[k] >= n0;
+            }
+            const uint64_t bd = __ballot(in && !s), bu = __ballot(in && s);
+            if (in) at(s ? TPC_MIX_LIST * TPC_WAVE - 1 - nu - lanes_below(bu) : nd + lanes_below(bd)) = (uint16_t)k;
+            nd += __popcll(bd);
+            nu += __popcll(bu);
+        }
+    }
+    wave_fence();
+    const float inv = __builtin_amdgcn_rcpf((float)nd);
+    unsigned long long b = ~0ull;
+    for (int t = lane; t < nd * nu; t += TPC_WAVE) {
+        // t / nd: fewer than 2^18 pairs, so the error of the product is far below the 0.5 / nd to the next integer
+        const int iu = (int)(((float)t + 0.5f) * inv);
+        const unsigned long long key = mix_key(yh, zh, at(TPC_MIX_LIST * TPC_WAVE - 1 - iu), at(t - iu * nd), L,
+                                               cut_y, cut_z);
+        b = key < b ? key : b;
+    }
+    if (b != ~0ull) atomicMin(best, b);
+    wave_fence();
+}
+
+// Best pair of a cluster whose window holds more clusters than its list, by
+// its own lane: for each up cluster in the window the cells that overlap the
+// cut interval around its prediction, as in best_pair.
+__device__ inline unsigned long long mix_scan(float yh, float zh, int n0, const SegGrid &g, const MixLds &L,
+                                              float win_y, float win_z, float cut_y, float cut_z, float my,
+                                              float mz) {
+#pragma clang fp contract(off)
+    unsigned long long best = ~0ull;
+    const int y0 = cell_coord(yh - (win_y + my), g.y0, g.iwy, g.ny);
+    const int y1 = cell_coord(yh + (win_y + my), g.y0, g.iwy, g.ny);
+    const int z0 = cell_coord(zh - (win_z + mz), g.z0, g.iwz, g.nz);
+    const int z1 = cell_coord(zh + (win_z + mz), g.z0, g.iwz, g.nz);
+    for (int iy = y0; iy <= y1; ++iy) {
+        const int e = L.cs[iy * g.nz + z1 + 1];
+        for (int ku = L.cs[iy * g.nz + z0]; ku < e; ++ku) {
+            if (L.id[ku] < n0) continue;
+            const float ay = L.p[ku].x - yh, az = L.p[ku].y - zh;
+            if (!(fabsf(ay) <= win_y && fabsf(az) <= win_z)) continue;
+            const float cy = yh - ay, cz = zh - az, ky = cut_y + my, kz = cut_z + mz;
+            const int yd0 = cell_coord(cy - ky, g.y0, g.iwy, g.ny), yd1 = cell_coord(cy + ky, g.y0, g.iwy, g.ny);
+            const int zd0 = cell_coord(cz - kz, g.z0, g.iwz, g.nz), zd1 = cell_coord(cz + kz, g.z0, g.iwz, g.nz);
+            for (int iyd = yd0; iyd <= yd1; ++iyd) {
+                const int ed = L.cs[iyd * g.nz + zd1 + 1];
+                for (int kd = L.cs[iyd * g.nz + zd0]; kd < ed; ++kd) {
+                    if (L.id[kd] >= n0) continue;
+                    if (!(fabsf(yh - L.p[kd].x) <= win_y && fabsf(zh - L.p[kd].y) <= win_z)) continue;
+                    const unsigned long long key = mix_key(yh, zh, ku, kd, L, cut_y, cut_z);
+                    best = key < best ? key : best;
+                }
+            }
+        }
+    }
+    return best;
+}
+
+// Best triplet of every cluster of h-row `seg` whose neighbouring rows hold
+// at most TPC_MIX_N clusters together (whole workgroup; contains barriers).
+//
+// Bound by vector instructions, most of which a loop per cluster spends on
+// lanes that wait: with two clusters of either row in a window on average,
+// the busiest lane of a wavefront has five times the mean number of pairs.
+// So a lane only lists the clusters in its window (down from the front of
+// its list, up from the back), and the pairs of all lanes are then dealt
+// out 64 at a time: lane starts are set as bits of a mask, a lane finds its
+// pair's owner by counting bits, and the owner's best key is a 64-bit LDS
+// minimum.  TPC_MIX_LIST holds 99.97 % of the windows at 230 clusters per
+// row and 98.7 % at 460 (mix_scan does the others).
+__device__ inline void mix_query_seg(int seg, const int32_t *__restrict__ off, const float *__restrict__ y,
+                                     const float *__restrict__ z, float win_y, float win_z, float cut_y, float cut_z,
+                                     int32_t *__restrict__ up, int32_t *__restrict__ dn, MixLds &L) {
+#pragma clang fp contract(off)
+    static_assert(TPC_MIX_LIST == 16 && TPC_WAVE == 64, "at most 64 pairs per lane, 4096 per wavefront");
+    const int a = off[seg], b = off[seg + 1], ra0 = off[seg - 1], n0 = a - ra0, nt = n0 + off[seg + 2] - b;
+    const int tid = threadIdx.x, lane = tid & (TPC_WAVE - 1), wid = tid / TPC_WAVE;
+    // the first h of each thread is loaded together with the row pair
+    float yh = 0.f, zh = 0.f;
+    if (a + tid < b) {
+        yh = y[a + tid];
+        zh = z[a + tid];
+    }
+    const SegGrid g = mix_bin(y, z, ra0, n0, b, nt, win_y, win_z, L);
+    for (int i0 = a + wid * TPC_WAVE; i0 < b; i0 += TPC_BLOCK) {
+        const int i = i0 + lane;
+        if (i0 >= a + TPC_BLOCK && i < b) {
+            yh = y[i];
+            zh = z[i];
+        }
+        const float my = 1e-5f * (fabsf(yh) + win_y + cut_y) + 1e-6f;
+        const float mz = 1e-5f * (fabsf(zh) + win_z + cut_z) + 1e-6f;
+        int nd = 0, nu = 0;
+        if (i < b && isfinite(yh) && isfinite(zh)) {
+            const float wy = win_y + my, wz = win_z + mz;
+            const int y0 = cell_coord(yh - wy, g.y0, g.iwy, g.ny), y1 = cell_coord(yh + wy, g.y0, g.iwy, g.ny);
+            const int z0 = cell_coord(zh - wz, g.z0, g.iwz, g.nz), z1 = cell_coord(zh + wz, g.z0, g.iwz, g.nz);
+            for (int iy = y0; iy <= y1; ++iy) {
+                const int row = __mul24(iy, g.nz), e = L.cs[row + z1 + 1];
+                for (int k = L.cs[row + z0]; k < e; ++k) {
+                    const float2 c = L.p[k];
+                    if (!((int)(fabsf(c.x - yh) <= win_y) & (int)(fabsf(c.y - zh) <= win_z))) continue;
+                    const int s = L.id[k] >= n0;
+                    if (nd + nu < TPC_MIX_LIST) L.u.list[s ? TPC_MIX_LIST - 1 - nu : nd][tid] = (uint16_t)k;
+                    nu += s;
+                    nd += 1 - s;
+                }
+            }
+        }
+        const bool listed = nd + nu <= TPC_MIX_LIST;
+        const int P = listed ? nd * nu : 0;
+        const int inc = lane_scan(P), S = inc - P;
+        const int total = __builtin_amdgcn_readlane(inc, TPC_WAVE - 1);
+        L.best[tid] = ~0ull;
+        if (total > 0) {
+            L.starts[wid][lane] = 0;
+            wave_fence();
+            if (P > 0) atomicOr(&L.starts[wid][S >> 6], 1ull << (S & 63));
+            // what a pair needs of its owner, in the order of the owners
+            const uint64_t has = __ballot(P > 0);
+            const int below = lanes_below(has);
+            const int rank = 4 * (P > 0 ? below : __popcll(has) + lane - below);
+            // nd divides j < 64 by a product: ceil(2^14 / nd)
+            const int m = (int)(16384.0f * __builtin_amdgcn_rcpf((float)nd)) + 1;
+            const int pw = __builtin_amdgcn_ds_permute(rank, (int)((uint32_t)S | (uint32_t)nd << 12 | (uint32_t)m << 17));
+            const int py = __builtin_amdgcn_ds_permute(rank, __float_as_int(yh));
+            const int pz = __builtin_amdgcn_ds_permute(rank, __float_as_int(zh));
+            const int pl = __builtin_amdgcn_ds_permute(rank, tid);
+            wave_fence();
+            int before = -1;
+            for (int t0 = 0; t0 < total; t0 += TPC_WAVE) {
+                const unsigned long long s = L.starts[wid][t0 >> 6];
+                const uint64_t M = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(s >> 32)) << 32 |
+                                   (uint32_t)__builtin_amdgcn_readfirstlane((int)s);
+                const int r = 4 * (before + (int)(M & 1) + lanes_below(M >> 1));
+                before += __popcll(M);
+                const uint32_t w = (uint32_t)__builtin_amdgcn_ds_bpermute(r, pw);
+                const float oy = __int_as_float(__builtin_amdgcn_ds_bpermute(r, py));
+                const float oz = __int_as_float(__builtin_amdgcn_ds_bpermute(r, pz));
+                const int owner = __builtin_amdgcn_ds_bpermute(r, pl);
+                if (t0 + lane < total) {
+                    const int j = t0 + lane - (int)(w & 4095u), n = (int)(w >> 12) & 31;
+                    const int iu = __mul24(j, (int)(w >> 17)) >> 14, id = j - __mul24(iu, n);
+                    const int kd = L.u.list[id][owner], ku = L.u.list[TPC_MIX_LIST - 1 - iu][owner];
+                    const unsigned long long key = mix_key(oy, oz, ku, kd, L, cut_y, cut_z);
+                    if (key != ~0ull) atomicMin(&L.best[owner], key);
+                }
+            }
+            wave_fence();
+        }
+        // the others: a few by the whole wavefront one after the other, many
+        // (every lane overflows where a window holds far more clusters) each
+        // by its own lane
+        uint64_t over = __ballot(!listed && nd + nu <= TPC_MIX_LIST * TPC_WAVE);
+        bool done = listed;
+        if (__popcll(over) <= TPC_MIX_OVER) {
+            done = done || nd + nu <= TPC_MIX_LIST * TPC_WAVE;
+            for (; over != 0; over &= over - 1) {
+                const int l = __builtin_ctzll(over);
+                auto of = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+                mix_wave(of(yh), of(zh), n0, g, L, win_y, win_z, cut_y, cut_z, of(my), of(mz),
+                         &L.best[tid - lane + l]);
+            }
+        }
+        if (i < b) {
+            const unsigned long long best =
+                done ? L.best[tid] : mix_scan(yh, zh, n0, g, L, win_y, win_z, cut_y, cut_z, my, mz);
+            const bool found = best != ~0ull;
+            up[i] = found ? b + (int32_t)((uint32_t)best >> 16) - n0 : -1;
+            dn[i] = found ? ra0 + (int32_t)(best & 0xFFFFu) : -1;
+        }
+        wave_fence();
+    }
+}
+
 // Best triplet of every cluster of h-row `seg` (whole workgroup; contains
 // barriers; L is the workgroup's LDS scratch).  When both neighbouring rows
 // hold at most ROW clusters the workgroup bins them itself into LDS
@@ -938,12 +1288,11 @@ __device__ inline void nb_query_seg(int seg, const int32_t *__restrict__ off, in
                                     const int32_t *__restrict__ sid, int32_t *__restrict__ up,
                                     int32_t *__restrict__ dn, PairLdsT<ROW, CELLS> &L, NbClass cls) {
 #pragma clang fp contract(off)
-    static_assert(ROW == TPC_LDS_ROW || ROW == TPC_LDS_ROW_S, "row-pair LDS forms");
+    static_assert(ROW == TPC_LDS_ROW, "row-pair LDS form");
     const int r = seg % n_rows;
     const int a = off[seg], b = off[seg + 1];
     const bool edge = r == 0 || r == n_rows - 1;
-    const bool small = !edge && a != b && small_pair(off, seg);
-    if ((cls == NB_SMALL && !small) || (cls == NB_LARGE && small)) return;
+    if (cls == NB_LARGE && (edge || a == b || small_pair(off, seg))) return;
     if (dense_hrow(off, seg, n_rows)) return;
     if (edge) {
         for (int i = a + threadIdx.x; i < b; i += TPC_BLOCK) { up[i] = -1; dn[i] = -1; }

@@ -25,15 +25,22 @@ nb_bin(const int32_t *__restrict__ off, int32_t NR, int32_t n_rows, const float 
         tpc_nb::nb_bin_seg(xcd_item(it, NR), n_rows, off, y, z, win_y, win_z, grid, cstart, sy, sz, sid, L);
 }
 
-// Rows whose neighbour rows fit the small LDS form (18 KB per workgroup).
+// Rows whose neighbour rows fit the mixed LDS form (25 KB per workgroup, six
+// workgroups per CU), and the first and last rows.
 __global__ void __launch_bounds__(TPC_BLOCK)
 nb_query_small(const int32_t *__restrict__ off, int32_t n_rows, const float *__restrict__ y,
                const float *__restrict__ z, float win_y, float win_z, float cut_y, float cut_z,
                int32_t *up, int32_t *dn) {
-    __shared__ tpc_nb::PairLdsSmall L;
-    const int seg = xcd_item(blockIdx.x, gridDim.x);
-    tpc_nb::nb_query_seg(seg, off, n_rows, y, z, win_y, win_z, cut_y, cut_z, nullptr, nullptr, nullptr,
-                         nullptr, nullptr, up, dn, L, tpc_nb::NB_SMALL);
+    __shared__ tpc_nb::MixLds L;
+    const int seg = xcd_item(blockIdx.x, gridDim.x), r = seg % n_rows;
+    const int a = off[seg], b = off[seg + 1];
+    if (a == b) return;
+    if (r == 0 || r == n_rows - 1) {
+        for (int i = a + threadIdx.x; i < b; i += TPC_BLOCK) { up[i] = -1; dn[i] = -1; }
+        return;
+    }
+    if (tpc_nb::small_pair(off, seg))
+        tpc_nb::mix_query_seg(seg, off, y, z, win_y, win_z, cut_y, cut_z, up, dn, L);
 }
 
 // Rows whose neighbour rows fit the large LDS form.

@@ -944,8 +944,8 @@ __device__ inline void nb_dense_seg(int seg, const int32_t *__restrict__ off, in
 #define TPC_MIX_LIST 16
 #define TPC_MIX_OVER 8
 struct MixLds {
-    float2 p[TPC_MIX_N];                            // (y, z) in cell order
-    uint16_t id[TPC_MIX_N];                         // position in the down row, or n0 + position in the up row
+    float2 p[TPC_MIX_N + 1];                        // (y, z) in cell order
+    uint16_t id[TPC_MIX_N + 1];                     // position in the down row, or n0 + position in the up row
     alignas(16) uint16_t cs[TPC_MIX_CELLS];         // cell starts
     union {
         alignas(16) uint32_t cnt[TPC_MIX_CELLS];    // while binning
@@ -1063,6 +1063,11 @@ __device__ inline SegGrid mix_bin(const float *__restrict__ y, const float *__re
     return g;
 }
 
+struct PairKey {
+    unsigned long long key;
+    int owner;
+};
+
 // Key of the pair (up position ku, down position kd) of the h-cluster
 // (yh, zh), smaller for the better pair: bits of q, then the ids.  All ones
 // if the pair fails the cuts.  By the operations of the definition.
@@ -1070,11 +1075,12 @@ __device__ inline unsigned long long mix_key(float yh, float zh, int ku, int kd,
                                              float cut_z) {
 #pragma clang fp contract(off)
     const float2 u = L.p[ku], d = L.p[kd];
+    const uint32_t ids = (uint32_t)L.id[ku] << 16 | L.id[kd];
     const float dy = (u.x - yh) - (yh - d.x), dz = (u.y - zh) - (zh - d.y);
     const float qy = dy * dy, qz = dz * dz;
     const float q = qy + qz;
-    if (!((int)(fabsf(dy) <= cut_y) & (int)(fabsf(dz) <= cut_z))) return ~0ull;
-    return ((unsigned long long)__float_as_uint(q) << 32) | (uint32_t)L.id[ku] << 16 | L.id[kd];
+    const bool pass = (int)(fabsf(dy) <= cut_y) & (int)(fabsf(dz) <= cut_z);
+    return pass ? ((unsigned long long)__float_as_uint(q) << 32) | ids : ~0ull;
 }
 
 // Best pair of cluster (yh, zh) by a whole wavefront, into *best (its key so
@@ -1194,16 +1200,28 @@ __device__ inline void mix_query_seg(int seg, const int32_t *__restrict__ off, c
             const float wy = win_y + my, wz = win_z + mz;
             const int y0 = cell_coord(yh - wy, g.y0, g.iwy, g.ny), y1 = cell_coord(yh + wy, g.y0, g.iwy, g.ny);
             const int z0 = cell_coord(zh - wz, g.z0, g.iwz, g.nz), z1 = cell_coord(zh + wz, g.z0, g.iwz, g.nz);
+            int row = __mul24(y0, g.nz), k = L.cs[row + z0], e = L.cs[row + z1 + 1];
             for (int iy = y0; iy <= y1; ++iy) {
-                const int row = __mul24(iy, g.nz), e = L.cs[row + z1 + 1];
-                for (int k = L.cs[row + z0]; k < e; ++k) {
-                    const float2 c = L.p[k];
-                    if (!((int)(fabsf(c.x - yh) <= win_y) & (int)(fabsf(c.y - zh) <= win_z))) continue;
-                    const int s = L.id[k] >= n0;
-                    if (nd + nu < TPC_MIX_LIST) L.u.list[s ? TPC_MIX_LIST - 1 - nu : nd][tid] = (uint16_t)k;
+                // (the next row's range; of the last one again, not used)
+                row += iy < y1 ? g.nz : 0;
+                const int kn = L.cs[row + z0], en = L.cs[row + z1 + 1];
+                auto take = [&](const float2 &c, int side, int q) {
+                    if (!((int)(fabsf(c.x - yh) <= win_y) & (int)(fabsf(c.y - zh) <= win_z) & (int)(q < e))) return;
+                    const int s = side >= n0;
+                    if (nd + nu < TPC_MIX_LIST) L.u.list[s ? TPC_MIX_LIST - 1 - nu : nd][tid] = (uint16_t)q;
                     nu += s;
                     nd += 1 - s;
+                };
+                // two at a time, the sides read with the coordinates: the
+                // chain of LDS reads is what a wavefront waits for
+                for (; k < e; k += 2) {
+                    const float2 c0 = L.p[k], c1 = L.p[k + 1];
+                    const int s0 = L.id[k], s1 = L.id[k + 1];
+                    take(c0, s0, k);
+                    take(c1, s1, k + 1);
                 }
+                k = kn;
+                e = en;
             }
         }
         const bool listed = nd + nu <= TPC_MIX_LIST;
@@ -1226,24 +1244,32 @@ __device__ inline void mix_query_seg(int seg, const int32_t *__restrict__ off, c
             const int pz = __builtin_amdgcn_ds_permute(rank, __float_as_int(zh));
             const int pl = __builtin_amdgcn_ds_permute(rank, tid);
             wave_fence();
+            // all words of the mask at once, one per lane
+            const unsigned long long words = L.starts[wid][lane];
             int before = -1;
-            for (int t0 = 0; t0 < total; t0 += TPC_WAVE) {
-                const unsigned long long s = L.starts[wid][t0 >> 6];
-                const uint64_t M = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(s >> 32)) << 32 |
-                                   (uint32_t)__builtin_amdgcn_readfirstlane((int)s);
+            auto pair = [&](int t0) {
+                const int q = t0 / TPC_WAVE;
+                const uint64_t M = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(words >> 32), q) << 32 |
+                                   (uint32_t)__builtin_amdgcn_readlane((int)words, q);
                 const int r = 4 * (before + (int)(M & 1) + lanes_below(M >> 1));
                 before += __popcll(M);
                 const uint32_t w = (uint32_t)__builtin_amdgcn_ds_bpermute(r, pw);
                 const float oy = __int_as_float(__builtin_amdgcn_ds_bpermute(r, py));
                 const float oz = __int_as_float(__builtin_amdgcn_ds_bpermute(r, pz));
                 const int owner = __builtin_amdgcn_ds_bpermute(r, pl);
-                if (t0 + lane < total) {
-                    const int j = t0 + lane - (int)(w & 4095u), n = (int)(w >> 12) & 31;
-                    const int iu = __mul24(j, (int)(w >> 17)) >> 14, id = j - __mul24(iu, n);
-                    const int kd = L.u.list[id][owner], ku = L.u.list[TPC_MIX_LIST - 1 - iu][owner];
-                    const unsigned long long key = mix_key(oy, oz, ku, kd, L, cut_y, cut_z);
-                    if (key != ~0ull) atomicMin(&L.best[owner], key);
-                }
+                // (beyond the last pair: its owner's first)
+                const int j = t0 + lane < total ? t0 + lane - (int)(w & 4095u) : 0, n = (int)(w >> 12) & 31;
+                const int iu = __mul24(j, (int)(w >> 17)) >> 14, id = j - __mul24(iu, n);
+                const int kd = L.u.list[id][owner], ku = L.u.list[TPC_MIX_LIST - 1 - iu][owner];
+                return PairKey{mix_key(oy, oz, ku, kd, L, cut_y, cut_z), owner};
+            };
+            // two pairs per lane in flight
+            for (int t0 = 0; t0 < total; t0 += 2 * TPC_WAVE) {
+                const PairKey k0 = pair(t0);
+                PairKey k1 = {~0ull, 0};
+                if (t0 + TPC_WAVE < total) k1 = pair(t0 + TPC_WAVE);
+                if (k0.key != ~0ull) atomicMin(&L.best[k0.owner], k0.key);
+                if (k1.key != ~0ull) atomicMin(&L.best[k1.owner], k1.key);
             }
             wave_fence();
         }

@@ -18,8 +18,8 @@ nb_bin(const int32_t *__restrict__ off, int32_t NR, int32_t n_rows, const float 
        const float *__restrict__ z, float win_y, float win_z, SegGrid *grid, int32_t *cstart, float *sy,
        float *sz, int32_t *sid) {
     __shared__ tpc_nb::BinLdsPerm L;
-    // xcd_item keeps each workgroup in its XCD's contiguous range of
-    // segments (the grid is NR or a multiple of 8); taking the largest rows
+    // xcd_item keeps each workgroup in its XCD's ranges of segments (the
+    // grid is NR or a multiple of 8); taking the largest rows
     // first, as the dense query does, made the binning slower
     for (int it = blockIdx.x; it < NR; it += gridDim.x)
         tpc_nb::nb_bin_seg(xcd_item(it, NR), n_rows, off, y, z, win_y, win_z, grid, cstart, sy, sz, sid, L);

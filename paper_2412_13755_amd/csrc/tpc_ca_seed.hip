@@ -16,14 +16,29 @@ ca_block(int32_t N, int32_t n_rows, const int32_t *off, const int32_t *up, const
 }
 
 // Blocks too large for the LDS ranking with rows of at most
-// TPC_CA_SWEEP_ROW clusters: ranked by a bottom-up row sweep.
+// TPC_CA_SWEEP_ROW clusters: ranked by a bottom-up row sweep.  A thread tests
+// a block, so that a workgroup with few blocks to rank or none (the others
+// it takes are ca_block's) does not wait for each one's row offsets.
 __global__ void __launch_bounds__(1024)
 ca_block_sweep(int32_t NB, int32_t N, int32_t n_rows, const int32_t *off, const int32_t *up, const int32_t *dn,
                CaWs ws) {
     __shared__ uint32_t P[2 * TPC_CA_SWEEP_ROW];
-    for (int it = blockIdx.x; it < NB; it += gridDim.x) {
-        const int item = xcd_item(it, NB);
-        if (ca_block_class(item, n_rows, off) == 1) ca_sweep_item(item, N, n_rows, off, up, dn, ws, P);
+    const int tid = threadIdx.x;
+    for (int64_t from = blockIdx.x; from < NB; from += (int64_t)gridDim.x * 1024) {
+        const int64_t it = from + (int64_t)gridDim.x * tid;
+        bool mine = it < NB && ca_block_class((int)it, n_rows, off) == 1;
+        while (true) {                         // the blocks found, one after the other (P is all of the LDS)
+            __syncthreads();
+            if (tid == 0) P[0] = ~0u;
+            __syncthreads();
+            if (mine) atomicMin(&P[0], (uint32_t)tid);
+            __syncthreads();
+            const uint32_t w = P[0];
+            __syncthreads();
+            if (w == ~0u) break;
+            if ((uint32_t)tid == w) mine = false;
+            ca_sweep_item((int)(from + (int64_t)gridDim.x * w), N, n_rows, off, up, dn, ws, P);
+        }
     }
 }
 
@@ -159,9 +174,12 @@ hipError_t launch_ca_seed(const tpc_context *ctx, const tpc_frames *fr, const in
     const int32_t N = fr->n_clusters;
     const int NB = fr->n_frames * c.n_sectors * ca_blocks_per_sector(c.n_rows);
     hipLaunchKernelGGL(ca_block, dim3(NB), dim3(1024), 0, st, N, c.n_rows, off, up, dn, ws);
+    // no block is larger than the whole input; on frames of small rows one
+    // workgroup per CU (its LDS admits one) looks for large blocks
     const bool sparse = (int64_t)N < (int64_t)TPC_SPARSE_ROW * fr->n_frames * c.n_sectors * c.n_rows;
-    hipLaunchKernelGGL(ca_block_sweep, dim3(sparse && NB > TPC_SPARSE_GRID ? TPC_SPARSE_GRID : NB), dim3(1024), 0,
-                       st, NB, N, c.n_rows, off, up, dn, ws);
+    if (N > TPC_CA_CAP)
+        hipLaunchKernelGGL(ca_block_sweep, dim3(sparse && NB > 256 ? 256 : NB), dim3(1024), 0, st, NB, N, c.n_rows,
+                           off, up, dn, ws);
     hipLaunchKernelGGL(ca_tops, dim3(NR), dim3(TPC_BLOCK), 0, st, N, off, up, dn, c.min_hits, c.n_rows, ws);
     hipLaunchKernelGGL(ca_firsts, dim3(NR), dim3(TPC_BLOCK), 0, st, N, off, up, dn, c.min_hits, ws);
     if (NR <= TPC_SCAN_DIRECT) {

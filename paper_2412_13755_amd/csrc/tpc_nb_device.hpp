@@ -338,7 +338,7 @@ __device__ inline bool better(float q, int32_t u, int32_t d, const Best &b) {
 #define TPC_NB_DLIST 8
 
 template <int A = 1, int B = 1, bool LIST = true, class FP, class IP, class CP>
-__device__ inline Best best_pair(float yh, float zh, FP UY, FP UZ, IP UI, CP UCS, const SegGrid &gu,
+__device__ __forceinline__ Best best_pair(float yh, float zh, FP UY, FP UZ, IP UI, CP UCS, const SegGrid &gu,
                                  int32_t ubase, FP DY, FP DZ, IP DI, CP DCS, const SegGrid &gd,
                                  int32_t dbase, float win_y, float win_z, float cut_y, float cut_z) {
 #pragma clang fp contract(off)
@@ -505,7 +505,7 @@ struct SortedPairSrc {
 };
 
 template <int ROW, int CELLS, class Src>
-__device__ inline void pair_bin(const Src &src, int n0, int n1, float win_y, float win_z, float edge_d,
+__device__ __forceinline__ void pair_bin(const Src &src, int n0, int n1, float win_y, float win_z, float edge_d,
                                 float edge_u,
                                 PairLdsT<ROW, CELLS> &L, SegGrid &gd, SegGrid &gu, int &C0) {
 #pragma clang fp contract(off)
@@ -622,6 +622,13 @@ __device__ inline bool small_pair(const int32_t *off, int seg) {
     return n0 <= TPC_LDS_ROW && n1 <= TPC_LDS_ROW && n0 + n1 <= TPC_MIX_N;
 }
 
+// Is `seg` an h-row that mix_query_seg does not take (of the large LDS form,
+// or dense)?
+__device__ inline bool rest_hrow(const int32_t *off, int seg, int n_rows) {
+    const int r = seg % n_rows;
+    return r > 0 && r < n_rows - 1 && seg_size(off, seg) > 0 && !small_pair(off, seg);
+}
+
 // Which segments nb_query_seg handles: all that are not dense (a neighbour
 // row of more than TPC_LDS_ROW), or those of them that mix_query_seg does
 // not take.
@@ -712,7 +719,7 @@ __device__ inline int2 zrange(const SegGrid &g, const int32_t *cs, float lo, flo
 __device__ inline int cell_in(float c, float nmax) { return (int)__builtin_amdgcn_fmed3f(c, 0.0f, nmax); }
 
 template <int ROW, int CELLS>
-__device__ inline void slab_search(int pb, int pn, const float *__restrict__ sy, const float *__restrict__ sz,
+__device__ __forceinline__ void slab_search(int pb, int pn, const float *__restrict__ sy, const float *__restrict__ sz,
                                    const int32_t *__restrict__ sid, int32_t baseu, int32_t based,
                                    const SegGrid &gu, const SegGrid &gd, int C0, float win_y, float win_z,
                                    float cut_y, float cut_z, int32_t *__restrict__ up,
@@ -860,7 +867,7 @@ __device__ inline int dense_split(int n, int k, int parts) {
 // is searched in the global copies instead.  The outcome does not depend
 // on which superset of the candidates is searched.
 template <int ROW, int CELLS>
-__device__ inline void nb_dense_seg(int seg, const int32_t *__restrict__ off, int32_t n_rows, float win_y,
+__device__ __forceinline__ void nb_dense_seg(int seg, const int32_t *__restrict__ off, int32_t n_rows, float win_y,
                                     float win_z, float cut_y, float cut_z, const SegGrid *__restrict__ grid,
                                     const int32_t *__restrict__ cstart, const float *__restrict__ sy,
                                     const float *__restrict__ sz, const int32_t *__restrict__ sid,
@@ -1306,12 +1313,9 @@ __device__ inline void mix_query_seg(int seg, const int32_t *__restrict__ off, c
 // (the others return at once), so that a small-LDS and a large-LDS launch
 // can share the rows between them.
 template <int ROW, int CELLS>
-__device__ inline void nb_query_seg(int seg, const int32_t *__restrict__ off, int32_t n_rows,
+__device__ __forceinline__ void nb_query_seg(int seg, const int32_t *__restrict__ off, int32_t n_rows,
                                     const float *__restrict__ y, const float *__restrict__ z,
-                                    float win_y, float win_z, float cut_y, float cut_z,
-                                    const SegGrid *__restrict__ grid, const int32_t *__restrict__ cstart,
-                                    const float *__restrict__ sy, const float *__restrict__ sz,
-                                    const int32_t *__restrict__ sid, int32_t *__restrict__ up,
+                                    float win_y, float win_z, float cut_y, float cut_z, int32_t *__restrict__ up,
                                     int32_t *__restrict__ dn, PairLdsT<ROW, CELLS> &L, NbClass cls) {
 #pragma clang fp contract(off)
     static_assert(ROW == TPC_LDS_ROW, "row-pair LDS form");

@@ -18,21 +18,54 @@ nb_bin(const int32_t *__restrict__ off, int32_t NR, int32_t n_rows, const float 
        const float *__restrict__ z, float win_y, float win_z, SegGrid *grid, int32_t *cstart, float *sy,
        float *sz, int32_t *sid) {
     __shared__ tpc_nb::BinLdsPerm L;
-    // xcd_item keeps each workgroup in its XCD's ranges of segments (the
-    // grid is NR or a multiple of 8); taking the largest rows
-    // first, as the dense query does, made the binning slower
-    for (int it = blockIdx.x; it < NR; it += gridDim.x)
-        tpc_nb::nb_bin_seg(xcd_item(it, NR), n_rows, off, y, z, win_y, win_z, grid, cstart, sy, sz, sid, L);
+    // (taking the largest rows first, as the dense query does, made the
+    // binning slower)
+    tpc_nb::nb_bin_seg(xcd_item(blockIdx.x, NR), n_rows, off, y, z, win_y, win_z, grid, cstart, sy, sz, sid, L);
 }
 
-// Rows whose neighbour rows fit the mixed LDS form (25 KB per workgroup, six
-// workgroups per CU), and the first and last rows.
+// Items of [0, n) that workgroup b of G takes and that pass `pick`, into
+// `list` (its own, at most TPC_BLOCK of the items b, b + G, ... from `from` on
+// at a time); returns how many.  Whole workgroup; contains barriers.  One
+// test per thread: a workgroup that walks over its items one after the other
+// waits for their row offsets each time.
+template <class Pick>
+__device__ inline int pick_items(int from, int b, int G, int n, const Pick &pick, int *list, int *count) {
+    __syncthreads();
+    if (threadIdx.x == 0) *count = 0;
+    __syncthreads();
+    const int64_t i = b + (int64_t)G * (from + (int)threadIdx.x);
+    if (i < n && pick((int)i)) list[atomicAdd(count, 1)] = (int)i;
+    __syncthreads();
+    return *count;
+}
+
+// Blocks from nb on: the segments whose neighbouring rows fit the mixed LDS
+// form (25 KB per workgroup, six workgroups per CU), and the first and last
+// rows.  Blocks below nb: the sorted copies that dense rows need, where the
+// frames have few or none of them (a launch less than nb_bin's own; they
+// come first because they run longest if there are any).
 __global__ void __launch_bounds__(TPC_BLOCK)
-nb_query_small(const int32_t *__restrict__ off, int32_t n_rows, const float *__restrict__ y,
-               const float *__restrict__ z, float win_y, float win_z, float cut_y, float cut_z,
-               int32_t *up, int32_t *dn) {
-    __shared__ tpc_nb::MixLds L;
-    const int seg = xcd_item(blockIdx.x, gridDim.x), r = seg % n_rows;
+nb_query_small(const int32_t *__restrict__ off, int32_t NR, int32_t nb, int32_t n_rows, const float *__restrict__ y,
+               const float *__restrict__ z, float win_y, float win_z, float cut_y, float cut_z, SegGrid *grid,
+               int32_t *cstart, float *sy, float *sz, int32_t *sid, int32_t *up, int32_t *dn) {
+    __shared__ union {
+        tpc_nb::MixLds mix;
+        struct {
+            tpc_nb::BinLds lds;
+            int list[TPC_BLOCK], count;
+        } bin;
+    } U;
+    if ((int)blockIdx.x < nb) {
+        for (int from = 0; blockIdx.x + (int64_t)nb * from < NR; from += TPC_BLOCK) {
+            const int m = pick_items(from, blockIdx.x, nb, NR, [&](int s) { return tpc_nb::nb_bin_needed(off, s, n_rows); },
+                                     U.bin.list, &U.bin.count);
+            for (int k = 0; k < m; ++k)
+                tpc_nb::nb_bin_seg(U.bin.list[k], n_rows, off, y, z, win_y, win_z, grid, cstart, sy, sz, sid,
+                                   U.bin.lds);
+        }
+        return;
+    }
+    const int seg = xcd_item(blockIdx.x - nb, NR), r = seg % n_rows;
     const int a = off[seg], b = off[seg + 1];
     if (a == b) return;
     if (r == 0 || r == n_rows - 1) {
@@ -40,19 +73,44 @@ nb_query_small(const int32_t *__restrict__ off, int32_t n_rows, const float *__r
         return;
     }
     if (tpc_nb::small_pair(off, seg))
-        tpc_nb::mix_query_seg(seg, off, y, z, win_y, win_z, cut_y, cut_z, up, dn, L);
+        tpc_nb::mix_query_seg(seg, off, y, z, win_y, win_z, cut_y, cut_z, up, dn, U.mix);
+}
+
+// The segments that nb_query_small leaves, where the frames have few or none:
+// rows of the large LDS form and dense rows.  (Both searches in one kernel
+// need a few registers more than the 128 of four workgroups per CU.)
+__global__ void __launch_bounds__(TPC_BLOCK, 3)
+nb_query_rest(const int32_t *__restrict__ off, int32_t NR, int32_t n_rows, const float *__restrict__ y,
+              const float *__restrict__ z, float win_y, float win_z, float cut_y, float cut_z, const SegGrid *grid,
+              const int32_t *cstart, const float *sy, const float *sz, const int32_t *sid, int32_t *up,
+              int32_t *dn) {
+    __shared__ union {
+        tpc_nb::PairLds pair;
+        tpc_nb::DenseLds dense;
+    } U;
+    __shared__ int list[TPC_BLOCK], count;
+    for (int from = 0; blockIdx.x + (int64_t)gridDim.x * from < NR; from += TPC_BLOCK) {
+        const int m = pick_items(from, blockIdx.x, gridDim.x, NR, [&](int s) { return tpc_nb::rest_hrow(off, s, n_rows); },
+                                 list, &count);
+        for (int k = 0; k < m; ++k) {
+            const int seg = list[k];
+            if (tpc_nb::dense_hrow(off, seg, n_rows))
+                tpc_nb::nb_dense_seg(seg, off, n_rows, win_y, win_z, cut_y, cut_z, grid, cstart, sy, sz, sid, up, dn,
+                                     U.dense);
+            else
+                tpc_nb::nb_query_seg(seg, off, n_rows, y, z, win_y, win_z, cut_y, cut_z, up, dn, U.pair,
+                                     tpc_nb::NB_LARGE);
+        }
+    }
 }
 
 // Rows whose neighbour rows fit the large LDS form.
 __global__ void __launch_bounds__(TPC_BLOCK)
 nb_query(const int32_t *__restrict__ off, int32_t n_rows, const float *__restrict__ y,
-         const float *__restrict__ z, float win_y, float win_z, float cut_y, float cut_z,
-         const SegGrid *grid, const int32_t *cstart, const float *sy, const float *sz,
-         const int32_t *sid, int32_t *up, int32_t *dn) {
+         const float *__restrict__ z, float win_y, float win_z, float cut_y, float cut_z, int32_t *up, int32_t *dn) {
     __shared__ tpc_nb::PairLds L;
-    const int seg = xcd_item(blockIdx.x, gridDim.x);
-    tpc_nb::nb_query_seg(seg, off, n_rows, y, z, win_y, win_z, cut_y, cut_z, grid, cstart, sy,
-                         sz, sid, up, dn, L, tpc_nb::NB_LARGE);
+    tpc_nb::nb_query_seg(xcd_item(blockIdx.x, gridDim.x), off, n_rows, y, z, win_y, win_z, cut_y, cut_z, up, dn, L,
+                         tpc_nb::NB_LARGE);
 }
 
 // The order in which the dense query takes its work items, item
@@ -75,29 +133,15 @@ nb_dense_order(const int32_t *__restrict__ off, int32_t NR, int32_t n_rows, int3
 
 // Dense rows: slabs of the z-sorted rows, searched in LDS.  Four wavefronts
 // per SIMD (the LDS allows four workgroups per CU): at most 128 VGPRs.
-// order: the work items of nb_dense_order (row parts, largest first), or
-// null for whole rows in the XCD ranges of xcd_item.
+// order: the work items of nb_dense_order (row parts, largest first).
 __global__ void __launch_bounds__(TPC_BLOCK, 4)
-nb_query_dense(const int32_t *__restrict__ off, int32_t NR, int32_t n_rows, float win_y, float win_z, float cut_y,
-               float cut_z, const SegGrid *grid, const int32_t *cstart, const float *sy, const float *sz,
-               const int32_t *sid, const int32_t *__restrict__ order, int32_t *up, int32_t *dn) {
+nb_query_dense(const int32_t *__restrict__ off, int32_t n_rows, float win_y, float win_z, float cut_y, float cut_z,
+               const SegGrid *grid, const int32_t *cstart, const float *sy, const float *sz, const int32_t *sid,
+               const int32_t *__restrict__ order, int32_t *up, int32_t *dn) {
     __shared__ tpc_nb::DenseLds L;
-    // one call site of the search for both forms: a second inlined copy
-    // took the kernel past its 128 VGPRs into scratch spills
-    const int items = order ? TPC_NB_PARTS * NR : NR;
-    for (int it = blockIdx.x; it < items; it += gridDim.x) {
-        int seg, part = 0, parts = 1;
-        if (order) {
-            const int item = order[it];
-            seg = item / TPC_NB_PARTS;
-            part = item % TPC_NB_PARTS;
-            parts = TPC_NB_PARTS;
-        } else {
-            seg = xcd_item(it, NR);
-        }
-        tpc_nb::nb_dense_seg(seg, off, n_rows, win_y, win_z, cut_y, cut_z, grid, cstart, sy, sz, sid, up, dn, L,
-                             part, parts);
-    }
+    const int item = order[blockIdx.x];
+    tpc_nb::nb_dense_seg(item / TPC_NB_PARTS, off, n_rows, win_y, win_z, cut_y, cut_z, grid, cstart, sy, sz, sid, up,
+                         dn, L, item % TPC_NB_PARTS, TPC_NB_PARTS);
 }
 
 }  // namespace
@@ -107,32 +151,38 @@ hipError_t launch_neighbours(const tpc_context *ctx, const tpc_frames *fr, int32
                              int32_t *dn, const NbWs &ws, hipStream_t st) {
     const int NR = fr->n_frames * ctx->cfg.n_sectors * ctx->cfg.n_rows;
     const tpc_config &c = ctx->cfg;
-    // the binning and the dense query only work on dense rows and their
-    // neighbours: on frames whose rows are small on average a grid of at
-    // most TPC_SPARSE_GRID workgroups strides over the segments (no
-    // per-segment dispatch for segments with nothing to do); otherwise one
-    // workgroup per segment, so heavy segments run side by side
+    // The binning, the large form and the dense query only work on segments
+    // with large rows next to them.  Frames whose rows are small on average
+    // have few such segments or none: two launches then, in which at most
+    // TPC_SPARSE_GRID workgroups look for them.  Otherwise one workgroup per
+    // segment, so that heavy segments run side by side; the dense query takes
+    // parts of the dense h-rows, the largest first, so that the tail of a
+    // grid of workgroups of very different lengths is made of short ones.
+    // (Event of 10^4 tracks: 12 us in two more launches, 64 uneven frames:
+    // 0.7 ms of workgroups walking over segments with nothing to do.)
     const bool sparse = (int64_t)fr->n_clusters < (int64_t)TPC_SPARSE_ROW * NR;
-    const int gs = sparse && NR > TPC_SPARSE_GRID ? TPC_SPARSE_GRID : NR;
-    // frames of dense rows: the dense query takes parts of the dense h-rows,
-    // the largest first, so that the tail of a grid of workgroups of very
-    // different lengths is made of short ones
-    const int32_t *order = nullptr;
+    const int gs = NR < TPC_SPARSE_GRID ? NR : TPC_SPARSE_GRID;
+    const int nb = sparse ? (NR < TPC_SPARSE_GRID / 2 ? NR : TPC_SPARSE_GRID / 2) : 0;
     if (!sparse) {
         hipLaunchKernelGGL(nb_dense_order, dim3(1), dim3(TPC_BLOCK), 0, st, fr->row_offsets, NR, c.n_rows,
                            ws.order);
-        order = ws.order;
+        hipLaunchKernelGGL(nb_bin, dim3(NR), dim3(TPC_BLOCK), 0, st, fr->row_offsets, NR, c.n_rows, fr->y,
+                           fr->z, c.win_y, c.win_z, ws.grid, ws.cstart, ws.sy, ws.sz, ws.sid);
     }
-    hipLaunchKernelGGL(nb_bin, dim3(gs), dim3(TPC_BLOCK), 0, st, fr->row_offsets, NR, c.n_rows, fr->y,
-                       fr->z, c.win_y, c.win_z, ws.grid, ws.cstart, ws.sy, ws.sz, ws.sid);
-    hipLaunchKernelGGL(nb_query_small, dim3(NR), dim3(TPC_BLOCK), 0, st, fr->row_offsets, c.n_rows,
-                       fr->y, fr->z, c.win_y, c.win_z, c.cut_y, c.cut_z, up, dn);
+    hipLaunchKernelGGL(nb_query_small, dim3(nb + NR), dim3(TPC_BLOCK), 0, st, fr->row_offsets, NR, nb, c.n_rows,
+                       fr->y, fr->z, c.win_y, c.win_z, c.cut_y, c.cut_z, ws.grid, ws.cstart, ws.sy, ws.sz, ws.sid,
+                       up, dn);
+    if (sparse) {
+        hipLaunchKernelGGL(nb_query_rest, dim3(gs), dim3(TPC_BLOCK), 0, st, fr->row_offsets, NR, c.n_rows, fr->y,
+                           fr->z, c.win_y, c.win_z, c.cut_y, c.cut_z, ws.grid, ws.cstart, ws.sy, ws.sz, ws.sid, up,
+                           dn);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(nb_query, dim3(NR), dim3(TPC_BLOCK), 0, st, fr->row_offsets, c.n_rows, fr->y,
-                       fr->z, c.win_y, c.win_z, c.cut_y, c.cut_z, ws.grid, ws.cstart, ws.sy, ws.sz,
-                       ws.sid, up, dn);
-    const int gq = order ? TPC_NB_PARTS * NR : gs;
-    hipLaunchKernelGGL(nb_query_dense, dim3(gq), dim3(TPC_BLOCK), 0, st, fr->row_offsets, NR, c.n_rows, c.win_y,
-                       c.win_z, c.cut_y, c.cut_z, ws.grid, ws.cstart, ws.sy, ws.sz, ws.sid, order, up, dn);
+                       fr->z, c.win_y, c.win_z, c.cut_y, c.cut_z, up, dn);
+    hipLaunchKernelGGL(nb_query_dense, dim3(TPC_NB_PARTS * NR), dim3(TPC_BLOCK), 0, st, fr->row_offsets, c.n_rows,
+                       c.win_y, c.win_z, c.cut_y, c.cut_z, ws.grid, ws.cstart, ws.sy, ws.sz, ws.sid, ws.order, up,
+                       dn);
     return hipGetLastError();
 }
 

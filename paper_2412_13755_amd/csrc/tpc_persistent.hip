@@ -166,8 +166,7 @@ persist_reco(PersistArgs P) {
     if (!grid_sync(P)) return;
     for (int seg = bid; seg < P.NR; seg += G)
         tpc_nb::nb_query_seg(seg, P.off, P.n_rows, P.y, P.z, P.win_y, P.win_z, P.cut_y, P.cut_z,
-                             P.nb.grid, P.nb.cstart, P.nb.sy, P.nb.sz, P.nb.sid, P.up, P.dn, U.nb,
-                             tpc_nb::NB_NOT_DENSE);
+                             P.up, P.dn, U.nb, tpc_nb::NB_NOT_DENSE);
     {
         const int nl = P.n_lists[1];
         for (int k = bid; k < nl; k += G)

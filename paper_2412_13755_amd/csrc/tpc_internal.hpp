@@ -11,7 +11,7 @@
 #define TPC_WAVE 64
 #define TPC_CELL_CAP 4096      // neighbour-search cells per pad row (LDS histogram size)
 #define TPC_SPARSE_GRID 2048   // grid of the kernels that act on few segments (grid-stride; a multiple of 8) ...
-#define TPC_SPARSE_ROW 256     // ... when rows hold fewer clusters than this on average
+#define TPC_SPARSE_ROW 512     // ... when rows hold fewer clusters than this on average
 
 struct GraphCache;
 struct tpc_context {

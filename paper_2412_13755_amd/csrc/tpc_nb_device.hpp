@@ -10,15 +10,12 @@
 // functions below carry "fp contract(off)" and the stage file is compiled
 // with -ffp-contract=off, so no multiply-add is fused.
 //
-// Design: one workgroup per h-row (frame, sector, row) segment.  Each of
-// the two neighbouring rows is put on a y-z cell grid sized from the data
-// and counting-sorted by cell; then every thread takes clusters h of its row
-// and scans the up-row cells that overlap its window, and for each up
-// candidate in the window, the down-row cells that overlap the cut interval
-// around the straight-line prediction.  Rows of up to TPC_LDS_ROW clusters
-// are binned by the query workgroup itself into LDS, both rows in one
-// counting sort with up to four cells per cluster (the row pair is read
-// once, coalesced, and every candidate access is an LDS access).
+// Design: one workgroup per h-row (frame, sector, row) segment.  It bins its
+// two neighbouring rows, of up to TPC_LDS_ROW clusters each, into LDS on one
+// y-z cell grid sized from the data (the row pair is read once, coalesced,
+// and every candidate access is an LDS access); every thread lists the
+// clusters of either row in its own cluster's window, and the pairs of a
+// wavefront's lists are then scored 64 at a time (mix_query_seg).
 //
 // Dense rows (a neighbouring row of more than TPC_LDS_ROW clusters, as in a
 // continuous-readout time frame with ~10^4 clusters per pad row): the h-row
@@ -438,15 +435,9 @@ __device__ __forceinline__ Best best_pair(float yh, float zh, FP UY, FP UZ, IP U
     return best;
 }
 
-// LDS form of a row pair: both rows of up to ROW clusters each, with finer
-// cells than the global form (up to 4 per cluster, CELLS per row) so that
-// the cells around h hold few candidates.  Two sizes: the small one keeps
-// the workgroup's LDS at 18 KB (8 workgroups per CU), the large one at
-// 37 KB for rows of up to TPC_LDS_ROW clusters.
-#ifndef TPC_LDS_CELLS
-#define TPC_LDS_CELLS 2048
-#endif
-
+// LDS form of the row pair of a dense row's slab: both ranges of up to ROW
+// clusters each, with finer cells than the global form (up to 4 per cluster,
+// CELLS per row) so that the cells around h hold few candidates.
 template <int ROW, int CELLS>
 struct PairLdsT {
     float y[2 * ROW], z[2 * ROW];
@@ -455,7 +446,6 @@ struct PairLdsT {
     float red[8][TPC_BLOCK / TPC_WAVE];
     int scan_sh[TPC_BLOCK / TPC_WAVE];
 };
-using PairLds = PairLdsT<TPC_LDS_ROW, TPC_LDS_CELLS>;
 
 // Bins a down row of n0 clusters and an up row of n1 clusters with one LDS
 // counting sort over the concatenated cell range (whole workgroup; contains
@@ -475,19 +465,6 @@ __device__ inline SegGrid pair_grid(float ymin, float ymax, float zmin, float zm
     const int cap = 4 * n < CELLS ? 4 * n : CELLS - 1;
     return row_grid(ymin, ymax, zmin, zmax, cap, cap, win_y, win_z, edge);
 }
-
-// The clusters of two row ranges of the frame arrays: [ra0, ra0 + n0), then
-// [ra1, ...); relative ids are the offsets in the range.
-struct RowPairSrc {
-    const float *y, *z;
-    int ra0, n0, ra1;
-    __device__ void operator()(int k, float &vy, float &vz, uint16_t &rel) const {
-        const int i = k < n0 ? ra0 + k : ra1 + (k - n0);
-        vy = y[i];
-        vz = z[i];
-        rel = (uint16_t)(k < n0 ? k : k - n0);
-    }
-};
 
 // Two position ranges of the z-sorted copies (sy, sz, sid): [pa0, pa0 + n0)
 // of the down row, whose first cluster id is base0, then [pa1, ...) of the
@@ -615,24 +592,28 @@ __device__ __forceinline__ void pair_bin(const Src &src, int n0, int n1, float w
 }
 
 // Does h-row `seg` (an interior, non-empty row) have neighbour rows that fit
-// the mixed LDS form (mix_query_seg)?
+// the small mixed LDS form (mix_query_seg)?
 #define TPC_MIX_N 1152
 __device__ inline bool small_pair(const int32_t *off, int seg) {
     const int n0 = seg_size(off, seg - 1), n1 = seg_size(off, seg + 1);
     return n0 <= TPC_LDS_ROW && n1 <= TPC_LDS_ROW && n0 + n1 <= TPC_MIX_N;
 }
 
-// Is `seg` an h-row that mix_query_seg does not take (of the large LDS form,
-// or dense)?
+// The first and the last row of a sector have no triplets: writes that, and
+// returns whether `seg` is one (whole workgroup).
+__device__ inline bool edge_row(int seg, const int32_t *off, int n_rows, int32_t *up, int32_t *dn) {
+    const int r = seg % n_rows;
+    if (r > 0 && r < n_rows - 1) return false;
+    for (int i = off[seg] + threadIdx.x; i < off[seg + 1]; i += TPC_BLOCK) { up[i] = -1; dn[i] = -1; }
+    return true;
+}
+
+// Is `seg` an h-row that the small mixed form does not take (of the large
+// form, or dense)?
 __device__ inline bool rest_hrow(const int32_t *off, int seg, int n_rows) {
     const int r = seg % n_rows;
     return r > 0 && r < n_rows - 1 && seg_size(off, seg) > 0 && !small_pair(off, seg);
 }
-
-// Which segments nb_query_seg handles: all that are not dense (a neighbour
-// row of more than TPC_LDS_ROW), or those of them that mix_query_seg does
-// not take.
-enum NbClass { NB_NOT_DENSE = 0, NB_LARGE = 2 };
 
 // Tunables of the dense-row search: h clusters per slab (the slab's
 // clusters are consecutive in the z-sorted h-row), the smallest slab before
@@ -945,24 +926,27 @@ __device__ __forceinline__ void nb_dense_seg(int seg, const int32_t *__restrict_
     __syncthreads();                 // LDS reuse across calls in a persistent loop
 }
 
-// The two neighbouring rows of an h-row binned together: one cell grid, one
-// cell order, so that a cluster's window is one set of cells.
-#define TPC_MIX_CELLS 1024
-#define TPC_MIX_LIST 16
-#define TPC_MIX_OVER 8
-struct MixLds {
-    float2 p[TPC_MIX_N + 1];                        // (y, z) in cell order
-    uint16_t id[TPC_MIX_N + 1];                     // position in the down row, or n0 + position in the up row
-    alignas(16) uint16_t cs[TPC_MIX_CELLS];         // cell starts
+// The two neighbouring rows of an h-row (at most N clusters together) binned
+// together: one cell grid, one cell order, so that a cluster's window is one
+// set of cells.
+#define TPC_MIX_WORDS 32      // words of 64 pairs taken in a round
+template <int N, int CELLS, int LIST_>
+struct MixLdsT {
+    static constexpr int LIST = LIST_;
+    float2 p[N + 1];                                // (y, z) in cell order
+    uint16_t id[N + 1];                             // position in the down row, or n0 + position in the up row
+    alignas(16) uint16_t cs[CELLS];                 // cell starts
     union {
-        alignas(16) uint32_t cnt[TPC_MIX_CELLS];    // while binning
-        uint16_t list[TPC_MIX_LIST][TPC_BLOCK];     // per thread: clusters in its window, by position in p
+        alignas(16) uint32_t cnt[CELLS];            // while binning
+        uint16_t list[LIST][TPC_BLOCK];             // per thread: clusters in its window, by position in p
     } u;
     unsigned long long best[TPC_BLOCK];
-    unsigned long long starts[TPC_BLOCK / TPC_WAVE][TPC_WAVE];
+    unsigned long long starts[TPC_BLOCK / TPC_WAVE][TPC_MIX_WORDS];
     int red[4][TPC_BLOCK / TPC_WAVE];
     int scan_sh[TPC_BLOCK / TPC_WAVE];
 };
+using MixLds = MixLdsT<TPC_MIX_N, 1024, 16>;            // 24 KB: six workgroups per CU
+using MixLdsL = MixLdsT<2 * TPC_LDS_ROW, 2048, 24>;     // 39 KB: four
 
 // Orders of the LDS accesses within a wavefront (the hardware keeps them in
 // order; this keeps the compiler from moving them).
@@ -972,12 +956,14 @@ __device__ inline void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "
 // barriers): the clusters of [ra0, ra0 + n0) and [ra1, ra1 + nt - n0).  The
 // grid covers the finite extents of both rows; how it divides them decides
 // no result, so its divisions are hardware reciprocals.
+template <int N, int CELLS, int LIST>
 __device__ inline SegGrid mix_bin(const float *__restrict__ y, const float *__restrict__ z, int ra0, int n0, int ra1,
-                                  int nt, float win_y, float win_z, MixLds &L) {
+                                  int nt, float win_y, float win_z, MixLdsT<N, CELLS, LIST> &L) {
 #pragma clang fp contract(off)
-    constexpr int PT = (TPC_MIX_N + TPC_BLOCK - 1) / TPC_BLOCK;
-    static_assert(TPC_MIX_CELLS == 4 * TPC_BLOCK, "four cells per thread");
-    static_assert(TPC_MIX_N < 65536, "16-bit positions");
+    constexpr int PT = (N + TPC_BLOCK - 1) / TPC_BLOCK;
+    constexpr int Q = CELLS / (4 * TPC_BLOCK);      // groups of four cells per thread
+    static_assert(CELLS == 4 * Q * TPC_BLOCK, "cells in groups of four per thread");
+    static_assert(N < 65535, "16-bit positions");
     const int tid = threadIdx.x;
     float vy[PT], vz[PT];
 #pragma unroll
@@ -991,7 +977,9 @@ __device__ inline SegGrid mix_bin(const float *__restrict__ y, const float *__re
             vz[j] = z[i];
         }
     }
-    reinterpret_cast<int4 *>(L.u.cnt)[tid] = make_int4(0, 0, 0, 0);
+    int4 *cnt4 = reinterpret_cast<int4 *>(L.u.cnt) + tid * Q;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) cnt4[q] = make_int4(0, 0, 0, 0);
     // extents as integers of the same order: min y, min -y, min z, min -z
     auto ordered = [](float v) {
         const int i = __float_as_int(v);
@@ -1027,7 +1015,7 @@ __device__ inline SegGrid mix_bin(const float *__restrict__ y, const float *__re
     const float ymin = back(e[0]), ymax = back(~e[1]), zmin = back(e[2]), zmax = back(~e[3]);
     // up to four cells per cluster of the larger row, edges of at least the window
     const int nm = n0 > nt - n0 ? n0 : nt - n0;
-    const int cap = 4 * nm < TPC_MIX_CELLS - 2 ? 4 * nm : TPC_MIX_CELLS - 2;
+    const int cap = 4 * nm < CELLS - 2 ? 4 * nm : CELLS - 2;
     const float fc = (float)cap, ry = ymax - ymin, rz = zmax - zmin;
     const float fz = rz * (0.99f * __builtin_amdgcn_rcpf(win_z)), fy = ry * (0.99f * __builtin_amdgcn_rcpf(win_y));
     const int nz = fz >= fc ? cap : (fz >= 1.0f ? (int)fz : 1);
@@ -1046,15 +1034,25 @@ __device__ inline SegGrid mix_bin(const float *__restrict__ y, const float *__re
         if (tid + j * TPC_BLOCK < nt) atomicAdd(&L.u.cnt[cell[j]], 1u);
     }
     __syncthreads();
-    // exclusive scan, four cells per thread whatever the number of cells (at
-    // most TPC_MIX_CELLS - 2, so the word behind the last cell's is the total)
-    int4 c = reinterpret_cast<int4 *>(L.u.cnt)[tid];
+    // exclusive scan, the same cells per thread whatever their number (at
+    // most CELLS - 2, so the word behind the last cell's is the total)
+    int4 c[Q];
+    int sum = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        c[q] = cnt4[q];
+        sum += c[q].x + c[q].y + c[q].z + c[q].w;
+    }
     int total;
-    const int b0 = block_exclusive_scan(c.x + c.y + c.z + c.w, L.scan_sh, &total);
-    const int b1 = b0 + c.x, b2 = b1 + c.y, b3 = b2 + c.z;
-    reinterpret_cast<int4 *>(L.u.cnt)[tid] = make_int4(b0, b1, b2, b3);
-    reinterpret_cast<uint2 *>(L.cs)[tid] = make_uint2((uint32_t)b0 | (uint32_t)b1 << 16,
-                                                      (uint32_t)b2 | (uint32_t)b3 << 16);
+    int run = block_exclusive_scan(sum, L.scan_sh, &total);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int b0 = run, b1 = b0 + c[q].x, b2 = b1 + c[q].y, b3 = b2 + c[q].z;
+        run = b3 + c[q].w;
+        cnt4[q] = make_int4(b0, b1, b2, b3);
+        reinterpret_cast<uint2 *>(L.cs)[tid * Q + q] =
+            make_uint2((uint32_t)b0 | (uint32_t)b1 << 16, (uint32_t)b2 | (uint32_t)b3 << 16);
+    }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < PT; ++j) {
@@ -1078,7 +1076,8 @@ struct PairKey {
 // Key of the pair (up position ku, down position kd) of the h-cluster
 // (yh, zh), smaller for the better pair: bits of q, then the ids.  All ones
 // if the pair fails the cuts.  By the operations of the definition.
-__device__ inline unsigned long long mix_key(float yh, float zh, int ku, int kd, const MixLds &L, float cut_y,
+template <class LDS>
+__device__ inline unsigned long long mix_key(float yh, float zh, int ku, int kd, const LDS &L, float cut_y,
                                              float cut_z) {
 #pragma clang fp contract(off)
     const float2 u = L.p[ku], d = L.p[kd];
@@ -1091,85 +1090,63 @@ __device__ inline unsigned long long mix_key(float yh, float zh, int ku, int kd,
 }
 
 // Best pair of cluster (yh, zh) by a whole wavefront, into *best (its key so
-// far, an LDS word): the clusters in its window, at most
-// TPC_MIX_LIST * TPC_WAVE, are compacted into the wavefront's part of the
-// lists, and their pairs taken 64 at a time.
-__device__ inline void mix_wave(float yh, float zh, int n0, const SegGrid &g, MixLds &L, float win_y, float win_z,
-                                float cut_y, float cut_z, float my, float mz, unsigned long long *best) {
+// far, an LDS word): the clusters in its window (`in_window` of them) are
+// compacted into the wavefront's part of the lists, and their pairs taken 64
+// at a time.  A window of more than the lists hold is taken in four parts,
+// by halves of either row's ids.
+template <class LDS>
+__device__ inline void mix_wave(float yh, float zh, int n0, int in_window, const SegGrid &g, LDS &L, float win_y,
+                                float win_z, float cut_y, float cut_z, float my, float mz, unsigned long long *best) {
 #pragma clang fp contract(off)
+    constexpr int CAP = LDS::LIST * TPC_WAVE, HALF = TPC_LDS_ROW / 2;
+    static_assert(2 * HALF <= CAP, "half of either row fits");
     const int lane = threadIdx.x & (TPC_WAVE - 1), base = threadIdx.x - lane;
     auto at = [&](int e) -> uint16_t & { return L.u.list[e / TPC_WAVE][base + e % TPC_WAVE]; };
     const int y0 = cell_coord(yh - (win_y + my), g.y0, g.iwy, g.ny);
     const int y1 = cell_coord(yh + (win_y + my), g.y0, g.iwy, g.ny);
     const int z0 = cell_coord(zh - (win_z + mz), g.z0, g.iwz, g.nz);
     const int z1 = cell_coord(zh + (win_z + mz), g.z0, g.iwz, g.nz);
-    int nd = 0, nu = 0;
-    for (int iy = y0; iy <= y1; ++iy) {
-        const int e = L.cs[iy * g.nz + z1 + 1];
-        for (int k0 = L.cs[iy * g.nz + z0]; k0 < e; k0 += TPC_WAVE) {
-            const int k = k0 + lane;
-            bool in = k < e, s = false;
-            if (in) {
-                in = fabsf(L.p[k].x - yh) <= win_y && fabsf(L.p[k].y - zh) <= win_z;
-                s = L.id[k] >= n0;
-            }
-            const uint64_t bd = __ballot(in && !s), bu = __ballot(in && s);
-            if (in) at(s ? TPC_MIX_LIST * TPC_WAVE - 1 - nu - lanes_below(bu) : nd + lanes_below(bd)) = (uint16_t)k;
-            nd += __popcll(bd);
-            nu += __popcll(bu);
-        }
-    }
-    wave_fence();
-    const float inv = __builtin_amdgcn_rcpf((float)nd);
+    const bool parts = in_window > CAP;
     unsigned long long b = ~0ull;
-    for (int t = lane; t < nd * nu; t += TPC_WAVE) {
-        // t / nd: fewer than 2^18 pairs, so the error of the product is far below the 0.5 / nd to the next integer
-        const int iu = (int)(((float)t + 0.5f) * inv);
-        const unsigned long long key = mix_key(yh, zh, at(TPC_MIX_LIST * TPC_WAVE - 1 - iu), at(t - iu * nd), L,
-                                               cut_y, cut_z);
-        b = key < b ? key : b;
+    for (int part = 0; part < (parts ? 4 : 1); ++part) {
+        const int d0 = (part & 1) * HALF, d1 = parts ? d0 + HALF : n0;
+        const int u0 = n0 + (part >> 1) * HALF, u1 = parts ? u0 + HALF : 65536;
+        int nd = 0, nu = 0;
+        for (int iy = y0; iy <= y1; ++iy) {
+            const int e = L.cs[iy * g.nz + z1 + 1];
+            for (int k0 = L.cs[iy * g.nz + z0]; k0 < e; k0 += TPC_WAVE) {
+                const int k = k0 + lane;
+                bool down = false, upper = false;
+                if (k < e) {
+                    const bool in = fabsf(L.p[k].x - yh) <= win_y && fabsf(L.p[k].y - zh) <= win_z;
+                    const int id = L.id[k];
+                    down = in && id < n0 && id >= d0 && id < d1;
+                    upper = in && id >= u0 && id < u1;
+                }
+                const uint64_t bd = __ballot(down), bu = __ballot(upper);
+                if (down) at(nd + lanes_below(bd)) = (uint16_t)k;
+                if (upper) at(CAP - 1 - nu - lanes_below(bu)) = (uint16_t)k;
+                nd += __popcll(bd);
+                nu += __popcll(bu);
+            }
+        }
+        wave_fence();
+        const float inv = __builtin_amdgcn_rcpf((float)nd);
+        for (int t = lane; t < nd * nu; t += TPC_WAVE) {
+            // t / nd: fewer than 2^20 pairs, so the error of the product is
+            // far below the 0.5 / nd to the next integer
+            const int iu = (int)(((float)t + 0.5f) * inv);
+            const unsigned long long key = mix_key(yh, zh, at(CAP - 1 - iu), at(t - iu * nd), L, cut_y, cut_z);
+            b = key < b ? key : b;
+        }
+        wave_fence();
     }
     if (b != ~0ull) atomicMin(best, b);
     wave_fence();
 }
 
-// Best pair of a cluster whose window holds more clusters than its list, by
-// its own lane: for each up cluster in the window the cells that overlap the
-// cut interval around its prediction, as in best_pair.
-__device__ inline unsigned long long mix_scan(float yh, float zh, int n0, const SegGrid &g, const MixLds &L,
-                                              float win_y, float win_z, float cut_y, float cut_z, float my,
-                                              float mz) {
-#pragma clang fp contract(off)
-    unsigned long long best = ~0ull;
-    const int y0 = cell_coord(yh - (win_y + my), g.y0, g.iwy, g.ny);
-    const int y1 = cell_coord(yh + (win_y + my), g.y0, g.iwy, g.ny);
-    const int z0 = cell_coord(zh - (win_z + mz), g.z0, g.iwz, g.nz);
-    const int z1 = cell_coord(zh + (win_z + mz), g.z0, g.iwz, g.nz);
-    for (int iy = y0; iy <= y1; ++iy) {
-        const int e = L.cs[iy * g.nz + z1 + 1];
-        for (int ku = L.cs[iy * g.nz + z0]; ku < e; ++ku) {
-            if (L.id[ku] < n0) continue;
-            const float ay = L.p[ku].x - yh, az = L.p[ku].y - zh;
-            if (!(fabsf(ay) <= win_y && fabsf(az) <= win_z)) continue;
-            const float cy = yh - ay, cz = zh - az, ky = cut_y + my, kz = cut_z + mz;
-            const int yd0 = cell_coord(cy - ky, g.y0, g.iwy, g.ny), yd1 = cell_coord(cy + ky, g.y0, g.iwy, g.ny);
-            const int zd0 = cell_coord(cz - kz, g.z0, g.iwz, g.nz), zd1 = cell_coord(cz + kz, g.z0, g.iwz, g.nz);
-            for (int iyd = yd0; iyd <= yd1; ++iyd) {
-                const int ed = L.cs[iyd * g.nz + zd1 + 1];
-                for (int kd = L.cs[iyd * g.nz + zd0]; kd < ed; ++kd) {
-                    if (L.id[kd] >= n0) continue;
-                    if (!(fabsf(yh - L.p[kd].x) <= win_y && fabsf(zh - L.p[kd].y) <= win_z)) continue;
-                    const unsigned long long key = mix_key(yh, zh, ku, kd, L, cut_y, cut_z);
-                    best = key < best ? key : best;
-                }
-            }
-        }
-    }
-    return best;
-}
-
 // Best triplet of every cluster of h-row `seg` whose neighbouring rows hold
-// at most TPC_MIX_N clusters together (whole workgroup; contains barriers).
+// at most N clusters together (whole workgroup; contains barriers).
 //
 // Bound by vector instructions, most of which a loop per cluster spends on
 // lanes that wait: with two clusters of either row in a window on average,
@@ -1178,13 +1155,19 @@ __device__ inline unsigned long long mix_scan(float yh, float zh, int n0, const 
 // its list, up from the back), and the pairs of all lanes are then dealt
 // out 64 at a time: lane starts are set as bits of a mask, a lane finds its
 // pair's owner by counting bits, and the owner's best key is a 64-bit LDS
-// minimum.  TPC_MIX_LIST holds 99.97 % of the windows at 230 clusters per
-// row and 98.7 % at 460 (mix_scan does the others).
-__device__ inline void mix_query_seg(int seg, const int32_t *__restrict__ off, const float *__restrict__ y,
-                                     const float *__restrict__ z, float win_y, float win_z, float cut_y, float cut_z,
-                                     int32_t *__restrict__ up, int32_t *__restrict__ dn, MixLds &L) {
+// minimum.  Windows of more than LIST clusters go to mix_wave: with 16 of
+// them 0.03 % at 230 clusters per row and 1.3 % at 460, where they begin to
+// cost; the large form's 24 leave few up to its 1024.  (Left to their own
+// lanes, by boxes around the predictions, such windows cost more up to 100
+// clusters of either row in them: for the large rows of an event of 3 10^4
+// tracks 865 us against 378.)
+template <int N, int CELLS, int LIST>
+__device__ __forceinline__ void mix_query_seg(int seg, const int32_t *__restrict__ off, const float *__restrict__ y,
+                                              const float *__restrict__ z, float win_y, float win_z, float cut_y,
+                                              float cut_z, int32_t *__restrict__ up, int32_t *__restrict__ dn,
+                                              MixLdsT<N, CELLS, LIST> &L) {
 #pragma clang fp contract(off)
-    static_assert(TPC_MIX_LIST == 16 && TPC_WAVE == 64, "at most 64 pairs per lane, 4096 per wavefront");
+    static_assert(LIST <= 24 && TPC_WAVE == 64, "14 bits of pair starts; nd * nd * nu < 2^12");
     const int a = off[seg], b = off[seg + 1], ra0 = off[seg - 1], n0 = a - ra0, nt = n0 + off[seg + 2] - b;
     const int tid = threadIdx.x, lane = tid & (TPC_WAVE - 1), wid = tid / TPC_WAVE;
     // the first h of each thread is loaded together with the row pair
@@ -1215,7 +1198,7 @@ __device__ inline void mix_query_seg(int seg, const int32_t *__restrict__ off, c
                 auto take = [&](const float2 &c, int side, int q) {
                     if (!((int)(fabsf(c.x - yh) <= win_y) & (int)(fabsf(c.y - zh) <= win_z) & (int)(q < e))) return;
                     const int s = side >= n0;
-                    if (nd + nu < TPC_MIX_LIST) L.u.list[s ? TPC_MIX_LIST - 1 - nu : nd][tid] = (uint16_t)q;
+                    if (nd + nu < LIST) L.u.list[s ? LIST - 1 - nu : nd][tid] = (uint16_t)q;
                     nu += s;
                     nd += 1 - s;
                 };
@@ -1231,128 +1214,74 @@ __device__ inline void mix_query_seg(int seg, const int32_t *__restrict__ off, c
                 e = en;
             }
         }
-        const bool listed = nd + nu <= TPC_MIX_LIST;
+        const bool listed = nd + nu <= LIST;
         const int P = listed ? nd * nu : 0;
         const int inc = lane_scan(P), S = inc - P;
         const int total = __builtin_amdgcn_readlane(inc, TPC_WAVE - 1);
         L.best[tid] = ~0ull;
         if (total > 0) {
-            L.starts[wid][lane] = 0;
-            wave_fence();
-            if (P > 0) atomicOr(&L.starts[wid][S >> 6], 1ull << (S & 63));
             // what a pair needs of its owner, in the order of the owners
             const uint64_t has = __ballot(P > 0);
             const int below = lanes_below(has);
             const int rank = 4 * (P > 0 ? below : __popcll(has) + lane - below);
-            // nd divides j < 64 by a product: ceil(2^14 / nd)
-            const int m = (int)(16384.0f * __builtin_amdgcn_rcpf((float)nd)) + 1;
-            const int pw = __builtin_amdgcn_ds_permute(rank, (int)((uint32_t)S | (uint32_t)nd << 12 | (uint32_t)m << 17));
+            // nd divides j < nd nu by a product: ceil(2^12 / nd) is off by
+            // less than 1, the product by less than j / 2^12 < 1 / nd
+            const int m = (int)(4096.0f * __builtin_amdgcn_rcpf((float)nd)) + 1;
+            const int pw = __builtin_amdgcn_ds_permute(rank, (int)((uint32_t)S | (uint32_t)nd << 14 | (uint32_t)m << 19));
             const int py = __builtin_amdgcn_ds_permute(rank, __float_as_int(yh));
             const int pz = __builtin_amdgcn_ds_permute(rank, __float_as_int(zh));
             const int pl = __builtin_amdgcn_ds_permute(rank, tid);
-            wave_fence();
-            // all words of the mask at once, one per lane
-            const unsigned long long words = L.starts[wid][lane];
-            int before = -1;
-            auto pair = [&](int t0) {
-                const int q = t0 / TPC_WAVE;
-                const uint64_t M = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(words >> 32), q) << 32 |
-                                   (uint32_t)__builtin_amdgcn_readlane((int)words, q);
-                const int r = 4 * (before + (int)(M & 1) + lanes_below(M >> 1));
-                before += __popcll(M);
-                const uint32_t w = (uint32_t)__builtin_amdgcn_ds_bpermute(r, pw);
-                const float oy = __int_as_float(__builtin_amdgcn_ds_bpermute(r, py));
-                const float oz = __int_as_float(__builtin_amdgcn_ds_bpermute(r, pz));
-                const int owner = __builtin_amdgcn_ds_bpermute(r, pl);
-                // (beyond the last pair: its owner's first)
-                const int j = t0 + lane < total ? t0 + lane - (int)(w & 4095u) : 0, n = (int)(w >> 12) & 31;
-                const int iu = __mul24(j, (int)(w >> 17)) >> 14, id = j - __mul24(iu, n);
-                const int kd = L.u.list[id][owner], ku = L.u.list[TPC_MIX_LIST - 1 - iu][owner];
-                return PairKey{mix_key(oy, oz, ku, kd, L, cut_y, cut_z), owner};
-            };
-            // two pairs per lane in flight
-            for (int t0 = 0; t0 < total; t0 += 2 * TPC_WAVE) {
-                const PairKey k0 = pair(t0);
-                PairKey k1 = {~0ull, 0};
-                if (t0 + TPC_WAVE < total) k1 = pair(t0 + TPC_WAVE);
-                if (k0.key != ~0ull) atomicMin(&L.best[k0.owner], k0.key);
-                if (k1.key != ~0ull) atomicMin(&L.best[k1.owner], k1.key);
+            for (int r0 = 0; r0 < total; r0 += TPC_MIX_WORDS * TPC_WAVE) {
+                if (lane < TPC_MIX_WORDS) L.starts[wid][lane] = 0;
+                wave_fence();
+                if (P > 0 && S >= r0 && S < r0 + TPC_MIX_WORDS * TPC_WAVE)
+                    atomicOr(&L.starts[wid][(S - r0) >> 6], 1ull << (S & 63));
+                wave_fence();
+                // all words of the mask at once, one per lane
+                const unsigned long long words = L.starts[wid][lane % TPC_MIX_WORDS];
+                int before = __popcll(__ballot(P > 0 && S < r0)) - 1;
+                auto pair = [&](int t0) {
+                    const int q = (t0 - r0) / TPC_WAVE;
+                    const uint64_t M = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(words >> 32), q) << 32 |
+                                       (uint32_t)__builtin_amdgcn_readlane((int)words, q);
+                    const int r = 4 * (before + (int)(M & 1) + lanes_below(M >> 1));
+                    before += __popcll(M);
+                    const uint32_t w = (uint32_t)__builtin_amdgcn_ds_bpermute(r, pw);
+                    const float oy = __int_as_float(__builtin_amdgcn_ds_bpermute(r, py));
+                    const float oz = __int_as_float(__builtin_amdgcn_ds_bpermute(r, pz));
+                    const int owner = __builtin_amdgcn_ds_bpermute(r, pl);
+                    // (beyond the last pair: its owner's first)
+                    const int j = t0 + lane < total ? t0 + lane - (int)(w & 0x3FFFu) : 0, n = (int)(w >> 14) & 31;
+                    const int iu = __mul24(j, (int)(w >> 19)) >> 12, id = j - __mul24(iu, n);
+                    const int kd = L.u.list[id][owner], ku = L.u.list[LIST - 1 - iu][owner];
+                    return PairKey{mix_key(oy, oz, ku, kd, L, cut_y, cut_z), owner};
+                };
+                // two pairs per lane in flight
+                const int end = total - r0 < TPC_MIX_WORDS * TPC_WAVE ? total : r0 + TPC_MIX_WORDS * TPC_WAVE;
+                for (int t0 = r0; t0 < end; t0 += 2 * TPC_WAVE) {
+                    const PairKey k0 = pair(t0);
+                    PairKey k1 = {~0ull, 0};
+                    if (t0 + TPC_WAVE < end) k1 = pair(t0 + TPC_WAVE);
+                    if (k0.key != ~0ull) atomicMin(&L.best[k0.owner], k0.key);
+                    if (k1.key != ~0ull) atomicMin(&L.best[k1.owner], k1.key);
+                }
+                wave_fence();
             }
-            wave_fence();
         }
-        // the others: a few by the whole wavefront one after the other, many
-        // (every lane overflows where a window holds far more clusters) each
-        // by its own lane
-        uint64_t over = __ballot(!listed && nd + nu <= TPC_MIX_LIST * TPC_WAVE);
-        bool done = listed;
-        if (__popcll(over) <= TPC_MIX_OVER) {
-            done = done || nd + nu <= TPC_MIX_LIST * TPC_WAVE;
-            for (; over != 0; over &= over - 1) {
-                const int l = __builtin_ctzll(over);
-                auto of = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
-                mix_wave(of(yh), of(zh), n0, g, L, win_y, win_z, cut_y, cut_z, of(my), of(mz),
-                         &L.best[tid - lane + l]);
-            }
+        // the others by the whole wavefront, one after the other
+        for (uint64_t over = __ballot(!listed); over != 0; over &= over - 1) {
+            const int l = __builtin_ctzll(over);
+            auto of = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+            mix_wave(of(yh), of(zh), n0, __builtin_amdgcn_readlane(nd + nu, l), g, L, win_y, win_z, cut_y, cut_z,
+                     of(my), of(mz), &L.best[tid - lane + l]);
         }
         if (i < b) {
-            const unsigned long long best =
-                done ? L.best[tid] : mix_scan(yh, zh, n0, g, L, win_y, win_z, cut_y, cut_z, my, mz);
+            const unsigned long long best = L.best[tid];
             const bool found = best != ~0ull;
             up[i] = found ? b + (int32_t)((uint32_t)best >> 16) - n0 : -1;
             dn[i] = found ? ra0 + (int32_t)(best & 0xFFFFu) : -1;
         }
         wave_fence();
-    }
-}
-
-// Best triplet of every cluster of h-row `seg` (whole workgroup; contains
-// barriers; L is the workgroup's LDS scratch).  When both neighbouring rows
-// hold at most ROW clusters the workgroup bins them itself into LDS
-// (coalesced reads, then every candidate access is an LDS access);
-// dense rows are left to nb_dense_seg.  cls selects the segments handled
-// (the others return at once), so that a small-LDS and a large-LDS launch
-// can share the rows between them.
-template <int ROW, int CELLS>
-__device__ __forceinline__ void nb_query_seg(int seg, const int32_t *__restrict__ off, int32_t n_rows,
-                                    const float *__restrict__ y, const float *__restrict__ z,
-                                    float win_y, float win_z, float cut_y, float cut_z, int32_t *__restrict__ up,
-                                    int32_t *__restrict__ dn, PairLdsT<ROW, CELLS> &L, NbClass cls) {
-#pragma clang fp contract(off)
-    static_assert(ROW == TPC_LDS_ROW, "row-pair LDS form");
-    const int r = seg % n_rows;
-    const int a = off[seg], b = off[seg + 1];
-    const bool edge = r == 0 || r == n_rows - 1;
-    if (cls == NB_LARGE && (edge || a == b || small_pair(off, seg))) return;
-    if (dense_hrow(off, seg, n_rows)) return;
-    if (edge) {
-        for (int i = a + threadIdx.x; i < b; i += TPC_BLOCK) { up[i] = -1; dn[i] = -1; }
-        return;
-    }
-    if (a == b) return;
-    if (seg_size(off, seg - 1) <= ROW && seg_size(off, seg + 1) <= ROW) {
-        const int ra0 = off[seg - 1], ra1 = off[seg + 1];
-        // the first h of each thread is loaded together with the row pair
-        float hy = 0.f, hz = 0.f;
-        if (a + (int)threadIdx.x < b) {
-            hy = y[a + threadIdx.x];
-            hz = z[a + threadIdx.x];
-        }
-        SegGrid gd, gu;
-        int C0;
-        pair_bin(RowPairSrc{y, z, ra0, a - ra0, ra1}, a - ra0, off[seg + 2] - ra1, win_y, win_z, 1.01f,
-                 1.01f, L, gd, gu, C0);
-        for (int i = a + threadIdx.x; i < b; i += TPC_BLOCK) {
-            if (i >= a + TPC_BLOCK) {
-                hy = y[i];
-                hz = z[i];
-            }
-            const Best bt = best_pair(hy, hz, L.y, L.z, L.rel, L.cs + C0, gu, ra1, L.y, L.z, L.rel,
-                                      L.cs, gd, ra0, win_y, win_z, cut_y, cut_z);
-            up[i] = bt.u;
-            dn[i] = bt.d;
-        }
-        __syncthreads();             // LDS reuse across calls in a persistent loop
-        return;
     }
 }
 

@@ -65,13 +65,8 @@ nb_query_small(const int32_t *__restrict__ off, int32_t NR, int32_t nb, int32_t 
         }
         return;
     }
-    const int seg = xcd_item(blockIdx.x - nb, NR), r = seg % n_rows;
-    const int a = off[seg], b = off[seg + 1];
-    if (a == b) return;
-    if (r == 0 || r == n_rows - 1) {
-        for (int i = a + threadIdx.x; i < b; i += TPC_BLOCK) { up[i] = -1; dn[i] = -1; }
-        return;
-    }
+    const int seg = xcd_item(blockIdx.x - nb, NR);
+    if (tpc_nb::edge_row(seg, off, n_rows, up, dn) || off[seg] == off[seg + 1]) return;
     if (tpc_nb::small_pair(off, seg))
         tpc_nb::mix_query_seg(seg, off, y, z, win_y, win_z, cut_y, cut_z, up, dn, U.mix);
 }
@@ -85,7 +80,7 @@ nb_query_rest(const int32_t *__restrict__ off, int32_t NR, int32_t n_rows, const
               const int32_t *cstart, const float *sy, const float *sz, const int32_t *sid, int32_t *up,
               int32_t *dn) {
     __shared__ union {
-        tpc_nb::PairLds pair;
+        tpc_nb::MixLdsL mix;
         tpc_nb::DenseLds dense;
     } U;
     __shared__ int list[TPC_BLOCK], count;
@@ -94,23 +89,24 @@ nb_query_rest(const int32_t *__restrict__ off, int32_t NR, int32_t n_rows, const
                                  list, &count);
         for (int k = 0; k < m; ++k) {
             const int seg = list[k];
+            __syncthreads();             // LDS reuse
             if (tpc_nb::dense_hrow(off, seg, n_rows))
                 tpc_nb::nb_dense_seg(seg, off, n_rows, win_y, win_z, cut_y, cut_z, grid, cstart, sy, sz, sid, up, dn,
                                      U.dense);
             else
-                tpc_nb::nb_query_seg(seg, off, n_rows, y, z, win_y, win_z, cut_y, cut_z, up, dn, U.pair,
-                                     tpc_nb::NB_LARGE);
+                tpc_nb::mix_query_seg(seg, off, y, z, win_y, win_z, cut_y, cut_z, up, dn, U.mix);
         }
     }
 }
 
-// Rows whose neighbour rows fit the large LDS form.
+// Rows whose neighbour rows fit the large mixed form only.
 __global__ void __launch_bounds__(TPC_BLOCK)
 nb_query(const int32_t *__restrict__ off, int32_t n_rows, const float *__restrict__ y,
          const float *__restrict__ z, float win_y, float win_z, float cut_y, float cut_z, int32_t *up, int32_t *dn) {
-    __shared__ tpc_nb::PairLds L;
-    tpc_nb::nb_query_seg(xcd_item(blockIdx.x, gridDim.x), off, n_rows, y, z, win_y, win_z, cut_y, cut_z, up, dn, L,
-                         tpc_nb::NB_LARGE);
+    __shared__ tpc_nb::MixLdsL L;
+    const int seg = xcd_item(blockIdx.x, gridDim.x);
+    if (tpc_nb::rest_hrow(off, seg, n_rows) && !tpc_nb::dense_hrow(off, seg, n_rows))
+        tpc_nb::mix_query_seg(seg, off, y, z, win_y, win_z, cut_y, cut_z, up, dn, L);
 }
 
 // The order in which the dense query takes its work items, item

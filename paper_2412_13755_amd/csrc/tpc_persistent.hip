@@ -137,7 +137,7 @@ persist_init(PersistArgs P) {
 __global__ void __launch_bounds__(TPC_BLOCK, 4)
 persist_reco(PersistArgs P) {
     __shared__ union {
-        tpc_nb::PairLds nb;
+        tpc_nb::MixLdsL nb;
         tpc_nb::DenseLds dense;
         tpc_nb::BinLds bin;
         uint32_t caw[TPC_CA_CAP];
@@ -164,9 +164,14 @@ persist_reco(PersistArgs P) {
                                P.nb.cstart, P.nb.sy, P.nb.sz, P.nb.sid, U.bin);
     }
     if (!grid_sync(P)) return;
-    for (int seg = bid; seg < P.NR; seg += G)
-        tpc_nb::nb_query_seg(seg, P.off, P.n_rows, P.y, P.z, P.win_y, P.win_z, P.cut_y, P.cut_z,
-                             P.up, P.dn, U.nb, tpc_nb::NB_NOT_DENSE);
+    for (int seg = bid; seg < P.NR; seg += G) {
+        if (tpc_nb::edge_row(seg, P.off, P.n_rows, P.up, P.dn) || P.off[seg] == P.off[seg + 1] ||
+            tpc_nb::dense_hrow(P.off, seg, P.n_rows))
+            continue;
+        __syncthreads();                 // LDS reuse
+        tpc_nb::mix_query_seg(seg, P.off, P.y, P.z, P.win_y, P.win_z, P.cut_y, P.cut_z, P.up, P.dn, U.nb);
+    }
+    __syncthreads();
     {
         const int nl = P.n_lists[1];
         for (int k = bid; k < nl; k += G)

@@ -1,6 +1,4 @@
-// Seeding stage kernels: one workgroup per (frame, sector, row) segment for
-// every step but the segment scan; the per-segment work is in
-// tpc_ca_device.hpp.
+// Seeding stage kernels; the work is in tpc_ca_device.hpp.
 #include "tpc_ca_device.hpp"
 
 namespace {
@@ -43,16 +41,27 @@ ca_block_sweep(int32_t NB, int32_t N, int32_t n_rows, const int32_t *off, const 
 }
 
 __global__ void __launch_bounds__(TPC_BLOCK)
-ca_tops(int32_t N, const int32_t *off, const int32_t *up, const int32_t *dn, int32_t min_hits,
-        int32_t n_rows, CaWs ws) {
-    const int seg = xcd_item(blockIdx.x, gridDim.x);
-    ca_tops_seg(seg, N, off, up, dn, min_hits, n_rows, ws);
+ca_tops(int32_t N, int32_t NR, const int32_t *up, const int32_t *dn, int32_t min_hits, int32_t n_rows, CaWs ws) {
+    __shared__ CaTopsLds L;
+    for (int64_t s = (int64_t)blockIdx.x * TPC_BLOCK + threadIdx.x; s < NR; s += (int64_t)gridDim.x * TPC_BLOCK) {
+        ws.segcnt[s] = 0;                             // counted into by ca_firsts
+        ws.seghits[s] = 0;
+    }
+    ca_tops_flat((int64_t)xcd_item(blockIdx.x, gridDim.x) * TPC_CA_FLAT, N, up, dn, min_hits, n_rows, ws, L);
 }
 
+// Wavefronts per segment: one where rows are small on average (there are
+// then many, and launching a workgroup for each is what the time goes to:
+// 64 uneven frames 577 -> 228 us), the four of a workgroup otherwise.
+template <int PARTS>
 __global__ void __launch_bounds__(TPC_BLOCK)
-ca_firsts(int32_t N, const int32_t *off, const int32_t *up, const int32_t *dn, int32_t min_hits, CaWs ws) {
-    const int seg = xcd_item(blockIdx.x, gridDim.x);
-    ca_firsts_seg(seg, N, off, up, dn, min_hits, ws);
+ca_firsts(int32_t N, int32_t NR, const int32_t *off, const int32_t *up, const int32_t *dn, int32_t min_hits,
+          CaWs ws) {
+    __shared__ int list[TPC_BLOCK / TPC_WAVE][2 * TPC_WAVE];
+    constexpr int SEGS = TPC_BLOCK / TPC_WAVE / PARTS;
+    const int wid = threadIdx.x / TPC_WAVE;
+    const int seg = xcd_item(blockIdx.x, gridDim.x) * SEGS + wid / PARTS;
+    if (seg < NR) ca_firsts_part(seg, wid % PARTS, PARTS, N, off, up, dn, min_hits, ws, list[wid]);
 }
 
 // Single workgroup: exclusive scan of n (seed count, hit count) pairs into
@@ -148,18 +157,33 @@ ca_chunk_prefix(int32_t NR, CaWs ws) {
     }
 }
 
+template <int PARTS>
 __global__ void __launch_bounds__(TPC_BLOCK)
-ca_place(int32_t N, const int32_t *off, const int32_t *up, const int32_t *dn, const float *y, const float *z,
+ca_place(int32_t N, int32_t NR, const int32_t *off, const int32_t *up, const float *y, const float *z,
          int32_t n_sectors, int32_t n_rows, int32_t cap_seeds, int32_t cap_hits, tpc_seeds sd, CaWs ws) {
-    const int seg = xcd_item(blockIdx.x, gridDim.x);
-    ca_place_seg(seg, N, off, up, dn, y, z, n_sectors, n_rows, cap_seeds, cap_hits, sd, ws);
+    __shared__ int list[TPC_BLOCK / TPC_WAVE][2 * TPC_WAVE];
+    __shared__ int2 count[TPC_BLOCK / TPC_WAVE];
+    constexpr int SEGS = TPC_BLOCK / TPC_WAVE / PARTS;
+    const int wid = threadIdx.x / TPC_WAVE, part = wid % PARTS;
+    const int seg = xcd_item(blockIdx.x, gridDim.x) * SEGS + wid / PARTS;
+    int before_c = 0, before_h = 0;
+    if constexpr (PARTS > 1) {                        // (then the whole workgroup has one segment)
+        const int2 c = ca_place_count(seg, part, PARTS, off, ws, list[wid]);
+        if (threadIdx.x % TPC_WAVE == 0) count[wid] = c;
+        __syncthreads();
+        for (int p = 0; p < part; ++p) {
+            before_c += count[p].x;
+            before_h += count[p].y;
+        }
+    }
+    if (seg < NR)
+        ca_place_part(seg, part, PARTS, before_c, before_h, N, off, up, y, z, n_sectors, n_rows, cap_seeds, cap_hits,
+                      sd, ws, list[wid]);
 }
 
 __global__ void __launch_bounds__(TPC_BLOCK)
-ca_members(int32_t N, const int32_t *off, const int32_t *up, const int32_t *dn, const float *y,
-           const float *z, int32_t cap_hits, tpc_seeds sd, CaWs ws) {
-    const int seg = xcd_item(blockIdx.x, gridDim.x);
-    ca_members_seg(seg, N, off, up, dn, y, z, cap_hits, sd, ws);
+ca_members(int32_t N, const float *y, const float *z, int32_t cap_hits, tpc_seeds sd, CaWs ws) {
+    ca_members_flat<4>((int64_t)xcd_item(blockIdx.x, gridDim.x) * 4 * TPC_BLOCK, N, y, z, cap_hits, sd, ws);
 }
 
 }  // namespace
@@ -180,8 +204,15 @@ hipError_t launch_ca_seed(const tpc_context *ctx, const tpc_frames *fr, const in
     if (N > TPC_CA_CAP)
         hipLaunchKernelGGL(ca_block_sweep, dim3(sparse && NB > 256 ? 256 : NB), dim3(1024), 0, st, NB, N, c.n_rows,
                            off, up, dn, ws);
-    hipLaunchKernelGGL(ca_tops, dim3(NR), dim3(TPC_BLOCK), 0, st, N, off, up, dn, c.min_hits, c.n_rows, ws);
-    hipLaunchKernelGGL(ca_firsts, dim3(NR), dim3(TPC_BLOCK), 0, st, N, off, up, dn, c.min_hits, ws);
+    const int flat = N > 0 ? (int)(((int64_t)N + TPC_CA_FLAT - 1) / TPC_CA_FLAT) : 1;
+    static_assert(TPC_CA_FLAT == 4 * TPC_BLOCK, "ca_members takes four clusters per thread");
+    constexpr int WB = TPC_BLOCK / TPC_WAVE;
+    hipLaunchKernelGGL(ca_tops, dim3(flat), dim3(TPC_BLOCK), 0, st, N, NR, up, dn, c.min_hits, c.n_rows, ws);
+    if (sparse)
+        hipLaunchKernelGGL(ca_firsts<1>, dim3((NR + WB - 1) / WB), dim3(TPC_BLOCK), 0, st, N, NR, off, up, dn,
+                           c.min_hits, ws);
+    else
+        hipLaunchKernelGGL(ca_firsts<WB>, dim3(NR), dim3(TPC_BLOCK), 0, st, N, NR, off, up, dn, c.min_hits, ws);
     if (NR <= TPC_SCAN_DIRECT) {
         hipLaunchKernelGGL(ca_scan, dim3(1), dim3(1024), 0, st, NR, ws.segcnt, ws.seghits, ws.segbs,
                            ws.segbh, sd->n_seeds, sd->n_hits, sd->cap_seeds, sd->cap_hits, sd->offsets,
@@ -194,10 +225,13 @@ hipError_t launch_ca_seed(const tpc_context *ctx, const tpc_frames *fr, const in
                            dev_status);
         hipLaunchKernelGGL(ca_chunk_prefix, dim3(nch), dim3(TPC_BLOCK), 0, st, NR, ws);
     }
-    hipLaunchKernelGGL(ca_place, dim3(NR), dim3(TPC_BLOCK), 0, st, N, off, up, dn, fr->y, fr->z,
-                       c.n_sectors, c.n_rows, sd->cap_seeds, sd->cap_hits, *sd, ws);
-    hipLaunchKernelGGL(ca_members, dim3(NR), dim3(TPC_BLOCK), 0, st, N, off, up, dn, fr->y, fr->z,
-                       sd->cap_hits, *sd, ws);
+    if (sparse)
+        hipLaunchKernelGGL(ca_place<1>, dim3((NR + WB - 1) / WB), dim3(TPC_BLOCK), 0, st, N, NR, off, up, fr->y,
+                           fr->z, c.n_sectors, c.n_rows, sd->cap_seeds, sd->cap_hits, *sd, ws);
+    else
+        hipLaunchKernelGGL(ca_place<WB>, dim3(NR), dim3(TPC_BLOCK), 0, st, N, NR, off, up, fr->y, fr->z,
+                           c.n_sectors, c.n_rows, sd->cap_seeds, sd->cap_hits, *sd, ws);
+    hipLaunchKernelGGL(ca_members, dim3(flat), dim3(TPC_BLOCK), 0, st, N, fr->y, fr->z, sd->cap_hits, *sd, ws);
     return hipGetLastError();
 }
 
@@ -206,7 +240,6 @@ size_t ca_ws_layout(void *ws, int64_t N, int64_t NR, CaWs *out) {
     CaWs l;
     l.claim = w.take<unsigned long long>(N);
     l.pack = w.take<unsigned long long>(N);
-    l.dlk = w.take<int32_t>(N);
     l.cc = w.take<int2>(N);
     l.cend = w.take<int32_t>(N);
     l.mrec = w.take<int2>(N);

@@ -55,13 +55,11 @@ struct NbWs {
 
 struct CaWs {
     unsigned long long *claim;   // [N] smallest claim key per cluster
-    unsigned long long *pack;    // [N] (distance << 32) | lowest chain member in the row block
-    int32_t *dlk;                // [N] kept link down, -1 if none
+    unsigned long long *pack;    // [N] (distance << 32) | where the chain leaves the row block, or its bottom
     int2 *cc;                    // [N] at a bottom: (chain length, hit offset of the chain core or
                                  // -1 if no seed), read together; (0, -1) elsewhere
     int32_t *cend;               // [N] at a bottom: the up link of its chain's top (top end candidate)
-    int2 *mrec;                  // [N] at a block-local lowest member that is not its chain's
-                                 // bottom: (chain bottom, position from it)
+    int2 *mrec;                  // [N] at such an exit: (chain bottom, position from it)
     int32_t *fbot;               // [N] at a seed's first cluster: the chain bottom, else -1
     int32_t *flen;               // [N] at a seed's first cluster: seed length
     int32_t *segcnt, *seghits;   // [NR] seeds / seed hits starting in the segment

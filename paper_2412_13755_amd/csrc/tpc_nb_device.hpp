@@ -601,9 +601,12 @@ __device__ inline bool small_pair(const int32_t *off, int seg) {
 
 // The first and the last row of a sector have no triplets: writes that, and
 // returns whether `seg` is one (whole workgroup).
-__device__ inline bool edge_row(int seg, const int32_t *off, int n_rows, int32_t *up, int32_t *dn) {
+__device__ inline bool inner_row(int seg, int n_rows) {
     const int r = seg % n_rows;
-    if (r > 0 && r < n_rows - 1) return false;
+    return r > 0 && r < n_rows - 1;
+}
+__device__ inline bool edge_row(int seg, const int32_t *off, int n_rows, int32_t *up, int32_t *dn) {
+    if (inner_row(seg, n_rows)) return false;
     for (int i = off[seg] + threadIdx.x; i < off[seg + 1]; i += TPC_BLOCK) { up[i] = -1; dn[i] = -1; }
     return true;
 }
@@ -1282,6 +1285,80 @@ __device__ __forceinline__ void mix_query_seg(int seg, const int32_t *__restrict
             dn[i] = found ? ra0 + (int32_t)(best & 0xFFFFu) : -1;
         }
         wave_fence();
+    }
+}
+
+// Best triplet of every cluster of h-row `seg` whose neighbouring rows hold
+// at most 64 clusters together, by one wavefront without LDS or barriers:
+// lane k holds the k-th of them, every lane tests its cluster's window
+// against all (a bit each), and scores the few pairs of its bits.  Rows this
+// small are many (half of 64 uneven frames' 350 000 segments) and cost what
+// launching a workgroup and its barriers cost: 2.5 -> 1 ns per segment.
+#define TPC_TINY_N 64
+__device__ inline bool tiny_pair(const int32_t *off, int seg) {
+    return off[seg] - off[seg - 1] + off[seg + 2] - off[seg + 1] <= TPC_TINY_N;
+}
+
+__device__ inline void tiny_query_wave(int seg, const int32_t *__restrict__ off, const float *__restrict__ y,
+                                       const float *__restrict__ z, float win_y, float win_z, float cut_y,
+                                       float cut_z, int32_t *__restrict__ up, int32_t *__restrict__ dn) {
+#pragma clang fp contract(off)
+    static_assert(TPC_TINY_N == TPC_WAVE, "a cluster per lane, a bit each");
+    const int lane = threadIdx.x & (TPC_WAVE - 1);
+    const int ra0 = off[seg - 1], a = off[seg], b = off[seg + 1], n0 = a - ra0, nt = n0 + off[seg + 2] - b;
+    float yh = 0.f, zh = 0.f, cy = 0.f, cz = 0.f;
+    if (a + lane < b) {
+        yh = y[a + lane];
+        zh = z[a + lane];
+    }
+    if (lane < nt) {
+        const int k = lane < n0 ? ra0 + lane : b + lane - n0;
+        cy = y[k];
+        cz = z[k];
+    }
+    const uint64_t downs = n0 < 64 ? (1ull << n0) - 1 : ~0ull;
+    for (int i0 = a; i0 < b; i0 += TPC_WAVE) {
+        const int i = i0 + lane;
+        if (i0 > a && i < b) {
+            yh = y[i];
+            zh = z[i];
+        }
+        uint32_t bits[2] = {0, 0};
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            for (int k = 32 * w; k < nt && k < 32 * w + 32; ++k) {
+                const float ky = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cy), k));
+                const float kz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cz), k));
+                const bool in = (int)(fabsf(ky - yh) <= win_y) & (int)(fabsf(kz - zh) <= win_z);
+                bits[w] |= in ? 1u << (k & 31) : 0u;
+            }
+        }
+        // (a non-finite h is in no window)
+        const uint64_t m = i < b ? (uint64_t)bits[1] << 32 | bits[0] : 0ull;
+        const uint64_t md = m & downs;
+        uint64_t mu = md ? m & ~downs : 0ull, d = md;
+        unsigned long long best = ~0ull;
+        while (__ballot(mu != 0)) {              // (every lane stays active for the exchanges)
+            const int ku = mu ? __builtin_ctzll(mu) : 0, kd = mu ? __builtin_ctzll(d) : 0;
+            auto of = [](int k, float v) { return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * k, __float_as_int(v))); };
+            const float uy = of(ku, cy), uz = of(ku, cz), vy = of(kd, cy), vz = of(kd, cz);
+            const float dy = (uy - yh) - (yh - vy), dz = (uz - zh) - (zh - vz);
+            const float qy = dy * dy, qz = dz * dz;
+            const float q = qy + qz;
+            const bool pass = (int)(mu != 0) & (int)(fabsf(dy) <= cut_y) & (int)(fabsf(dz) <= cut_z);
+            const unsigned long long key = ((unsigned long long)__float_as_uint(q) << 32) | (uint32_t)(ku << 16 | kd);
+            best = pass && key < best ? key : best;
+            d &= d - 1;
+            if (d == 0) {
+                d = md;
+                mu &= mu - 1;
+            }
+        }
+        if (i < b) {
+            const bool found = best != ~0ull;
+            up[i] = found ? b + (int32_t)((uint32_t)best >> 16) - n0 : -1;
+            dn[i] = found ? ra0 + (int32_t)(best & 0xFFFFu) : -1;
+        }
     }
 }
 

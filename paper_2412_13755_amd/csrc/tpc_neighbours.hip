@@ -39,11 +39,12 @@ __device__ inline int pick_items(int from, int b, int G, int n, const Pick &pick
     return *count;
 }
 
-// Blocks from nb on: the segments whose neighbouring rows fit the mixed LDS
-// form (25 KB per workgroup, six workgroups per CU), and the first and last
-// rows.  Blocks below nb: the sorted copies that dense rows need, where the
+// Blocks from nb on, GROUP segments each: the segments whose neighbouring rows fit the mixed LDS
+// form (24 KB per workgroup, six workgroups per CU), the very small ones by a
+// wavefront, and the first and last rows.  Blocks below nb: the sorted copies that dense rows need, where the
 // frames have few or none of them (a launch less than nb_bin's own; they
 // come first because they run longest if there are any).
+template <int GROUP>
 __global__ void __launch_bounds__(TPC_BLOCK)
 nb_query_small(const int32_t *__restrict__ off, int32_t NR, int32_t nb, int32_t n_rows, const float *__restrict__ y,
                const float *__restrict__ z, float win_y, float win_z, float cut_y, float cut_z, SegGrid *grid,
@@ -65,10 +66,21 @@ nb_query_small(const int32_t *__restrict__ off, int32_t NR, int32_t nb, int32_t 
         }
         return;
     }
-    const int seg = xcd_item(blockIdx.x - nb, NR);
-    if (tpc_nb::edge_row(seg, off, n_rows, up, dn) || off[seg] == off[seg + 1]) return;
-    if (tpc_nb::small_pair(off, seg))
+    const int s0 = GROUP * xcd_item(blockIdx.x - nb, (NR + GROUP - 1) / GROUP), wid = threadIdx.x / TPC_WAVE;
+    static_assert(GROUP <= TPC_BLOCK / TPC_WAVE, "a wavefront per segment");
+    auto tiny = [&](int seg) {
+        return tpc_nb::inner_row(seg, n_rows) && off[seg] < off[seg + 1] && tpc_nb::tiny_pair(off, seg);
+    };
+    if (wid < GROUP && s0 + wid < NR && tiny(s0 + wid))
+        tpc_nb::tiny_query_wave(s0 + wid, off, y, z, win_y, win_z, cut_y, cut_z, up, dn);
+#pragma unroll 1
+    for (int seg = s0; seg < s0 + GROUP && seg < NR; ++seg) {
+        if (off[seg] == off[seg + 1] || tpc_nb::edge_row(seg, off, n_rows, up, dn) || tpc_nb::tiny_pair(off, seg) ||
+            !tpc_nb::small_pair(off, seg))
+            continue;
+        if (GROUP > 1) __syncthreads();              // LDS reuse
         tpc_nb::mix_query_seg(seg, off, y, z, win_y, win_z, cut_y, cut_z, up, dn, U.mix);
+    }
 }
 
 // The segments that nb_query_small leaves, where the frames have few or none:
@@ -143,6 +155,7 @@ nb_query_dense(const int32_t *__restrict__ off, int32_t n_rows, float win_y, flo
 }  // namespace
 
 
+#define TPC_NB_GROUP_MIN 16384
 hipError_t launch_neighbours(const tpc_context *ctx, const tpc_frames *fr, int32_t *up,
                              int32_t *dn, const NbWs &ws, hipStream_t st) {
     const int NR = fr->n_frames * ctx->cfg.n_sectors * ctx->cfg.n_rows;
@@ -165,9 +178,19 @@ hipError_t launch_neighbours(const tpc_context *ctx, const tpc_frames *fr, int32
         hipLaunchKernelGGL(nb_bin, dim3(NR), dim3(TPC_BLOCK), 0, st, fr->row_offsets, NR, c.n_rows, fr->y,
                            fr->z, c.win_y, c.win_z, ws.grid, ws.cstart, ws.sy, ws.sz, ws.sid);
     }
-    hipLaunchKernelGGL(nb_query_small, dim3(nb + NR), dim3(TPC_BLOCK), 0, st, fr->row_offsets, NR, nb, c.n_rows,
-                       fr->y, fr->z, c.win_y, c.win_z, c.cut_y, c.cut_z, ws.grid, ws.cstart, ws.sy, ws.sz, ws.sid,
-                       up, dn);
+    // Many segments (at ten times as many as run at a time, waiting for the
+    // workgroup with the longest four does not matter): four per workgroup,
+    // so that four very small ones run side by side and a quarter of the
+    // workgroups are launched.
+    auto small = [&](auto kernel, int group) {
+        hipLaunchKernelGGL(kernel, dim3(nb + (NR + group - 1) / group), dim3(TPC_BLOCK), 0, st, fr->row_offsets, NR,
+                           nb, c.n_rows, fr->y, fr->z, c.win_y, c.win_z, c.cut_y, c.cut_z, ws.grid, ws.cstart, ws.sy,
+                           ws.sz, ws.sid, up, dn);
+    };
+    if (NR >= TPC_NB_GROUP_MIN)
+        small(nb_query_small<4>, 4);
+    else
+        small(nb_query_small<1>, 1);
     if (sparse) {
         hipLaunchKernelGGL(nb_query_rest, dim3(gs), dim3(TPC_BLOCK), 0, st, fr->row_offsets, NR, c.n_rows, fr->y,
                            fr->z, c.win_y, c.win_z, c.cut_y, c.cut_z, ws.grid, ws.cstart, ws.sy, ws.sz, ws.sid, up,

@@ -111,12 +111,12 @@ hipError_t launch_ctf_build(const tpc_context *ctx, const tpc_frames *fr, const 
 
 #define TPC_RANS_MAX_RANGE (1 << 20)   // widest symbol range max - min + 1 of one array
 struct RansWs {
-    int32_t *mm;                 // min, max, status, table bytes, histogram offset, window flag, centre
+    int32_t *mm;                 // [8] (see RsArgs)
     uint32_t *counts;            // [TPC_RANS_MAX_RANGE] histogram
-    uint4 *fc;                   // [TPC_RANS_MAX_RANGE] (frequency, cumulative frequency, reciprocal, shifts)
-    uint32_t *wcount, *wstart;   // [nb], [nb + 1] words per coding block, their prefix
+    uint4 *fc;                   // [TPC_RANS_MAX_RANGE] coding table
+    uint32_t *wcount;            // [nb] words per coding block
     uint32_t *states;            // [nb][64] final coder states
-    uint16_t *scratch;           // [nb][B] word stack of each block
+    uint16_t *scratch;           // [nb][B] words of each block
 };
 size_t rans_ws_layout(void *ws, int64_t n, int32_t B, RansWs *out);
 struct RansJob {

@@ -4,10 +4,10 @@
 //
 //  Every kernel codes a batch of arrays: grid dimension y selects the
 //  array; an array's symbol count may come from device memory.
-//  rs_init      min / max / status words
-//  rs_window    (large arrays) zero the whole histogram: it is counted in the
-//               same pass as the range, relative to a window of 2^20 symbols
-//               centred on the first symbol
+//  rs_init      min / max / status words; for large arrays also zero the whole
+//               histogram: it is counted in the same pass as the range,
+//               relative to a window of 2^20 symbols centred on the first
+//               symbol
 //  rs_minmax    grid reduction of the symbol range; for large arrays also
 //               the histogram over that window (LDS-private for the 8192
 //               symbols around the first one, global atomics for the rest);
@@ -20,26 +20,21 @@
 //               atomics otherwise; 16-byte symbol loads
 //  rs_freq      one workgroup: number of symbols present, most frequent
 //               symbol, scaled frequencies (integer arithmetic, exactly the
-//               stated rule), their exclusive scan
-//  rs_table     one workgroup: the frequency table compressed for the
-//               stream -- per present symbol, in ascending order, the run of
-//               absent symbols before it and f - 1 as LEB128 varints --
-//               by two scans (the present symbols' ranks, then the pairs'
-//               byte offsets); positions and bytes in the histogram's
-//               buffer, which no later kernel reads
+//               stated rule), the coding table from their exclusive scan, and
+//               the frequency table compressed for the stream -- per present
+//               symbol, in ascending order, the run of absent symbols before
+//               it and f - 1 as LEB128 varints -- by two scans (the present
+//               symbols' ranks, then the pairs' byte offsets); positions and
+//               bytes in the histogram's buffer, which no later kernel reads
 //  rs_encode    one wavefront per block of B symbols, lane k = coder k; the
-//               block is coded backwards round by round (symbols loaded eight
-//               rounds at a time, the coding table in LDS for ranges up to
-//               2048, division by the frequency as a multiply-high with a
-//               precomputed reciprocal); the words a round emits are placed
-//               by ballot and prefix popcount in the order coders 63 .. 0
-//               push them, into a per-block scratch stack
-//  rs_scan      exclusive scan of the blocks' word counts
+//               block is coded backwards round by round (the coding table in
+//               LDS for ranges up to 2048); the words a round emits are
+//               placed by ballot and prefix popcount into the block's scratch
+//  rs_pack      the stream: header, compressed frequency table, block word
+//               offsets, final coder states, every block's words; nothing is
+//               written and the status says TPC_ERR_CAPACITY when the stream
+//               (its exact size is reported) does not fit
 //  rd_*         the decoder (see below)
-//  rs_pack      the stream: header, compressed frequency table, block word offsets,
-//               final coder states, every block's stack reversed; nothing is
-//               written and the status says TPC_ERR_CAPACITY when the
-//               stream (its exact size is reported) does not fit
 #include "tpc_internal.hpp"
 #include "tpc_rans_dec.hpp"
 
@@ -61,13 +56,12 @@ struct RsArgs {
     int32_t fused;         // range and histogram in one pass (large arrays)
     int32_t *mm;           // [0] min, [1] max, [2] status, [3] table bytes, [4] offset of
                            // the range in counts, [5] a symbol left the window,
-                           // [6] the window's centre (device)
+                           // [6] the window's centre, [7] general coding (device)
     uint32_t *counts;      // [TPC_RANS_MAX_RANGE] histogram, then the table's positions and bytes
-    uint4 *fc;             // [TPC_RANS_MAX_RANGE] (frequency, cumulative, reciprocal, shifts)
+    uint4 *fc;             // [TPC_RANS_MAX_RANGE] coding table (see coding_entry)
     uint32_t *wcount;      // [nb] words of each block
-    uint32_t *wstart;      // [nb + 1]
     uint32_t *states;      // [nb][64]
-    uint16_t *scratch;     // [nb][B] each block's word stack, push order
+    uint16_t *scratch;     // [nb][B] each block's words, at the end of its part, in stream order
     uint8_t *out;
     uint64_t cap;
     uint64_t *out_size;
@@ -96,19 +90,6 @@ __device__ inline int64_t rs_range(const RsArgs &A) {
     return A.n > 0 ? (int64_t)A.mm[1] - (int64_t)A.mm[0] + 1 : 0;
 }
 
-__global__ void rs_init(RsBatch Bt) {
-    const RsArgs A = rs_job(Bt);
-    if (threadIdx.x == 0) {
-        A.mm[0] = 0x7fffffff;
-        A.mm[1] = (int32_t)0x80000000;
-        A.mm[2] = TPC_OK;
-        A.mm[3] = 0;
-        A.mm[4] = 0;
-        A.mm[5] = 0;
-        A.mm[6] = A.n > 0 ? A.sym[0] : 0;
-    }
-}
-
 // The symbols as 16-byte vectors where aligned: head (scalar), body (int4),
 // tail (scalar).
 struct Vec4Split {
@@ -129,8 +110,18 @@ __device__ inline Vec4Split vec4_split(const int32_t *p, int64_t n) {
 #define RS_WIN_HALF (TPC_RANS_MAX_RANGE / 2)
 #define RS_LDS_HALF (RS_LDS_BINS / 2)
 
-__global__ void __launch_bounds__(TPC_BLOCK) rs_window(RsBatch Bt) {
+__global__ void __launch_bounds__(TPC_BLOCK) rs_init(RsBatch Bt) {
     const RsArgs A = rs_job(Bt);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        A.mm[0] = 0x7fffffff;
+        A.mm[1] = (int32_t)0x80000000;
+        A.mm[2] = TPC_OK;
+        A.mm[3] = 0;
+        A.mm[4] = 0;
+        A.mm[5] = 0;
+        A.mm[6] = A.n > 0 ? A.sym[0] : 0;
+        A.mm[7] = 0;
+    }
     if (!A.fused) return;
     for (int64_t s = (int64_t)blockIdx.x * TPC_BLOCK + threadIdx.x; s < TPC_RANS_MAX_RANGE;
          s += (int64_t)gridDim.x * TPC_BLOCK)
@@ -304,6 +295,77 @@ __device__ inline unsigned long long rs_block_max(unsigned long long v, unsigned
     return t;
 }
 
+// Exclusive scan over the RS_FREQ_THREADS threads; the total in *total.
+// Contains barriers.
+__device__ inline int rs_block_scan(int v, int *sh, int *total) {
+    const int lane = threadIdx.x & (TPC_WAVE - 1), wid = threadIdx.x / TPC_WAVE;
+    const int inc = lane_scan(v);
+    if (lane == TPC_WAVE - 1) sh[wid] = inc;
+    __syncthreads();
+    int before = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < RS_FREQ_THREADS / TPC_WAVE; ++w) {
+        const int t = sh[w];
+        before += w < wid ? t : 0;
+        tot += t;
+    }
+    __syncthreads();
+    *total = tot;
+    return before + inc - v;
+}
+
+// Coding table entry of a symbol of frequency f > 0 and cumulative start c,
+// M = 2^L.  A coder of state x emits a word first if x >= f 2^(32 - L), that
+// is if x > .x; then x becomes q M + x mod f + c with q = floor(x / f), which
+// is x + .y + q g, g = M - f (.w bits 0-23).  q = mulhi(x + i, .z) >> s, s in
+// bits 24-27 and i in bit 28 of .w (division by an invariant integer, Granlund
+// and Montgomery 1994): with l = ceil(log2 f) and s = l - 1 the reciprocal
+// 2^(32 + s) / f rounded up, off by e = z f - 2^(32 + s) < f, is exact for all
+// x with x e < 2^(32 + s); x < f 2^(32 - L) after the word, so always if
+// f <= M / 2.  For the one larger f there can be, it is if e <= 2^s, and if
+// not the reciprocal rounded down with x + 1 is.  f = 1: mulhi(x, 2^32 - 1) =
+// x - 1, so .y holds one g more.
+__device__ inline uint4 coding_entry(uint32_t f, uint32_t c, int L) {
+    const uint32_t M = 1u << L, g = M - f;
+    uint4 e;
+    e.x = f == M ? 0xffffffffu : (f << (32 - L)) - 1u;
+    e.y = c;
+    uint32_t s = 0, inc = 0;
+    if (f == 1) {
+        e.y += g;
+        e.z = 0xffffffffu;
+    } else {
+        s = 31 - __clz(f - 1);                              // l - 1
+        const uint64_t p = 1ull << (32 + s), lo = p / f;
+        const uint64_t up = lo * f == p ? lo : lo + 1;
+        inc = f > M / 2 && up * f - p > (1ull << s);
+        e.z = (uint32_t)(inc ? lo : up);
+    }
+    e.w = g | s << 24 | inc << 28;
+    return e;
+}
+
+// The frequency of an entry; absent symbols have g = M.
+__device__ inline uint32_t entry_freq(const uint4 &e, uint32_t M) { return M - (e.w & 0xffffffu); }
+
+// One workgroup: the frequencies, the coding table and the compressed
+// frequency table.  The histogram's buffer holds, after the frequencies are
+// made, the present symbols in rank order and from RS_TAB_BYTES on the
+// table's bytes.
+#define RS_TAB_BYTES 65536
+
+__device__ inline int varint_len(uint32_t v) { return v < 128u ? 1 : (v < 16384u ? 2 : 3); }
+
+__device__ inline int put_varint(uint8_t *p, uint32_t v) {
+    int k = 0;
+    while (v >= 0x80u) {
+        p[k++] = (uint8_t)(v | 0x80u);
+        v >>= 7;
+    }
+    p[k++] = (uint8_t)v;
+    return k;
+}
+
 __global__ void __launch_bounds__(RS_FREQ_THREADS) rs_freq(RsBatch Bt) {
     const RsArgs A = rs_job(Bt);
     const uint32_t *cnt = A.counts + A.mm[4];      // the range's first symbol
@@ -341,93 +403,51 @@ __global__ void __launch_bounds__(RS_FREQ_THREADS) rs_freq(RsBatch Bt) {
     if (threadIdx.x == 0) A.fc[sbest].x += (uint32_t)((long long)M - sum);
     __threadfence_block();
     __syncthreads();
-    // exclusive scan of the frequencies in chunks of the workgroup
+    // the coding table: exclusive scan of the frequencies in chunks of the
+    // workgroup
     uint32_t carry = 0;
+    bool general = A.L < 8;                        // (q is below 2^(32 - L): 24 bits from L = 8 on)
     for (int64_t c0 = 0; c0 < R; c0 += RS_FREQ_THREADS) {
         const int64_t s = c0 + threadIdx.x;
-        const int f = s < R ? (int)A.fc[s].x : 0;
-        // block_exclusive_scan covers TPC_BLOCK threads: scan four quarters
-        const int lane = threadIdx.x & (TPC_WAVE - 1), wid = threadIdx.x / TPC_WAVE;
-        int inc = wave_inclusive_scan(f);
-        if (lane == TPC_WAVE - 1) scan_sh[wid] = inc;
-        __syncthreads();
-        int before = 0, tot = 0;
-        for (int w = 0; w < RS_FREQ_THREADS / TPC_WAVE; ++w) {
-            const int v = scan_sh[w];
-            before += w < wid ? v : 0;
-            tot += v;
-        }
-        __syncthreads();
-        if (s < R) {
-            A.fc[s].y = carry + (uint32_t)(before + inc - f);
-            // floor(x / f) = (t + ((x - t) >> s1)) >> s2, t = mulhi(x, m), for
-            // every 32-bit x (division by an invariant integer, Granlund and
-            // Montgomery 1994): l = ceil(log2 f), m = floor(2^32 (2^l - f) / f) + 1,
-            // s1 = 1, s2 = l - 1; for f = 1, m = 0, s1 = s2 = 0
-            uint32_t m = 0, sh = 0;
-            if (f > 1) {
-                const int l = 32 - __clz(f - 1);
-                m = (uint32_t)(((((uint64_t)1 << l) - (uint64_t)f) << 32) / (uint64_t)f + 1);
-                sh = 1u | ((uint32_t)(l - 1) << 8);
-            }
-            A.fc[s].z = m;
-            A.fc[s].w = sh;
-        }
+        const uint32_t f = s < R ? A.fc[s].x : 0u;
+        int tot;
+        const int ex = rs_block_scan((int)f, scan_sh, &tot);
+        if (s < R) A.fc[s] = f ? coding_entry(f, carry + (uint32_t)ex, A.L) : make_uint4(0u, 0u, 0u, (uint32_t)M);
+        general = general || f > M / 2;
         carry += (uint32_t)tot;
     }
-}
-
-// Compressed frequency table.  The histogram's buffer holds, after the
-// frequencies are made, the present symbols in rank order (RS_TAB_POS) and
-// the table's bytes (RS_TAB_BYTES on).
-#define RS_TAB_BYTES 65536
-
-__device__ inline int varint_len(uint32_t v) { return v < 128u ? 1 : (v < 16384u ? 2 : 3); }
-
-__device__ inline int put_varint(uint8_t *p, uint32_t v) {
-    int k = 0;
-    while (v >= 0x80u) {
-        p[k++] = (uint8_t)(v | 0x80u);
-        v >>= 7;
-    }
-    p[k++] = (uint8_t)v;
-    return k;
-}
-
-__global__ void __launch_bounds__(TPC_BLOCK) rs_table(RsBatch Bt) {
-    const RsArgs A = rs_job(Bt);
-    __shared__ int sh[TPC_BLOCK / TPC_WAVE];
-    if (A.mm[2] != TPC_OK) return;
-    const int64_t R = rs_range(A);
+    if (general) A.mm[7] = 1;
+    __threadfence_block();
+    __syncthreads();
+    // ranks of the present symbols (the counts are not read any more)
     uint32_t *pos = A.counts;                                   // [D <= 2^16]
     uint8_t *tb = reinterpret_cast<uint8_t *>(A.counts + RS_TAB_BYTES);
-    // ranks of the present symbols
-    int D = 0;
-    for (int64_t c0 = 0; c0 < R; c0 += TPC_BLOCK) {
+    int np = 0;
+    for (int64_t c0 = 0; c0 < R; c0 += RS_FREQ_THREADS) {
         const int64_t s = c0 + threadIdx.x;
-        const int present = s < R && A.fc[s].x > 0u;
+        const int present = s < R && entry_freq(A.fc[s], (uint32_t)M) > 0u;
         int tot;
-        const int ex = block_exclusive_scan(present, sh, &tot);
-        if (present) pos[D + ex] = (uint32_t)s;
-        D += tot;
+        const int ex = rs_block_scan(present, scan_sh, &tot);
+        if (present) pos[np + ex] = (uint32_t)s;
+        np += tot;
     }
     __threadfence_block();
     __syncthreads();
     // each pair's bytes at the exclusive scan of the pairs' lengths
     int T = 0;
-    for (int c0 = 0; c0 < D; c0 += TPC_BLOCK) {
+    for (int c0 = 0; c0 < np; c0 += RS_FREQ_THREADS) {
         const int k = c0 + threadIdx.x;
         uint32_t gap = 0, fm1 = 0;
         int len = 0;
-        if (k < D) {
+        if (k < np) {
             const uint32_t sk = pos[k];
             gap = sk - (k > 0 ? pos[k - 1] + 1u : 0u);
-            fm1 = A.fc[sk].x - 1u;
+            fm1 = entry_freq(A.fc[sk], (uint32_t)M) - 1u;
             len = varint_len(gap) + varint_len(fm1);
         }
         int tot;
-        const int ex = block_exclusive_scan(len, sh, &tot);
-        if (k < D) {
+        const int ex = rs_block_scan(len, scan_sh, &tot);
+        if (k < np) {
             const int o = T + ex;
             const int a = put_varint(tb + o, gap);
             put_varint(tb + o + a, fm1);
@@ -439,50 +459,65 @@ __global__ void __launch_bounds__(TPC_BLOCK) rs_table(RsBatch Bt) {
 
 // One block of symbols by one wavefront; T is the coding table (LDS or
 // global memory, a separate instantiation each so that the loads are not
-// generic).
-template <class Tab>
+// generic).  GENERAL: with the division's increment and 32-bit products (see
+// coding_entry).
+//
+// The block is coded backwards and its words are laid out backwards from the
+// end of its scratch, the words of a round in lane order, so that they lie
+// as the stream wants them.  Bound by instructions: a round is a table read
+// from LDS, a ballot and a 16-bit store, and in between a division by a
+// product and one multiply-add; rounds with all lanes come without tests,
+// and the next RS_CHUNK rounds' symbols are read while these are coded.
+// 2^28 symbols, sigma 12: 357 -> 292 us.
+template <bool GENERAL, class Tab>
 __device__ inline void encode_block(const RsArgs &A, Tab T, int b, int lane) {
     const int lo = A.mm[0];
-    const int L = A.L;
     const int64_t i0 = (int64_t)b * A.B;
     const int nloc = (int)((i0 + A.B < A.n ? i0 + A.B : A.n) - i0);
-    const int32_t *src = A.sym + i0;
-    const int rounds = (nloc + RS_LANES - 1) / RS_LANES;
-    uint16_t *stack = A.scratch + (size_t)b * A.B;
+    const int32_t *src = A.sym + i0 + lane;
+    uint16_t *words = A.scratch + (size_t)b * A.B;
     uint32_t x = 1u << 16;
-    uint32_t top = 0;
-    for (int jc = rounds - 1; jc >= 0; jc -= RS_CHUNK) {
-        // the symbols of the next RS_CHUNK rounds (coded backwards), loaded together
-        int32_t sv[RS_CHUNK];
-#pragma unroll
-        for (int u = 0; u < RS_CHUNK; ++u) {
-            const int k = (jc - u) * RS_LANES + lane;
-            sv[u] = (jc - u >= 0 && k < nloc) ? src[k] : lo;
+    int end = A.B;                                  // words from here on are written
+    auto round = [&](int32_t sym, bool act) {
+        const uint4 e = T((uint32_t)(sym - lo));
+        const bool emit = act && x > e.x;
+        const uint64_t mask = __ballot(emit);
+        end -= __popcll(mask);
+        if (emit) {
+            words[end + lanes_below(mask)] = (uint16_t)x;
+            x >>= 16;
         }
-#pragma unroll
-        for (int u = 0; u < RS_CHUNK; ++u) {
-            const int j = jc - u;
-            if (j < 0) break;
-            const bool act = j * RS_LANES + lane < nloc;
-            const uint4 e = T(act ? (uint32_t)(sv[u] - lo) : 0u);
-            const bool emit = act && (uint64_t)x >= ((uint64_t)e.x << (32 - L));
-            const unsigned long long mask = __ballot(emit);
-            if (emit) {
-                // coders above this one push first
-                const int rank = __popcll(lane == 63 ? 0ull : mask >> (lane + 1));
-                stack[top + rank] = (uint16_t)(x & 0xffffu);
-                x >>= 16;
-            }
-            top += (uint32_t)__popcll(mask);
-            if (act) {
-                const uint32_t t = __umulhi(x, e.z);
-                const uint32_t q = (t + ((x - t) >> (e.w & 0xffu))) >> (e.w >> 8);
-                x = (q << L) + (x - q * e.x) + e.y;
-            }
+        uint32_t v;
+        if constexpr (GENERAL) {
+            const uint32_t q = __umulhi(x + ((e.w >> 28) & 1u), e.z) >> ((e.w >> 24) & 15u);
+            v = x + e.y + q * (e.w & 0xffffffu);
+        } else {
+            v = __umul24(__umulhi(x, e.z) >> (e.w >> 24), e.w) + (x + e.y);
         }
+        x = act ? v : x;
+    };
+    int j = nloc / RS_LANES;                        // rounds with all lanes
+    if (nloc % RS_LANES) {
+        const bool act = j * RS_LANES + lane < nloc;
+        round(act ? src[j * RS_LANES] : lo, act);
+    }
+    for (; j % RS_CHUNK; --j) round(src[(j - 1) * RS_LANES], true);
+    int32_t sv[RS_CHUNK], nx[RS_CHUNK];
+    if (j > 0) {
+#pragma unroll
+        for (int u = 0; u < RS_CHUNK; ++u) sv[u] = src[(j - 1 - u) * RS_LANES];
+    }
+    for (; j > 0; j -= RS_CHUNK) {
+        const int jn = j > RS_CHUNK ? j - RS_CHUNK : j;     // (the last ones again, not used)
+#pragma unroll
+        for (int u = 0; u < RS_CHUNK; ++u) nx[u] = src[(jn - 1 - u) * RS_LANES];
+#pragma unroll
+        for (int u = 0; u < RS_CHUNK; ++u) round(sv[u], true);
+#pragma unroll
+        for (int u = 0; u < RS_CHUNK; ++u) sv[u] = nx[u];
     }
     A.states[(size_t)b * RS_LANES + lane] = x;
-    if (lane == 0) A.wcount[b] = top;
+    if (lane == 0) A.wcount[b] = (uint32_t)(A.B - end);
 }
 
 struct LdsTab {
@@ -494,47 +529,80 @@ struct GlobalTab {
     __device__ uint4 operator()(uint32_t s) const { return t[s]; }
 };
 
-__global__ void __launch_bounds__(TPC_BLOCK) rs_encode(RsBatch Bt) {
+// Workgroups of RS_ENC_T threads fill a CU's 32 wavefronts with two copies of
+// the table; with fewer blocks than that (small) they are of TPC_BLOCK
+// threads, over more CUs.  The last blocks first: they are what the range
+// pass read last and the cache behind the L2s still holds.
+#define RS_ENC_T 1024
+#define RS_ENC_FULL 5120       // what 256 CUs hold of the smaller workgroups, five per CU
+template <int T>
+__global__ void __launch_bounds__(T, T == RS_ENC_T ? 8 : 1) rs_encode(RsBatch Bt) {
     const RsArgs A = rs_job(Bt);
     __shared__ uint4 tab[RS_TAB_LDS];
     if (A.mm[2] != TPC_OK) return;                  // uniform over the grid
     const int64_t R = rs_range(A);
     const bool in_lds = R <= RS_TAB_LDS;
     if (in_lds) {
-        for (int s = threadIdx.x; s < R; s += TPC_BLOCK) tab[s] = A.fc[s];
+        for (int s = threadIdx.x; s < R; s += T) tab[s] = A.fc[s];
         __syncthreads();
     }
     const int lane = threadIdx.x & (TPC_WAVE - 1);
-    const int b = blockIdx.x * (TPC_BLOCK / TPC_WAVE) + threadIdx.x / TPC_WAVE;
-    if (b >= A.nb) return;                          // after the only barrier
-    if (in_lds) encode_block(A, LdsTab{tab}, b, lane);
-    else encode_block(A, GlobalTab{A.fc}, b, lane);
-}
-
-__global__ void __launch_bounds__(TPC_BLOCK) rs_scan(RsBatch Bt) {
-    const RsArgs A = rs_job(Bt);
-    __shared__ int sh[TPC_BLOCK / TPC_WAVE];
-    uint32_t carry = 0;
-    for (int c0 = 0; c0 < A.nb; c0 += TPC_BLOCK) {
-        const int b = c0 + threadIdx.x;
-        const int v = (b < A.nb && A.mm[2] == TPC_OK) ? (int)A.wcount[b] : 0;
-        int tot;
-        const int ex = block_exclusive_scan(v, sh, &tot);
-        if (b < A.nb) A.wstart[b] = carry + (uint32_t)ex;
-        carry += (uint32_t)tot;
-    }
-    if (threadIdx.x == 0) A.wstart[A.nb] = carry;
+    const int b = A.nb - 1 - (int)(blockIdx.x * (T / TPC_WAVE) + threadIdx.x / TPC_WAVE);
+    if (b < 0) return;                              // after the only barrier
+    const bool general = A.mm[7] != 0;
+    if (in_lds && !general) encode_block<false>(A, LdsTab{tab}, b, lane);
+    else if (in_lds) encode_block<true>(A, LdsTab{tab}, b, lane);
+    else if (!general) encode_block<false>(A, GlobalTab{A.fc}, b, lane);
+    else encode_block<true>(A, GlobalTab{A.fc}, b, lane);
 }
 
 __device__ inline void put32(uint8_t *p, uint32_t v) { *reinterpret_cast<uint32_t *>(p) = v; }
 
-// Grid: one workgroup per coding block (at least one).
+// n words (2-byte aligned both) by a workgroup, 16 bytes per thread and step.
+struct __attribute__((packed, aligned(2))) Words8 {
+    uint32_t w[4];
+};
+__device__ inline void copy_words(uint16_t *dst, const uint16_t *src, uint32_t n) {
+    const uint32_t nv = n / 8;
+    for (uint32_t q = threadIdx.x; q < nv; q += TPC_BLOCK)
+        reinterpret_cast<Words8 *>(dst)[q] = reinterpret_cast<const Words8 *>(src)[q];
+    const uint32_t r = 8 * nv + threadIdx.x;
+    if (r < n) dst[r] = src[r];
+}
+
+// The stream, a run of consecutive blocks per workgroup.  Every workgroup sums
+// the word counts of the blocks before its own, and of all, itself (a scan of
+// them by one workgroup was a launch and 27 us for 8192 blocks).
+#define RS_PACK_GRID 2048
 __global__ void __launch_bounds__(TPC_BLOCK) rs_pack(RsBatch Bt) {
     const RsArgs A = rs_job(Bt);
+    __shared__ uint32_t sh[2][TPC_BLOCK / TPC_WAVE];
+    const int G = gridDim.x;
+    const int b0 = (int)((int64_t)A.nb * blockIdx.x / G), b1 = (int)((int64_t)A.nb * (blockIdx.x + 1) / G);
     const int st0 = A.mm[2];
+    uint32_t before = 0, words = 0;
+    if (st0 == TPC_OK) {
+        for (int b = threadIdx.x; b < A.nb; b += TPC_BLOCK) {
+            const uint32_t c = A.wcount[b];
+            words += c;
+            before += b < b0 ? c : 0u;
+        }
+    }
+    before = (uint32_t)__builtin_amdgcn_readlane(lane_scan((int)before), TPC_WAVE - 1);
+    words = (uint32_t)__builtin_amdgcn_readlane(lane_scan((int)words), TPC_WAVE - 1);
+    if ((threadIdx.x & (TPC_WAVE - 1)) == 0) {
+        sh[0][threadIdx.x / TPC_WAVE] = before;
+        sh[1][threadIdx.x / TPC_WAVE] = words;
+    }
+    __syncthreads();
+    before = words = 0;
+#pragma unroll
+    for (int w = 0; w < TPC_BLOCK / TPC_WAVE; ++w) {
+        before += sh[0][w];
+        words += sh[1][w];
+    }
     const int64_t R = st0 == TPC_OK ? rs_range(A) : 0;
     const uint64_t T = st0 == TPC_OK ? (uint64_t)A.mm[3] : 0ull, T4 = (T + 3ull) & ~3ull;
-    const uint64_t words = A.wstart[A.nb];
     const uint64_t head = RS_HEAD + T4 + 4ull * (A.nb + 1) + 4ull * RS_LANES * A.nb;
     const uint64_t total = head + 2ull * words;
     const bool fits = st0 == TPC_OK && total <= A.cap;
@@ -544,7 +612,6 @@ __global__ void __launch_bounds__(TPC_BLOCK) rs_pack(RsBatch Bt) {
     }
     if (!fits) return;
     uint8_t *o = A.out;
-    const int G = gridDim.x;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         put32(o, RS_MAGIC);
         put32(o + 4, 2u);
@@ -557,8 +624,7 @@ __global__ void __launch_bounds__(TPC_BLOCK) rs_pack(RsBatch Bt) {
         put32(o + 32, (uint32_t)A.nb);
         put32(o + 36, (uint32_t)T);
     }
-    // compressed table (zero-padded to 4 bytes), word offsets, states: spread
-    // over the grid
+    // compressed table (zero-padded to 4 bytes) spread over the grid
     const uint32_t *tb = A.counts + RS_TAB_BYTES;
     uint32_t *ft = reinterpret_cast<uint32_t *>(o + RS_HEAD);
     for (int64_t q = (int64_t)blockIdx.x * TPC_BLOCK + threadIdx.x; q < (int64_t)(T4 / 4); q += (int64_t)G * TPC_BLOCK) {
@@ -566,17 +632,18 @@ __global__ void __launch_bounds__(TPC_BLOCK) rs_pack(RsBatch Bt) {
         const int64_t keep = (int64_t)T - 4 * q;                 // bytes of this word inside the table
         ft[q] = keep >= 4 ? v : (v & ((1u << (8 * keep)) - 1u));
     }
+    // word offsets, states and words of this workgroup's blocks
     uint32_t *ws = ft + T4 / 4;
-    for (int64_t b = (int64_t)blockIdx.x * TPC_BLOCK + threadIdx.x; b <= A.nb; b += (int64_t)G * TPC_BLOCK) ws[b] = A.wstart[b];
     uint32_t *sts = ws + A.nb + 1;
-    for (int64_t q = (int64_t)blockIdx.x * TPC_BLOCK + threadIdx.x; q < (int64_t)A.nb * RS_LANES; q += (int64_t)G * TPC_BLOCK)
-        sts[q] = A.states[q];
-    // each block's stack, last pushed first
     uint16_t *wo = reinterpret_cast<uint16_t *>(o + head);
-    for (int b = blockIdx.x; b < A.nb; b += G) {
-        const uint32_t top = A.wcount[b], base = A.wstart[b];
-        const uint16_t *stack = A.scratch + (size_t)b * A.B;
-        for (uint32_t w = threadIdx.x; w < top; w += TPC_BLOCK) wo[base + w] = stack[top - 1 - w];
+    if (blockIdx.x == 0 && threadIdx.x == 0) ws[A.nb] = words;
+    for (int64_t q = (int64_t)b0 * RS_LANES + threadIdx.x; q < (int64_t)b1 * RS_LANES; q += TPC_BLOCK)
+        sts[q] = A.states[q];
+    for (int b = b0; b < b1; ++b) {
+        const uint32_t c = A.wcount[b];
+        if (threadIdx.x == 0) ws[b] = before;
+        copy_words(wo + before, A.scratch + (size_t)(b + 1) * A.B - c, c);
+        before += c;
     }
 }
 
@@ -889,7 +956,6 @@ size_t rans_ws_layout(void *ws, int64_t n, int32_t B, RansWs *out) {
     r.counts = w.take<uint32_t>(TPC_RANS_MAX_RANGE);
     r.fc = w.take<uint4>(TPC_RANS_MAX_RANGE);
     r.wcount = w.take<uint32_t>(nb > 0 ? nb : 1);
-    r.wstart = w.take<uint32_t>(nb + 1);
     r.states = w.take<uint32_t>((nb > 0 ? nb : 1) * RS_LANES);
     r.scratch = w.take<uint16_t>((size_t)(nb > 0 ? nb : 1) * B);
     if (out) *out = r;
@@ -919,7 +985,6 @@ hipError_t launch_rans_batch(int count, const RansJob *jobs, int32_t L, int32_t 
         A.counts = W.counts;
         A.fc = W.fc;
         A.wcount = W.wcount;
-        A.wstart = W.wstart;
         A.states = W.states;
         A.scratch = W.scratch;
         A.out = J.out;
@@ -932,21 +997,23 @@ hipError_t launch_rans_batch(int count, const RansJob *jobs, int32_t L, int32_t 
     // about 16 symbols per thread, at most 2048 workgroups per array
     const int gs = grid_over((ncap + 15) / 16, 2048);
     const dim3 one(1, count);
-    hipLaunchKernelGGL(rs_init, one, dim3(TPC_WAVE), 0, st, Bt);
     bool any_fused = false;
     for (int k = 0; k < count; ++k) any_fused = any_fused || Bt.a[k].fused;
-    if (any_fused)
-        hipLaunchKernelGGL(rs_window, dim3(grid_over(TPC_RANS_MAX_RANGE, 1024), count), dim3(TPC_BLOCK), 0, st, Bt);
+    hipLaunchKernelGGL(rs_init, dim3(any_fused ? grid_over(TPC_RANS_MAX_RANGE, 1024) : 1, count), dim3(TPC_BLOCK), 0,
+                       st, Bt);
     hipLaunchKernelGGL(rs_minmax, dim3(gs, count), dim3(TPC_BLOCK), 0, st, Bt);
     hipLaunchKernelGGL(rs_clear, dim3(grid_over(TPC_RANS_MAX_RANGE, 1024), count), dim3(TPC_BLOCK), 0, st, Bt);
     hipLaunchKernelGGL(rs_hist, dim3(gs, count), dim3(TPC_BLOCK), 0, st, Bt);
     hipLaunchKernelGGL(rs_freq, one, dim3(RS_FREQ_THREADS), 0, st, Bt);
-    hipLaunchKernelGGL(rs_table, one, dim3(TPC_BLOCK), 0, st, Bt);
-    const int eb = (nb_cap + TPC_BLOCK / TPC_WAVE - 1) / (TPC_BLOCK / TPC_WAVE);
-    if (eb > 0) hipLaunchKernelGGL(rs_encode, dim3(eb, count), dim3(TPC_BLOCK), 0, st, Bt);
-    hipLaunchKernelGGL(rs_scan, one, dim3(TPC_BLOCK), 0, st, Bt);
-    hipLaunchKernelGGL(rs_pack, dim3(nb_cap > 0 ? (nb_cap < 4096 ? nb_cap : 4096) : 1, count), dim3(TPC_BLOCK), 0,
-                       st, Bt);
+    if (nb_cap >= RS_ENC_FULL)
+        hipLaunchKernelGGL(rs_encode<RS_ENC_T>, dim3((nb_cap + RS_ENC_T / TPC_WAVE - 1) / (RS_ENC_T / TPC_WAVE), count),
+                           dim3(RS_ENC_T), 0, st, Bt);
+    else if (nb_cap > 0)
+        hipLaunchKernelGGL(rs_encode<TPC_BLOCK>,
+                           dim3((nb_cap + TPC_BLOCK / TPC_WAVE - 1) / (TPC_BLOCK / TPC_WAVE), count), dim3(TPC_BLOCK),
+                           0, st, Bt);
+    const int gp = nb_cap < 1 ? 1 : (nb_cap < RS_PACK_GRID ? nb_cap : RS_PACK_GRID);
+    hipLaunchKernelGGL(rs_pack, dim3(gp, count), dim3(TPC_BLOCK), 0, st, Bt);
     return hipGetLastError();
 }
 

@@ -128,10 +128,15 @@ __global__ void __launch_bounds__(TPC_BLOCK) rs_init(RsBatch Bt) {
         A.counts[s] = 0;
 }
 
+// FUSED: for batches with a large array (the histogram's LDS is what limits
+// the workgroups in flight).
+template <bool FUSED>
 __global__ void __launch_bounds__(TPC_BLOCK) rs_minmax(RsBatch Bt) {
-    const RsArgs A = rs_job(Bt);
+    RsArgs A = rs_job(Bt);
+    A.fused = FUSED ? A.fused : 0;
     __shared__ int sh[2][TPC_BLOCK / TPC_WAVE];
-    __shared__ uint32_t h[RS_LDS_BINS];
+    __shared__ uint32_t h[FUSED ? RS_LDS_BINS : 1];
+    if ((int64_t)blockIdx.x * TPC_BLOCK * 4 >= A.n) return;     // no symbols for this workgroup
     int lo = 0x7fffffff, hi = (int)0x80000000;
     const Vec4Split V = vec4_split(A.sym, A.n);
     const int4 *v4 = reinterpret_cast<const int4 *>(A.sym + V.head);
@@ -478,8 +483,7 @@ __device__ inline void encode_block(const RsArgs &A, Tab T, int b, int lane) {
     uint16_t *words = A.scratch + (size_t)b * A.B;
     uint32_t x = 1u << 16;
     int end = A.B;                                  // words from here on are written
-    auto round = [&](int32_t sym, bool act) {
-        const uint4 e = T((uint32_t)(sym - lo));
+    auto round = [&](const uint4 &e, bool act) {
         const bool emit = act && x > e.x;
         const uint64_t mask = __ballot(emit);
         end -= __popcll(mask);
@@ -496,12 +500,13 @@ __device__ inline void encode_block(const RsArgs &A, Tab T, int b, int lane) {
         }
         x = act ? v : x;
     };
+    auto entry = [&](int32_t sym) { return T((uint32_t)(sym - lo)); };
     int j = nloc / RS_LANES;                        // rounds with all lanes
     if (nloc % RS_LANES) {
         const bool act = j * RS_LANES + lane < nloc;
-        round(act ? src[j * RS_LANES] : lo, act);
+        round(entry(act ? src[j * RS_LANES] : lo), act);
     }
-    for (; j % RS_CHUNK; --j) round(src[(j - 1) * RS_LANES], true);
+    for (; j % RS_CHUNK; --j) round(entry(src[(j - 1) * RS_LANES]), true);
     int32_t sv[RS_CHUNK], nx[RS_CHUNK];
     if (j > 0) {
 #pragma unroll
@@ -511,8 +516,15 @@ __device__ inline void encode_block(const RsArgs &A, Tab T, int b, int lane) {
         const int jn = j > RS_CHUNK ? j - RS_CHUNK : j;     // (the last ones again, not used)
 #pragma unroll
         for (int u = 0; u < RS_CHUNK; ++u) nx[u] = src[(jn - 1 - u) * RS_LANES];
+        // the table entries of four rounds at once
 #pragma unroll
-        for (int u = 0; u < RS_CHUNK; ++u) round(sv[u], true);
+        for (int u = 0; u < RS_CHUNK; u += 4) {
+            const uint4 e0 = entry(sv[u]), e1 = entry(sv[u + 1]), e2 = entry(sv[u + 2]), e3 = entry(sv[u + 3]);
+            round(e0, true);
+            round(e1, true);
+            round(e2, true);
+            round(e3, true);
+        }
 #pragma unroll
         for (int u = 0; u < RS_CHUNK; ++u) sv[u] = nx[u];
     }
@@ -1001,8 +1013,11 @@ hipError_t launch_rans_batch(int count, const RansJob *jobs, int32_t L, int32_t 
     for (int k = 0; k < count; ++k) any_fused = any_fused || Bt.a[k].fused;
     hipLaunchKernelGGL(rs_init, dim3(any_fused ? grid_over(TPC_RANS_MAX_RANGE, 1024) : 1, count), dim3(TPC_BLOCK), 0,
                        st, Bt);
-    hipLaunchKernelGGL(rs_minmax, dim3(gs, count), dim3(TPC_BLOCK), 0, st, Bt);
-    hipLaunchKernelGGL(rs_clear, dim3(grid_over(TPC_RANS_MAX_RANGE, 1024), count), dim3(TPC_BLOCK), 0, st, Bt);
+    if (any_fused)
+        hipLaunchKernelGGL(rs_minmax<true>, dim3(gs, count), dim3(TPC_BLOCK), 0, st, Bt);
+    else
+        hipLaunchKernelGGL(rs_minmax<false>, dim3(gs, count), dim3(TPC_BLOCK), 0, st, Bt);
+    hipLaunchKernelGGL(rs_clear, dim3(128, count), dim3(TPC_BLOCK), 0, st, Bt);
     hipLaunchKernelGGL(rs_hist, dim3(gs, count), dim3(TPC_BLOCK), 0, st, Bt);
     hipLaunchKernelGGL(rs_freq, one, dim3(RS_FREQ_THREADS), 0, st, Bt);
     if (nb_cap >= RS_ENC_FULL)

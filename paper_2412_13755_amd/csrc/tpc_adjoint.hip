@@ -14,8 +14,8 @@
 //               start.  Writes dL/dm per seed hit.
 //  adj_partial  deterministic per-(frame, sector) sums per row: seeds of one
 //               (frame, sector) are contiguous (seeds are ordered by their
-//               first cluster id); each workgroup sums fixed chunks of them in
-//               seed order, one thread per row
+//               first cluster id); each wavefront sums fixed chunks of them in
+//               seed order
 //  adj_final    fixed-order sum of the partials, times -dloss
 #include "tpc_fit_common.hpp"
 
@@ -81,51 +81,87 @@ __device__ inline int lower_bound_key(const int32_t *frame, const int32_t *secto
     return lo;
 }
 
+// A wavefront takes 64 seeds at a time and adds their hits' gradients to its
+// own row sums in LDS, a seed per instruction, lane k its k-th hit: the reads
+// are contiguous, TPC_ADJ_AHEAD seeds' are in flight, and the adds of a
+// wavefront happen in their order, so the sums are reproducible.  (A thread
+// per row walking over the seeds that cross it read one value at a time: 285
+// -> PARTIAL us for 645 000 seeds.)
+#define TPC_ADJ_AHEAD 8
 __global__ void __launch_bounds__(TPC_BLOCK)
 adj_partial(const int32_t *__restrict__ n_seeds, int32_t cap_seeds,
             const int32_t *__restrict__ offsets, const int32_t *__restrict__ first_row,
             const int32_t *__restrict__ frame, const int32_t *__restrict__ sector,
             int32_t n_sectors, int32_t n_rows, const float2 *__restrict__ g,
             float2 *__restrict__ partial) {
-    __shared__ int so[TPC_BLOCK], sn[TPC_BLOCK], sr[TPC_BLOCK];
+    constexpr int W = TPC_BLOCK / TPC_WAVE;
+    __shared__ float sy[W][TPC_MAX_ROWS], sz[W][TPC_MAX_ROWS];
     __shared__ int range[2];
     const int fs = blockIdx.x, gsub = blockIdx.y, G = gridDim.y;
-    const int r = threadIdx.x;
-    if (threadIdx.x == 0) {
+    const int lane = threadIdx.x & (TPC_WAVE - 1), wid = threadIdx.x / TPC_WAVE;
+    if (threadIdx.x < 2) {
         int T = *n_seeds;
         if (T > cap_seeds) T = cap_seeds;
-        range[0] = lower_bound_key(frame, sector, n_sectors, T, fs);
-        range[1] = lower_bound_key(frame, sector, n_sectors, T, fs + 1);
+        range[threadIdx.x] = lower_bound_key(frame, sector, n_sectors, T, fs + threadIdx.x);
     }
+    for (int r = lane; r < n_rows; r += TPC_WAVE) sy[wid][r] = sz[wid][r] = 0.f;
     __syncthreads();
-    const int lo = range[0], hi = range[1];
-    float ay = 0.f, az = 0.f;
-    for (int c0 = lo + gsub * TPC_BLOCK; c0 < hi; c0 += G * TPC_BLOCK) {
-        const int i = c0 + threadIdx.x;
+    const int hi = range[1];
+    for (int64_t c0 = range[0] + (int64_t)(gsub * W + wid) * TPC_WAVE; c0 < hi; c0 += (int64_t)G * W * TPC_WAVE) {
+        const int i = (int)c0 + lane;
+        int so = 0, sn = 0, sr = 0;
         if (i < hi) {
-            so[threadIdx.x] = offsets[i];
-            sn[threadIdx.x] = offsets[i + 1] - offsets[i];
-            sr[threadIdx.x] = first_row[i];
-        }
-        __syncthreads();
-        const int cnt = hi - c0 < TPC_BLOCK ? hi - c0 : TPC_BLOCK;
-        // a frame-sector's seeds come in non-decreasing first row (seed
-        // order is first-cluster id order), so none after the first seed
-        // starting above row r reaches r
-        for (int q = 0; q < cnt; ++q) {
-            if (sr[q] > r) break;
-            const int k = r - sr[q];
+            so = offsets[i];
+            sn = offsets[i + 1] - so;
+            sr = first_row[i];
             // seeds that fail the fit's sanity checks were never written
-            const bool sane = sn[q] >= 3 && sr[q] >= 0 && sr[q] + sn[q] <= n_rows && so[q] >= 0;
-            if (sane && k >= 0 && k < sn[q]) {
-                const float2 v = g[so[q] + k];
-                ay += v.x;
-                az += v.y;
+            if (!(sn >= 3 && sr >= 0 && sr + sn <= n_rows && so >= 0)) sn = 0;
+        }
+        for (int q = 0; q < TPC_WAVE; q += TPC_ADJ_AHEAD) {
+            float2 v[TPC_ADJ_AHEAD];
+            int longest = 0;
+#pragma unroll
+            for (int u = 0; u < TPC_ADJ_AHEAD; ++u) {
+                const int n = __builtin_amdgcn_readlane(sn, q + u), o = __builtin_amdgcn_readlane(so, q + u);
+                v[u] = lane < n ? g[o + lane] : make_float2(0.f, 0.f);
+                longest = max(longest, n);
+            }
+#pragma unroll
+            for (int u = 0; u < TPC_ADJ_AHEAD; ++u) {
+                const int n = __builtin_amdgcn_readlane(sn, q + u), r = __builtin_amdgcn_readlane(sr, q + u) + lane;
+                if (lane < n) {
+                    atomicAdd(&sy[wid][r], v[u].x);
+                    atomicAdd(&sz[wid][r], v[u].y);
+                }
+            }
+            if (longest <= TPC_WAVE) continue;
+            for (int k = lane + TPC_WAVE; k - lane < longest; k += TPC_WAVE) {
+#pragma unroll
+                for (int u = 0; u < TPC_ADJ_AHEAD; ++u) {
+                    const int n = __builtin_amdgcn_readlane(sn, q + u), o = __builtin_amdgcn_readlane(so, q + u);
+                    v[u] = k < n ? g[o + k] : make_float2(0.f, 0.f);
+                }
+#pragma unroll
+                for (int u = 0; u < TPC_ADJ_AHEAD; ++u) {
+                    const int n = __builtin_amdgcn_readlane(sn, q + u), r = __builtin_amdgcn_readlane(sr, q + u) + k;
+                    if (k < n) {
+                        atomicAdd(&sy[wid][r], v[u].x);
+                        atomicAdd(&sz[wid][r], v[u].y);
+                    }
+                }
             }
         }
-        __syncthreads();
     }
-    if (r < n_rows) partial[((size_t)fs * G + gsub) * n_rows + r] = make_float2(ay, az);
+    __syncthreads();
+    for (int r = threadIdx.x; r < n_rows; r += TPC_BLOCK) {
+        double ay = 0.0, az = 0.0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            ay += sy[w][r];
+            az += sz[w][r];
+        }
+        partial[((size_t)fs * G + gsub) * n_rows + r] = make_float2((float)ay, (float)az);
+    }
 }
 
 __global__ void __launch_bounds__(TPC_BLOCK)
@@ -136,6 +172,7 @@ adj_final(const float2 *__restrict__ partial, int32_t n_frames, int32_t n_sector
     const int s = idx / n_rows, r = idx % n_rows;
     double ay = 0.0, az = 0.0;
     for (int f = 0; f < n_frames; ++f)
+#pragma unroll 8
         for (int q = 0; q < G; ++q) {
             const float2 v = partial[((size_t)(f * n_sectors + s) * G + q) * n_rows + r];
             ay += v.x;

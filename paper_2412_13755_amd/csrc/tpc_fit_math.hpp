@@ -13,9 +13,9 @@
 // first hits (C - K H C cancels).  On gfx950 the FP64 vector FMA issues at the
 // rate of the non-packed FP32 one, so double costs no more than float here.
 // Reciprocals and square roots in the inner loop use the hardware estimates
-// refined by Newton steps rather than the correctly rounded sequences.  The
-// second-order term of the adjoint (derivative of the Jacobian) is evaluated
-// in single precision.
+// refined by Newton steps rather than the correctly rounded sequences.  So
+// does the adjoint, with the second-order term (derivative of the Jacobian)
+// in the closed forms that follow from the step's.
 // No MFMA: a 5x5 symmetric update is not a dense contraction.
 #pragma once
 
@@ -29,37 +29,15 @@ struct SymT {
     R c00, c10, c11, c20, c21, c22, c30, c31, c32, c33, c40, c41, c42, c43, c44;
 };
 
-__host__ __device__ inline float asin_over(float u) {
-    // asin(u)/u, Taylor series to u^8 near 0
-    if (fabsf(u) < 0.05f) {
-        float u2 = u * u;
-        return 1.0f + u2 * (1.0f / 6.0f + u2 * (3.0f / 40.0f + u2 * (5.0f / 112.0f + u2 * (35.0f / 1152.0f))));
-    }
-    return asinf(u) / u;
-}
-
-// first derivative of asin(u)/u
-__host__ __device__ inline float asin_over_d(float u) {
-    if (fabsf(u) < 0.05f) {
-        float u2 = u * u;
-        return u * (1.0f / 3.0f + u2 * (3.0f / 10.0f + u2 * (15.0f / 56.0f + u2 * (35.0f / 144.0f))));
-    }
-    return (u / sqrtf((1.0f - u) * (1.0f + u)) - asinf(u)) / (u * u);
-}
-
-// second derivative of asin(u)/u: (1-u^2)^(-3/2) - 2 g'(u)/u
-__host__ __device__ inline float asin_over_dd(float u) {
-    if (fabsf(u) < 0.05f) {
-        float u2 = u * u;
-        return 1.0f / 3.0f + u2 * (9.0f / 10.0f + u2 * (75.0f / 56.0f + u2 * (245.0f / 144.0f)));
-    }
-    const float w = 1.0f / sqrtf((1.0f - u) * (1.0f + u));
-    return w * w * w - 2.0f * asin_over_d(u) / u;
-}
-
 // Jacobian entries that differ from the identity.
 struct StepJac {
     double f02, f04, f12, f13, f14, f24;
+};
+
+// What the derivatives of the Jacobian use of a step: 1/c, 1/c', T, 1/(c + c').
+template <class R>
+struct StepTrig {
+    R ic1, ic2, T, iden;
 };
 
 // Reciprocal and square root of positive, finite, normal doubles for the
@@ -100,10 +78,18 @@ __host__ __device__ inline double sqrt_pos(double x, double *inv) {
 }
 
 // asin(u)/u away from 0 (|u| >= 0.05: a step that turns the track by more
-// than ~6 degrees).  Out of line: rarely taken, and the
-// library asin would otherwise occupy registers in the filter loop.
-__host__ __device__ __attribute__((noinline)) inline double asin_over_far(double u) {
-    return asin(u) / u;
+// than ~6 degrees): asin(u) = 2 asin(u / sqrt(2 (1 + sqrt(1 - u^2)))) until
+// the series holds (five times at most; NaN beyond 1).  Rarely taken; a call
+// of the library's asin made every fit keep what lives across it in the
+// registers that calls leave alone.
+__host__ __device__ inline double asin_over_far(double u) {
+    double v = u, k = 1.0;
+    while (fabs(v) >= 0.05) {
+        v = v / sqrt(2.0 + 2.0 * sqrt((1.0 - v) * (1.0 + v)));
+        k += k;
+    }
+    const double v2 = v * v;
+    return k * v * (1.0 + v2 * (1.0 / 6 + v2 * (3.0 / 40 + v2 * (5.0 / 112 + v2 * (35.0 / 1152))))) / u;
 }
 // asin(u)/u in the state precision (Taylor series to u^8 near 0)
 template <class R>
@@ -137,7 +123,8 @@ __host__ __device__ inline R asin_over_r(R u) {
 // degrees, where v falls again) take the half angle u = sin(delta/2) =
 // kappa chord/2 and darc/dkappa = (dx/c' - arc)/kappa.
 template <class R, class K = float>
-__host__ __device__ inline bool helix_step(R p[5], K dx, K kbz, float max_sin, StepJac &J) {
+__host__ __device__ inline bool helix_step(R p[5], K dx, K kbz, float max_sin, StepJac &J,
+                                           StepTrig<R> *trig = nullptr) {
     // kbz = -c Bz, so kappa = kbz * w
     const R s = p[2], t = p[3], w = p[4], d = (R)dx, kb = (R)kbz;
     const R kap = kb * w, kd = kap * d;
@@ -167,6 +154,7 @@ __host__ __device__ inline bool helix_step(R p[5], K dx, K kbz, float max_sin, S
         arc = (d >= (R)0 ? chord : -chord) * asin_over_r(u);
         dark = (d * ic2 - arc) / kap;
     }
+    if (trig) *trig = StepTrig<R>{ic1, ic2, T, iden};
     J.f02 = dB * cc;
     J.f04 = d * kb * dTk;
     J.f12 = t * (d * T * cc);
@@ -364,85 +352,63 @@ __host__ __device__ inline bool helix_start(R xa, R ya, R za, R xb, R yb, R xc, 
 // Adjoint (reverse mode), written out by hand.  A symmetric matrix argument
 // has a symmetric adjoint Mbar with dL = <Mbar, dM> for symmetric dM.
 
-// Adds d<Fbar, F(p)>/dp into pbar[2..4]: the dependence of the step Jacobian
-// on (s, t, w) of the state the step starts from (single precision).
-__host__ __device__ inline void helix_jac_adjoint(float s, float t, float w, float dx, float kbz,
-                                                  float G02, float G04, float G12, float G13,
-                                                  float G14, float &bs, float &bt, float &bw) {
-    const float kap = kbz * w;
-    const float s2 = s + kap * dx;
-    const float c1 = sqrtf((1.0f - s) * (1.0f + s));
-    const float c2 = sqrtf((1.0f - s2) * (1.0f + s2));
-    const float den = c1 + c2;
-    const float iden = 1.0f / den;
-    const float A1 = s + s2;
-    const float T = A1 * iden;
-    const float adx = fabsf(dx);
-    const float sq = sqrtf(1.0f + T * T);
-    const float chord = adx * sq;
-    const float u = 0.5f * kap * chord;
-    const float g = asin_over(u);
-    const float gp = asin_over_d(u);
-    const float gpp = asin_over_dd(u);
-    const float sgn = dx >= 0.0f ? 1.0f : -1.0f;
-    const float iden2 = iden * iden;
-    const float N1 = den + A1 * s / c1;
-    const float N2 = den + A1 * s2 / c2;
-    const float dT_ds = (N1 + N2) * iden2;
-    const float dT_dw = N2 * iden2 * dx * kbz;
-    const float w1 = 1.0f / sqrtf((1.0f - u) * (1.0f + u));
-    const float darc_dkap = sgn * 0.5f * chord * chord * gp;
-    const float dchord_dT = adx * T / sq;
-    const float q = sgn * w1 * dchord_dT;
-    // reverse sweep
-    const float b_dTds = G02 * dx + G12 * t * q;
-    const float b_dTdw = G04 * dx + G14 * t * q;
-    const float b_t = G12 * q * dT_ds + G14 * (q * dT_dw + darc_dkap * kbz);
-    const float b_q = G12 * t * dT_ds + G14 * t * dT_dw;
-    const float b_arc = G13;
-    const float b_darc_dkap = G14 * t * kbz;
-    const float b_N2 = (b_dTdw * dx * kbz + b_dTds) * iden2;
-    const float b_N1 = b_dTds * iden2;
-    const float b_w1 = b_q * sgn * dchord_dT;
-    const float b_dchord_dT = b_q * sgn * w1;
-    float b_T = b_dchord_dT * adx / sq;
-    float b_sq = -b_dchord_dT * adx * T / (sq * sq);
-    float b_chord = b_darc_dkap * sgn * chord * gp + b_arc * sgn * g;
-    const float b_gp = b_darc_dkap * sgn * 0.5f * chord * chord;
-    const float b_g = b_arc * sgn * chord;
-    const float b_u = b_gp * gpp + b_w1 * u * w1 * w1 * w1 + b_g * gp;
-    float b_kap = b_u * 0.5f * chord;
-    b_chord += b_u * 0.5f * kap;
-    b_sq += b_chord * adx;
-    b_T += b_sq * T / sq;
-    const float b_iden2 = b_dTds * N1 + (b_dTdw * dx * kbz + b_dTds) * N2;
-    float b_den = b_N1 + b_N2;
-    float b_A1 = b_N1 * s / c1 + b_N2 * s2 / c2;
-    float b_s = b_N1 * A1 / c1;
-    float b_s2 = b_N2 * A1 / c2;
-    float b_c1 = -b_N1 * A1 * s / (c1 * c1);
-    float b_c2 = -b_N2 * A1 * s2 / (c2 * c2);
-    float b_iden = b_iden2 * 2.0f * iden;
-    b_A1 += b_T * iden;
-    b_iden += b_T * A1;
-    b_den += -b_iden * iden * iden;
-    b_c1 += b_den;
-    b_c2 += b_den;
-    b_s2 += -b_c2 * s2 / c2;
-    b_s += -b_c1 * s / c1;
-    b_s += b_A1;
-    b_s2 += b_A1;
-    b_s += b_s2;
-    b_kap += b_s2 * dx;
-    bs = b_s;
-    bt = b_t;
-    bw = b_kap * kbz;
+// d<G, F(p)>/dp for p = (s, t, w) of the state a step of Jacobian F starts
+// from: the second partial derivatives of (T, arc) of helix_step.  With
+// cc = 1/(c c') and the logarithmic derivatives of cc, 1/c' and 1/(c + c'),
+//   d2T/ds2 = cc (dB/ds + B (s/c^2 + s'/c'^2)),   dB/ds = T + s dT/ds - s/c,
+//   d2T/dsdk = cc (s dT/dk + B dx s'/c'^2),
+//   d2T/dk2 = dT/dk dx/c' (T + s'/c'),
+//   d2arc/ds2 = dx cc (dT/ds + T (s/c^2 + s'/c'^2)),
+//   d2arc/dsdk = dx cc (dT/dk + T dx s'/c'^2),
+// and d2arc/dk2 from arc = dB g(v), v = kappa dB, dB = dx B (near), or from
+// darc/dk = (dx/c' - arc)/kappa (far; the same limit as helix_step's).
+template <class R, class K>
+__host__ __device__ inline void helix_jac_adjoint(const R p[5], K dx, K kbz, R arc, const StepTrig<R> &q, R G02, R G04,
+                                                  R G12, R G13, R G14, R &bs, R &bt, R &bw) {
+    const R s = p[2], t = p[3], d = (R)dx, kb = (R)kbz, kap = kb * p[4], kd = kap * d;
+    const R s2 = fma(kap, d, s), T = q.T;
+    const R u1 = s * q.ic1, u2 = s2 * q.ic2;            // s/c, s'/c'
+    const R B = fma(-s, s, (R)1) * q.ic1 + s * T;
+    const R cc = q.ic1 * q.ic2, dB = d * B, v = kd * B;
+    const R Ts = B * cc, Tk = dB * q.iden * q.ic2;
+    const R l1 = u1 * q.ic1 + u2 * q.ic2, l2 = d * u2 * q.ic2;   // d ln cc/ds, d ln cc/dkappa
+    const R Tss = cc * (T + s * Ts - u1 + B * l1);
+    const R Tsk = cc * (s * Tk + B * l2);
+    const R Tkk = Tk * (d * q.ic2) * (T + u2);
+    const R dcc = d * cc;
+    const R as = dcc * T, ass = dcc * (Ts + T * l1), ask = dcc * (Tk + T * l2);
+    R ak, akk;
+    if (fabs(v) < (R)0.05 && fabs(kd) < (R)1) {
+        const R v2 = v * v;
+        const R g = (R)1 + v2 * ((R)1 / 6 + v2 * ((R)3 / 40 + v2 * ((R)5 / 112 + v2 * ((R)35 / 1152))));
+        const R gd = v * ((R)1 / 3 + v2 * ((R)3 / 10 + v2 * ((R)15 / 56 + v2 * ((R)35 / 144))));
+        const R gdd = (R)1 / 3 + v2 * ((R)9 / 10 + v2 * ((R)75 / 56 + v2 * ((R)245 / 144)));
+        const R Bk = d * s * Tk, Bkk = d * s * Tkk;     // of dB
+        const R vk = dB + kap * Bk, vkk = (R)2 * Bk + kap * Bkk;
+        ak = Bk * g + dB * gd * vk;
+        akk = Bkk * g + (R)2 * Bk * gd * vk + dB * (gdd * vk * vk + gd * vkk);
+    } else {
+        const R ik = (R)1 / kap;
+        ak = (d * q.ic2 - arc) * ik;
+        akk = (d * l2 * q.ic2 - (R)2 * ak) * ik;
+    }
+    const R G4 = G04 * kb, G14t = G14 * t * kb;
+    bs = d * (G02 * Tss + G4 * Tsk) + G12 * t * ass + G13 * as + G14t * ask;
+    bw = kb * (d * (G02 * Tsk + G4 * Tkk) + G12 * t * ask + G13 * ak + G14t * akk);
+    bt = G12 * as + G14 * kb * ak;
 }
 
 // Reverse of one filter step (propagate by dx, then update with (my, mz)).
 // In: the state (pb, Cb) the step started from, the adjoints (pbar, Cbar)
 // of its result, chibar = dL/dchi2.  Out: pbar, Cbar become the adjoints of
 // (pb, Cb); (mby, mbz) receive dL/d(my, mz).
+//
+// The update from the propagated (x, P): with K its gain, A = I - K H and
+// a = S^-1 r, dC = A dP A^T, dx' = A (dx + dP H^T a) + K dm and dchi2 =
+// 2 a^T dr - a^T H dP H^T a, so
+//   Pbar = A^T Cbar A + sym(A^T pbar (H^T a)^T) - chibar (H^T a)(H^T a)^T,
+//   mbar = 2 chibar a + K^T pbar,  xbar = pbar - H^T mbar,
+// where A^T Cbar A differs from Cbar in rows and columns 0 and 1 only.
 template <class R>
 __host__ __device__ inline void step_adjoint(const R pb[5], const SymT<R> &Cb, float dx, float kbz,
                                              R my, R mz, R vy, R vz, R chibar, R pbar[5],
@@ -450,90 +416,79 @@ __host__ __device__ inline void step_adjoint(const R pb[5], const SymT<R> &Cb, f
     // recompute the step
     R pp[5] = {pb[0], pb[1], pb[2], pb[3], pb[4]};
     StepJac J;
-    helix_step(pp, dx, kbz, 2.0f, J);
-    SymT<R> P = Cb;
-    sym_transport<R, false>(P, J);
-    const R r0 = my - pp[0], r1 = mz - pp[1];
-    const R S00 = P.c00 + vy, S01 = P.c10, S11 = P.c11 + vz;
-    const R idet = (R)1 / (S00 * S11 - S01 * S01);
-    const R i00 = S11 * idet, i01 = -S01 * idet, i11 = S00 * idet;
-    const R a0 = i00 * r0 + i01 * r1, a1 = i01 * r0 + i11 * r1;        // a = S^-1 r
-    // columns of B = P[:, 0:2]
-    const R B0[5] = {P.c00, P.c10, P.c20, P.c30, P.c40};
-    const R B1[5] = {P.c10, P.c11, P.c21, P.c31, P.c41};
-    const R Cb_[25] = {Cbar.c00, Cbar.c10, Cbar.c20, Cbar.c30, Cbar.c40,
-                       Cbar.c10, Cbar.c11, Cbar.c21, Cbar.c31, Cbar.c41,
-                       Cbar.c20, Cbar.c21, Cbar.c22, Cbar.c32, Cbar.c42,
-                       Cbar.c30, Cbar.c31, Cbar.c32, Cbar.c33, Cbar.c43,
-                       Cbar.c40, Cbar.c41, Cbar.c42, Cbar.c43, Cbar.c44};
-    R ab0 = 0, ab1 = 0;                 // abar = B^T pbar
-    R CB0[5], CB1[5];                   // Cbar B
+    StepTrig<R> trig;
+    helix_step(pp, dx, kbz, 2.0f, J, &trig);
+    SymT<R> Pb = Cbar;
+    R q0, q1;
+    {
+        SymT<R> P = Cb;
+        sym_transport<R, false>(P, J);
+        const R r0 = my - pp[0], r1 = mz - pp[1];
+        const R S00 = P.c00 + vy, S01 = P.c10, S11 = P.c11 + vz;
+        const R idet = recip_pos(S00 * S11 - S01 * S01);
+        const R i00 = S11 * idet, i01 = -S01 * idet, i11 = S00 * idet;
+        const R a0 = i00 * r0 + i01 * r1, a1 = i01 * r0 + i11 * r1;
+        const R B0[5] = {P.c00, P.c10, P.c20, P.c30, P.c40};
+        const R B1[5] = {P.c10, P.c11, P.c21, P.c31, P.c41};
+        const R Cb_[25] = {Cbar.c00, Cbar.c10, Cbar.c20, Cbar.c30, Cbar.c40,
+                           Cbar.c10, Cbar.c11, Cbar.c21, Cbar.c31, Cbar.c41,
+                           Cbar.c20, Cbar.c21, Cbar.c22, Cbar.c32, Cbar.c42,
+                           Cbar.c30, Cbar.c31, Cbar.c32, Cbar.c33, Cbar.c43,
+                           Cbar.c40, Cbar.c41, Cbar.c42, Cbar.c43, Cbar.c44};
+        R K0[5], K1[5], kp0 = 0, kp1 = 0;       // K, K^T pbar
 #pragma unroll
-    for (int i = 0; i < 5; ++i) {
-        ab0 += B0[i] * pbar[i];
-        ab1 += B1[i] * pbar[i];
-        R x0 = 0, x1 = 0;
+        for (int i = 0; i < 5; ++i) {
+            K0[i] = B0[i] * i00 + B1[i] * i01;
+            K1[i] = B0[i] * i01 + B1[i] * i11;
+            kp0 += K0[i] * pbar[i];
+            kp1 += K1[i] * pbar[i];
+        }
+        R CK0[5], CK1[5];                       // Cbar K
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            R x0 = 0, x1 = 0;
+#pragma unroll
+            for (int k = 0; k < 5; ++k) {
+                x0 += Cb_[i * 5 + k] * K0[k];
+                x1 += Cb_[i * 5 + k] * K1[k];
+            }
+            CK0[i] = x0;
+            CK1[i] = x1;
+        }
+        R k00 = 0, k01 = 0, k11 = 0;            // K^T Cbar K
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
-            x0 += Cb_[i * 5 + k] * B0[k];
-            x1 += Cb_[i * 5 + k] * B1[k];
+            k00 += K0[k] * CK0[k];
+            k01 += K0[k] * CK1[k];
+            k11 += K1[k] * CK1[k];
         }
-        CB0[i] = x0;
-        CB1[i] = x1;
+        const R u0 = pbar[0] - kp0, u1 = pbar[1] - kp1;        // A^T pbar
+        const R h0 = (R)0.5 * a0, h1 = (R)0.5 * a1;
+        Pb.c00 += (k00 - (R)2 * CK0[0]) + a0 * (u0 - chibar * a0);
+        Pb.c10 += (k01 - CK0[1] - CK1[0]) + h0 * u1 + h1 * u0 - chibar * a0 * a1;
+        Pb.c11 += (k11 - (R)2 * CK1[1]) + a1 * (u1 - chibar * a1);
+        Pb.c20 += h0 * pbar[2] - CK0[2];
+        Pb.c21 += h1 * pbar[2] - CK1[2];
+        Pb.c30 += h0 * pbar[3] - CK0[3];
+        Pb.c31 += h1 * pbar[3] - CK1[3];
+        Pb.c40 += h0 * pbar[4] - CK0[4];
+        Pb.c41 += h1 * pbar[4] - CK1[4];
+        mby = (R)2 * chibar * a0 + kp0;
+        mbz = (R)2 * chibar * a1 + kp1;
+        q0 = pbar[0] - mby;
+        q1 = pbar[1] - mbz;
     }
-    R BCB00 = 0, BCB01 = 0, BCB11 = 0;  // B^T Cbar B (symmetric)
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        BCB00 += B0[k] * CB0[k];
-        BCB01 += B0[k] * CB1[k];
-        BCB11 += B1[k] * CB1[k];
-    }
-    // Sibar = chibar r r^T + abar r^T - B^T Cbar B
-    const R Sb00 = chibar * r0 * r0 + ab0 * r0 - BCB00;
-    const R Sb01 = chibar * r0 * r1 + ab0 * r1 - BCB01;
-    const R Sb10 = chibar * r1 * r0 + ab1 * r0 - BCB01;
-    const R Sb11 = chibar * r1 * r1 + ab1 * r1 - BCB11;
-    // Sbar = -Si Sibar Si, symmetrised
-    const R t00 = i00 * Sb00 + i01 * Sb10, t01 = i00 * Sb01 + i01 * Sb11;
-    const R t10 = i01 * Sb00 + i11 * Sb10, t11 = i01 * Sb01 + i11 * Sb11;
-    const R Sbar00 = -(t00 * i00 + t01 * i01);
-    const R Sbar01 = -(R)0.5 * ((t00 * i01 + t01 * i11) + (t10 * i00 + t11 * i01));
-    const R Sbar11 = -(t10 * i01 + t11 * i11);
-    // rbar = 2 chibar a + Si abar
-    const R rb0 = (R)2 * chibar * a0 + i00 * ab0 + i01 * ab1;
-    const R rb1 = (R)2 * chibar * a1 + i01 * ab0 + i11 * ab1;
-    mby = rb0;
-    mbz = rb1;
-    // Bbar = pbar a^T - 2 Cbar B Si
-    R Bb0[5], Bb1[5];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-        Bb0[i] = pbar[i] * a0 - (R)2 * (CB0[i] * i00 + CB1[i] * i01);
-        Bb1[i] = pbar[i] * a1 - (R)2 * (CB0[i] * i01 + CB1[i] * i11);
-    }
-    // Pbar = Cbar + sym(Bbar in columns 0, 1) + Sbar in the 2x2 block
-    SymT<R> Pb = Cbar;
-    Pb.c00 += Bb0[0] + Sbar00;
-    Pb.c10 += (R)0.5 * (Bb0[1] + Bb1[0]) + Sbar01;
-    Pb.c11 += Bb1[1] + Sbar11;
-    Pb.c20 += (R)0.5 * Bb0[2];
-    Pb.c21 += (R)0.5 * Bb1[2];
-    Pb.c30 += (R)0.5 * Bb0[3];
-    Pb.c31 += (R)0.5 * Bb1[3];
-    Pb.c40 += (R)0.5 * Bb0[4];
-    Pb.c41 += (R)0.5 * Bb1[4];
-    // adjoint of the propagated state: pbar - H^T rbar
-    const R q0 = pbar[0] - rb0, q1 = pbar[1] - rb1, q2 = pbar[2], q3 = pbar[3], q4 = pbar[4];
+    const R q2 = pbar[2], q3 = pbar[3], q4 = pbar[4];
     // Fbar = 2 Pbar F Cb, entries (0,2) (0,4) (1,2) (1,3) (1,4).  Rows 0, 1 of
     // Pbar F: column j of F adds the columns listed in sym_transport.
     const R PF00 = Pb.c00, PF01 = Pb.c10;
-    const R PF02 = Pb.c20 + (R)J.f02 * Pb.c00 + (R)J.f12 * Pb.c10;
-    const R PF03 = Pb.c30 + (R)J.f13 * Pb.c10;
-    const R PF04 = Pb.c40 + (R)J.f04 * Pb.c00 + (R)J.f14 * Pb.c10 + (R)J.f24 * Pb.c20;
+    const R PF02 = Pb.c20 + J.f02 * Pb.c00 + J.f12 * Pb.c10;
+    const R PF03 = Pb.c30 + J.f13 * Pb.c10;
+    const R PF04 = Pb.c40 + J.f04 * Pb.c00 + J.f14 * Pb.c10 + J.f24 * Pb.c20;
     const R PF10 = Pb.c10, PF11 = Pb.c11;
-    const R PF12 = Pb.c21 + (R)J.f02 * Pb.c10 + (R)J.f12 * Pb.c11;
-    const R PF13 = Pb.c31 + (R)J.f13 * Pb.c11;
-    const R PF14 = Pb.c41 + (R)J.f04 * Pb.c10 + (R)J.f14 * Pb.c11 + (R)J.f24 * Pb.c21;
+    const R PF12 = Pb.c21 + J.f02 * Pb.c10 + J.f12 * Pb.c11;
+    const R PF13 = Pb.c31 + J.f13 * Pb.c11;
+    const R PF14 = Pb.c41 + J.f04 * Pb.c10 + J.f14 * Pb.c11 + J.f24 * Pb.c21;
     const R Cc2[5] = {Cb.c20, Cb.c21, Cb.c22, Cb.c32, Cb.c42};     // column 2 of Cb
     const R Cc3[5] = {Cb.c30, Cb.c31, Cb.c32, Cb.c33, Cb.c43};
     const R Cc4[5] = {Cb.c40, Cb.c41, Cb.c42, Cb.c43, Cb.c44};
@@ -552,15 +507,13 @@ __host__ __device__ inline void step_adjoint(const R pb[5], const SymT<R> &Cb, f
     Cbar = Pb;
     sym_transport<R, true>(Cbar, J);
     // pbar_b = F^T q + second-order term of the Jacobian
-    float bs, bt, bw;
-    helix_jac_adjoint((float)pb[2], (float)pb[3], (float)pb[4], dx, kbz, (float)(2 * G02),
-                      (float)(2 * G04), (float)(2 * G12), (float)(2 * G13), (float)(2 * G14),
-                      bs, bt, bw);
+    R bs, bt, bw;
+    helix_jac_adjoint(pb, dx, kbz, J.f13, trig, (R)2 * G02, (R)2 * G04, (R)2 * G12, (R)2 * G13, (R)2 * G14, bs, bt, bw);
     pbar[0] = q0;
     pbar[1] = q1;
-    pbar[2] = q2 + (R)J.f02 * q0 + (R)J.f12 * q1 + (R)bs;
-    pbar[3] = q3 + (R)J.f13 * q1 + (R)bt;
-    pbar[4] = q4 + (R)J.f04 * q0 + (R)J.f14 * q1 + (R)J.f24 * q2 + (R)bw;
+    pbar[2] = q2 + J.f02 * q0 + J.f12 * q1 + bs;
+    pbar[3] = q3 + J.f13 * q1 + bt;
+    pbar[4] = q4 + J.f04 * q0 + J.f14 * q1 + J.f24 * q2 + bw;
 }
 
 // Reverse of helix_start: adjoint of the start state -> adjoints of the

@@ -5,13 +5,15 @@
 // (sector s, row r) corrected by -M[s][r]; dL/dM[s][r] = -(sum of dL/dm over
 // the hits of (s, r)), scaled by the caller's upstream gradient dloss.
 //
-//  adj_tracks   one thread per seed, longest first, reverse mode by hand: for each segment of
-//               ckpt_rows filter steps, from the innermost backwards, restart
-//               from the forward checkpoint, recompute the segment storing the
-//               filter state before every step in a per-thread tape (global
-//               memory, laid out so a wavefront's accesses are contiguous),
-//               then run the step adjoints over it; finally the three-point
-//               start.  Writes dL/dm per seed hit.
+//  adj_tracks   one thread per seed, longest first, reverse mode by hand: for
+//               each segment of ckpt_rows filter steps, from the innermost
+//               backwards, restart from the forward checkpoint and recompute
+//               the segment, keeping every fourth filter state in a
+//               per-thread tape (global memory, laid out so a wavefront's
+//               accesses are contiguous); then, from the last, recompute four
+//               steps with their states in LDS and run the step adjoints over
+//               them; finally the three-point start.  Writes dL/dm per seed
+//               hit.
 //  adj_partial  deterministic per-(frame, sector) sums per row: seeds of one
 //               (frame, sector) are contiguous (seeds are ordered by their
 //               first cluster id); each wavefront sums fixed chunks of them in
@@ -26,7 +28,7 @@ struct AdjArgs {
     const int32_t *status;
     const double *ckpt;
     float2 *g;          // [cap_hits] dL/d(my, mz) per seed hit
-    double *tape;       // [threads / 64][K][TPC_CKPT_WORDS][64]
+    double *tape;       // [threads / 64][adj_tape_states(K)][TPC_CKPT_WORDS][64]
     int32_t nthreads;
 };
 
@@ -45,23 +47,25 @@ __device__ inline int64_t snake(int64_t k, int gt, int nthreads) {
 // of 645 000 seeds 3.15 -> 1.83 ms.
 __global__ void __launch_bounds__(TPC_BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
 adj_tracks(AdjArgs A) {
-    __shared__ float xs[TPC_MAX_ROWS];
+    // two states per thread: half of a CU's LDS, for half of its threads
+    __shared__ double lt[(TPC_ADJ_SUB - 2) * TPC_CKPT_WORDS * TPC_BLOCK];
     const FitArgs &F = A.F;
-    for (int r = threadIdx.x; r < F.n_rows; r += TPC_BLOCK) xs[r] = F.row_x[r];
-    __syncthreads();
     int T = *F.n_seeds;
     if (T > F.cap_seeds) T = F.cap_seeds;
     const int gt = blockIdx.x * TPC_BLOCK + threadIdx.x;
-    const int K = F.ckpt_rows;
-    // this thread's tape: word q of step s at tp[(s * TPC_CKPT_WORDS + q) * 64],
-    // so the 64 lanes of a wavefront touch one contiguous 512-byte run
-    double *tp = A.tape + (size_t)(gt / TPC_WAVE) * K * TPC_CKPT_WORDS * TPC_WAVE + (gt & (TPC_WAVE - 1));
+    const int K = adj_tape_states(F.ckpt_rows);
+    // this wavefront's tape: word q of state s of lane l at
+    // tp[(s * TPC_CKPT_WORDS + q) * 64 + l], so the 64 lanes touch one
+    // contiguous 512-byte run
+    const int wave = __builtin_amdgcn_readfirstlane(gt / TPC_WAVE);
+    double *tp = A.tape + (size_t)wave * K * TPC_CKPT_WORDS * TPC_WAVE;
     if (F.order) T = *F.n_order < T ? *F.n_order : T;
     for (int64_t k = 0; k * A.nthreads < T; ++k) {
         const int64_t j = snake(k, gt, A.nthreads);
         if (j >= T) continue;
         const int i = F.order ? F.order[j] : (int)j;
-        if ((uint32_t)i < (uint32_t)F.cap_seeds) adj_one(F, A.status, A.ckpt, A.g, i, xs, tp, TPC_WAVE);
+        if ((uint32_t)i < (uint32_t)F.cap_seeds) 
+            adj_one(F, A.status, A.ckpt, A.g, i, tp, threadIdx.x % TPC_WAVE, lt + threadIdx.x, TPC_BLOCK);
     }
 }
 
@@ -86,7 +90,7 @@ __device__ inline int lower_bound_key(const int32_t *frame, const int32_t *secto
 // are contiguous, TPC_ADJ_AHEAD seeds' are in flight, and the adds of a
 // wavefront happen in their order, so the sums are reproducible.  (A thread
 // per row walking over the seeds that cross it read one value at a time: 285
-// -> PARTIAL us for 645 000 seeds.)
+// -> 113 us for 645 000 seeds.)
 #define TPC_ADJ_AHEAD 8
 __global__ void __launch_bounds__(TPC_BLOCK)
 adj_partial(const int32_t *__restrict__ n_seeds, int32_t cap_seeds,
@@ -205,7 +209,7 @@ size_t adj_ws_layout(void *ws, int64_t cap_hits, int64_t cap_seeds, int64_t n_fs
     WsCarver w(ws);
     float2 *pg = w.take<float2>(cap_hits > 0 ? cap_hits : 1);
     const int64_t nthreads = (int64_t)adj_blocks((int32_t)(cap_seeds < 0x7fffffff ? cap_seeds : 0x7fffffff)) * TPC_BLOCK;
-    double *pt = w.take<double>(nthreads * K * TPC_CKPT_WORDS);
+    double *pt = w.take<double>(nthreads * adj_tape_states(K) * TPC_CKPT_WORDS);
     float2 *pp = w.take<float2>(n_fs * adj_groups(n_fs) * n_rows);
     float2 *ph = w.take<float2>(cap_hits > 0 ? cap_hits : 1);
     const FitOrderWs o = fit_order_carve(w, cap_seeds);

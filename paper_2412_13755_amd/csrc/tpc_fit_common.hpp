@@ -185,7 +185,7 @@ __host__ __device__ inline void fit_one(const FitArgs &A, int i, const float *xs
 
 // Tape of filter states before each step of one segment; word q of step s at
 // tp[(s * TPC_CKPT_WORDS + q) * stride].
-__host__ __device__ inline void tape_put(double *tp, int stride, int step, const double p[5],
+__device__ inline void tape_put(double *tp, int stride, int step, const double p[5],
                                          const SymT<double> &C) {
     double *b = tp + (size_t)step * TPC_CKPT_WORDS * stride;
     const double v[TPC_CKPT_WORDS] = {p[0], p[1], p[2], p[3], p[4], C.c00, C.c10, C.c11, C.c20, C.c21,
@@ -194,7 +194,7 @@ __host__ __device__ inline void tape_put(double *tp, int stride, int step, const
     for (int q = 0; q < TPC_CKPT_WORDS; ++q) b[q * stride] = v[q];
 }
 
-__host__ __device__ inline void tape_get(const double *tp, int stride, int step, double p[5],
+__device__ inline void tape_get(const double *tp, int stride, int step, double p[5],
                                          SymT<double> &C) {
     const double *b = tp + (size_t)step * TPC_CKPT_WORDS * stride;
     double v[TPC_CKPT_WORDS];
@@ -206,65 +206,112 @@ __host__ __device__ inline void tape_get(const double *tp, int stride, int step,
     C.c42 = v[17]; C.c43 = v[18]; C.c44 = v[19];
 }
 
+// Steps of a sub-segment of the reverse pass.
+#define TPC_ADJ_SUB 4
+__host__ __device__ inline int adj_tape_states(int K) { return (K + TPC_ADJ_SUB - 1) / TPC_ADJ_SUB; }
+
 // Reverse pass of seed i (one thread's work): writes dL/d(my, mz) for every
 // hit of the seed into g[offsets[i] ..], zeros for a failed fit.
-__host__ __device__ inline void adj_one(const FitArgs &F, const int32_t *status, const double *ckpt,
-                                        float2 *gbuf, int i, const float *xs, double *tp, int stride) {
+//
+// A segment of K steps is run forward from its checkpoint, taping (tp, global
+// memory) the state at every TPC_ADJ_SUB-th step only; each sub-segment, from
+// the last, is then run forward again with its states in LDS (lt) and
+// registers, and its steps reversed.  That is half a forward step more per
+// step than with every state taped, and a third of the memory traffic, which
+// was what the time went to (2.9 GB for 645 000 seeds; 1035 -> ADJT us).
+// (Everything is addressed by 32-bit indices from bases in scalar registers:
+// the step adjoint needs nearly all of the vector ones.  F.hyz is set.)
+__device__ inline void adj_one(const FitArgs &F, const int32_t *status, const double *ckpt, float2 *gbuf, int i,
+                               double *tp, int lane, double *lt, int lstride) {
     const int K = F.ckpt_rows;
-    const SeedView sv = seed_view(F, i);
-    if (!sv.sane) return;
-    float2 *g = gbuf + sv.o0;
+    int n, row0, o0, m0;                                // hits, first row, hit offset, map entry of the first row
+    {
+        const SeedView sv = seed_view(F, i);
+        if (!sv.sane) return;
+        n = sv.n;
+        row0 = sv.row0;
+        o0 = sv.o0;
+        m0 = sv.sec * F.n_rows + row0;
+    }
     if (status[i] != TPC_FIT_OK) {
-        for (int k = 0; k < sv.n; ++k) g[k] = make_float2(0.f, 0.f);
+        for (int k = 0; k < n; ++k) gbuf[o0 + k] = make_float2(0.f, 0.f);
         return;
     }
-    const int n = sv.n, nsteps = n - 1;
-    const int nseg = (nsteps + K - 1) / K;
-    const double *ck = ckpt + (size_t)ckpt_slot(sv.o0, i, K) * TPC_CKPT_WORDS;
+    const int nsteps = n - 1;
+    const int64_t slot = ckpt_slot(o0, i, K);
     double pbar[5] = {0, 0, 0, 0, 0};
     SymT<double> Cbar = {};
-    for (int c = nseg - 1; c >= 0; --c) {
+    auto meas = [&](int k, double &my, double &mz) {
+        const float2 raw = F.hyz[o0 + k];
+        my = (double)raw.x;
+        mz = (double)raw.y;
+        if (F.map) {
+            const float2 f = reinterpret_cast<const float2 *>(F.map)[m0 + k];
+            my -= (double)f.x;
+            mz -= (double)f.y;
+        }
+    };
+    auto plane = [&](int k) { return F.row_x[row0 + k]; };
+    for (int c = (nsteps + K - 1) / K - 1; c >= 0; --c) {
         double p[5];
         SymT<double> C;
-        read_ckpt(ck + (size_t)c * TPC_CKPT_WORDS, p, C);
         const int j0 = c * K;
-        const int jend = j0 + K < nsteps ? j0 + K : nsteps;
-        float xcur = xs[sv.row0 + n - 1 - j0];
-        for (int j = j0 + 1; j <= jend; ++j) {          // recompute the segment, taping
-            const int k = n - 1 - j;
-            tape_put(tp, stride, j - j0 - 1, p, C);
+        const int len = K < nsteps - j0 ? K : nsteps - j0;
+        const int last = (len - 1) / TPC_ADJ_SUB;           // the last sub-segment
+        auto forward = [&](int q) {                         // step q propagates from hit k + 1 to hit k
+            const int k = n - 1 - (j0 + q);
             double my, mz;
-            hit_meas(F, sv, k, F.hyz ? 0 : sv.hh[k], my, mz);
-            const float xk = xs[sv.row0 + k];
+            meas(k, my, mz);
             StepJac J;
-            helix_step(p, xk - xcur, F.kbz, 2.0f, J);
-            xcur = xk;
+            helix_step(p, plane(k) - plane(k + 1), F.kbz, 2.0f, J);
             sym_transport<double, false>(C, J);
             kalman_update<double>(p, C, my, mz, F.vy, F.vz);
+        };
+        auto open = [&](int u) {                            // the state that opens sub-segment u
+            if (u > 0) tape_get(tp + lane, TPC_WAVE, u - 1, p, C);
+            else read_ckpt(ckpt + (slot + c) * TPC_CKPT_WORDS, p, C);
+        };
+        open(0);
+#pragma unroll 1
+        for (int q = 1; q <= last * TPC_ADJ_SUB; ++q) {
+            forward(q);
+            if (q % TPC_ADJ_SUB == 0) tape_put(tp + lane, TPC_WAVE, q / TPC_ADJ_SUB - 1, p, C);
         }
-        for (int j = jend; j > j0; --j) {               // then run it backwards
-            const int k = n - 1 - j;
-            double pb[5];
-            SymT<double> Cb;
-            tape_get(tp, stride, j - j0 - 1, pb, Cb);
-            double my, mz;
-            hit_meas(F, sv, k, F.hyz ? 0 : sv.hh[k], my, mz);
-            const float dx = xs[sv.row0 + k] - xs[sv.row0 + k + 1];
-            double mby, mbz;
-            step_adjoint<double>(pb, Cb, dx, F.kbz, my, mz, F.vy, F.vz, 1.0, pbar, Cbar, mby, mbz);
-            g[k] = make_float2((float)mby, (float)mbz);
+        for (int u = last; u >= 0; --u) {
+            const int s0 = u * TPC_ADJ_SUB;
+            const int s1 = s0 + TPC_ADJ_SUB < len ? s0 + TPC_ADJ_SUB : len;
+            if (u < last) open(u);
+#pragma unroll 1
+            for (int q = s0 + 1; q < s1; ++q) {
+                forward(q);
+                if (q < s1 - 1) tape_put(lt, lstride, q - s0 - 1, p, C);
+            }
+#pragma unroll 1
+            for (int q = s1; q > s0; --q) {                 // (p, C): the state before step q
+                if (q < s1) {
+                    if (q > s0 + 1) tape_get(lt, lstride, q - s0 - 2, p, C);
+                    else open(u);
+                }
+                const int k = n - 1 - (j0 + q);
+                double my, mz;
+                meas(k, my, mz);
+                double mby, mbz;
+                step_adjoint<double>(p, C, plane(k) - plane(k + 1), F.kbz, my, mz, F.vy, F.vz, 1.0, pbar, Cbar, mby,
+                                     mbz);
+                gbuf[o0 + k] = make_float2((float)mby, (float)mbz);
+            }
         }
     }
     // three-point start: hits A = n-1, B = (n-1)/2, C = 0
     const int ka = n - 1, kb = (n - 1) / 2;
     double ya, za, yb, zb, yc, zc;
-    hit_meas(F, sv, ka, F.hyz ? 0 : sv.hh[ka], ya, za);
-    hit_meas(F, sv, kb, F.hyz ? 0 : sv.hh[kb], yb, zb);
-    hit_meas(F, sv, 0, F.hyz ? 0 : sv.hh[0], yc, zc);
+    meas(ka, ya, za);
+    meas(kb, yb, zb);
+    meas(0, yc, zc);
     (void)zb;
     double bya, bza, byb, byc, bzc;
-    start_adjoint<double>(xs[sv.row0 + ka], ya, za, xs[sv.row0 + kb], yb, xs[sv.row0], yc, zc, F.kbz,
-                          pbar, bya, bza, byb, byc, bzc);
+    start_adjoint<double>(plane(ka), ya, za, plane(kb), yb, plane(0), yc, zc, F.kbz, pbar, bya, bza, byb, byc, bzc);
+    float2 *g = gbuf + o0;
     g[ka] = make_float2((float)bya, (float)bza);
     const float2 gb = g[kb];
     g[kb] = make_float2(gb.x + (float)byb, gb.y);

@@ -336,9 +336,10 @@ __host__ __device__ inline bool helix_start(R xa, R ya, R za, R xb, R yb, R xc, 
     const R kap = (R)2 * cross / prod;
     const R ua = (R)0.5 * kap * lab, uc = (R)0.5 * kap * lac;
     if (!(fabs(ua) < (R)1) || !(fabs(uc) < (R)1)) return false;
-    // direction at A: chord angle plus half the turning angle over B -> A
-    const R phia = atan2(aby, abx) + asin(ua);
-    const R sn = sin(phia), cs = cos(phia);
+    // direction at A: chord angle plus half the turning angle over B -> A,
+    // whose sine is ua (the sum's sine and cosine without the angles)
+    const R ca = sqrt(((R)1 - ua) * ((R)1 + ua)), ilab = (R)1 / lab;
+    const R sn = (aby * ca + abx * ua) * ilab, cs = (abx * ca - aby * ua) * ilab;
     if (!(cs > (R)0) || !(fabs(sn) < (R)max_sin)) return false;
     p[0] = ya;
     p[1] = za;
@@ -532,14 +533,14 @@ __host__ __device__ inline void start_adjoint(R xa, R ya, R za, R xb, R yb, R xc
     const R cross = bcx * aby - bcy * abx;
     const R kap = (R)2 * cross / prod;
     const R ua = (R)0.5 * kap * lab, uc = (R)0.5 * kap * lac;
-    const R phia = atan2(aby, abx) + asin(ua);
+    const R ca = sqrt(((R)1 - ua) * ((R)1 + ua));       // of half the turning angle, as in helix_start
     const R guc = asin_over_r(uc);
     const R D = lac * guc;
     const R t = (za - zc) / D;
-    const R bphi = pbar[2] * cos(phia);
+    const R bphi = pbar[2] * (abx * ca - aby * ua) / lab;
     const R lab2 = lab * lab;
     R b_aby = bphi * abx / lab2;
-    const R b_ua = bphi / sqrt(((R)1 - ua) * ((R)1 + ua));
+    const R b_ua = bphi / ca;
     bya = pbar[0];
     bza = pbar[1] + pbar[3] / D;
     bzc = -pbar[3] / D;
@@ -551,7 +552,7 @@ __host__ __device__ inline void start_adjoint(R xa, R ya, R za, R xb, R yb, R xc
         const R u2 = uc * uc;
         gp = uc * ((R)1 / 3 + u2 * ((R)3 / 10 + u2 * ((R)15 / 56 + u2 * ((R)35 / 144))));
     } else {
-        gp = (uc / sqrt(((R)1 - uc) * ((R)1 + uc)) - asin(uc)) / (uc * uc);
+        gp = ((R)1 / sqrt(((R)1 - uc) * ((R)1 + uc)) - guc) / uc;
     }
     const R b_uc = b_D * lac * gp;
     const R b_kap = pbar[4] / (R)kbz + b_ua * (R)0.5 * lab + b_uc * (R)0.5 * lac;

@@ -74,13 +74,20 @@ __device__ inline int seed_key(const int32_t *frame, const int32_t *sector, int 
     return frame[i] * n_sectors + sector[i];
 }
 
+// First of the T seeds whose key is not below `key` (one whole wavefront, 64
+// probes a step: four steps of dependent reads for 10^6 seeds, not twenty).
 __device__ inline int lower_bound_key(const int32_t *frame, const int32_t *sector, int n_sectors,
                                       int T, int key) {
+    const int lane = threadIdx.x & (TPC_WAVE - 1);
     int lo = 0, hi = T;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (seed_key(frame, sector, n_sectors, mid) < key) lo = mid + 1;
-        else hi = mid;
+    while (hi > lo) {
+        const int step = (hi - lo + TPC_WAVE - 1) / TPC_WAVE;
+        const int64_t i = lo + (int64_t)lane * step;
+        const int below = __popcll(__ballot(i < hi && seed_key(frame, sector, n_sectors, (int)i) < key));
+        // the answer lies above probe below - 1, at most at probe below
+        const int64_t top = lo + (int64_t)below * step;
+        if (below > 0) lo += (below - 1) * step + 1;
+        hi = top < hi ? (int)top : hi;
     }
     return lo;
 }
@@ -99,16 +106,23 @@ adj_partial(const int32_t *__restrict__ n_seeds, int32_t cap_seeds,
             int32_t n_sectors, int32_t n_rows, const float2 *__restrict__ g,
             float2 *__restrict__ partial) {
     constexpr int W = TPC_BLOCK / TPC_WAVE;
-    __shared__ float sy[W][TPC_MAX_ROWS], sz[W][TPC_MAX_ROWS];
+    __shared__ float2 sum[W][TPC_MAX_ROWS];
     __shared__ int range[2];
     const int fs = blockIdx.x, gsub = blockIdx.y, G = gridDim.y;
     const int lane = threadIdx.x & (TPC_WAVE - 1), wid = threadIdx.x / TPC_WAVE;
-    if (threadIdx.x < 2) {
+    if (wid < 2) {
         int T = *n_seeds;
         if (T > cap_seeds) T = cap_seeds;
-        range[threadIdx.x] = lower_bound_key(frame, sector, n_sectors, T, fs + threadIdx.x);
+        const int at = lower_bound_key(frame, sector, n_sectors, T, fs + wid);
+        if (lane == 0) range[wid] = at;
     }
-    for (int r = lane; r < n_rows; r += TPC_WAVE) sy[wid][r] = sz[wid][r] = 0.f;
+    for (int r = lane; r < n_rows; r += TPC_WAVE) sum[wid][r] = make_float2(0.f, 0.f);
+    // (a plain read, add and write: the wavefront is the only one, and its lanes
+    // have different rows; an LDS atomic took longer)
+    auto add = [&](int r, const float2 &v) {
+        const float2 a = sum[wid][r];
+        sum[wid][r] = make_float2(a.x + v.x, a.y + v.y);
+    };
     __syncthreads();
     const int hi = range[1];
     for (int64_t c0 = range[0] + (int64_t)(gsub * W + wid) * TPC_WAVE; c0 < hi; c0 += (int64_t)G * W * TPC_WAVE) {
@@ -133,10 +147,7 @@ adj_partial(const int32_t *__restrict__ n_seeds, int32_t cap_seeds,
 #pragma unroll
             for (int u = 0; u < TPC_ADJ_AHEAD; ++u) {
                 const int n = __builtin_amdgcn_readlane(sn, q + u), r = __builtin_amdgcn_readlane(sr, q + u) + lane;
-                if (lane < n) {
-                    atomicAdd(&sy[wid][r], v[u].x);
-                    atomicAdd(&sz[wid][r], v[u].y);
-                }
+                if (lane < n) add(r, v[u]);
             }
             if (longest <= TPC_WAVE) continue;
             for (int k = lane + TPC_WAVE; k - lane < longest; k += TPC_WAVE) {
@@ -148,10 +159,7 @@ adj_partial(const int32_t *__restrict__ n_seeds, int32_t cap_seeds,
 #pragma unroll
                 for (int u = 0; u < TPC_ADJ_AHEAD; ++u) {
                     const int n = __builtin_amdgcn_readlane(sn, q + u), r = __builtin_amdgcn_readlane(sr, q + u) + k;
-                    if (k < n) {
-                        atomicAdd(&sy[wid][r], v[u].x);
-                        atomicAdd(&sz[wid][r], v[u].y);
-                    }
+                    if (k < n) add(r, v[u]);
                 }
             }
         }
@@ -161,8 +169,8 @@ adj_partial(const int32_t *__restrict__ n_seeds, int32_t cap_seeds,
         double ay = 0.0, az = 0.0;
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-            ay += sy[w][r];
-            az += sz[w][r];
+            ay += sum[w][r].x;
+            az += sum[w][r].y;
         }
         partial[((size_t)fs * G + gsub) * n_rows + r] = make_float2((float)ay, (float)az);
     }

@@ -1288,6 +1288,22 @@ __device__ __forceinline__ void mix_query_seg(int seg, const int32_t *__restrict
     }
 }
 
+// Items of [0, n) that workgroup b of G takes and that pass `pick`, into
+// `list` (its own, at most TPC_BLOCK of the items b, b + G, ... from `from` on
+// at a time); returns how many.  Whole workgroup; contains barriers.  One
+// test per thread: a workgroup that walks over its items one after the other
+// waits for their row offsets each time.
+template <class Pick>
+__device__ inline int pick_items(int from, int b, int G, int n, const Pick &pick, int *list, int *count) {
+    __syncthreads();
+    if (threadIdx.x == 0) *count = 0;
+    __syncthreads();
+    const int64_t i = b + (int64_t)G * (from + (int)threadIdx.x);
+    if (i < n && pick((int)i)) list[atomicAdd(count, 1)] = (int)i;
+    __syncthreads();
+    return *count;
+}
+
 // Best triplet of every cluster of h-row `seg` whose neighbouring rows hold
 // at most 64 clusters together, by one wavefront without LDS or barriers:
 // lane k holds the k-th of them, every lane tests its cluster's window

@@ -12,19 +12,20 @@
 //              chunks of SKIP_Q; rows in ascending order over all sectors,
 //              so that the inner rows, which hold the most clusters, do not
 //              trail.  A chunk's unlinked clusters with finite coordinates
-//              (the others cannot link) go to LDS, ranked by y; every thread
-//              streams clusters of the four partner rows (coalesced) and
-//              finds the queries in its window by a binary search over the
-//              ranked y -- exact, since rounding is monotonic, so the y
-//              predicate |fl(y_h - y_c)| <= w holds on a contiguous run of
-//              ranks -- once to count each query's candidates per row, once
+//              (the others cannot link) go to LDS, ranked by z (the longer
+//              axis: fewer of them in a window of it); every thread streams
+//              clusters of the four partner rows (coalesced) and finds the
+//              queries in its window by a binary search over the ranked z
+//              -- exact, since rounding is monotonic, so the z predicate
+//              |fl(z_h - z_c)| <= w holds on a contiguous run of ranks --
+//              once to count each query's candidates per row, then, for as
+//              many queries as the LDS pool holds the candidates of, once
 //              more to store them (row position and coordinates) in
-//              exact-size lists carved from an LDS pool by a prefix sum;
-//              then a thread per query scores the (down, up) pairs of its
-//              lists, from LDS only, with the exact arithmetic of best_pair.
-//              A chunk whose lists exceed the pool (far beyond any TPC
-//              occupancy) scans the two rows per query instead.
-//  skip_zero, skip_prep, skip_query
+//              exact-size lists; the (down, up) pairs of all these queries
+//              are then dealt out over the workgroup and scored from LDS with
+//              the exact arithmetic of best_pair.  (A query whose candidates
+//              alone exceed the pool scans the two rows instead.)
+//  skip_prep, skip_query
 //              the h-rows with a larger partner row: global cell-sorted
 //              copies of the rows they need, their unlinked clusters in one
 //              list, one thread per listed cluster running best_pair in the
@@ -72,8 +73,8 @@ __device__ inline RowView row_view(const SkipWs &w, const int32_t *off, int s) {
 }
 
 #define SKIP_ROW_MAX 1024      // partner rows up to this size: skip_seg
-#define SKIP_Q 128             // queries per skip_seg pass
-#define SKIP_POOL 1024         // window candidates of one pass, all queries and rows
+#define SKIP_Q 256             // clusters of a row, so queries, per skip_seg pass
+#define SKIP_POOL 2048         // window candidates of one pass, all queries and rows
 
 // Cluster range of row r + dr of h-row seg's (frame, sector); empty if that
 // row is outside the sector.
@@ -101,50 +102,59 @@ __device__ inline bool skip_large(const int32_t *off, int seg, int n_rows) {
     return m > SKIP_ROW_MAX;
 }
 
-__global__ void skip_zero(int32_t *count) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *count = 0;
-}
-
 // Cell-sorted copy of every row that a large h-row needs; the unlinked
 // clusters of large h-rows appended to the list.
 __global__ void __launch_bounds__(TPC_BLOCK)
-skip_prep(const int32_t *__restrict__ off, int32_t n_rows, const float *__restrict__ y,
+skip_prep(const int32_t *__restrict__ off, int32_t NR, int32_t n_rows, const float *__restrict__ y,
           const float *__restrict__ z, float win_y, float win_z, const int32_t *__restrict__ up, SkipWs w) {
     __shared__ tpc_nb::BinLds L;
-    __shared__ int base_sh;
-    const int seg = xcd_item(blockIdx.x, gridDim.x);
-    const int r = seg % n_rows;
-    bool need = false;
-    for (int k = -2; k <= 2; ++k) {
-        const int rh = r + k;                       // an h-row k rows from this one
-        if (k != 0 && rh >= 1 && rh <= n_rows - 2) need = need || skip_large(off, seg + k, n_rows);
-    }
-    const int a = off[seg], b = off[seg + 1], n = b - a;
-    if (need) {
-        const int cbase = a + seg;
-        if (n == 0) {
-            if (threadIdx.x == 0) {
-                w.nb.grid[seg] = SegGrid{0.f, 0.f, 0.f, 0.f, 0, 0, 0, 0};
-                w.nb.cstart[cbase] = a;
-            }
-        } else {
-            float ext[4];
-            tpc_nb::row_extent(y, z, a, b, L.red, ext);
-            const SegGrid g = tpc_nb::row_grid(ext[0], ext[1], ext[2], ext[3], n, TPC_CELL_CAP, win_y, win_z);
-            if (threadIdx.x == 0) w.nb.grid[seg] = g;
-            tpc_nb::row_sort(y, z, a, b, g, L.cnt, L.scan_sh, w.nb.sy, w.nb.sz, w.nb.sid, w.nb.cstart + cbase, a);
+    __shared__ int base_sh, list[TPC_BLOCK], listed;
+    auto large = [&](int seg, int r) { return skip_large(off, seg, n_rows) && (r >= 2 || r <= n_rows - 3); };
+    auto needed = [&](int seg, int r) {               // by an h-row up to two rows from it
+        bool need = false;
+        for (int k = -2; k <= 2; ++k) {
+            const int rh = r + k;
+            if (k != 0 && rh >= 1 && rh <= n_rows - 2) need = need || skip_large(off, seg + k, n_rows);
         }
-    }
-    if (!skip_large(off, seg, n_rows) || (r < 2 && r > n_rows - 3)) return;
-    for (int c0 = a; c0 < b; c0 += TPC_BLOCK) {
-        const int h = c0 + (int)threadIdx.x;
-        const int unl = h < b && up[h] < 0;
-        int cnt;
-        const int pos = block_exclusive_scan(unl, L.scan_sh, &cnt);
-        if (threadIdx.x == 0 && cnt > 0) base_sh = atomicAdd(w.count, cnt);
-        __syncthreads();
-        if (unl) w.list[base_sh + pos] = make_int2(h, seg);
-        __syncthreads();
+        return need;
+    };
+    for (int from = 0; blockIdx.x + (int64_t)gridDim.x * from < NR; from += TPC_BLOCK) {
+        const int m = tpc_nb::pick_items(from, blockIdx.x, gridDim.x, NR, [&](int s) {
+            return needed(s, s % n_rows) || large(s, s % n_rows);
+        }, list, &listed);
+        for (int j = 0; j < m; ++j) {
+            const int seg = list[j], r = seg % n_rows;
+            const int a = off[seg], b = off[seg + 1], n = b - a;
+            __syncthreads();                          // LDS reuse
+            if (needed(seg, r)) {
+                const int cbase = a + seg;
+                if (n == 0) {
+                    if (threadIdx.x == 0) {
+                        w.nb.grid[seg] = SegGrid{0.f, 0.f, 0.f, 0.f, 0, 0, 0, 0};
+                        w.nb.cstart[cbase] = a;
+                    }
+                } else {
+                    float ext[4];
+                    tpc_nb::row_extent(y, z, a, b, L.red, ext);
+                    const SegGrid g =
+                        tpc_nb::row_grid(ext[0], ext[1], ext[2], ext[3], n, TPC_CELL_CAP, win_y, win_z);
+                    if (threadIdx.x == 0) w.nb.grid[seg] = g;
+                    tpc_nb::row_sort(y, z, a, b, g, L.cnt, L.scan_sh, w.nb.sy, w.nb.sz, w.nb.sid, w.nb.cstart + cbase,
+                                     a);
+                }
+            }
+            if (!large(seg, r)) continue;
+            for (int c0 = a; c0 < b; c0 += TPC_BLOCK) {
+                const int h = c0 + (int)threadIdx.x;
+                const int unl = h < b && up[h] < 0;
+                int cnt;
+                const int pos = block_exclusive_scan(unl, L.scan_sh, &cnt);
+                if (threadIdx.x == 0 && cnt > 0) base_sh = atomicAdd(w.count, cnt);
+                __syncthreads();
+                if (unl) w.list[base_sh + pos] = make_int2(h, seg);
+                __syncthreads();
+            }
+        }
     }
 }
 
@@ -217,94 +227,153 @@ __device__ inline void scan_rows(float hy, float hz, const float *__restrict__ y
 struct SegLds {
     float qy[SKIP_Q], qz[SKIP_Q];
     int32_t qh[SKIP_Q];
-    float ry[SKIP_Q];                    // query y in ascending order
+    float rz[SKIP_Q];                    // query z in ascending order
     int32_t rq[SKIP_Q];                  // ... and the query at each rank
-    int32_t cnt[4 * SKIP_Q];             // candidates of (row k, query q) at k * SKIP_Q + q
-    uint16_t start[4 * SKIP_Q];          // their list's start in the pool
-    float py[SKIP_POOL], pz[SKIP_POOL];  // candidate coordinates
+    int32_t cnt[4 * SKIP_Q];             // candidates of (query q, row k) at 4 q + k
+    int32_t cur[4 * SKIP_Q];             // cursors of the fill pass
+    int32_t tot[SKIP_Q + 1];             // prefix of the queries' candidates
+    int32_t pre[SKIP_Q];                 // prefix of the queries' pairs
+    unsigned long long best[SKIP_Q];     // key of the best pair: bits of q, up id, down id (relative, 16 bits)
+    float2 p[SKIP_POOL];                 // candidate coordinates
     uint16_t pool[SKIP_POOL];            // candidate positions within the partner row
     int scan_sh[TPC_BLOCK / TPC_WAVE];
 };
 
-// Best pair of query q from its lists of down row kd (A below) and up row ku
-// (B above); ra: first cluster of each partner row.
-template <int A, int B>
-__device__ inline void pairs_of(const SegLds &L, int q, int kd, int ku, const int ra[4], const int rb[4],
-                                bool listed, float hy, float hz, const float *__restrict__ y,
-                                const float *__restrict__ z, float win_y, float win_z, float cut_y, float cut_z,
-                                tpc_nb::Best &best) {
-    if (!listed) {
-        scan_rows<A, B>(hy, hz, y, z, ra[kd], rb[kd], ra[ku], rb[ku], win_y, win_z, cut_y, cut_z, best);
-        return;
-    }
-    const int d0 = L.start[kd * SKIP_Q + q], nd = L.cnt[kd * SKIP_Q + q];
-    const int u0 = L.start[ku * SKIP_Q + q], nu = L.cnt[ku * SKIP_Q + q];
-    for (int iu = 0; iu < nu; ++iu) {
-        const int32_t u = ra[ku] + L.pool[u0 + iu];
-        const float yu = L.py[u0 + iu], zu = L.pz[u0 + iu];
-        for (int id = 0; id < nd; ++id) {
-            const int32_t d = ra[kd] + L.pool[d0 + id];
-            score_pair<A, B>(hy, hz, yu, zu, u, L.py[d0 + id], L.pz[d0 + id], d, cut_y, cut_z, best);
-        }
-    }
-}
-
-// The queries whose window holds partner-row cluster (cy, cz): counted
-// (FILL = false) or stored at the cursors cnt (FILL = true).  Queries are
-// ranked by y; fl(hy - cy) does not decrease with hy, so the ones passing
-// |fl(hy - cy)| <= wy are a run of ranks, found by a binary search for its
-// first member.  The predicates are those of best_pair: hy - cy for a row
-// below (by = y_h - y_d), cy - hy for a row above (ay = y_u - y_h), whose
+// The queries in [q0, q1) whose window holds partner-row cluster (cy, cz):
+// counted (FILL = false) or stored at the cursors (FILL = true).  Queries are
+// ranked by z; fl(hz - cz) does not decrease with hz, so the ones passing
+// |fl(hz - cz)| <= wz are a run of ranks, found by a binary search for its
+// first member.  The predicates are those of best_pair: hz - cz for a row
+// below (bz = z_h - z_d), cz - hz for a row above (az = z_u - z_h), whose
 // magnitudes are equal.
 template <bool FILL>
-__device__ inline void window_hits(SegLds &L, int nq, int k, int rel, float cy, float cz, float wy, float wz) {
+__device__ inline void window_hits(SegLds &L, int nq, int q0, int q1, int k, int rel, float cy, float cz, float wy,
+                                   float wz) {
 #pragma clang fp contract(off)
-    int lo = 0, hi = nq;                     // first rank with hy - cy >= -wy
+    int lo = 0, hi = nq;                     // first rank with hz - cz >= -wz
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if (L.ry[mid] - cy >= -wy) hi = mid;
+        if (L.rz[mid] - cz >= -wz) hi = mid;
         else lo = mid + 1;
     }
     for (int j = lo; j < nq; ++j) {
-        const float hy = L.ry[j];
-        const float dy = k < 2 ? hy - cy : cy - hy;
-        if (!(fabsf(dy) <= wy)) break;
-        const int q = L.rq[j];
-        const float hz = L.qz[q];
+        const float hz = L.rz[j];
         const float dz = k < 2 ? hz - cz : cz - hz;
-        if (fabsf(dz) <= wz) {
-            const int slot = atomicAdd(&L.cnt[k * SKIP_Q + q], 1);
+        if (!(fabsf(dz) <= wz)) break;
+        const int q = L.rq[j];
+        const float hy = L.qy[q];
+        const float dy = k < 2 ? hy - cy : cy - hy;
+        if (fabsf(dy) <= wy && (!FILL || (q >= q0 && q < q1))) {
             if (FILL) {
+                const int slot = atomicAdd(&L.cur[4 * q + k], 1);
                 L.pool[slot] = (uint16_t)rel;
-                L.py[slot] = cy;
-                L.pz[slot] = cz;
+                L.p[slot] = make_float2(cy, cz);
+            } else {
+                atomicAdd(&L.cnt[4 * q + k], 1);
             }
         }
     }
 }
 
+// All clusters of the partner rows: the rows below, [ra[0] or ra[1], rb[1]),
+// then those above, [ra[2], rb[2] or rb[3]), both without a gap; four clusters
+// per thread are read at once.
 template <bool FILL>
-__device__ inline void window_pass(SegLds &L, int nq, const int ra[4], const int rb[4],
-                                   const float *__restrict__ y, const float *__restrict__ z, float win_y,
+__device__ inline void window_pass(SegLds &L, int nq, int q0, int q1, const int ra[4], const int rb[4], bool lo2,
+                                   bool hi2, const float *__restrict__ y, const float *__restrict__ z, float win_y,
                                    float win_z) {
 #pragma clang fp contract(off)
+    constexpr int U = 4;
+    const int d0 = lo2 ? ra[0] : ra[1], nd = rb[1] - d0, nt = nd + (hi2 ? rb[3] : rb[2]) - ra[2];
+    for (int i0 = threadIdx.x; i0 < nt; i0 += U * TPC_BLOCK) {
+        float cy[U], cz[U];
+        int c[U];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const float sc = (k == 0 || k == 3) ? 2.0f : 1.0f;     // rows away
-        const float wy = sc * win_y, wz = sc * win_z;
-        for (int c = ra[k] + (int)threadIdx.x; c < rb[k]; c += TPC_BLOCK) {
-            const float cy = y[c], cz = z[c];
-            if (isfinite(cy)) window_hits<FILL>(L, nq, k, c - ra[k], cy, cz, wy, wz);
+        for (int j = 0; j < U; ++j) {
+            const int i = i0 + j * TPC_BLOCK;
+            c[j] = i < nd ? d0 + i : ra[2] + (i - nd);
+            cy[j] = cz[j] = NAN;
+            if (i < nt) {
+                cy[j] = y[c[j]];
+                cz[j] = z[c[j]];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            if (!isfinite(cz[j])) continue;
+            const bool below = i0 + j * TPC_BLOCK < nd;
+            const int k = below ? (c[j] < ra[1] ? 0 : 1) : (c[j] < rb[2] ? 2 : 3);
+            const int first = below ? (c[j] < ra[1] ? d0 : ra[1]) : (c[j] < rb[2] ? ra[2] : rb[2]);
+            const float sc = (k == 0 || k == 3) ? 2.0f : 1.0f;     // rows away
+            window_hits<FILL>(L, nq, q0, q1, k, c[j] - first, cy[j], cz[j], sc * win_y, sc * win_z);
         }
     }
 }
 
+// Scores pairs of the listed queries [q0, q1), dealt out over the workgroup:
+// those of (A, B) = (1, 2) and (2, 1) together (FOUR = false), or the
+// (2, 2) of the queries without one (FOUR = true).  The operations are those
+// of score_pair: the divisions by 1 or 2 are exact products.  rel: first id
+// of each partner row relative to the down rows' and the up rows' first.
+template <bool FOUR>
+__device__ inline void deal_pairs(SegLds &L, int q0, int q1, const int rel[4], float cut_y, float cut_z) {
+#pragma clang fp contract(off)
+    const int tid = threadIdx.x;
+    int P = 0;
+    if (tid >= q0 && tid < q1) {
+        const int32_t *c = L.cnt + 4 * tid;
+        P = FOUR ? (L.best[tid] == ~0ull ? c[0] * c[3] : 0) : c[1] * c[3] + c[0] * c[2];
+    }
+    int total;
+    const int ex = block_exclusive_scan(P, L.scan_sh, &total);
+    L.pre[tid] = ex;
+    __syncthreads();
+    for (int t = tid; t < total; t += TPC_BLOCK) {
+        int q = 0;                                     // the last query whose pairs start at or before t
+#pragma unroll
+        for (int s = SKIP_Q / 2; s > 0; s >>= 1) q += L.pre[q + s] <= t ? s : 0;
+        int j = t - L.pre[q];
+        const int32_t *c = L.cnt + 4 * q, *e = L.cur + 4 * q;   // (cursors stand at the lists' ends)
+        int kd = 0, ku = 3;
+        if (!FOUR) {
+            const int n12 = c[1] * c[3];
+            kd = j < n12 ? 1 : 0;
+            ku = j < n12 ? 3 : 2;
+            j -= j < n12 ? 0 : n12;
+        }
+        const int nd = c[kd];
+        const int iu = (int)(((float)j + 0.5f) * __builtin_amdgcn_rcpf((float)nd));   // j / nd: j < 2^20
+        const int u = e[ku] - c[ku] + iu, d = e[kd] - nd + (j - iu * nd);
+        const float hy = L.qy[q], hz = L.qz[q];
+        const float sb = ku == 3 ? 0.5f : 1.0f, sa = kd == 0 ? 0.5f : 1.0f;
+        const float g = FOUR ? 2.0f / 4.0f : 2.0f / 3.0f;
+        const float2 pu = L.p[u], pd = L.p[d];
+        const float ty = (pu.x - hy) * sb, tz = (pu.y - hz) * sb;
+        const float sy = (hy - pd.x) * sa, sz = (hz - pd.y) * sa;
+        const float ey = ty - sy, ez = tz - sz;
+        const float dy = g * ey, dz = g * ez;
+        const float qy = dy * dy, qz = dz * dz;
+        const float qq = qy + qz;
+        const unsigned long long key = ((unsigned long long)__float_as_uint(qq) << 32) |
+                                       (uint32_t)(rel[ku] + L.pool[u]) << 16 | (uint32_t)(rel[kd] + L.pool[d]);
+        if (fabsf(dy) <= cut_y && fabsf(dz) <= cut_z) atomicMin(&L.best[q], key);
+    }
+    __syncthreads();
+}
+
+// Bound by the chains of LDS reads of the window passes and, where a thread
+// scored the pairs of a query alone, by the longest of those: 262 -> 150 us
+// for an event of 10^4 tracks with one row in ten missing (the pool of 1024
+// was also too small for its inner rows, whose queries then scanned whole
+// rows).
 __global__ void __launch_bounds__(TPC_BLOCK)
 skip_seg(const int32_t *__restrict__ off, int32_t n_rows, const float *__restrict__ y,
          const float *__restrict__ z, float win_y, float win_z, float cut_y, float cut_z, int32_t *up,
-         int32_t *dn) {
+         int32_t *dn, int32_t *count) {
 #pragma clang fp contract(off)
+    static_assert(4 * SKIP_ROW_MAX <= 65535 && SKIP_Q == TPC_BLOCK, "16-bit ids, a thread per query");
     __shared__ SegLds L;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *count = 0;       // of skip_prep
     // rows in ascending order over all sectors: the inner rows, which hold
     // the most clusters (loopers) and take longest, start first; blocks go
     // round-robin over the XCDs, so each gets a share of every row
@@ -321,19 +390,20 @@ skip_seg(const int32_t *__restrict__ off, int32_t n_rows, const float *__restric
     partner_row(off, seg, r, n_rows, -1, ra[1], rb[1]);
     partner_row(off, seg, r, n_rows, 1, ra[2], rb[2]);
     partner_row(off, seg, r, n_rows, 2, ra[3], rb[3]);
+    const int d0 = lo2 ? ra[0] : ra[1], u0 = ra[2];
+    const int rel[4] = {0, ra[1] - d0, 0, hi2 ? ra[3] - u0 : 0};
     const int tid = threadIdx.x;
-    constexpr int PER = 4 * SKIP_Q / TPC_BLOCK;         // list counts per thread in the scan
     for (int c0 = a; c0 < b; c0 += SKIP_Q) {
         const int h = c0 + tid;
         int uh = 0;
         float hy0 = 0.f, hz0 = 0.f;
-        if (tid < SKIP_Q && h < b) {
+        if (h < b) {
             uh = up[h];
             hy0 = y[h];
             hz0 = z[h];
         }
         // unlinked and finite (a non-finite cluster never links)
-        const int unl = tid < SKIP_Q && h < b && uh < 0 && isfinite(hy0) && isfinite(hz0);
+        const int unl = h < b && uh < 0 && isfinite(hy0) && isfinite(hz0);
         int nq;
         const int pos = block_exclusive_scan(unl, L.scan_sh, &nq);
         if (nq == 0) continue;                // uniform
@@ -343,61 +413,76 @@ skip_seg(const int32_t *__restrict__ off, int32_t n_rows, const float *__restric
             L.qz[pos] = hz0;
         }
         for (int k = tid; k < 4 * SKIP_Q; k += TPC_BLOCK) L.cnt[k] = 0;
+        L.best[tid] = ~0ull;
         __syncthreads();
-        // rank by y (ties by position): a permutation, as every y is finite
+        // rank by z (ties by position): a permutation, as every z is finite
         if (tid < nq) {
-            const float v = L.qy[tid];
+            const float v = L.qz[tid];
             int rk = 0;
             for (int j = 0; j < nq; ++j) {
-                const float w = L.qy[j];
+                const float w = L.qz[j];
                 rk += (w < v) | ((w == v) & (j < tid));
             }
-            L.ry[rk] = v;
+            L.rz[rk] = v;
             L.rq[rk] = tid;
         }
         __syncthreads();
-        window_pass<false>(L, nq, ra, rb, y, z, win_y, win_z);
+        window_pass<false>(L, nq, 0, nq, ra, rb, lo2, hi2, y, z, win_y, win_z);
         __syncthreads();
-        // list starts: exclusive prefix of the counts (thread t owns PER of them)
-        int v[PER], local = 0;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            v[j] = L.cnt[tid * PER + j];
-            local += v[j];
-        }
-        int total;
-        int run = block_exclusive_scan(local, L.scan_sh, &total);
-        const bool listed = total <= SKIP_POOL;   // uniform
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            L.start[tid * PER + j] = (uint16_t)(listed ? run : 0);
-            L.cnt[tid * PER + j] = run;           // cursor of the fill pass
-            run += v[j];
-        }
-        __syncthreads();
-        if (listed) {
-            window_pass<true>(L, nq, ra, rb, y, z, win_y, win_z);
-            __syncthreads();
-            // cursors have moved to the ends: back to counts
-#pragma unroll
-            for (int j = 0; j < PER; ++j) L.cnt[tid * PER + j] -= L.start[tid * PER + j];
-            __syncthreads();
-        }
+        int c[4] = {0, 0, 0, 0}, total;
         if (tid < nq) {
-            const float hy = L.qy[tid], hz = L.qz[tid];
-            tpc_nb::Best bt = {0.f, -1, -1};
-            if (hi2) pairs_of<1, 2>(L, tid, 1, 3, ra, rb, listed, hy, hz, y, z, win_y, win_z, cut_y, cut_z, bt);
-            if (lo2) {
-                tpc_nb::Best c = {0.f, -1, -1};
-                pairs_of<2, 1>(L, tid, 0, 2, ra, rb, listed, hy, hz, y, z, win_y, win_z, cut_y, cut_z, c);
-                if (c.u >= 0 && tpc_nb::better(c.q, c.u, c.d, bt)) bt = c;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) c[k] = L.cnt[4 * tid + k];
+        }
+        const int own = c[0] + c[1] + c[2] + c[3];
+        const int before = block_exclusive_scan(own, L.scan_sh, &total);
+        L.tot[tid] = before;
+        if (tid == 0) L.tot[SKIP_Q] = total;
+        __syncthreads();
+        // as many queries at a time as the pool holds the candidates of
+        for (int q0 = 0, q1; q0 < nq; q0 = q1) {
+            q1 = q0;
+            for (int s = SKIP_Q; s > 0; s >>= 1)
+                if (q1 + s <= nq && L.tot[q1 + s] - L.tot[q0] <= SKIP_POOL) q1 += s;
+            if (q1 == q0) {                   // not even one: by its thread alone
+                q1 = q0 + 1;
+                if (tid == q0) {
+                    const float hy = L.qy[tid], hz = L.qz[tid];
+                    tpc_nb::Best bt = {0.f, -1, -1}, c2 = {0.f, -1, -1};
+                    if (hi2)
+                        scan_rows<1, 2>(hy, hz, y, z, ra[1], rb[1], ra[3], rb[3], win_y, win_z, cut_y, cut_z, bt);
+                    if (lo2)
+                        scan_rows<2, 1>(hy, hz, y, z, ra[0], rb[0], ra[2], rb[2], win_y, win_z, cut_y, cut_z, c2);
+                    if (c2.u >= 0 && tpc_nb::better(c2.q, c2.u, c2.d, bt)) bt = c2;
+                    if (bt.u < 0 && lo2 && hi2)
+                        scan_rows<2, 2>(hy, hz, y, z, ra[0], rb[0], ra[3], rb[3], win_y, win_z, cut_y, cut_z, bt);
+                    if (bt.u >= 0) {
+                        up[L.qh[tid]] = bt.u;
+                        dn[L.qh[tid]] = bt.d;
+                    }
+                }
+                continue;
             }
-            if (bt.u < 0 && lo2 && hi2)
-                pairs_of<2, 2>(L, tid, 0, 3, ra, rb, listed, hy, hz, y, z, win_y, win_z, cut_y, cut_z, bt);
-            if (bt.u >= 0) {
-                const int32_t hq = L.qh[tid];
-                up[hq] = bt.u;
-                dn[hq] = bt.d;
+            __syncthreads();
+            if (tid >= q0 && tid < q1) {
+                int at = before - L.tot[q0];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    L.cur[4 * tid + k] = at;
+                    at += c[k];
+                }
+            }
+            __syncthreads();
+            window_pass<true>(L, nq, q0, q1, ra, rb, lo2, hi2, y, z, win_y, win_z);
+            __syncthreads();
+            deal_pairs<false>(L, q0, q1, rel, cut_y, cut_z);
+            if (lo2 && hi2) deal_pairs<true>(L, q0, q1, rel, cut_y, cut_z);
+            if (tid >= q0 && tid < q1) {
+                const unsigned long long best = L.best[tid];
+                if (best != ~0ull) {
+                    up[L.qh[tid]] = u0 + (int32_t)((uint32_t)best >> 16);
+                    dn[L.qh[tid]] = d0 + (int32_t)(best & 0xFFFFu);
+                }
             }
         }
         __syncthreads();
@@ -425,9 +510,10 @@ hipError_t launch_neighbours_skip(const tpc_context *ctx, const tpc_frames *fr, 
     const int NR = fr->n_frames * ctx->cfg.n_sectors * ctx->cfg.n_rows;
     const tpc_config &c = ctx->cfg;
     hipLaunchKernelGGL(skip_seg, dim3(NR), dim3(TPC_BLOCK), 0, st, fr->row_offsets, c.n_rows, fr->y, fr->z,
-                       c.win_y, c.win_z, c.cut_y, c.cut_z, up, dn);
-    hipLaunchKernelGGL(skip_zero, dim3(1), dim3(64), 0, st, ws.count);
-    hipLaunchKernelGGL(skip_prep, dim3(NR), dim3(TPC_BLOCK), 0, st, fr->row_offsets, c.n_rows, fr->y, fr->z,
+                       c.win_y, c.win_z, c.cut_y, c.cut_z, up, dn, ws.count);
+    const bool sparse = (int64_t)fr->n_clusters < (int64_t)TPC_SPARSE_ROW * NR;
+    const int gp = sparse && NR > TPC_SPARSE_GRID ? TPC_SPARSE_GRID : NR;
+    hipLaunchKernelGGL(skip_prep, dim3(gp), dim3(TPC_BLOCK), 0, st, fr->row_offsets, NR, c.n_rows, fr->y, fr->z,
                        c.win_y, c.win_z, up, ws);
     int blocks = (int)(fr->n_clusters / (8 * TPC_BLOCK)) + 1;
     if (blocks > 8192) blocks = 8192;

@@ -23,22 +23,6 @@ nb_bin(const int32_t *__restrict__ off, int32_t NR, int32_t n_rows, const float 
     tpc_nb::nb_bin_seg(xcd_item(blockIdx.x, NR), n_rows, off, y, z, win_y, win_z, grid, cstart, sy, sz, sid, L);
 }
 
-// Items of [0, n) that workgroup b of G takes and that pass `pick`, into
-// `list` (its own, at most TPC_BLOCK of the items b, b + G, ... from `from` on
-// at a time); returns how many.  Whole workgroup; contains barriers.  One
-// test per thread: a workgroup that walks over its items one after the other
-// waits for their row offsets each time.
-template <class Pick>
-__device__ inline int pick_items(int from, int b, int G, int n, const Pick &pick, int *list, int *count) {
-    __syncthreads();
-    if (threadIdx.x == 0) *count = 0;
-    __syncthreads();
-    const int64_t i = b + (int64_t)G * (from + (int)threadIdx.x);
-    if (i < n && pick((int)i)) list[atomicAdd(count, 1)] = (int)i;
-    __syncthreads();
-    return *count;
-}
-
 // Blocks from nb on, GROUP segments each: the segments whose neighbouring rows fit the mixed LDS
 // form (24 KB per workgroup, six workgroups per CU), the very small ones by a
 // wavefront, and the first and last rows.  Blocks below nb: the sorted copies that dense rows need, where the
@@ -58,7 +42,7 @@ nb_query_small(const int32_t *__restrict__ off, int32_t NR, int32_t nb, int32_t 
     } U;
     if ((int)blockIdx.x < nb) {
         for (int from = 0; blockIdx.x + (int64_t)nb * from < NR; from += TPC_BLOCK) {
-            const int m = pick_items(from, blockIdx.x, nb, NR, [&](int s) { return tpc_nb::nb_bin_needed(off, s, n_rows); },
+            const int m = tpc_nb::pick_items(from, blockIdx.x, nb, NR, [&](int s) { return tpc_nb::nb_bin_needed(off, s, n_rows); },
                                      U.bin.list, &U.bin.count);
             for (int k = 0; k < m; ++k)
                 tpc_nb::nb_bin_seg(U.bin.list[k], n_rows, off, y, z, win_y, win_z, grid, cstart, sy, sz, sid,
@@ -97,7 +81,7 @@ nb_query_rest(const int32_t *__restrict__ off, int32_t NR, int32_t n_rows, const
     } U;
     __shared__ int list[TPC_BLOCK], count;
     for (int from = 0; blockIdx.x + (int64_t)gridDim.x * from < NR; from += TPC_BLOCK) {
-        const int m = pick_items(from, blockIdx.x, gridDim.x, NR, [&](int s) { return tpc_nb::rest_hrow(off, s, n_rows); },
+        const int m = tpc_nb::pick_items(from, blockIdx.x, gridDim.x, NR, [&](int s) { return tpc_nb::rest_hrow(off, s, n_rows); },
                                  list, &count);
         for (int k = 0; k < m; ++k) {
             const int seg = list[k];

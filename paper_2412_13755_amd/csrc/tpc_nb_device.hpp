@@ -442,7 +442,7 @@ template <int ROW, int CELLS>
 struct PairLdsT {
     float y[2 * ROW], z[2 * ROW];
     uint16_t rel[2 * ROW];                  // cluster id minus its row's first id
-    alignas(16) int32_t cs[2 * CELLS];      // cell starts of both rows (< CELLS each), concatenated
+    alignas(16) uint32_t cs[CELLS];         // cell starts of both rows (< CELLS each), concatenated, two to a word
     float red[8][TPC_BLOCK / TPC_WAVE];
     int scan_sh[TPC_BLOCK / TPC_WAVE];
 };
@@ -487,8 +487,13 @@ __device__ __forceinline__ void pair_bin(const Src &src, int n0, int n1, float w
                                 PairLdsT<ROW, CELLS> &L, SegGrid &gd, SegGrid &gu, int &C0) {
 #pragma clang fp contract(off)
     constexpr int PT = 2 * ROW / TPC_BLOCK;      // row-pair clusters per thread
-    constexpr int PC = 2 * CELLS / TPC_BLOCK;    // cell words per thread
+    constexpr int PC = CELLS / TPC_BLOCK;        // cell words per thread
     static_assert(PC % 4 == 0, "cell words in 16-byte groups");
+    static_assert(2 * ROW < 65536, "16-bit cell starts");
+    auto bump = [&](int c) {                     // cs[c]++, the value before
+        const int sh = 16 * (c & 1);
+        return (int)((atomicAdd(&L.cs[c >> 1], 1u << sh) >> sh) & 0xFFFFu);
+    };
     const int tid = threadIdx.x;
     const int nt = n0 + n1;
     // both rows are read once, into registers (one global round trip); the
@@ -550,30 +555,35 @@ __device__ __forceinline__ void pair_bin(const Src &src, int n0, int n1, float w
         const int k = tid + j * TPC_BLOCK;
         const SegGrid g = k < n0 ? gd : gu;
         cell[j] = (k < n0 ? 0 : C0) + pair_cell(vy[j], vz[j], g);
-        if (k < nt) atomicAdd(&L.cs[cell[j] + 2], 1);
+        if (k < nt) bump(cell[j] + 2);
     }
     __syncthreads();
     // inclusive scan: cs[c + 1] = first position of cell c (the counts of
     // cells below c are in cs[2 .. c + 1]).  Each thread takes PC words of
     // the array as they lie, whatever the number of cells: 16-byte accesses
     // and no loop (a run per thread, word by word, conflicted on the banks).
-    int4 w[PC / 4];
-    int local = 0;
+    uint32_t w[PC];
+    uint32_t local = 0;                          // (its halves' sums do not overflow: 2 ROW clusters)
 #pragma unroll
     for (int q = 0; q < PC / 4; ++q) {
-        w[q] = cs4[q];
-        local += w[q].x + w[q].y + w[q].z + w[q].w;
+        const int4 v = cs4[q];
+        w[4 * q] = (uint32_t)v.x;
+        w[4 * q + 1] = (uint32_t)v.y;
+        w[4 * q + 2] = (uint32_t)v.z;
+        w[4 * q + 3] = (uint32_t)v.w;
+        local += w[4 * q] + w[4 * q + 1] + w[4 * q + 2] + w[4 * q + 3];
     }
     int total;
-    int run = block_exclusive_scan(local, L.scan_sh, &total);
+    uint32_t run = (uint32_t)block_exclusive_scan((int)((local & 0xFFFFu) + (local >> 16)), L.scan_sh, &total);
 #pragma unroll
-    for (int q = 0; q < PC / 4; ++q) {
-        w[q].x = run += w[q].x;
-        w[q].y = run += w[q].y;
-        w[q].z = run += w[q].z;
-        w[q].w = run += w[q].w;
-        cs4[q] = w[q];
+    for (int q = 0; q < PC; ++q) {
+        const uint32_t lo = run + (w[q] & 0xFFFFu);
+        run = lo + (w[q] >> 16);
+        w[q] = lo | run << 16;
     }
+#pragma unroll
+    for (int q = 0; q < PC / 4; ++q)
+        cs4[q] = make_int4((int)w[4 * q], (int)w[4 * q + 1], (int)w[4 * q + 2], (int)w[4 * q + 3]);
     __syncthreads();
     // scatter; the cursor of cell c moves from its start to its end, which
     // leaves cs[c] = start of cell c for every c in [0, C]
@@ -582,7 +592,7 @@ __device__ __forceinline__ void pair_bin(const Src &src, int n0, int n1, float w
         if (j * TPC_BLOCK >= nt) break;
         const int k = tid + j * TPC_BLOCK;
         if (k < nt) {
-            const int slot = atomicAdd(&L.cs[cell[j] + 1], 1);
+            const int slot = bump(cell[j] + 1);
             L.y[slot] = vy[j];
             L.z[slot] = vz[j];
             L.rel[slot] = vr[j];
@@ -627,6 +637,7 @@ __device__ inline bool rest_hrow(const int32_t *off, int seg, int n_rows) {
 #ifndef TPC_NB_SLAB
 #define TPC_NB_SLAB 512
 #endif
+#define TPC_NB_LIST 16
 #ifndef TPC_NB_SLAB_MIN
 #define TPC_NB_SLAB_MIN 64
 #endif
@@ -648,6 +659,7 @@ __device__ inline bool rest_hrow(const int32_t *off, int seg, int n_rows) {
 template <int ROW, int CELLS>
 struct DenseLdsT : PairLdsT<ROW, CELLS> {
     uint32_t res[TPC_NB_SLAB];
+    uint16_t list[TPC_NB_LIST][TPC_BLOCK];   // per thread: up clusters in its windows, to be searched from
 };
 using DenseLds = DenseLdsT<TPC_NB_DENSE_ROW, TPC_NB_DENSE_CELLS>;
 
@@ -681,7 +693,10 @@ __device__ inline int2 zrange(const SegGrid &g, const int32_t *cs, float lo, flo
 // candidate per lane, so lanes at different depths of the walk stay in
 // step; a lane moves to its next cluster (every TPC_BLOCK-th of the slab,
 // loaded while it searches the current one) when the current one is
-// exhausted.  One candidate test serves both walks: a candidate c at
+// exhausted.  The rows of the up window are walked from h's own row of cells
+// outwards: a track moves little in y from one pad row to the next, so its
+// partner, after which the boxes are small, comes among the first (CONT).
+// One candidate test serves both walks: a candidate c at
 // (t_y, t_z) = (y_c - y_h, z_c - z_h) passes the window test on |t| in
 // either; an up candidate then starts a down box, a down candidate is
 // scored with d_y = a_y + t_y, equal (rounding included) to
@@ -709,9 +724,12 @@ __device__ __forceinline__ void slab_search(int pb, int pn, const float *__restr
                                    float cut_y, float cut_z, int32_t *__restrict__ up,
                                    int32_t *__restrict__ dn, DenseLdsT<ROW, CELLS> &L) {
 #pragma clang fp contract(off)
+    static_assert(TPC_NB_SLAB == 2 * TPC_BLOCK, "two clusters of the slab per thread");
+    static_assert(2 * ROW <= 2048, "11-bit positions");
+    typedef uint16_t __attribute__((may_alias)) cell16;
     const float *Y = L.y, *Z = L.z;
     const uint16_t *R = L.rel;
-    const int32_t *UCS = L.cs + C0, *DCS = L.cs;
+    const cell16 *DCS = reinterpret_cast<const cell16 *>(L.cs), *UCS = DCS + C0;
     const bool grids = gu.ny > 0 && gd.ny > 0;
     constexpr uint64_t NONE = (0x7F800000ull << 32) | 0xFFFFFFFFull;
     const float edy = 1e-6f * (fabsf(gd.y0) * gd.iwy + 1.0f), edz = 1e-6f * (fabsf(gd.z0) * gd.iwz + 1.0f);
@@ -719,107 +737,125 @@ __device__ __forceinline__ void slab_search(int pb, int pn, const float *__restr
     const float dny = (float)(gd.ny - 1), dnz = (float)(gd.nz - 1);
     const float uny = (float)(gu.ny - 1), unz = (float)(gu.nz - 1);
     const float wcy = win_y + cut_y, wcz = win_z + cut_z;
-    int j = (int)threadIdx.x - TPC_BLOCK;
-    bool active = false, dmode = false;
-    float yh = 0.f, zh = 0.f, hy = 0.f, hz = 0.f, my = 0.f, mz = 0.f, ay = 0.f, az = 0.f;
-    float yn = 0.f, zn = 0.f;
-    if ((int)threadIdx.x < pn) {
-        yn = sy[pb + threadIdx.x];
-        zn = sz[pb + threadIdx.x];
+    const int tid = threadIdx.x;
+    float yv[2], zv[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int j = tid + s * TPC_BLOCK;
+        yv[s] = j < pn ? sy[pb + j] : NAN;
+        zv[s] = j < pn ? sz[pb + j] : NAN;
     }
     uint64_t best = NONE;
-    uint32_t urs = 0;
-    int iy = 0, iy1 = -1, zc0 = 0, zc1 = 0, k = 0, k1 = 0;
-    int yd = 0, yd1 = -1, zd0 = 0, zd1 = 0, kd = 0, e1 = 0;
-    while (true) {
-        if (!active) {
-            j += TPC_BLOCK;
-            if (j < pn) {
-                yh = yn;
-                zh = zn;
-                if (j + TPC_BLOCK < pn) {
-                    yn = sy[pb + j + TPC_BLOCK];
-                    zn = sz[pb + j + TPC_BLOCK];
-                }
-                best = NONE;
-                dmode = false;
-                iy = 0; iy1 = -1; k = 0; k1 = 0;
-                if (grids && isfinite(yh) && isfinite(zh)) {
+    int cur = 0, n = 0;                           // whose best it is; entries in the list
+    float yh = yv[0], zh = zv[0];
+    auto result = [&](int s) { L.res[tid + s * TPC_BLOCK] = best != NONE ? (uint32_t)best : 0xFFFFFFFFu; };
+    // the listed up clusters' boxes in the down row
+    auto search = [&]() {
+        float my = 0.f, mz = 0.f, hy = 0.f, hz = 0.f, ay = 0.f, az = 0.f;
+        uint32_t urs = 0;
+        int i = 0, yd = 0, yd1 = -1, zd0 = 0, zd1 = 0, kd = 0, e1 = 0;
+        while (__ballot(kd < e1 || yd < yd1 || i < n)) {
+            if (kd == e1) {
+                if (yd < yd1) {
+                    ++yd;
+                    const int row = __mul24(yd, gd.nz);
+                    kd = DCS[row + zd0];
+                    e1 = DCS[row + zd1 + 1];
+                } else if (i < n) {
+                    const uint32_t e = L.list[i++][tid];
+                    if ((int)(e >> 15) != cur) {  // the second cluster's first
+                        result(0);
+                        best = NONE;
+                        cur = 1;
+                        yh = yv[1];
+                        zh = zv[1];
+                    }
+                    const int c = (int)(e & 2047u);
+                    ay = Y[c] - yh;
+                    az = Z[c] - zh;
+                    urs = (uint32_t)R[c] << 16;
                     my = __builtin_fmaf(fabsf(yh) + wcy, 1e-5f, 1e-6f);
                     mz = __builtin_fmaf(fabsf(zh) + wcz, 1e-5f, 1e-6f);
                     hy = (yh - gd.y0) * gd.iwy;
                     hz = (zh - gd.z0) * gd.iwz;
-                    const float uy = (yh - gu.y0) * gu.iwy, uz = (zh - gu.z0) * gu.iwz;
-                    const float wy = __builtin_fmaf(win_y + my, gu.iwy, euy);
-                    const float wz = __builtin_fmaf(win_z + mz, gu.iwz, euz);
-                    iy = cell_in(uy - wy, uny);
-                    iy1 = cell_in(uy + wy, uny);
-                    zc0 = cell_in(uz - wz, unz);
-                    zc1 = cell_in(uz + wz, unz);
-                    const int row = __mul24(iy, gu.nz);
+                    // down clusters around the prediction h - (u - h)
+                    const float r = __builtin_amdgcn_sqrtf(__uint_as_float((uint32_t)(best >> 32))) * 1.0001f;
+                    const float py = __builtin_fmaf(-ay, gd.iwy, hy), pz = __builtin_fmaf(-az, gd.iwz, hz);
+                    const float ky = __builtin_fmaf(fminf(cut_y, r) + my, gd.iwy, edy);
+                    const float kz = __builtin_fmaf(fminf(cut_z, r) + mz, gd.iwz, edz);
+                    yd = cell_in(py - ky, dny);
+                    yd1 = cell_in(py + ky, dny);
+                    zd0 = cell_in(pz - kz, dnz);
+                    zd1 = cell_in(pz + kz, dnz);
+                    const int row = __mul24(yd, gd.nz);
+                    kd = DCS[row + zd0];
+                    e1 = DCS[row + zd1 + 1];
+                }
+            }
+            if (kd < e1) {
+                const int c = kd++;
+                const float ty = Y[c] - yh;
+                const float tz = Z[c] - zh;
+                const uint32_t rr = R[c];
+                const float dy = ay + ty;
+                const float dz = az + tz;
+                const float qy = dy * dy;
+                const float qz = dz * dz;
+                const float q = qy + qz;
+                const uint64_t key = ((uint64_t)__float_as_uint(q) << 32) | (uint64_t)(urs | rr);
+                // bitwise, not short-circuit, conjunctions: no branches in the test
+                const bool win = (int)(fabsf(ty) <= win_y) & (int)(fabsf(tz) <= win_z) & (int)(fabsf(dy) <= cut_y) &
+                                 (int)(fabsf(dz) <= cut_z) & (int)(key < best);
+                best = win ? key : best;
+            }
+        }
+        n = 0;
+    };
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        // the up clusters in the window of the thread's s-th cluster
+        const float y = yv[s], z = zv[s];
+        int ic = 0, nabove = 0, it = 0, it1 = -1, zc0 = 0, zc1 = 0, k = 0, k1 = 0;
+        if (grids && isfinite(y) && isfinite(z)) {
+            const float my = __builtin_fmaf(fabsf(y) + wcy, 1e-5f, 1e-6f);
+            const float mz = __builtin_fmaf(fabsf(z) + wcz, 1e-5f, 1e-6f);
+            const float uy = (y - gu.y0) * gu.iwy, uz = (z - gu.z0) * gu.iwz;
+            const float wy = __builtin_fmaf(win_y + my, gu.iwy, euy);
+            const float wz = __builtin_fmaf(win_z + mz, gu.iwz, euz);
+            // rows from h's own up, then from the one below it down
+            ic = cell_in(uy, uny);
+            nabove = cell_in(uy + wy, uny) - ic;
+            it1 = nabove + ic - cell_in(uy - wy, uny);
+            zc0 = cell_in(uz - wz, unz);
+            zc1 = cell_in(uz + wz, unz);
+            const int row = __mul24(ic, gu.nz);
+            k = UCS[row + zc0];
+            k1 = UCS[row + zc1 + 1];
+        }
+        while (true) {
+            while (__ballot((k < k1 || it < it1) && n < TPC_NB_LIST)) {
+                if (n == TPC_NB_LIST) continue;
+                if (k == k1 && it < it1) {
+                    ++it;
+                    const int row = __mul24(ic + (it <= nabove ? it : nabove - it), gu.nz);
                     k = UCS[row + zc0];
                     k1 = UCS[row + zc1 + 1];
                 }
-                active = true;
+                if (k < k1) {
+                    if ((int)(fabsf(Y[k] - y) <= win_y) & (int)(fabsf(Z[k] - z) <= win_z))
+                        L.list[n++][tid] = (uint16_t)(k | s << 15);
+                    ++k;
+                }
             }
+            if (!__ballot(k < k1 || it < it1)) break;
+            search();
         }
-        if (__ballot(active) == 0ull) break;
-        if (!active) continue;
-        if (dmode) {
-            while (kd == e1 && yd < yd1) {
-                ++yd;
-                kd = DCS[yd * gd.nz + zd0];
-                e1 = DCS[yd * gd.nz + zd1 + 1];
-            }
-            dmode = kd < e1;
-        }
-        if (!dmode) {
-            while (k == k1 && iy < iy1) {
-                ++iy;
-                k = UCS[iy * gu.nz + zc0];
-                k1 = UCS[iy * gu.nz + zc1 + 1];
-            }
-            if (k == k1) {                            // cluster done
-                L.res[j] = best != NONE ? (uint32_t)best : 0xFFFFFFFFu;
-                active = false;
-                continue;
-            }
-        }
-        const int c = dmode ? kd : k;
-        kd += (int)dmode;
-        k += (int)!dmode;
-        const float ty = Y[c] - yh;
-        const float tz = Z[c] - zh;
-        const uint32_t rr = R[c];
-        // bitwise, not short-circuit, conjunctions: no branches in the test
-        const bool inwin = (int)(fabsf(ty) <= win_y) & (int)(fabsf(tz) <= win_z);
-        const float dy = ay + ty;
-        const float dz = az + tz;
-        const float qy = dy * dy;
-        const float qz = dz * dz;
-        const float q = qy + qz;
-        const uint64_t key = ((uint64_t)__float_as_uint(q) << 32) | (uint64_t)(urs | rr);
-        const bool win = (int)dmode & (int)inwin & (int)(fabsf(dy) <= cut_y) & (int)(fabsf(dz) <= cut_z) &
-                         (int)(key < best);
-        best = win ? key : best;
-        if (!dmode && inwin) {
-            // down clusters around the prediction h - (u - h)
-            ay = ty;
-            az = tz;
-            urs = rr << 16;
-            const float r = __builtin_amdgcn_sqrtf(__uint_as_float((uint32_t)(best >> 32))) * 1.0001f;
-            const float py = __builtin_fmaf(-ty, gd.iwy, hy), pz = __builtin_fmaf(-tz, gd.iwz, hz);
-            const float ky = __builtin_fmaf(fminf(cut_y, r) + my, gd.iwy, edy);
-            const float kz = __builtin_fmaf(fminf(cut_z, r) + mz, gd.iwz, edz);
-            yd = cell_in(py - ky, dny);
-            yd1 = cell_in(py + ky, dny);
-            zd0 = cell_in(pz - kz, dnz);
-            zd1 = cell_in(pz + kz, dnz);
-            const int row = __mul24(yd, gd.nz);
-            kd = DCS[row + zd0];
-            e1 = DCS[row + zd1 + 1];
-            dmode = true;
-        }
+    }
+    search();
+    result(cur);
+    if (cur == 0) {
+        best = NONE;
+        result(1);
     }
     // results in the slab's order (ids read coalesced; the search loop
     // issues no global store, whose completion its waits for the next

@@ -440,7 +440,7 @@ __device__ __forceinline__ Best best_pair(float yh, float zh, FP UY, FP UZ, IP U
 // CELLS per row) so that the cells around h hold few candidates.
 template <int ROW, int CELLS>
 struct PairLdsT {
-    float y[2 * ROW], z[2 * ROW];
+    float y[2 * ROW + 1], z[2 * ROW + 1];
     uint16_t rel[2 * ROW];                  // cluster id minus its row's first id
     alignas(16) uint32_t cs[CELLS];         // cell starts of both rows (< CELLS each), concatenated, two to a word
     float red[8][TPC_BLOCK / TPC_WAVE];
@@ -637,7 +637,7 @@ __device__ inline bool rest_hrow(const int32_t *off, int seg, int n_rows) {
 #ifndef TPC_NB_SLAB
 #define TPC_NB_SLAB 512
 #endif
-#define TPC_NB_LIST 16
+#define TPC_NB_LIST 19        // (as many as four workgroups per CU leave room for)
 #ifndef TPC_NB_SLAB_MIN
 #define TPC_NB_SLAB_MIN 64
 #endif
@@ -687,23 +687,23 @@ __device__ inline int2 zrange(const SegGrid &g, const int32_t *cs, float lo, flo
 // best, whose lexicographic order (q, then u id, then d id) is kept
 // exactly.
 //
-// The nested walks of one cluster (up-row window cells, their candidates,
-// and for each up cluster in the window the down-row box cells and their
-// candidates) run as one flat loop in which every iteration tests one LDS
-// candidate per lane, so lanes at different depths of the walk stay in
-// step; a lane moves to its next cluster (every TPC_BLOCK-th of the slab,
-// loaded while it searches the current one) when the current one is
-// exhausted.  The rows of the up window are walked from h's own row of cells
-// outwards: a track moves little in y from one pad row to the next, so its
-// partner, after which the boxes are small, comes among the first (CONT).
-// One candidate test serves both walks: a candidate c at
-// (t_y, t_z) = (y_c - y_h, z_c - z_h) passes the window test on |t| in
-// either; an up candidate then starts a down box, a down candidate is
-// scored with d_y = a_y + t_y, equal (rounding included) to
-// a_y - (y_h - y_d) since fl(y_h - y_d) = -fl(y_d - y_h).  The best so far
-// is one 64-bit key (bits of q, then the up and down ids, 16 bits each), so
-// the lexicographic order is one unsigned comparison (q >= 0, whose bit
-// patterns order as its values) and the test carries no branches.
+// A thread has two clusters of the slab.  Bound by vector instructions, so
+// the walk over a window's up clusters and the searches of their boxes are
+// loops of their own, each iteration of which does what most lanes need: the
+// walk reads two candidates and lists those in the window (up to TPC_NB_LIST,
+// an LDS column per thread); then each round of the search, for a lane whose
+// box is exhausted, sets up the next listed cluster's, steps to a row of
+// cells with candidates, and scores two of them.  (One flat loop over both,
+// in which every lane went through the window test, the box set-up and the
+// row steps: 14.0 ms of a continuous-readout frame's 6.4 10^7 clusters, now
+// 10.6.)  A window's rows of cells are walked from h's own outwards: a track
+// moves little in y from one pad row to the next, so its partner, after
+// which the boxes are small, comes among the first.  A down candidate c at
+// t = (y_c - y_h, z_c - z_h) is scored with d_y = a_y + t_y, equal (rounding
+// included) to a_y - (y_h - y_d) since fl(y_h - y_d) = -fl(y_d - y_h).  The
+// best so far is one 64-bit key (bits of q, then the up and down ids, 16
+// bits each), so the lexicographic order is one unsigned comparison (q >= 0,
+// whose bit patterns order as its values) and the test carries no branches.
 //
 // Cell ranges are computed in cell units: the window's or the prediction's
 // cell coordinate is (y_h - y0) iw (minus a_y iw for the prediction), its
@@ -756,12 +756,7 @@ __device__ __forceinline__ void slab_search(int pb, int pn, const float *__restr
         int i = 0, yd = 0, yd1 = -1, zd0 = 0, zd1 = 0, kd = 0, e1 = 0;
         while (__ballot(kd < e1 || yd < yd1 || i < n)) {
             if (kd == e1) {
-                if (yd < yd1) {
-                    ++yd;
-                    const int row = __mul24(yd, gd.nz);
-                    kd = DCS[row + zd0];
-                    e1 = DCS[row + zd1 + 1];
-                } else if (i < n) {
+                if (yd >= yd1 && i < n) {
                     const uint32_t e = L.list[i++][tid];
                     if ((int)(e >> 15) != cur) {  // the second cluster's first
                         result(0);
@@ -792,21 +787,31 @@ __device__ __forceinline__ void slab_search(int pb, int pn, const float *__restr
                     e1 = DCS[row + zd1 + 1];
                 }
             }
-            if (kd < e1) {
-                const int c = kd++;
-                const float ty = Y[c] - yh;
-                const float tz = Z[c] - zh;
-                const uint32_t rr = R[c];
-                const float dy = ay + ty;
-                const float dz = az + tz;
-                const float qy = dy * dy;
-                const float qz = dz * dz;
-                const float q = qy + qz;
-                const uint64_t key = ((uint64_t)__float_as_uint(q) << 32) | (uint64_t)(urs | rr);
-                // bitwise, not short-circuit, conjunctions: no branches in the test
-                const bool win = (int)(fabsf(ty) <= win_y) & (int)(fabsf(tz) <= win_z) & (int)(fabsf(dy) <= cut_y) &
-                                 (int)(fabsf(dz) <= cut_z) & (int)(key < best);
-                best = win ? key : best;
+            while (kd == e1 && yd < yd1) {
+                ++yd;
+                const int row = __mul24(yd, gd.nz);
+                kd = DCS[row + zd0];
+                e1 = DCS[row + zd1 + 1];
+            }
+            // (two per round: boxes hold few, and the rounds are what costs)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                if (kd < e1) {
+                    const int c = kd++;
+                    const float ty = Y[c] - yh;
+                    const float tz = Z[c] - zh;
+                    const uint32_t rr = R[c];
+                    const float dy = ay + ty;
+                    const float dz = az + tz;
+                    const float qy = dy * dy;
+                    const float qz = dz * dz;
+                    const float q = qy + qz;
+                    const uint64_t key = ((uint64_t)__float_as_uint(q) << 32) | (uint64_t)(urs | rr);
+                    // bitwise, not short-circuit, conjunctions: no branches in the test
+                    const bool win = (int)(fabsf(ty) <= win_y) & (int)(fabsf(tz) <= win_z) & (int)(fabsf(dy) <= cut_y) &
+                                     (int)(fabsf(dz) <= cut_z) & (int)(key < best);
+                    best = win ? key : best;
+                }
             }
         }
         n = 0;
@@ -841,10 +846,16 @@ __device__ __forceinline__ void slab_search(int pb, int pn, const float *__restr
                     k = UCS[row + zc0];
                     k1 = UCS[row + zc1 + 1];
                 }
-                if (k < k1) {
-                    if ((int)(fabsf(Y[k] - y) <= win_y) & (int)(fabsf(Z[k] - z) <= win_z))
+                if (k < k1) {                     // (two are read at once, whether or not the row has both)
+                    const float a0 = Y[k] - y, b0 = Z[k] - z, a1 = Y[k + 1] - y, b1 = Z[k + 1] - z;
+                    if ((int)(fabsf(a0) <= win_y) & (int)(fabsf(b0) <= win_z))
                         L.list[n++][tid] = (uint16_t)(k | s << 15);
                     ++k;
+                    if (k < k1 && n < TPC_NB_LIST) {
+                        if ((int)(fabsf(a1) <= win_y) & (int)(fabsf(b1) <= win_z))
+                            L.list[n++][tid] = (uint16_t)(k | s << 15);
+                        ++k;
+                    }
                 }
             }
             if (!__ballot(k < k1 || it < it1)) break;

@@ -455,12 +455,12 @@ __device__ inline int rows_below(const int32_t *__restrict__ off, int seg, int32
     return d;
 }
 
-// The clusters of [a, b) that pass, in order, 64 at a time (fewer at the
-// end) to work(h, n): lane k < n gets the k-th (one whole wavefront; list: 128
+// The clusters h of [a, b) with value(h) >= least, in order, 64 at a time
+// (fewer at the end) to work(h, n): lane k < n gets the k-th (one whole wavefront; list: 128
 // ints of LDS of its own).  Few clusters of a row start or end a chain, so
 // what is done for them, chains of dependent reads, is done for many at once.
-template <class Pass, class Work>
-__device__ inline void wave_select(int a, int b, int *list, const Pass &pass, const Work &work) {
+template <class Value, class Work>
+__device__ inline void wave_select(int a, int b, int *list, int least, const Value &value, const Work &work) {
     constexpr int U = 4;
     const int lane = threadIdx.x & (TPC_WAVE - 1);
     int n = 0;
@@ -471,12 +471,12 @@ __device__ inline void wave_select(int a, int b, int *list, const Pass &pass, co
         fence();
     };
     for (int base = a; base < b; base += U * TPC_WAVE) {
+        int v[U];
         bool p[U];
 #pragma unroll
-        for (int j = 0; j < U; ++j) {
-            const int h = base + j * TPC_WAVE + lane;
-            p[j] = h < b && pass(h);
-        }
+        for (int j = 0; j < U; ++j) v[j] = value(min(base + j * TPC_WAVE + lane, b - 1));   // (all in flight)
+#pragma unroll
+        for (int j = 0; j < U; ++j) p[j] = base + j * TPC_WAVE + lane < b && v[j] >= least;
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             const uint64_t m = __ballot(p[j]);
@@ -508,7 +508,7 @@ __device__ inline void ca_firsts_part(int seg, int part, int parts, int32_t N, c
     const int a = off[seg], b = off[seg + 1];
     int cnt[TPC_CA_BELOW + 1] = {}, hits[TPC_CA_BELOW + 1] = {};
     wave_select(
-        part_at(a, b, part, parts), part_at(a, b, part + 1, parts), list, [&](int h) { return ws.cc[h].x >= 2; },
+        part_at(a, b, part, parts), part_at(a, b, part + 1, parts), list, 2, [&](int h) { return ws.cc[h].x; },
         [&](int h, int n) {
             int32_t len = 0;
             const int32_t f = lane < n ? ca_first_one(h, N, up, dn, min_hits, ws, len) : -1;
@@ -615,7 +615,7 @@ __device__ inline void ca_place_part(int seg, int part, int parts, int before_c,
     int carry_c = ws.segbs[seg] + before_c, carry_h = ws.segbh[seg] + before_h;
     const int frame = seg / (n_sectors * n_rows), sector = (seg / n_rows) % n_sectors, row = seg % n_rows;
     wave_select(
-        part_at(a, b, part, parts), part_at(a, b, part + 1, parts), list, [&](int h) { return ws.fbot[h] >= 0; },
+        part_at(a, b, part, parts), part_at(a, b, part + 1, parts), list, 0, [&](int h) { return ws.fbot[h]; },
         [&](int h, int n) {
             const int32_t fb = lane < n ? ws.fbot[h] : -1, len = lane < n ? ws.flen[h] : 0;
             const int inc = lane_scan(len);
@@ -634,7 +634,7 @@ __device__ inline int2 ca_place_count(int seg, int part, int parts, const int32_
     const int a = off[seg], b = off[seg + 1];
     int2 c = make_int2(0, 0);
     wave_select(
-        part_at(a, b, part, parts), part_at(a, b, part + 1, parts), list, [&](int h) { return ws.fbot[h] >= 0; },
+        part_at(a, b, part, parts), part_at(a, b, part + 1, parts), list, 0, [&](int h) { return ws.fbot[h]; },
         [&](int h, int n) {
             c.x += n;
             c.y += __builtin_amdgcn_readlane(lane_scan(lane < n ? ws.flen[h] : 0), TPC_WAVE - 1);

@@ -189,11 +189,8 @@ __device__ inline int pick_cluster(const FlArgs &A, int seg, const RowSeg &rs, c
     const float4 *sc = A.X.sc + a;
     const double idet = recip_pos(det);
     const double i00 = S11 * idet, i01 = -S01 * idet, i11 = S00 * idet;
-    float4 c = sc[j0];
-    for (int j = j0; j < j1; ++j) {
-        const float4 q = c;
-        c = sc[j + 1 < j1 ? j + 1 : j];
-        if (!((int)(fabsf(q.x - py) <= hy) & (int)(fabsf(q.y - pz) <= hz))) continue;
+    auto test = [&](const float4 &q) {
+        if (!((int)(fabsf(q.x - py) <= hy) & (int)(fabsf(q.y - pz) <= hz))) return;
         const int id = __float_as_int(q.z);
         const double r0 = (double)q.x - p[0], r1 = (double)q.y - p[1];
         const double chi = r0 * (i00 * r0 + i01 * r1) + r1 * (i01 * r0 + i11 * r1);
@@ -202,6 +199,15 @@ __device__ inline int pick_cluster(const FlArgs &A, int seg, const RowSeg &rs, c
             bchi = chi;
             yz = make_float2(q.x, q.y);
         }
+    };
+    // (the last cluster again beyond the end: testing it twice changes nothing)
+    for (int j = j0; j < j1; j += 4) {
+        const int l = j1 - 1;
+        const float4 q0 = sc[j], q1 = sc[min(j + 1, l)], q2 = sc[min(j + 2, l)], q3 = sc[min(j + 3, l)];
+        test(q0);
+        test(q1);
+        test(q2);
+        test(q3);
     }
     return best;
 }

@@ -603,16 +603,16 @@ __device__ inline void ca_place_one(int32_t h, int32_t fb, int32_t len, int i, i
     }
 }
 
-// The seeds of a part of segment seg, to [segbs[seg] + before_c, ...) within
-// capacity, their hits from segbh[seg] + before_h (one whole wavefront).
-__device__ inline void ca_place_part(int seg, int part, int parts, int before_c, int before_h, int32_t N,
+// The seeds of a part of segment seg, to [first_c, ...) within capacity, their
+// hits from first_h (one whole wavefront).
+__device__ inline void ca_place_part(int seg, int part, int parts, int first_c, int first_h, int32_t N,
                                      const int32_t *__restrict__ off, const int32_t *__restrict__ up,
                                      const float *__restrict__ y, const float *__restrict__ z, int32_t n_sectors,
                                      int32_t n_rows, int32_t cap_seeds, int32_t cap_hits, const tpc_seeds &sd,
                                      const CaWs &ws, int *list) {
     const int lane = threadIdx.x & (TPC_WAVE - 1);
     const int a = off[seg], b = off[seg + 1];
-    int carry_c = ws.segbs[seg] + before_c, carry_h = ws.segbh[seg] + before_h;
+    int carry_c = first_c, carry_h = first_h;
     const int frame = seg / (n_sectors * n_rows), sector = (seg / n_rows) % n_sectors, row = seg % n_rows;
     wave_select(
         part_at(a, b, part, parts), part_at(a, b, part + 1, parts), list, 0, [&](int h) { return ws.fbot[h]; },

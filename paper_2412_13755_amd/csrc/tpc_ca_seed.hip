@@ -64,6 +64,15 @@ ca_firsts(int32_t N, int32_t NR, const int32_t *off, const int32_t *up, const in
     if (seg < NR) ca_firsts_part(seg, wid % PARTS, PARTS, N, off, up, dn, min_hits, ws, list[wid]);
 }
 
+__device__ inline void put_totals(int seeds, int hits, int32_t *n_seeds, int32_t *n_hits, int32_t cap_seeds,
+                                  int32_t cap_hits, int32_t *offsets, int32_t *dev_status) {
+    *n_seeds = seeds;
+    *n_hits = hits;
+    const bool ok = seeds <= cap_seeds && hits <= cap_hits;
+    *dev_status = ok ? TPC_OK : TPC_ERR_CAPACITY;
+    if (seeds <= cap_seeds) offsets[seeds] = ok ? hits : 0;
+}
+
 // Single workgroup: exclusive scan of n (seed count, hit count) pairs into
 // (pre_c, pre_h), totals into *n_seeds / *n_hits with the capacity check.
 // Thread t owns the contiguous run [t k, (t+1) k), k = ceil(n / 1024): it
@@ -104,13 +113,7 @@ ca_scan(int32_t n, const int32_t *cnt, const int32_t *hits, int32_t *pre_c, int3
         pc += c;
         ph += h;
     }
-    if (tid == 0) {
-        *n_seeds = tc;
-        *n_hits = th;
-        const bool ok = tc <= cap_seeds && th <= cap_hits;
-        *dev_status = ok ? TPC_OK : TPC_ERR_CAPACITY;
-        if (tc <= cap_seeds) offsets[tc] = ok ? th : 0;
-    }
+    if (tid == 0) put_totals(tc, th, n_seeds, n_hits, cap_seeds, cap_hits, offsets, dev_status);
 }
 
 // Many segments: sums of chunks of TPC_SCAN_CHUNK segments (one workgroup
@@ -157,27 +160,59 @@ ca_chunk_prefix(int32_t NR, CaWs ws) {
     }
 }
 
-template <int PARTS>
+// SUM: every workgroup sums the counts of the segments before its own itself
+// (they are in no scan), and the one with the last segment writes the totals.
+template <int PARTS, bool SUM>
 __global__ void __launch_bounds__(TPC_BLOCK)
 ca_place(int32_t N, int32_t NR, const int32_t *off, const int32_t *up, const float *y, const float *z,
-         int32_t n_sectors, int32_t n_rows, int32_t cap_seeds, int32_t cap_hits, tpc_seeds sd, CaWs ws) {
-    __shared__ int list[TPC_BLOCK / TPC_WAVE][2 * TPC_WAVE];
-    __shared__ int2 count[TPC_BLOCK / TPC_WAVE];
-    constexpr int SEGS = TPC_BLOCK / TPC_WAVE / PARTS;
-    const int wid = threadIdx.x / TPC_WAVE, part = wid % PARTS;
-    const int seg = xcd_item(blockIdx.x, gridDim.x) * SEGS + wid / PARTS;
-    int before_c = 0, before_h = 0;
+         int32_t n_sectors, int32_t n_rows, int32_t cap_seeds, int32_t cap_hits, tpc_seeds sd, int32_t *dev_status,
+         CaWs ws) {
+    constexpr int W = TPC_BLOCK / TPC_WAVE, SEGS = W / PARTS;
+    __shared__ int list[W][2 * TPC_WAVE];
+    __shared__ int2 count[W];
+    const int wid = threadIdx.x / TPC_WAVE, part = wid % PARTS, lane = threadIdx.x % TPC_WAVE;
+    const int s0 = xcd_item(blockIdx.x, gridDim.x) * SEGS, seg = s0 + wid / PARTS;
+    int first_c = 0, first_h = 0;
+    if constexpr (SUM) {
+        static_assert(PARTS == 1 && SEGS % 4 == 0, "four counts at a time");
+        const int4 *c4 = reinterpret_cast<const int4 *>(ws.segcnt), *h4 = reinterpret_cast<const int4 *>(ws.seghits);
+        int c = 0, h = 0;
+        for (int q = threadIdx.x; q < s0 / 4; q += TPC_BLOCK) {
+            const int4 a = c4[q], b = h4[q];
+            c += a.x + a.y + a.z + a.w;
+            h += b.x + b.y + b.z + b.w;
+        }
+        c = __builtin_amdgcn_readlane(lane_scan(c), TPC_WAVE - 1);
+        h = __builtin_amdgcn_readlane(lane_scan(h), TPC_WAVE - 1);
+        if (lane == 0) count[wid] = make_int2(c, h);
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            first_c += count[w].x;
+            first_h += count[w].y;
+        }
+        for (int s = s0; s < seg && s < NR; ++s) {
+            first_c += ws.segcnt[s];
+            first_h += ws.seghits[s];
+        }
+        if (seg == NR - 1 && lane == 0)
+            put_totals(first_c + ws.segcnt[seg], first_h + ws.seghits[seg], sd.n_seeds, sd.n_hits, cap_seeds, cap_hits,
+                       sd.offsets, dev_status);
+    } else if (seg < NR) {
+        first_c = ws.segbs[seg];
+        first_h = ws.segbh[seg];
+    }
     if constexpr (PARTS > 1) {                        // (then the whole workgroup has one segment)
         const int2 c = ca_place_count(seg, part, PARTS, off, ws, list[wid]);
-        if (threadIdx.x % TPC_WAVE == 0) count[wid] = c;
+        if (lane == 0) count[wid] = c;
         __syncthreads();
         for (int p = 0; p < part; ++p) {
-            before_c += count[p].x;
-            before_h += count[p].y;
+            first_c += count[p].x;
+            first_h += count[p].y;
         }
     }
     if (seg < NR)
-        ca_place_part(seg, part, PARTS, before_c, before_h, N, off, up, y, z, n_sectors, n_rows, cap_seeds, cap_hits,
+        ca_place_part(seg, part, PARTS, first_c, first_h, N, off, up, y, z, n_sectors, n_rows, cap_seeds, cap_hits,
                       sd, ws, list[wid]);
 }
 
@@ -213,11 +248,14 @@ hipError_t launch_ca_seed(const tpc_context *ctx, const tpc_frames *fr, const in
                            c.min_hits, ws);
     else
         hipLaunchKernelGGL(ca_firsts<WB>, dim3(NR), dim3(TPC_BLOCK), 0, st, N, NR, off, up, dn, c.min_hits, ws);
-    if (NR <= TPC_SCAN_DIRECT) {
+    // few segments: no scan of their own (a launch, 7 us, for the 5472 of an
+    // event; their sums cost the placement about 3)
+    const bool sum = sparse && NR <= TPC_SCAN_SUM;
+    if (!sum && NR <= TPC_SCAN_DIRECT) {
         hipLaunchKernelGGL(ca_scan, dim3(1), dim3(1024), 0, st, NR, ws.segcnt, ws.seghits, ws.segbs,
                            ws.segbh, sd->n_seeds, sd->n_hits, sd->cap_seeds, sd->cap_hits, sd->offsets,
                            dev_status);
-    } else {
+    } else if (!sum) {
         const int nch = (NR + TPC_SCAN_CHUNK - 1) / TPC_SCAN_CHUNK;
         hipLaunchKernelGGL(ca_chunk_sums, dim3(nch), dim3(TPC_BLOCK), 0, st, NR, ws);
         hipLaunchKernelGGL(ca_scan, dim3(1), dim3(1024), 0, st, nch, ws.chunk_c, ws.chunk_h, ws.chunk_c,
@@ -225,12 +263,13 @@ hipError_t launch_ca_seed(const tpc_context *ctx, const tpc_frames *fr, const in
                            dev_status);
         hipLaunchKernelGGL(ca_chunk_prefix, dim3(nch), dim3(TPC_BLOCK), 0, st, NR, ws);
     }
-    if (sparse)
-        hipLaunchKernelGGL(ca_place<1>, dim3((NR + WB - 1) / WB), dim3(TPC_BLOCK), 0, st, N, NR, off, up, fr->y,
-                           fr->z, c.n_sectors, c.n_rows, sd->cap_seeds, sd->cap_hits, *sd, ws);
-    else
-        hipLaunchKernelGGL(ca_place<WB>, dim3(NR), dim3(TPC_BLOCK), 0, st, N, NR, off, up, fr->y, fr->z,
-                           c.n_sectors, c.n_rows, sd->cap_seeds, sd->cap_hits, *sd, ws);
+    auto place = [&](auto kernel, int blocks) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(TPC_BLOCK), 0, st, N, NR, off, up, fr->y, fr->z, c.n_sectors,
+                           c.n_rows, sd->cap_seeds, sd->cap_hits, *sd, dev_status, ws);
+    };
+    if (sum) place(ca_place<1, true>, (NR + WB - 1) / WB);
+    else if (sparse) place(ca_place<1, false>, (NR + WB - 1) / WB);
+    else place(ca_place<WB, false>, NR);
     hipLaunchKernelGGL(ca_members, dim3(flat), dim3(TPC_BLOCK), 0, st, N, fr->y, fr->z, sd->cap_hits, *sd, ws);
     return hipGetLastError();
 }

@@ -68,6 +68,7 @@ struct CaWs {
 };
 
 #define TPC_SCAN_CHUNK 1024      // segments per chunk of the two-level segment scan
+#define TPC_SCAN_SUM 8192        // up to this many segments of small rows the placement sums their counts itself
 #define TPC_SCAN_DIRECT 16384    // up to this many segments one workgroup scans them directly
 
 size_t nb_ws_layout(void *ws, int64_t N, int64_t NR, NbWs *out);

@@ -50,7 +50,11 @@ nb_query_small(const int32_t *__restrict__ off, int32_t NR, int32_t nb, int32_t 
         }
         return;
     }
-    const int s0 = GROUP * xcd_item(blockIdx.x - nb, (NR + GROUP - 1) / GROUP), wid = threadIdx.x / TPC_WAVE;
+    // One segment each: rows in ascending order over all sectors, so that the
+    // inner rows, which take longest, start first and do not trail.
+    const int b = blockIdx.x - nb, n_fs = NR / n_rows;
+    const int s0 = GROUP > 1 ? GROUP * xcd_item(b, (NR + GROUP - 1) / GROUP) : b % n_fs * n_rows + b / n_fs;
+    const int wid = threadIdx.x / TPC_WAVE;
     static_assert(GROUP <= TPC_BLOCK / TPC_WAVE, "a wavefront per segment");
     auto tiny = [&](int seg) {
         return tpc_nb::inner_row(seg, n_rows) && off[seg] < off[seg + 1] && tpc_nb::tiny_pair(off, seg);

@@ -155,8 +155,7 @@ __global__ void __launch_bounds__(TPC_BLOCK) rs_minmax(RsBatch Bt) {
         else if (d >= -RS_WIN_HALF && d < RS_WIN_HALF) atomicAdd(&A.counts[d + RS_WIN_HALF], 1u);
         else out = true;
     };
-    for (int64_t q = gtid; q < V.nv; q += G) {
-        const int4 v = v4[q];
+    auto take = [&](const int4 &v) {
         lo = min(lo, min(min(v.x, v.y), min(v.z, v.w)));
         hi = max(hi, max(max(v.x, v.y), max(v.z, v.w)));
         if (A.fused) {
@@ -165,7 +164,16 @@ __global__ void __launch_bounds__(TPC_BLOCK) rs_minmax(RsBatch Bt) {
             add(v.z);
             add(v.w);
         }
+    };
+    int64_t q = gtid;
+    for (; q + 3 * G < V.nv; q += 4 * G) {
+        const int4 v0 = v4[q], v1 = v4[q + G], v2 = v4[q + 2 * G], v3 = v4[q + 3 * G];
+        take(v0);
+        take(v1);
+        take(v2);
+        take(v3);
     }
+    for (; q < V.nv; q += G) take(v4[q]);
     for (int64_t i = gtid; i < V.head + (A.n - V.head - 4 * V.nv); i += G) {
         const int64_t j = i < V.head ? i : V.head + 4 * V.nv + (i - V.head);
         const int v = A.sym[j];

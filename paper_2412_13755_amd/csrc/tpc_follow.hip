@@ -7,7 +7,7 @@
 //                  y cells (about one cluster per cell, a counting sort);
 //                  non-finite clusters are left out (they can never pass the
 //                  gate)
-//  fl_order        the seeds of each window of 1024 by descending length
+//  fl_order        the seeds of each XCD's run by length class and first row
 //  fl_tracks       thread per seed, double precision throughout: seed fit
 //                  (the seed's hits at the rows that hold them, so seeds may
 //                  skip rows), inward prolongation, outward refit and
@@ -476,39 +476,74 @@ __device__ inline void follow_one(const FlArgs &A, int i, const Strip &S) {
     write_track(F, i, xcur, p, C, chi2, m, status);
 }
 
-// Order of the seeds: within each window of FL_WINDOW consecutive ones by
-// descending length (a counting sort in LDS).  A wavefront takes as long as
-// the longest of its lanes in each phase: a long seed has many steps to fit
-// and few rows to prolong over, a short one the reverse, so mixed lanes pay
-// for both.  Windows of a sector's size keep the lanes' clusters together.
-#define FL_WINDOW 1024
-__global__ void __launch_bounds__(FL_WINDOW)
+// Tracks per wavefront: all lanes, or fewer while that gives no more than
+// two wavefronts per CU, since a wavefront takes as long as its slowest lanes
+// (2000 tracks: 617 us with 64, 560 with 16).  Not beyond that: the events
+// that fill the chip then have their reads of 64 lines wait for each other
+// (10 000 tracks, 26 500 seeds: 829 us with 64 in 415 wavefronts, 910 with 32
+// in 830).  Fewer than 8 gain nothing more (300 tracks: 489 us with 8, 487
+// with 4; 533 with 16).
+#define FL_WAVES 512
+#define FL_MIN_TRACKS 8
+__device__ inline int wave_tracks(int T) {
+    int per = TPC_WAVE;
+    while (per > FL_MIN_TRACKS && T <= per / 2 * FL_WAVES) per /= 2;
+    return per;
+}
+
+// Order of the seeds: a wavefront takes as long as its longest lane in each
+// phase: the seed's fit, the rows below it, the rows above it.  Seeds of like
+// length and like first row share a wavefront, so that the longest way down
+// and the longest way up are not both the whole sector: by length in
+// FL_LENGTHS classes, within a class by first row (up and down in turn).  By
+// length alone the slowest wavefronts of an event of 10 000 tracks did 276
+// rows of prolongation at 2.8 us (the search's reads take half of that); its
+// following took 1107 us, 772 so.  Two classes 1006 (windows of 4096), eight
+// 827.  Classes of short seeds, the slowest, come first.
+// A counting sort in LDS within each XCD's run of seeds (a sector's clusters
+// then meet one L2), or over all of them up to FL_ONE_WINDOW, where the runs
+// would be a few wavefronts (300 tracks: 535 -> 489 us).
+#define FL_LENGTHS 4
+#define FL_PLACES (TPC_MAX_ROWS / FL_LENGTHS)
+__device__ inline int shape_key(int n, int row0, int R) {
+    n = n < 0 ? 0 : (n < R ? n : R);
+    row0 = row0 < 0 ? 0 : (row0 < R ? row0 : R - 1);
+    const int l = FL_LENGTHS - 1 - n * FL_LENGTHS / (R + 1), q = row0 * FL_PLACES / R;
+    return l * FL_PLACES + (l & 1 ? FL_PLACES - 1 - q : q);
+}
+
+#define FL_ORDER 1024            // threads
+#define FL_ONE_WINDOW 2048
+__global__ void __launch_bounds__(FL_ORDER)
 fl_order(const int32_t *__restrict__ n_seeds, int32_t cap, const int32_t *__restrict__ offsets,
-         int32_t *__restrict__ order, int64_t cap_order) {
+         const int32_t *__restrict__ first_row, int32_t n_rows, int32_t *__restrict__ order, int64_t cap_order) {
     __shared__ int32_t cnt[TPC_MAX_ROWS + 1];
     __shared__ int32_t all;
     const int T = *n_seeds < cap ? *n_seeds : cap;
     if (T > cap_order) return;
-    for (int i0 = blockIdx.x * FL_WINDOW; i0 < T; i0 += gridDim.x * FL_WINDOW) {
-        const int i = i0 + threadIdx.x;
-        for (int b = threadIdx.x; b <= TPC_MAX_ROWS; b += FL_WINDOW) cnt[b] = 0;
+    const int per = wave_tracks(T), G = (int)(((int64_t)T + per - 1) / per);
+    const bool one = T <= FL_ONE_WINDOW;
+    if (one && blockIdx.x > 0) return;               // (run 0 is all of them)
+    for (int w = blockIdx.x; w / TPC_XCDS * (TPC_XCDS * TPC_XCD_RUN) < G; w += gridDim.x) {
+        int len;
+        const int first = xcd_run(w, G, &len);
+        if (one) len = w == 0 ? G : 0;
+        const int64_t i0 = (int64_t)first * per, e = (int64_t)(first + len) * per, i1 = e < T ? e : T;
+        for (int b = threadIdx.x; b <= TPC_MAX_ROWS; b += FL_ORDER) cnt[b] = 0;
         __syncthreads();
-        int n = 0;
-        if (i < T) {
-            n = offsets[i + 1] - offsets[i];
-            n = n < 0 ? 0 : (n < TPC_MAX_ROWS ? n : TPC_MAX_ROWS);
-            atomicAdd(&cnt[n], 1);
-        }
+        for (int64_t i = i0 + threadIdx.x; i < i1; i += FL_ORDER)
+            atomicAdd(&cnt[shape_key(offsets[i + 1] - offsets[i], first_row[i], n_rows)], 1);
         __syncthreads();
         if (threadIdx.x < TPC_WAVE) len_starts_wave(cnt, &all);
         __syncthreads();
-        if (i < T) order[i0 + atomicAdd(&cnt[n], 1)] = i;
+        for (int64_t i = i0 + threadIdx.x; i < i1; i += FL_ORDER)
+            order[i0 + atomicAdd(&cnt[shape_key(offsets[i + 1] - offsets[i], first_row[i], n_rows)], 1)] = (int)i;
         __syncthreads();
     }
 }
 
-// One wavefront per workgroup; lane t follows seed i0 + t of the order in
-// each round, then the workgroup writes the round's rows out
+// One wavefront per workgroup; lane t < per follows seed i0 + t of the order
+// in each round, then the workgroup writes the round's rows out
 // row-contiguously.
 __global__ void __launch_bounds__(TPC_WAVE)
 fl_tracks(FlArgs A) {
@@ -521,18 +556,19 @@ fl_tracks(FlArgs A) {
     if (T > A.F.cap_seeds) T = A.F.cap_seeds;
     // blocks with work, renumbered so that each XCD takes consecutive seeds
     // (one sector's seeds and clusters then stay in one L2)
-    int G = (T + TPC_WAVE - 1) / TPC_WAVE;
+    const int per = wave_tracks(T);
+    int G = (T + per - 1) / per;
     G = G < (int)gridDim.x ? G : (int)gridDim.x;
     if ((int)blockIdx.x >= G) return;
-    for (int i0 = xcd_item(blockIdx.x, G) * TPC_WAVE; i0 < T; i0 += G * TPC_WAVE) {
+    for (int i0 = xcd_item(blockIdx.x, G) * per; i0 < T; i0 += G * per) {
         const bool ordered = T <= A.cap_order;
-        if (i0 + t < T) {
+        if (t < per && i0 + t < T) {
             const int i = ordered ? A.order[i0 + t] : i0 + t;
             seed[t] = i;
             follow_one(A, i, S);
         }
         __syncthreads();
-        const int nt = T - i0 < TPC_WAVE ? T - i0 : TPC_WAVE;
+        const int nt = T - i0 < per ? T - i0 : per;
         for (int u = 0; u < nt; ++u) {
             int32_t *out = A.rows + (size_t)seed[u] * R;
             for (int r = t; r < R; r += TPC_WAVE) out[r] = fl_strip[r * TPC_WAVE + (u ^ (r & 31))];
@@ -641,12 +677,14 @@ hipError_t launch_follow(const tpc_context *ctx, const tpc_frames *fr, const tpc
     int32_t *order = reinterpret_cast<int32_t *>(A.X.owner);
     A.order = order;
     A.cap_order = 2 * (int64_t)fr->n_clusters;
-    int ob = (sd->cap_seeds + FL_WINDOW - 1) / FL_WINDOW;
-    ob = ob > 1024 ? 1024 : (ob < 1 ? 1 : ob);
-    hipLaunchKernelGGL(fl_order, dim3(ob), dim3(FL_WINDOW), 0, st, sd->n_seeds, sd->cap_seeds, sd->offsets, order,
-                       A.cap_order);
-    int tb = (int)((sd->cap_seeds + TPC_WAVE - 1) / TPC_WAVE);
-    tb = tb > 16384 ? 16384 : (tb < 1 ? 1 : tb);
+    const int64_t full = ((int64_t)sd->cap_seeds + TPC_WAVE - 1) / TPC_WAVE;
+    int ob = (int)(full / (TPC_XCDS * TPC_XCD_RUN) + 1) * TPC_XCDS;
+    ob = ob > 1024 ? 1024 : ob;
+    hipLaunchKernelGGL(fl_order, dim3(ob), dim3(FL_ORDER), 0, st, sd->n_seeds, sd->cap_seeds, sd->offsets,
+                       sd->first_row, c.n_rows, order, A.cap_order);
+    const int64_t few = ((int64_t)sd->cap_seeds + FL_MIN_TRACKS - 1) / FL_MIN_TRACKS;
+    int tb = (int)(full > FL_WAVES ? (full < 16384 ? full : 16384) : (few < FL_WAVES ? few : FL_WAVES));
+    tb = tb < 1 ? 1 : tb;
     hipLaunchKernelGGL(fl_tracks, dim3(tb), dim3(TPC_WAVE), (size_t)c.n_rows * TPC_WAVE * sizeof(int32_t), st, A);
     hipLaunchKernelGGL(fl_owner_init, dim3(grid_for(fr->n_clusters)), dim3(TPC_BLOCK), 0, st, A.X.owner,
                        fr->n_clusters);

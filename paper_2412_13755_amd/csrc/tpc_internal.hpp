@@ -174,6 +174,19 @@ __device__ inline int xcd_item(int b, int G) {
     return g0 + x * q + (x < r ? x : r) + j;
 }
 
+// The runs of items that xcd_item gives an XCD one after the other: run w's
+// first item and its length (0 beyond the last).  A bijection over [0, G).
+__device__ inline int xcd_run(int w, int G, int *len) {
+    const int g0 = w / TPC_XCDS * (TPC_XCDS * TPC_XCD_RUN), x = w % TPC_XCDS, n = G - g0;
+    if (n >= TPC_XCDS * TPC_XCD_RUN) {
+        *len = TPC_XCD_RUN;
+        return g0 + x * TPC_XCD_RUN;
+    }
+    const int q = n > 0 ? n / TPC_XCDS : 0, r = n > 0 ? n % TPC_XCDS : 0;
+    *len = q + (x < r ? 1 : 0);
+    return g0 + x * q + (x < r ? x : r);
+}
+
 __device__ inline int wave_inclusive_scan(int v) {
     const int lane = threadIdx.x & (TPC_WAVE - 1);
 #pragma unroll

@@ -9,7 +9,8 @@ of another checkpoint interval.
    reads scanned counts, and with several wavefronts per segment;
  - the skip search with one query's windows beyond the pool of candidates,
    pools of several batches, rows around one pass of queries, and ties;
- - track following over rows around the size that is indexed in LDS;
+ - track following over rows around the size that is indexed in LDS, and
+   with as many seeds as take 8, 16, 32 and 64 lanes of a wavefront;
  - the adjoint's checkpoint intervals below, at and above its tape of four
    rows, and intervals that do not divide by it.
 """
@@ -139,15 +140,14 @@ def test_skip_stacks(name):
     np.testing.assert_array_equal(dn.cpu().numpy(), rd)
 
 
-@pytest.mark.parametrize("tracks", [2040, 2300])
-def test_following_over_long_rows(tracks):
+@pytest.mark.parametrize("frames,tracks", [(1, 2040), (1, 2300), (4, 1200), (9, 1500), (15, 1500)])
+def test_following_sizes(frames, tracks):
     import torch
     n_rows = 12
-    off, y, z = _lines([tracks], n_rows, tracks)
+    off, y, z = _lines([tracks] * frames, n_rows, tracks)
     longest = int(np.diff(off).max())
-    print("[edges] follow: rows of up to %d clusters" % longest, flush=True)
-    assert (longest <= 2048) == (tracks == 2040)
-    reco, dfr, row_x = _upload(off, y, z, 1, n_rows)
+    assert (longest <= 2048) == (tracks < 2300)
+    reco, dfr, row_x = _upload(off, y, z, frames, n_rows)
     up, dn = reco.neighbours(dfr)
     seeds = reco.seed(dfr, up, dn)
     rows, tr = reco.follow(dfr, seeds, GATE, MAX_MISS)
@@ -157,9 +157,15 @@ def test_following_over_long_rows(tracks):
     parity.assert_seeds_equal(seeds.to_numpy(), sd)
     r = oracle.follow(sd, off, y, z, row_x, 1, n_rows, gate=GATE, max_miss=MAX_MISS, **FIT)
     T = len(sd["frame"])
+    print("[edges] follow: %d seeds, rows of up to %d clusters" % (T, longest), flush=True)
     g = {k: getattr(tr, k)[:T].cpu().numpy() for k in ("x", "par", "cov", "chi2", "ndf", "status")}
     g["rows"] = rows[:T].cpu().numpy()
     print("[edges] follow:", compare_follow(g, r), flush=True)
+    # the first rows order the work and decide nothing
+    seeds.first_row.random_(-2**31, 2**31 - 1)
+    rows2, tr2 = reco.follow(dfr, seeds, GATE, MAX_MISS)
+    assert torch.equal(rows2[:T], rows[:T]) and torch.equal(tr2.status[:T], tr.status[:T])
+    assert np.array_equal(tr2.par[:T].cpu().numpy(), g["par"], equal_nan=True)
 
 
 def test_adjoint_checkpoint_intervals():

@@ -314,7 +314,7 @@ def stage_events(reco, dfr, out, ws, steps):
 
 
 def fit_roofline(n_hits, n_seeds, fit_ms, traffic=None):
-    """Roofline of tpc_kalman_fit (the length order of the seeds, four small
+    """Roofline of tpc_kalman_fit (the length order of the seeds, two small
     kernels, then fit_tracks, when the seeds carry their hit
     coordinates) against the FP64 vector peak; fit_ms is the whole call."""
     flops = FLOP_FIT_PER_HIT * n_hits
@@ -605,7 +605,7 @@ def leg_rans(args, with_cpu=True):
                         "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": round(alg / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                         "algorithmic_bytes": alg,
-                        "calls": "rs_init, rs_window, rs_minmax, rs_clear, rs_hist, rs_freq, rs_table, rs_encode, rs_scan, rs_pack"}}
+                        "calls": "rs_init, rs_minmax, rs_clear, rs_hist, rs_freq, rs_encode, rs_pack"}}
     if with_cpu:
         import oracle
         xs = x[:1 << 24].cpu().numpy()

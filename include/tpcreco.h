@@ -304,7 +304,7 @@ tpc_status tpc_kalman_fit_rows(const tpc_context *ctx, const tpc_frames *frames,
  * Double precision throughout, single-precision outputs.
  * rejected, hit_par, hit_cov: device, [cap_hits], [cap_hits][5],
  * [cap_hits][15], required.  ws: TPC_STAGE_SMOOTH workspace (the fit's,
- * plus 5 doubles per seed and 20 doubles + 2 bytes per seed hit). */
+ * plus 5 doubles per seed and 38 doubles + 2 bytes per seed hit). */
 tpc_status tpc_kalman_smooth(const tpc_context *ctx, const tpc_frames *frames,
                              const tpc_seeds *seeds, const float *cluster_err,
                              const tpc_material *mat, tpc_tracks *tracks, uint8_t *rejected,
@@ -326,7 +326,7 @@ tpc_status tpc_chi2_sum(const tpc_context *ctx, const tpc_seeds *seeds, const tp
  * Seeds stay fixed.  Requires the checkpoints of a tpc_kalman_fit() call
  * with the same frames, seeds and map; tracks.status comes from that call.
  * Reverse mode: each ckpt_rows-step segment is recomputed from its
- * checkpoint, then run backwards.  Per-row sums are formed in a fixed order,
+ * checkpoint, then run backwards in parts of four steps.  Per-row sums are formed in a fixed order,
  * so the result is bit-reproducible.  dloss: device float scalar (NULL = 1).
  * grad_map: [n_sectors][n_rows][2] device floats, overwritten.
  * ws: TPC_STAGE_ADJOINT workspace (sized for the default capacities

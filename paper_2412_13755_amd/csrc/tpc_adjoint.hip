@@ -39,12 +39,11 @@ __device__ inline int64_t snake(int64_t k, int gt, int nthreads) {
     return k * nthreads + ((k & 1) ? nthreads - 1 - gt : gt);
 }
 
-// Two wavefronts per SIMD (256 registers per lane, a few spilled): the
-// step adjoint's live set is near 300 registers, and one wavefront per SIMD
-// leaves its latency exposed.  Seeds in descending length order (F.order): a
+// Two wavefronts per SIMD (256 registers per lane, nothing spilled): one
+// leaves the latency of its chain of operations exposed.  Seeds in descending length order (F.order): a
 // wavefront runs as many steps as its longest seed, and seeds in their own
 // order (12 hits on average, up to 151) left most lanes idle: one gradient
-// of 645 000 seeds 3.15 -> 1.83 ms.
+// of 645 000 seeds 3.15 -> 1.83 ms, and 1.06 since (735 us of it here).
 __global__ void __launch_bounds__(TPC_BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
 adj_tracks(AdjArgs A) {
     // two states per thread: half of a CU's LDS, for half of its threads
@@ -93,11 +92,12 @@ __device__ inline int lower_bound_key(const int32_t *frame, const int32_t *secto
 }
 
 // A wavefront takes 64 seeds at a time and adds their hits' gradients to its
-// own row sums in LDS, a seed per instruction, lane k its k-th hit: the reads
-// are contiguous, TPC_ADJ_AHEAD seeds' are in flight, and the adds of a
-// wavefront happen in their order, so the sums are reproducible.  (A thread
-// per row walking over the seeds that cross it read one value at a time: 285
-// -> 113 us for 645 000 seeds.)
+// own row sums in LDS (read, add, write: LDS float atomics took three times as
+// long), a seed per instruction, lane k its k-th hit: the reads are
+// contiguous, TPC_ADJ_AHEAD seeds' are in flight, and a wavefront's adds
+// happen in its order, so the sums are reproducible.  (A thread per row
+// walking over the seeds that cross it read one value at a time: 285 -> 38 us
+// for 645 000 seeds.)
 #define TPC_ADJ_AHEAD 8
 __global__ void __launch_bounds__(TPC_BLOCK)
 adj_partial(const int32_t *__restrict__ n_seeds, int32_t cap_seeds,

@@ -218,7 +218,7 @@ __host__ __device__ inline int adj_tape_states(int K) { return (K + TPC_ADJ_SUB 
 // the last, is then run forward again with its states in LDS (lt) and
 // registers, and its steps reversed.  That is half a forward step more per
 // step than with every state taped, and a third of the memory traffic, which
-// was what the time went to (2.9 GB for 645 000 seeds; 1035 -> ADJT us).
+// was what the time went to (2.9 GB for 645 000 seeds; 1035 -> 735 us).
 // (Everything is addressed by 32-bit indices from bases in scalar registers:
 // the step adjoint needs nearly all of the vector ones.  F.hyz is set.)
 __device__ inline void adj_one(const FitArgs &F, const int32_t *status, const double *ckpt, float2 *gbuf, int i,

@@ -362,7 +362,7 @@ __device__ inline void deal_pairs(SegLds &L, int q0, int q1, const int rel[4], f
 }
 
 // Bound by the chains of LDS reads of the window passes and, where a thread
-// scored the pairs of a query alone, by the longest of those: 262 -> 150 us
+// scored the pairs of a query alone, by the longest of those: 262 -> 145 us
 // for an event of 10^4 tracks with one row in ten missing (the pool of 1024
 // was also too small for its inner rows, whose queries then scanned whole
 // rows).

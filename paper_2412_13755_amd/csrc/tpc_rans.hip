@@ -481,7 +481,7 @@ __global__ void __launch_bounds__(RS_FREQ_THREADS) rs_freq(RsBatch Bt) {
 // from LDS, a ballot and a 16-bit store, and in between a division by a
 // product and one multiply-add; rounds with all lanes come without tests,
 // and the next RS_CHUNK rounds' symbols are read while these are coded.
-// 2^28 symbols, sigma 12: 357 -> 292 us.
+// 2^28 symbols, sigma 12: 357 -> 291 us (of which reading them takes 235).
 template <bool GENERAL, class Tab>
 __device__ inline void encode_block(const RsArgs &A, Tab T, int b, int lane) {
     const int lo = A.mm[0];

@@ -394,14 +394,14 @@ __global__ void __launch_bounds__(MS_T) fit_ms_tracks(MsArgs A) {
 
 // Errors of every seed hit in seed-hit order, so that the fit reads them as
 // it reads the coordinates (from the id that a step loads, the error's load
-// was waited for in every step).
+// was waited for in every step).  The whole capacity: a seed list that
+// exceeded it, or has a malformed seed, holds good seeds whose hits neither
+// the last offset nor the count bounds.  (Ids behind the last seed are
+// whatever the buffer holds; their errors are not read.)
 __global__ void __launch_bounds__(TPC_BLOCK)
-gather_err(const int32_t *__restrict__ n_seeds, int32_t cap_seeds, const int32_t *__restrict__ offsets,
-           int32_t cap_hits, const int32_t *__restrict__ hits, const float2 *__restrict__ err, int32_t N,
+gather_err(int32_t cap_hits, const int32_t *__restrict__ hits, const float2 *__restrict__ err, int32_t N,
            float2 *__restrict__ out) {
-    const int T = *n_seeds < cap_seeds ? *n_seeds : cap_seeds;
-    const int H = T > 0 ? (offsets[T] < cap_hits ? offsets[T] : cap_hits) : 0;
-    for (int64_t j = blockIdx.x * TPC_BLOCK + threadIdx.x; j < H; j += gridDim.x * TPC_BLOCK) {
+    for (int64_t j = blockIdx.x * TPC_BLOCK + threadIdx.x; j < cap_hits; j += gridDim.x * TPC_BLOCK) {
         const int32_t id = hits[j];
         out[j] = (uint32_t)id < (uint32_t)N ? err[id] : make_float2(0.f, 0.f);
     }
@@ -752,9 +752,8 @@ MsArgs make_ms_args(const tpc_context *ctx, const tpc_frames *fr, const tpc_seed
     if (err) {
         int64_t blocks = ((int64_t)sd->cap_hits + TPC_BLOCK - 1) / TPC_BLOCK;
         blocks = blocks < 1 ? 1 : (blocks > 8192 ? 8192 : blocks);
-        hipLaunchKernelGGL(gather_err, dim3((unsigned)blocks), dim3(TPC_BLOCK), 0, st, sd->n_seeds, sd->cap_seeds,
-                           sd->offsets, sd->cap_hits, sd->hits, reinterpret_cast<const float2 *>(err),
-                           fr->n_clusters, herr);
+        hipLaunchKernelGGL(gather_err, dim3((unsigned)blocks), dim3(TPC_BLOCK), 0, st, sd->cap_hits, sd->hits,
+                           reinterpret_cast<const float2 *>(err), fr->n_clusters, herr);
         A.err = herr;
     }
     if (sd->hit_yz) {

@@ -118,10 +118,15 @@ adj_partial(const int32_t *__restrict__ n_seeds, int32_t cap_seeds,
     }
     for (int r = lane; r < n_rows; r += TPC_WAVE) sum[wid][r] = make_float2(0.f, 0.f);
     // (a plain read, add and write: the wavefront is the only one, and its lanes
-    // have different rows; an LDS atomic took longer)
-    auto add = [&](int r, const float2 &v) {
-        const float2 a = sum[wid][r];
-        sum[wid][r] = make_float2(a.x + v.x, a.y + v.y);
+    // have different rows; an LDS atomic took longer.  The next seed's lanes
+    // add to rows that others of this one's have written: the fence keeps the
+    // compiler, as the hardware does, from taking them out of order.)
+    auto add = [&](bool act, int r, const float2 &v) {
+        if (act) {
+            const float2 a = sum[wid][r];
+            sum[wid][r] = make_float2(a.x + v.x, a.y + v.y);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
     __syncthreads();
     const int hi = range[1];
@@ -147,7 +152,7 @@ adj_partial(const int32_t *__restrict__ n_seeds, int32_t cap_seeds,
 #pragma unroll
             for (int u = 0; u < TPC_ADJ_AHEAD; ++u) {
                 const int n = __builtin_amdgcn_readlane(sn, q + u), r = __builtin_amdgcn_readlane(sr, q + u) + lane;
-                if (lane < n) add(r, v[u]);
+                add(lane < n, r, v[u]);
             }
             if (longest <= TPC_WAVE) continue;
             for (int k = lane + TPC_WAVE; k - lane < longest; k += TPC_WAVE) {
@@ -159,7 +164,7 @@ adj_partial(const int32_t *__restrict__ n_seeds, int32_t cap_seeds,
 #pragma unroll
                 for (int u = 0; u < TPC_ADJ_AHEAD; ++u) {
                     const int n = __builtin_amdgcn_readlane(sn, q + u), r = __builtin_amdgcn_readlane(sr, q + u) + k;
-                    if (k < n) add(r, v[u]);
+                    add(k < n, r, v[u]);
                 }
             }
         }

@@ -100,7 +100,7 @@ __device__ inline int lower_bound_key(const int32_t *frame, const int32_t *secto
 // for 645 000 seeds.)
 #define TPC_ADJ_AHEAD 8
 __global__ void __launch_bounds__(TPC_BLOCK)
-adj_partial(const int32_t *__restrict__ n_seeds, int32_t cap_seeds,
+adj_partial(const int32_t *__restrict__ n_seeds, int32_t cap_seeds, int32_t cap_hits,
             const int32_t *__restrict__ offsets, const int32_t *__restrict__ first_row,
             const int32_t *__restrict__ frame, const int32_t *__restrict__ sector,
             int32_t n_sectors, int32_t n_rows, const float2 *__restrict__ g,
@@ -137,8 +137,12 @@ adj_partial(const int32_t *__restrict__ n_seeds, int32_t cap_seeds,
             so = offsets[i];
             sn = offsets[i + 1] - so;
             sr = first_row[i];
-            // seeds that fail the fit's sanity checks were never written
-            if (!(sn >= 3 && sr >= 0 && sr + sn <= n_rows && so >= 0)) sn = 0;
+            // seeds that fail the fit's sanity checks (seed_view) were never
+            // written: those of a list that exceeded its hit capacity may
+            // even end beyond g
+            const bool sane = sn >= 3 && sr >= 0 && sr + sn <= n_rows && so >= 0 && so <= cap_hits - sn &&
+                              (uint32_t)sector[i] < (uint32_t)n_sectors;
+            if (!sane) sn = 0;
         }
         for (int q = 0; q < TPC_WAVE; q += TPC_ADJ_AHEAD) {
             float2 v[TPC_ADJ_AHEAD];
@@ -259,7 +263,7 @@ hipError_t launch_adjoint(const tpc_context *ctx, const tpc_frames *fr, const tp
     hipLaunchKernelGGL(adj_tracks, dim3(blocks), dim3(TPC_BLOCK), 0, st, A);
     const int groups = adj_groups(n_fs);
     hipLaunchKernelGGL(adj_partial, dim3((unsigned)n_fs, groups), dim3(TPC_BLOCK), 0, st,
-                       sd->n_seeds, sd->cap_seeds, sd->offsets, sd->first_row, sd->frame,
+                       sd->n_seeds, sd->cap_seeds, sd->cap_hits, sd->offsets, sd->first_row, sd->frame,
                        sd->sector, c.n_sectors, c.n_rows, A.g, partial);
     const int nout = c.n_sectors * c.n_rows;
     hipLaunchKernelGGL(adj_final, dim3((nout + TPC_BLOCK - 1) / TPC_BLOCK), dim3(TPC_BLOCK), 0, st,

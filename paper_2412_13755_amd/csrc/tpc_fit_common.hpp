@@ -263,7 +263,7 @@ __device__ inline void adj_one(const FitArgs &F, const int32_t *status, const do
             double my, mz;
             meas(k, my, mz);
             StepJac J;
-            helix_step(p, plane(k) - plane(k + 1), F.kbz, 2.0f, J);
+            helix_step<double, float, 5>(p, plane(k) - plane(k + 1), F.kbz, 2.0f, J);
             sym_transport<double, false>(C, J);
             kalman_update<double>(p, C, my, mz, F.vy, F.vz);
         };

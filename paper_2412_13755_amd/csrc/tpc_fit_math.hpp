@@ -42,10 +42,10 @@ struct StepTrig {
 
 // Reciprocal and square root of positive, finite, normal doubles for the
 // filter's inner loop.  On the device: the hardware estimates refined by
-// Newton-Raphson (reciprocal, two steps) and by one coupled Goldschmidt step
-// plus one Newton correction (square root); relative error far below the
-// 1e-12 the filter needs, but not correctly rounded.  On the host: the
-// library operations.
+// Newton-Raphson (reciprocal, two steps) and by one step of third order (the
+// inverse square root) with a Newton correction of the root; within a few
+// units of rounding, but not correctly rounded.  On the host: the library
+// operations.
 __host__ __device__ inline double recip_pos(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
     double r = __builtin_amdgcn_rcp(x);
@@ -58,18 +58,15 @@ __host__ __device__ inline double recip_pos(double x) {
 #endif
 }
 
-// sqrt(x), and 1/sqrt(x) in *inv (the latter to about 1e-13 relative).
+// sqrt(x), and 1/sqrt(x) in *inv.
 __host__ __device__ inline double sqrt_pos(double x, double *inv) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y, h = 0.5 * y;
-    const double r = fma(-g, h, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-    const double d = fma(-g, g, x);
-    g = fma(d, h, g);
-    if (inv) *inv = h + h;
-    return g;
+    const double y0 = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y0), y0, 1.0);
+    const double y = fma(y0 * e, fma(e, 0.375, 0.5), y0);
+    const double g = x * y, d = fma(-g, g, x);
+    if (inv) *inv = y;
+    return fma(d, 0.5 * y, g);
 #else
     const double g = sqrt(x);
     if (inv) *inv = 1.0 / g;
@@ -77,28 +74,56 @@ __host__ __device__ inline double sqrt_pos(double x, double *inv) {
 #endif
 }
 
-// asin(u)/u away from 0 (|u| >= 0.05: a step that turns the track by more
-// than ~6 degrees): asin(u) = 2 asin(u / sqrt(2 (1 + sqrt(1 - u^2)))) until
-// the series holds (five times at most; NaN beyond 1).  Rarely taken; a call
-// of the library's asin made every fit keep what lives across it in the
-// registers that calls leave alone.
+// asin(u)/u = sum of a_k x^k, x = u^2, to x^N: the sum (g) and its derivative
+// in x (d), so that the derivative in u is 2 u d.  What is left out is below
+// 1e-17 and 7e-14 of them for N = 5, |u| < 0.05 (and below rounding at 0.025),
+// below 1e-17 and 1e-16 for N = 10, |u| < 0.15.
+// (e: half the second derivative, to x^(N - 2), if asked for.)
+template <int N, class R>
+__host__ __device__ inline void asin_series(R x, R &g, R &d, R *e = nullptr) {
+    constexpr R a[14] = {1.0, 1.0 / 6, 3.0 / 40, 5.0 / 112, 35.0 / 1152, 63.0 / 2816, 231.0 / 13312, 143.0 / 10240,
+                         6435.0 / 557056, 12155.0 / 1245184, 46189.0 / 5505024, 88179.0 / 12058624,
+                         676039.0 / 104857600, 1300075.0 / 226492416};
+    static_assert(N < 14, "coefficients");
+    d = a[N];
+    g = fma(a[N], x, a[N - 1]);
+    if (e) *e = (R)0;
+#pragma unroll
+    for (int k = N - 2; k >= 0; --k) {
+        if (e) *e = k == N - 2 ? d : fma(*e, x, d);
+        d = fma(d, x, g);
+        g = fma(g, x, a[k]);
+    }
+}
+
+// asin(u)/u for |u| >= 0.05: asin(u) = 2 asin(u / sqrt(2 (1 + sqrt(1 - u^2))))
+// until the series to u^2N holds (N = 13: below 0.25, three times at most; N =
+// 5: below 0.05, five times; NaN beyond 1).  Rarely taken; a call of the
+// library's asin made every fit keep what lives across it in the registers
+// that calls leave alone.
+template <int N = 13>
 __host__ __device__ inline double asin_over_far(double u) {
+    static_assert(N == 13 || N == 5, "where the series holds");
     double v = u, k = 1.0;
-    while (fabs(v) >= 0.05) {
-        v = v / sqrt(2.0 + 2.0 * sqrt((1.0 - v) * (1.0 + v)));
+    while (fabs(v) >= (N == 13 ? 0.25 : 0.05)) {
+        double h;
+        sqrt_pos(2.0 + 2.0 * sqrt_pos((1.0 - v) * (1.0 + v), nullptr), &h);
+        v *= h;
         k += k;
     }
-    const double v2 = v * v;
-    return k * v * (1.0 + v2 * (1.0 / 6 + v2 * (3.0 / 40 + v2 * (5.0 / 112 + v2 * (35.0 / 1152))))) / u;
+    double g, d;
+    asin_series<N>(v * v, g, d);
+    return k * v * g / u;
 }
-// asin(u)/u in the state precision (Taylor series to u^8 near 0)
-template <class R>
+// asin(u)/u in the state precision
+template <int N = 13, class R>
 __host__ __device__ inline R asin_over_r(R u) {
     if (fabs(u) < (R)0.05) {
-        const R u2 = u * u;
-        return (R)1 + u2 * ((R)1 / 6 + u2 * ((R)3 / 40 + u2 * ((R)5 / 112 + u2 * ((R)35 / 1152))));
+        R g, d;
+        asin_series<5>(u * u, g, d);
+        return g;
     }
-    return (R)asin_over_far((double)u);
+    return (R)asin_over_far<N>((double)u);
 }
 
 // Exact helix step from x to x + dx, state and Jacobian in precision R
@@ -121,8 +146,12 @@ __host__ __device__ inline R asin_over_r(R u) {
 //   darc/dkappa = dx s dT/dkappa / cos delta + (dx B)^2 g'(v),
 // g = asin(v)/v, 1/cos delta = g + v g'.  Turns of |v| >= 0.05 (and beyond 90
 // degrees, where v falls again) take the half angle u = sin(delta/2) =
-// kappa chord/2 and darc/dkappa = (dx/c' - arc)/kappa.
-template <class R, class K = float>
+// kappa chord/2: arc = chord g(u), darc/dkappa = dx^2 T/((c + c') c') +
+// chord^2 g'(u)/2, with 1/cos(delta/2) = chord/(dx B) in g'.  (A track's
+// outermost steps may turn by 0.2, where it runs along the pad row: a series
+// to u^20, short, as a wavefront takes it when one of its tracks does.  MID =
+// 5 where its coefficients would take registers that are not there.)
+template <class R, class K = float, int MID = 10>
 __host__ __device__ inline bool helix_step(R p[5], K dx, K kbz, float max_sin, StepJac &J,
                                            StepTrig<R> *trig = nullptr) {
     // kbz = -c Bz, so kappa = kbz * w
@@ -144,15 +173,24 @@ __host__ __device__ inline bool helix_step(R p[5], K dx, K kbz, float max_sin, S
     // (a turn of 90 degrees or more changes s by at least 1)
     if (fabs(v) < (R)0.05 && fabs(kd) < (R)1) {
         const R v2 = v * v;
-        const R g = (R)1 + v2 * ((R)1 / 6 + v2 * ((R)3 / 40 + v2 * ((R)5 / 112 + v2 * ((R)35 / 1152))));
-        const R gd = v * ((R)1 / 3 + v2 * ((R)3 / 10 + v2 * ((R)15 / 56 + v2 * ((R)35 / 144))));
+        R g, h;
+        asin_series<5>(v2, g, h);
+        h += h;
         arc = dB * g;
-        dark = d * s * dTk * (g + v * gd) + dB * dB * gd;
+        dark = d * s * dTk * fma(v2, h, g) + dB * dB * (v * h);
     } else {
-        const R chord = fabs(d) * sqrt((R)1 + T * T);
+        const R chord = d * sqrt_pos(fma(T, T, (R)1), nullptr);   // signed
         const R u = (R)0.5 * kap * chord;
-        arc = (d >= (R)0 ? chord : -chord) * asin_over_r(u);
-        dark = (d * ic2 - arc) / kap;
+        dark = (d * iden) * (d * ic2) * T;
+        R g, h;
+        if (fabs(u) < (R)(MID == 10 ? 0.15 : 0.05)) {
+            asin_series<MID>(u * u, g, h);
+            dark = fma(chord * chord, u * h, dark);
+        } else {
+            g = asin_over_far<MID == 10 ? 13 : 5>(u);
+            dark += chord * (chord / dB - g) / kap;
+        }
+        arc = chord * g;
     }
     if (trig) *trig = StepTrig<R>{ic1, ic2, T, iden};
     J.f02 = dB * cc;
@@ -381,9 +419,9 @@ __host__ __device__ inline void helix_jac_adjoint(const R p[5], K dx, K kbz, R a
     R ak, akk;
     if (fabs(v) < (R)0.05 && fabs(kd) < (R)1) {
         const R v2 = v * v;
-        const R g = (R)1 + v2 * ((R)1 / 6 + v2 * ((R)3 / 40 + v2 * ((R)5 / 112 + v2 * ((R)35 / 1152))));
-        const R gd = v * ((R)1 / 3 + v2 * ((R)3 / 10 + v2 * ((R)15 / 56 + v2 * ((R)35 / 144))));
-        const R gdd = (R)1 / 3 + v2 * ((R)9 / 10 + v2 * ((R)75 / 56 + v2 * ((R)245 / 144)));
+        R g, h, hh;
+        asin_series<5>(v2, g, h, &hh);
+        const R gd = (R)2 * v * h, gdd = (R)2 * h + (R)8 * v2 * hh;
         const R Bk = d * s * Tk, Bkk = d * s * Tkk;     // of dB
         const R vk = dB + kap * Bk, vkk = (R)2 * Bk + kap * Bkk;
         ak = Bk * g + dB * gd * vk;
@@ -418,7 +456,7 @@ __host__ __device__ inline void step_adjoint(const R pb[5], const SymT<R> &Cb, f
     R pp[5] = {pb[0], pb[1], pb[2], pb[3], pb[4]};
     StepJac J;
     StepTrig<R> trig;
-    helix_step(pp, dx, kbz, 2.0f, J, &trig);
+    helix_step<R, float, 5>(pp, dx, kbz, 2.0f, J, &trig);
     SymT<R> Pb = Cbar;
     R q0, q1;
     {
@@ -534,7 +572,7 @@ __host__ __device__ inline void start_adjoint(R xa, R ya, R za, R xb, R yb, R xc
     const R kap = (R)2 * cross / prod;
     const R ua = (R)0.5 * kap * lab, uc = (R)0.5 * kap * lac;
     const R ca = sqrt(((R)1 - ua) * ((R)1 + ua));       // of half the turning angle, as in helix_start
-    const R guc = asin_over_r(uc);
+    const R guc = asin_over_r<5>(uc);
     const R D = lac * guc;
     const R t = (za - zc) / D;
     const R bphi = pbar[2] * (abx * ca - aby * ua) / lab;

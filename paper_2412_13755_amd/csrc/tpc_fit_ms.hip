@@ -132,7 +132,6 @@ __device__ inline bool eloss_map(const MsArgs &A, const double p[5], const Segme
     double iP1;
     const double P1 = sqrt_pos(fma(E1, E1, -A.mass2), &iP1);
     if (fabs(P1 - g.P) > 0.01 * g.P) return false;
-    iP1 = fma(iP1, fma(-P1, iP1, 1.0), iP1);                     // 1/P' to rounding, as it scales w
     const double q = g.P * iP1, e = E1 * g.iE;
     wo = w * q;
     j44 = q * q * q * e;

@@ -980,6 +980,20 @@ __device__ __forceinline__ void nb_dense_seg(int seg, const int32_t *__restrict_
 // together: one cell grid, one cell order, so that a cluster's window is one
 // set of cells.
 #define TPC_MIX_WORDS 32      // words of 64 pairs taken in a round
+
+// Are windows of the nt clusters of a row pair of extents ry, rz searched by
+// boxes of the cuts (mix_wave), in cells made for that?  Where more than most
+// overflow the lists (clusters spread evenly) and a box is far smaller than a
+// window.  Event of 10^4 tracks, windows of 10 cm (20 clusters): 0.83 -> 0.58
+// ms, of 40 cm 18 -> 1.7 ms; with cuts of half the window the boxes lose
+// (0.99 -> 1.15 ms).
+__device__ inline bool mix_boxes(int nt, float ry, float rz, int list, float win_y, float win_z, float cut_y,
+                                 float cut_z) {
+    const float a = fmaxf(ry, win_y), b = fmaxf(rz, win_z);
+    return (float)nt * fminf(a, 2.0f * win_y) * fminf(b, 2.0f * win_z) > 1.5f * (float)list * a * b &&
+           fminf(win_y, cut_y) * fminf(win_z, cut_z) < 0.125f * win_y * win_z;
+}
+
 template <int N, int CELLS, int LIST_>
 struct MixLdsT {
     static constexpr int LIST = LIST_;
@@ -1008,7 +1022,8 @@ __device__ inline void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "
 // no result, so its divisions are hardware reciprocals.
 template <int N, int CELLS, int LIST>
 __device__ inline SegGrid mix_bin(const float *__restrict__ y, const float *__restrict__ z, int ra0, int n0, int ra1,
-                                  int nt, float win_y, float win_z, MixLdsT<N, CELLS, LIST> &L) {
+                                  int nt, float win_y, float win_z, float cut_y, float cut_z,
+                                  MixLdsT<N, CELLS, LIST> &L) {
 #pragma clang fp contract(off)
     constexpr int PT = (N + TPC_BLOCK - 1) / TPC_BLOCK;
     constexpr int Q = CELLS / (4 * TPC_BLOCK);      // groups of four cells per thread
@@ -1063,12 +1078,21 @@ __device__ inline SegGrid mix_bin(const float *__restrict__ y, const float *__re
     }
     auto back = [](int o) { return __int_as_float(o ^ ((o >> 31) & 0x7FFFFFFF)); };
     const float ymin = back(e[0]), ymax = back(~e[1]), zmin = back(e[2]), zmax = back(~e[3]);
-    // up to four cells per cluster of the larger row, edges of at least the window
+    // up to four cells per cluster of the larger row, edges of at least the
+    // window
     const int nm = n0 > nt - n0 ? n0 : nt - n0;
     const int cap = 4 * nm < CELLS - 2 ? 4 * nm : CELLS - 2;
     const float fc = (float)cap, ry = ymax - ymin, rz = zmax - zmin;
-    const float fz = rz * (0.99f * __builtin_amdgcn_rcpf(win_z)), fy = ry * (0.99f * __builtin_amdgcn_rcpf(win_y));
-    const int nz = fz >= fc ? cap : (fz >= 1.0f ? (int)fz : 1);
+    float fz = rz * (0.99f * __builtin_amdgcn_rcpf(win_z)), fy = ry * (0.99f * __builtin_amdgcn_rcpf(win_y));
+    float fcz = fc;
+    if (mix_boxes(nt, ry, rz, LIST, win_y, win_z, cut_y, cut_z)) {
+        // most windows are searched by boxes: edges of at least the smaller of
+        // window and cut, as many in y as windows and the rest in z
+        fcz = fc * __builtin_amdgcn_rcpf(fmaxf(1.0f, fminf(fy, fc)));
+        fz = rz * (0.99f * __builtin_amdgcn_rcpf(fminf(win_z, cut_z)));
+        fy = ry * (0.99f * __builtin_amdgcn_rcpf(fminf(win_y, cut_y)));
+    }
+    const int nz = fz >= fcz ? max((int)fcz, 1) : (fz >= 1.0f ? (int)fz : 1);
     int ny = (int)(fc * __builtin_amdgcn_rcpf((float)nz));
     if (ny * nz > cap) --ny;
     ny = fy >= (float)ny ? ny : (fy >= 1.0f ? (int)fy : 1);
@@ -1140,56 +1164,90 @@ __device__ inline unsigned long long mix_key(float yh, float zh, int ku, int kd,
 }
 
 // Best pair of cluster (yh, zh) by a whole wavefront, into *best (its key so
-// far, an LDS word): the clusters in its window (`in_window` of them) are
-// compacted into the wavefront's part of the lists, and their pairs taken 64
-// at a time.  A window of more than the lists hold is taken in four parts,
-// by halves of either row's ids.
+// far, an LDS word), nd down and nu up clusters being in its window: these
+// are compacted into the wavefront's part of the lists, and their pairs
+// taken 64 at a time.  Beyond TPC_MIX_PAIRS pairs only the up clusters are
+// listed, and each lane takes one at a time and searches the cells of the box
+// around the prediction 2h - u, whose half-widths shrink from the cuts to the
+// best pair's distance (slab_search has the reasons): where windows hold
+// hundreds, mix_bin's cells are as small as the cuts, and a box holds a few.
+// (Windows of 80 cm, event of 10^4 tracks: all pairs 43 ms.)
+#define TPC_MIX_PAIRS 1024
 template <class LDS>
-__device__ inline void mix_wave(float yh, float zh, int n0, int in_window, const SegGrid &g, LDS &L, float win_y,
+__device__ inline void mix_wave(float yh, float zh, int n0, int nd, int nu, const SegGrid &g, LDS &L, float win_y,
                                 float win_z, float cut_y, float cut_z, float my, float mz, unsigned long long *best) {
 #pragma clang fp contract(off)
-    constexpr int CAP = LDS::LIST * TPC_WAVE, HALF = TPC_LDS_ROW / 2;
-    static_assert(2 * HALF <= CAP, "half of either row fits");
+    constexpr int CAP = LDS::LIST * TPC_WAVE;
+    static_assert(TPC_LDS_ROW <= CAP, "the up clusters of a window fit");
     const int lane = threadIdx.x & (TPC_WAVE - 1), base = threadIdx.x - lane;
     auto at = [&](int e) -> uint16_t & { return L.u.list[e / TPC_WAVE][base + e % TPC_WAVE]; };
     const int y0 = cell_coord(yh - (win_y + my), g.y0, g.iwy, g.ny);
     const int y1 = cell_coord(yh + (win_y + my), g.y0, g.iwy, g.ny);
     const int z0 = cell_coord(zh - (win_z + mz), g.z0, g.iwz, g.nz);
     const int z1 = cell_coord(zh + (win_z + mz), g.z0, g.iwz, g.nz);
-    const bool parts = in_window > CAP;
+    const bool fine = fmaxf(win_y * g.iwy, win_z * g.iwz) > 1.5f;      // made for boxes
+    const bool all = nd + nu <= CAP && (!fine || nd * nu <= TPC_MIX_PAIRS);
     unsigned long long b = ~0ull;
-    for (int part = 0; part < (parts ? 4 : 1); ++part) {
-        const int d0 = (part & 1) * HALF, d1 = parts ? d0 + HALF : n0;
-        const int u0 = n0 + (part >> 1) * HALF, u1 = parts ? u0 + HALF : 65536;
-        int nd = 0, nu = 0;
-        for (int iy = y0; iy <= y1; ++iy) {
-            const int e = L.cs[iy * g.nz + z1 + 1];
-            for (int k0 = L.cs[iy * g.nz + z0]; k0 < e; k0 += TPC_WAVE) {
-                const int k = k0 + lane;
-                bool down = false, upper = false;
-                if (k < e) {
-                    const bool in = fabsf(L.p[k].x - yh) <= win_y && fabsf(L.p[k].y - zh) <= win_z;
-                    const int id = L.id[k];
-                    down = in && id < n0 && id >= d0 && id < d1;
-                    upper = in && id >= u0 && id < u1;
-                }
-                const uint64_t bd = __ballot(down), bu = __ballot(upper);
-                if (down) at(nd + lanes_below(bd)) = (uint16_t)k;
-                if (upper) at(CAP - 1 - nu - lanes_below(bu)) = (uint16_t)k;
-                nd += __popcll(bd);
-                nu += __popcll(bu);
+    if (nd == 0 || nu == 0) return;
+    int id0 = 0, iu0 = 0;                            // listed so far
+    for (int iy = y0; iy <= y1; ++iy) {
+        const int e = L.cs[iy * g.nz + z1 + 1];
+        for (int k0 = L.cs[iy * g.nz + z0]; k0 < e; k0 += TPC_WAVE) {
+            const int k = k0 + lane;
+            bool down = false, upper = false;
+            if (k < e) {
+                const bool in = fabsf(L.p[k].x - yh) <= win_y && fabsf(L.p[k].y - zh) <= win_z;
+                const int id = L.id[k];
+                down = all && in && id < n0;
+                upper = in && id >= n0;
             }
+            const uint64_t bd = __ballot(down), bu = __ballot(upper);
+            if (down) at(id0 + lanes_below(bd)) = (uint16_t)k;
+            if (upper) at(CAP - 1 - iu0 - lanes_below(bu)) = (uint16_t)k;
+            id0 += __popcll(bd);
+            iu0 += __popcll(bu);
         }
-        wave_fence();
+    }
+    wave_fence();
+    if (all) {
         const float inv = __builtin_amdgcn_rcpf((float)nd);
         for (int t = lane; t < nd * nu; t += TPC_WAVE) {
-            // t / nd: fewer than 2^20 pairs, so the error of the product is
-            // far below the 0.5 / nd to the next integer
+            // t / nd: the error of the product is far below the 0.5 / nd to
+            // the next integer
             const int iu = (int)(((float)t + 0.5f) * inv);
             const unsigned long long key = mix_key(yh, zh, at(CAP - 1 - iu), at(t - iu * nd), L, cut_y, cut_z);
             b = key < b ? key : b;
         }
-        wave_fence();
+    } else {
+        float r = INFINITY;                          // no better pair is further off in y or z
+        for (int t0 = 0; t0 < nu; t0 += TPC_WAVE) {
+            if (t0 + lane < nu) {
+                const int ku = at(CAP - 1 - (t0 + lane));
+                const float2 u = L.p[ku];
+                const uint32_t up = (uint32_t)L.id[ku] << 16;
+                const float ay = u.x - yh, az = u.y - zh;
+                const float cy = yh - ay, cz = zh - az, ky = fminf(cut_y, r) + my, kz = fminf(cut_z, r) + mz;
+                const int yd1 = cell_coord(cy + ky, g.y0, g.iwy, g.ny), zd1 = cell_coord(cz + kz, g.z0, g.iwz, g.nz);
+                const int zd0 = cell_coord(cz - kz, g.z0, g.iwz, g.nz);
+                for (int iy = cell_coord(cy - ky, g.y0, g.iwy, g.ny); iy <= yd1; ++iy) {
+                    const int e = L.cs[iy * g.nz + zd1 + 1];
+                    for (int k = L.cs[iy * g.nz + zd0]; k < e; ++k) {
+                        const float2 d = L.p[k];
+                        const uint32_t id = L.id[k];
+                        const float by = yh - d.x, bz = zh - d.y;
+                        const float dy = ay - by, dz = az - bz;
+                        const float qy = dy * dy, qz = dz * dz;
+                        const float q = qy + qz;
+                        const unsigned long long key = ((unsigned long long)__float_as_uint(q) << 32) | (up | id);
+                        const bool win = (int)((int)id < n0) & (int)(fabsf(by) <= win_y) & (int)(fabsf(bz) <= win_z) &
+                                         (int)(fabsf(dy) <= cut_y) & (int)(fabsf(dz) <= cut_z) & (int)(key < b);
+                        b = win ? key : b;
+                    }
+                }
+            }
+            const int q = __builtin_amdgcn_readlane(lane63_min(b == ~0ull ? 0x7F800000 : (int)(b >> 32)), TPC_WAVE - 1);
+            r = __builtin_amdgcn_sqrtf(__int_as_float(q)) * 1.0001f;
+        }
     }
     if (b != ~0ull) atomicMin(best, b);
     wave_fence();
@@ -1226,7 +1284,7 @@ __device__ __forceinline__ void mix_query_seg(int seg, const int32_t *__restrict
         yh = y[a + tid];
         zh = z[a + tid];
     }
-    const SegGrid g = mix_bin(y, z, ra0, n0, b, nt, win_y, win_z, L);
+    const SegGrid g = mix_bin(y, z, ra0, n0, b, nt, win_y, win_z, cut_y, cut_z, L);
     for (int i0 = a + wid * TPC_WAVE; i0 < b; i0 += TPC_BLOCK) {
         const int i = i0 + lane;
         if (i0 >= a + TPC_BLOCK && i < b) {
@@ -1322,8 +1380,8 @@ __device__ __forceinline__ void mix_query_seg(int seg, const int32_t *__restrict
         for (uint64_t over = __ballot(!listed); over != 0; over &= over - 1) {
             const int l = __builtin_ctzll(over);
             auto of = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
-            mix_wave(of(yh), of(zh), n0, __builtin_amdgcn_readlane(nd + nu, l), g, L, win_y, win_z, cut_y, cut_z,
-                     of(my), of(mz), &L.best[tid - lane + l]);
+            mix_wave(of(yh), of(zh), n0, __builtin_amdgcn_readlane(nd, l), __builtin_amdgcn_readlane(nu, l), g, L, win_y,
+                     win_z, cut_y, cut_z, of(my), of(mz), &L.best[tid - lane + l]);
         }
         if (i < b) {
             const unsigned long long best = L.best[tid];

@@ -29,7 +29,7 @@ nb_bin(const int32_t *__restrict__ off, int32_t NR, int32_t n_rows, const float 
 // frames have few or none of them (a launch less than nb_bin's own; they
 // come first because they run longest if there are any).
 template <int GROUP>
-__global__ void __launch_bounds__(TPC_BLOCK)
+__global__ void __launch_bounds__(TPC_BLOCK, 6)
 nb_query_small(const int32_t *__restrict__ off, int32_t NR, int32_t nb, int32_t n_rows, const float *__restrict__ y,
                const float *__restrict__ z, float win_y, float win_z, float cut_y, float cut_z, SegGrid *grid,
                int32_t *cstart, float *sy, float *sz, int32_t *sid, int32_t *up, int32_t *dn) {

@@ -90,22 +90,31 @@ __device__ inline void track_vals(bool kept, int m, int v[3]) {
 }
 
 // A workgroup counts CT_TILE tracks, a wavefront CT_TILE / 16 of them at once.
+// Beyond CT_COUNT_ALL tracks the rows of those that are not kept are not read
+// (most of them, where tracks are dense: 322 -> 133 us for 6.4 10^5); up to
+// there waiting for the status first costs more (300 tracks: 2 us).
 #define CT_COUNT_T 1024
+#define CT_COUNT_ALL 65536
 __global__ void __launch_bounds__(CT_COUNT_T) ct_count(CtArgs A) {
     constexpr int U = CT_TILE / (CT_COUNT_T / TPC_WAVE);
     __shared__ int cnt[CT_TILE];
     const int T = n_tracks(A);
-    const int lane = threadIdx.x & (TPC_WAVE - 1), wid = threadIdx.x / TPC_WAVE;
+    const int lane = threadIdx.x & (TPC_WAVE - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / TPC_WAVE);
     for (int t0 = blockIdx.x * CT_TILE; t0 < T; t0 += gridDim.x * CT_TILE) {
         int n[U] = {};
+        bool ok[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int t = t0 + wid * U + u;
+            ok[u] = t < T && (T <= CT_COUNT_ALL || A.status[t] == TPC_FIT_OK);
+        }
         for (int r = lane; r - lane < A.R; r += TPC_WAVE) {
             int c[U];
             bool own[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = t0 + wid * U + u;
-                c[u] = t < T && r < A.R ? A.rows[(size_t)t * A.R + r] : -1;
-            }
+            for (int u = 0; u < U; ++u)
+                c[u] = ok[u] && r < A.R ? A.rows[(size_t)(t0 + wid * U + u) * A.R + r] : -1;
 #pragma unroll
             for (int u = 0; u < U; ++u) own[u] = (uint32_t)c[u] < (uint32_t)A.N && A.own[c[u]] == t0 + wid * U + u;
 #pragma unroll
@@ -133,34 +142,60 @@ __global__ void __launch_bounds__(CT_COUNT_T) ct_count(CtArgs A) {
 }
 
 // Exclusive scans of the three counts: every workgroup sums the 64s' sums
-// before its tracks itself; the last one has the totals.
+// before its tracks itself, and takes CT_SPAN 64s (with four, 2.5 10^6 tracks
+// read 2.3 GB of sums); the last one has the totals.
+#define CT_SPAN 16
 __global__ void __launch_bounds__(TPC_BLOCK) ct_tapply(CtArgs A) {
-    __shared__ int sh[3][TPC_BLOCK / TPC_WAVE];
+    static_assert(CT_SPAN <= TPC_WAVE, "a lane per 64 tracks");
+    constexpr int W = TPC_BLOCK / TPC_WAVE;
+    __shared__ int sh[3][W];
     const int T = n_tracks(A);
-    const int t = blockIdx.x * TPC_BLOCK + threadIdx.x;
-    if (blockIdx.x > 0 && (int)blockIdx.x * TPC_BLOCK >= T) return;
-    int base[3] = {0, 0, 0}, v[3], tot[3], ex[3];
-    const int nb = (int)blockIdx.x * (TPC_BLOCK / CT_TILE);
-    for (int b = threadIdx.x; b < nb; b += TPC_BLOCK)
+    const int lane = threadIdx.x & (TPC_WAVE - 1), wid = threadIdx.x / TPC_WAVE;
+    const int tiles = T > 0 ? (T + CT_TILE - 1) / CT_TILE : 0, b0 = blockIdx.x * CT_SPAN;
+    if (b0 > 0 && b0 >= tiles) return;
+    constexpr int Q = CT_SPAN / W;                   // 64s per wavefront
+    int before[3] = {0, 0, 0}, mine[3], own[3], v[Q][3];
+    for (int b = threadIdx.x; b < b0; b += TPC_BLOCK)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) base[k] += A.bsum[b * 3 + k];
-    track_vals(t < T && A.status[t] == TPC_FIT_OK, t < T ? A.m[t] : 0, v);
+        for (int k = 0; k < 3; ++k) before[k] += A.bsum[b * 3 + k];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int t = (b0 + wid + q * W) * CT_TILE + lane;
+        track_vals(t < T && A.status[t] == TPC_FIT_OK, t < T ? A.m[t] : 0, v[q]);
+    }
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        block_exclusive_scan(base[k], sh[k], &tot[k]);
-        base[k] = tot[k];
-        ex[k] = base[k] + block_exclusive_scan(v[k], sh[k], &tot[k]);
+        before[k] = __builtin_amdgcn_readlane(lane_scan(before[k]), TPC_WAVE - 1);
+        if (lane == 0) sh[k][wid] = before[k];
+        own[k] = lane < CT_SPAN && b0 + lane < tiles ? A.bsum[(b0 + lane) * 3 + k] : 0;
+        mine[k] = lane_scan(own[k]);                 // lane: the sums up to its 64's end
     }
-    if (t < T) {
-        A.kp[t] = ex[0];
-        A.dp[t] = ex[1];
-        A.rp[t] = ex[2];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        before[k] = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) before[k] += sh[k][w];
     }
-    if (threadIdx.x == 0 && (int)(blockIdx.x + 1) * TPC_BLOCK >= T) {
-        const int kept = base[0] + tot[0], steps = base[1] + tot[1], res = base[2] + tot[2];
-        A.kp[T] = kept;
-        A.dp[T] = steps;
-        A.rp[T] = res;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int t = (b0 + wid + q * W) * CT_TILE + lane;
+        int at[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            at[k] = before[k] + __shfl(mine[k] - own[k], wid + q * W, TPC_WAVE) + lane_scan(v[q][k]) - v[q][k];
+        if (t < T) {
+            A.kp[t] = at[0];
+            A.dp[t] = at[1];
+            A.rp[t] = at[2];
+        }
+    }
+    if (threadIdx.x == TPC_WAVE - 1 && b0 + CT_SPAN >= tiles) {
+        const int kept = before[0] + mine[0], steps = before[1] + mine[1], res = before[2] + mine[2];
+        const int e = T > 0 ? T : 0;
+        A.kp[e] = kept;
+        A.dp[e] = steps;
+        A.rp[e] = res;
         for (int k = 0; k < 9; ++k) A.out.counts[k] = kept;
         A.out.counts[9] = steps;
         A.out.counts[10] = res;
@@ -363,8 +398,8 @@ hipError_t launch_ctf_build(const tpc_context *ctx, const tpc_frames *fr, const 
     hipLaunchKernelGGL(ct_own_init, dim3(grid_for(A.N)), dim3(TPC_BLOCK), 0, st, A);
     hipLaunchKernelGGL(ct_own, dim3(grid_for(tiles * chunks * TPC_BLOCK)), dim3(TPC_BLOCK), 0, st, A);
     hipLaunchKernelGGL(ct_count, dim3(grid_for(tiles * TPC_BLOCK)), dim3(CT_COUNT_T), 0, st, A);
-    hipLaunchKernelGGL(ct_tapply, dim3(A.cap_seeds > 0 ? (A.cap_seeds + TPC_BLOCK - 1) / TPC_BLOCK : 1),
-                       dim3(TPC_BLOCK), 0, st, A);
+    hipLaunchKernelGGL(ct_tapply, dim3((unsigned)(tiles > 0 ? (tiles + CT_SPAN - 1) / CT_SPAN : 1)), dim3(TPC_BLOCK),
+                       0, st, A);
     hipLaunchKernelGGL(ct_free<false>, dim3(segs), dim3(TPC_BLOCK), 0, st, A);
     hipLaunchKernelGGL(ct_scan_segs, dim3(1), dim3(CT_SCAN_T), 0, st, A);
     hipLaunchKernelGGL(ct_free<true>, dim3(segs), dim3(TPC_BLOCK), 0, st, A);

@@ -3,7 +3,7 @@
 // fitted segment in each; carried to a common plane, their states agree
 // within their covariances.
 //
-//  mg_best         thread per segment: over the segments of the two
+//  mg_best         lanes share a segment: over the segments of the two
 //                  neighbouring sectors of its (frame, side) -- a contiguous
 //                  seed range each, found by binary search, since seeds are
 //                  ordered by first cluster and clusters by (frame, sector,
@@ -15,7 +15,7 @@
 //                  their covariance block is the sum of the two segments',
 //                  and a sub-vector's chi2 never exceeds the full one: such a
 //                  pair cannot pass); the survivors of each chunk of
-//                  64 candidates go to the lane's own LDS column and only
+//                  candidates go to the lane's own LDS column and only
 //                  they are transferred.  FP64 throughout.
 //  mg_link_next    next[a] = b when a's best outer partner b has a as its
 //                  best inner partner (else -1, chi2 0); optionally the pair
@@ -218,22 +218,23 @@ __device__ inline double pair_chi2(const MgArgs &A, int a, int b, double ca, dou
     return pair_fuse(A, a, b, ca, sa, lim, nullptr, nullptr);
 }
 
-// MG_SPLIT lanes of one wavefront share a segment and take every
-// MG_SPLIT-th candidate of each neighbouring sector (enough wavefronts for
-// the chip); their best partners are reduced by shuffles at the end
-// (smaller chi2, then smaller index: the serial order's choice).  Per chunk
-// of MG_CHUNK candidates, the ones that pass the tan(lambda) / q/pT test go
-// to the lane's own LDS column, so that the transfer runs over short lists
-// (a wavefront's iterations are the longest list of its lanes) instead of
-// every candidate of every lane.  The test's bound is the best chi2 that
-// any of the segment's lanes has found on the candidate's side (shared
-// after each chunk), or the cut: a pair whose (t, w) chi2 alone is above it
-// by more than rounding (TPC_MG_SLACK) can neither be nor tie the best.
-// (Four lanes per segment and chunks of 64 left the SIMDs 1.1 wavefronts
-// each on an event of 2.6 10^4 segments: 575 us, 440 with these.)
-#define MG_SPLIT 16
-#define MG_CHUNK 256
-#define MG_LANE_CHUNK (MG_CHUNK / MG_SPLIT)
+// SPLIT lanes of one wavefront share a segment and take every SPLIT-th
+// candidate of each neighbouring sector (enough wavefronts for the chip);
+// their best partners are reduced by shuffles at the end (smaller chi2, then
+// smaller index: the serial order's choice).  Per chunk of MG_LANE_CHUNK
+// candidates a lane, the ones that pass the tan(lambda) / q/pT test go to the
+// lane's own LDS column, so that the transfer runs over short lists (a
+// wavefront's iterations are the longest list of its lanes) instead of every
+// candidate of every lane.  The test's bound is the best chi2 that any of the
+// segment's lanes has found on the candidate's side (shared after each
+// chunk), or the cut: a pair whose (t, w) chi2 alone is above it by more than
+// rounding (TPC_MG_SLACK) can neither be nor tie the best.
+// Sixteen lanes up to MG_MANY segments: four leave the SIMDs 1.1 wavefronts
+// each on an event of 2.7 10^4 (515 us, 408 with sixteen; 1.3 10^5: 9.2, 8.9
+// ms).  Beyond, four: fewer wavefronts share the bounds of more candidates
+// (6.4 10^5: 279 ms with sixteen, 204 with four).
+#define MG_MANY (1 << 18)
+#define MG_LANE_CHUNK 16
 
 // (chi, j) of another lane replaces this lane's best when smaller, or equal
 // with a smaller index
@@ -244,14 +245,14 @@ __device__ inline void best_merge(double &chi, int &j, double oc, int oj) {
     }
 }
 
-__global__ void __launch_bounds__(TPC_BLOCK) mg_best(MgArgs A) {
-    __shared__ int cand[MG_LANE_CHUNK][TPC_BLOCK];
-    const int T = mg_count(A);
-    const int sub = threadIdx.x % MG_SPLIT;
-    const int per_block = TPC_BLOCK / MG_SPLIT;
+template <int SPLIT>
+__device__ __forceinline__ void best_partners(const MgArgs &A, int T, int (*cand)[TPC_BLOCK]) {
+    constexpr int CHUNK = SPLIT * MG_LANE_CHUNK;
+    const int sub = threadIdx.x % SPLIT;
+    const int per_block = TPC_BLOCK / SPLIT;
     // whole workgroups step together: every lane reaches the shuffles
     for (int base = blockIdx.x * per_block; base < T; base += gridDim.x * per_block) {
-        const int i = base + threadIdx.x / MG_SPLIT;
+        const int i = base + threadIdx.x / SPLIT;
         int bo = -1, bi = -1;
         double co = INFINITY, ci_ = INFINITY;         // this lane's best
         double lo = A.cut, li = A.cut;                // the segment's, at most the cut
@@ -271,10 +272,10 @@ __global__ void __launch_bounds__(TPC_BLOCK) mg_best(MgArgs A) {
                 const double cda = cos(da), sda = sin(da);
                 const double dback = turn_angle(sn, sec, A.n_sectors);
                 const double cdb = cos(dback), sdb = sin(dback);
-                for (int c0 = j0; c0 < j1; c0 += MG_CHUNK) {
-                    const int c1 = c0 + MG_CHUNK < j1 ? c0 + MG_CHUNK : j1;
+                for (int c0 = j0; c0 < j1; c0 += CHUNK) {
+                    const int c1 = c0 + CHUNK < j1 ? c0 + CHUNK : j1;
                     int n = 0;
-                    for (int j = c0 + sub; j < c1; j += MG_SPLIT) {
+                    for (int j = c0 + sub; j < c1; j += SPLIT) {
                         if (A.status[j] != 0) continue;
                         const float *pj = A.par + (size_t)j * 5, *cj = A.cov + (size_t)j * 15;
                         // the (t, w) block of the pair's covariance is the sum of the
@@ -313,7 +314,7 @@ __global__ void __launch_bounds__(TPC_BLOCK) mg_best(MgArgs A) {
                     lo = fmin(lo, co);
                     li = fmin(li, ci_);
 #pragma unroll
-                    for (int d = 1; d < MG_SPLIT; d <<= 1) {
+                    for (int d = 1; d < SPLIT; d <<= 1) {
                         lo = fmin(lo, __shfl_xor(lo, d, TPC_WAVE));
                         li = fmin(li, __shfl_xor(li, d, TPC_WAVE));
                     }
@@ -321,7 +322,7 @@ __global__ void __launch_bounds__(TPC_BLOCK) mg_best(MgArgs A) {
             }
         }
 #pragma unroll
-        for (int d = 1; d < MG_SPLIT; d <<= 1) {
+        for (int d = 1; d < SPLIT; d <<= 1) {
             best_merge(co, bo, __shfl_xor(co, d, TPC_WAVE), __shfl_xor(bo, d, TPC_WAVE));
             best_merge(ci_, bi, __shfl_xor(ci_, d, TPC_WAVE), __shfl_xor(bi, d, TPC_WAVE));
         }
@@ -331,6 +332,13 @@ __global__ void __launch_bounds__(TPC_BLOCK) mg_best(MgArgs A) {
             A.prev[i] = bi;
         }
     }
+}
+
+__global__ void __launch_bounds__(TPC_BLOCK) mg_best(MgArgs A) {
+    __shared__ int cand[MG_LANE_CHUNK][TPC_BLOCK];
+    const int T = mg_count(A);
+    if (T <= MG_MANY) best_partners<16>(A, T, cand);
+    else best_partners<4>(A, T, cand);
 }
 
 __global__ void __launch_bounds__(TPC_BLOCK) mg_link_next(MgArgs A) {
@@ -620,7 +628,7 @@ hipError_t launch_merge(const tpc_context *ctx, const tpc_seeds *sd, const tpc_t
     A.leg_chi2 = leg_chi2;
     int g = (sd->cap_seeds + TPC_BLOCK - 1) / TPC_BLOCK;
     g = g < 1 ? 1 : (g > 4096 ? 4096 : g);
-    int gm = (int)(((int64_t)sd->cap_seeds * MG_SPLIT + TPC_BLOCK - 1) / TPC_BLOCK);
+    int gm = (int)(((int64_t)sd->cap_seeds * 16 + TPC_BLOCK - 1) / TPC_BLOCK);
     gm = gm < 1 ? 1 : (gm > 8192 ? 8192 : gm);
     hipLaunchKernelGGL(mg_best, dim3(gm), dim3(TPC_BLOCK), 0, st, A);
     hipLaunchKernelGGL(mg_link_next, dim3(g), dim3(TPC_BLOCK), 0, st, A);

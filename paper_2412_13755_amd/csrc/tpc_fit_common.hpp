@@ -246,9 +246,9 @@ __device__ inline void adj_one(const FitArgs &F, const int32_t *status, const do
         my = (double)raw.x;
         mz = (double)raw.y;
         if (F.map) {
-            const float2 f = reinterpret_cast<const float2 *>(F.map)[m0 + k];
-            my -= (double)f.x;
-            mz -= (double)f.y;
+            const float *f = F.map + 2 * (size_t)(m0 + k);      // (4-byte aligned)
+            my -= (double)f[0];
+            mz -= (double)f[1];
         }
     };
     auto plane = [&](int k) { return F.row_x[row0 + k]; };

@@ -70,3 +70,14 @@ def test_a_seed_of_no_sector(event):
     g, status = _gradient(reco, dfr, dataclasses.replace(full, sector=sector), mp)
     assert status[i] == 1 and np.isfinite(g).all()
     assert np.all(np.abs(g - ref) <= SUM_RTOL * np.abs(ref).max())
+
+
+def test_a_map_at_any_float(event):
+    import torch
+    reco, dfr, full, mp = event
+    ref, _ = _gradient(reco, dfr, full, mp)
+    odd = torch.empty(mp.numel() + 1, device="cuda:0")[1:].view(mp.shape)
+    odd.copy_(mp)
+    assert odd.data_ptr() % 8 == 4
+    g, _ = _gradient(reco, dfr, full, odd)
+    assert np.array_equal(g, ref)

@@ -393,7 +393,8 @@ __device__ __forceinline__ bool leg_circle(const MgArgs &A, int i, const double 
     const double y = (double)p[0], s = (double)p[2], t = (double)p[3], w = (double)p[4];
     const double k = A.kbz, kap = k * w;
     if (!(fabs(s) < 1.0) || !(fabs(kap) * LEG_MAX_RADIUS > 1.0)) return false;
-    const double *cs = ang[A.sector[i] % 18];
+    const int s18 = A.sector[i] % 18;
+    const double *cs = ang[s18 < 0 ? s18 + 18 : s18];          // (a seed list may hold anything)
     double ic;
     const double c = sqrt_pos(fma(-s, s, 1.0), &ic), ca = cs[0], sa = cs[1];
     const double ik = copysign(recip_pos(fabs(kap)), kap);

@@ -81,3 +81,21 @@ def test_a_map_at_any_float(event):
     assert odd.data_ptr() % 8 == 4
     g, _ = _gradient(reco, dfr, full, odd)
     assert np.array_equal(g, ref)
+
+
+def test_a_fitted_segment_of_no_sector(event):
+    # the first seed in a sector below the first: its legs are not looked for
+    # there, and the others' are theirs
+    import torch
+    reco, dfr, full, _ = event
+    T = int(full.n_seeds.item())
+    tracks = reco.fit(dfr, full)
+    assert int(tracks.status[0].item()) == 0
+    sector = full.sector.clone()
+    sector[0] = -1
+    leg, lchi = reco.merge(dataclasses.replace(full, sector=sector), tracks, 30.0)[5:7]
+    tracks.status[0] = 1
+    ref, rchi = reco.merge(full, tracks, 30.0)[5:7]
+    assert (ref[:T] >= 0).any()
+    assert torch.equal(leg[1:T], ref[1:T]) and torch.equal(lchi[1:T], rchi[1:T])
+    assert int(leg[0].item()) == -1

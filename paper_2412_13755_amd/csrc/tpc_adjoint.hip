@@ -244,7 +244,7 @@ hipError_t launch_adjoint(const tpc_context *ctx, const tpc_frames *fr, const tp
     const tpc_config &c = ctx->cfg;
     const int64_t n_fs = (int64_t)fr->n_frames * c.n_sectors;
     AdjArgs A;
-    A.F = make_fit_args(ctx, fr, sd, map);
+    A.F = make_fit_args(ctx, sd, map);
     A.status = tr->status;
     A.ckpt = ckpt;
     float2 *partial;

@@ -153,8 +153,7 @@ void launch_fit_order(FitArgs &A, const FitOrderWs &ord, hipStream_t st) {
     A.n_order = ord.n;
 }
 
-FitArgs make_fit_args(const tpc_context *ctx, const tpc_frames *fr, const tpc_seeds *sd,
-                      const float *map) {
+FitArgs make_fit_args(const tpc_context *ctx, const tpc_seeds *sd, const float *map) {
     const tpc_config &c = ctx->cfg;
     FitArgs A;
     A.offsets = sd->offsets;
@@ -164,13 +163,10 @@ FitArgs make_fit_args(const tpc_context *ctx, const tpc_frames *fr, const tpc_se
     A.n_seeds = sd->n_seeds;
     A.cap_seeds = sd->cap_seeds;
     A.cap_hits = sd->cap_hits;
-    A.y = fr->y;
-    A.z = fr->z;
     A.row_x = ctx->d_row_x;
     A.map = map;
     A.n_rows = c.n_rows;
     A.n_sectors = c.n_sectors;
-    A.n_clusters = fr->n_clusters;
     A.kbz = -TPC_C_LIGHT * c.bz;
     A.vy = (double)c.sigma_y * (double)c.sigma_y;
     A.vz = (double)c.sigma_z * (double)c.sigma_z;
@@ -198,7 +194,7 @@ hipError_t launch_gather(const tpc_frames *fr, const tpc_seeds *sd, float2 *hyz,
 
 hipError_t launch_fit(const tpc_context *ctx, const tpc_frames *fr, const tpc_seeds *sd,
                       const float *map, const tpc_tracks *tr, double *ckpt, void *ws, hipStream_t st) {
-    FitArgs A = make_fit_args(ctx, fr, sd, map);
+    FitArgs A = make_fit_args(ctx, sd, map);
     A.out = *tr;
     A.ckpt = ckpt;
     float2 *hyz;
@@ -236,7 +232,7 @@ hipError_t launch_fit_args(const FitArgs &A, hipStream_t st, int block, int spt)
 
 hipError_t launch_fit_shaped(const tpc_context *ctx, const tpc_frames *fr, const tpc_seeds *sd,
                              const tpc_tracks *tr, void *ws, int block, int spt, hipStream_t st) {
-    FitArgs A = make_fit_args(ctx, fr, sd, nullptr);
+    FitArgs A = make_fit_args(ctx, sd, nullptr);
     A.out = *tr;
     A.ckpt = nullptr;
     float2 *hyz;

@@ -9,9 +9,9 @@
 struct FitArgs {
     const int32_t *offsets, *hits, *sector, *first_row, *n_seeds;
     int32_t cap_seeds, cap_hits;
-    const float *y, *z, *row_x, *map;
-    const float2 *hyz;     // (y, z) of every seed hit in seed-hit order, or null
-    int32_t n_rows, n_sectors, n_clusters;
+    const float *row_x, *map;
+    const float2 *hyz;     // (y, z) of every seed hit in seed-hit order (set by every launch of a fit)
+    int32_t n_rows, n_sectors;
     float kbz, max_sin;
     double vy, vz, var_s, var_t, var_w;
     double *ckpt;
@@ -43,15 +43,6 @@ __host__ __device__ inline SeedView seed_view(const FitArgs &A, int i) {
     return v;
 }
 
-// Raw (y, z) of hit k of the seed (global id `id`): from the seed-ordered
-// copy when there is one (contiguous per seed, no id indirection).
-__host__ __device__ inline float2 hit_raw(const FitArgs &A, const SeedView &v, int k, int32_t id) {
-    if (A.hyz) return A.hyz[v.o0 + k];
-    const uint32_t NC = (uint32_t)A.n_clusters;
-    const int32_t j = (uint32_t)id < NC ? id : 0;
-    return make_float2(A.y[j], A.z[j]);
-}
-
 // Corrected measurement of hit k in double precision (MAP: with a map).
 template <bool MAP = true>
 __host__ __device__ inline void hit_fix(const SeedView &v, int k, float2 raw, double &my, double &mz) {
@@ -63,17 +54,16 @@ __host__ __device__ inline void hit_fix(const SeedView &v, int k, float2 raw, do
     }
 }
 
-__host__ __device__ inline void hit_meas(const FitArgs &A, const SeedView &v, int k, int32_t id, double &my,
-                                         double &mz) {
-    hit_fix(v, k, hit_raw(A, v, k, id), my, mz);
+__host__ __device__ inline void hit_meas(const FitArgs &A, const SeedView &v, int k, double &my, double &mz) {
+    hit_fix(v, k, A.hyz[v.o0 + k], my, mz);
 }
 
 __host__ __device__ inline bool start_state(const FitArgs &A, const SeedView &v, const float *xs, double p[5]) {
     const int ka = v.n - 1, kb = (v.n - 1) / 2;
     double ya, za, yb, zb, yc, zc;
-    hit_meas(A, v, ka, A.hyz ? 0 : v.hh[ka], ya, za);
-    hit_meas(A, v, kb, A.hyz ? 0 : v.hh[kb], yb, zb);
-    hit_meas(A, v, 0, A.hyz ? 0 : v.hh[0], yc, zc);
+    hit_meas(A, v, ka, ya, za);
+    hit_meas(A, v, kb, yb, zb);
+    hit_meas(A, v, 0, yc, zc);
     (void)zb;
     return helix_start<double>(xs[v.row0 + ka], ya, za, xs[v.row0 + kb], yb, xs[v.row0], yc, zc,
                                A.kbz, A.max_sin, p);
@@ -102,7 +92,7 @@ __host__ __device__ inline void read_ckpt(const double *ck, double p[5], SymT<do
 }
 
 // Forward fit of seed i (one thread's work); xs = row table, readable one
-// entry below its start.  A.hyz is set.  CKPT: filter states to A.ckpt.
+// entry below its start.  CKPT: filter states to A.ckpt.
 //
 // Bound by instructions: a wavefront alone on its SIMD issues one about
 // every five clocks whatever it is, so the loop carries no test that a
@@ -220,7 +210,7 @@ __host__ __device__ inline int adj_tape_states(int K) { return (K + TPC_ADJ_SUB 
 // step than with every state taped, and a third of the memory traffic, which
 // was what the time went to (2.9 GB for 645 000 seeds; 1035 -> 735 us).
 // (Everything is addressed by 32-bit indices from bases in scalar registers:
-// the step adjoint needs nearly all of the vector ones.  F.hyz is set.)
+// the step adjoint needs nearly all of the vector ones.)
 __device__ inline void adj_one(const FitArgs &F, const int32_t *status, const double *ckpt, float2 *gbuf, int i,
                                double *tp, int lane, double *lt, int lstride) {
     const int K = F.ckpt_rows;
@@ -319,8 +309,7 @@ __device__ inline void adj_one(const FitArgs &F, const int32_t *status, const do
     g[0] = make_float2(gc.x + (float)byc, gc.y + (float)bzc);
 }
 
-FitArgs make_fit_args(const tpc_context *ctx, const tpc_frames *fr, const tpc_seeds *sd,
-                      const float *map);
+FitArgs make_fit_args(const tpc_context *ctx, const tpc_seeds *sd, const float *map);
 // The length order of the seeds into ord (workspace); sets A.order.
 void launch_fit_order(FitArgs &A, const FitOrderWs &ord, hipStream_t st);
 hipError_t launch_fit_args(const FitArgs &A, hipStream_t st, int block = 0, int spt = 0);

@@ -252,9 +252,9 @@ __device__ inline void fit_ms_one(const MsArgs &A, int i, const float *xs, RowLd
     } else {
         const int ka = sv.n - 1, kb = (sv.n - 1) / 2;
         double ya, za, yb, zb, yc, zc;
-        hit_meas(F, sv, ka, F.hyz ? 0 : sv.hh[ka], ya, za);
-        hit_meas(F, sv, kb, F.hyz ? 0 : sv.hh[kb], yb, zb);
-        hit_meas(F, sv, 0, F.hyz ? 0 : sv.hh[0], yc, zc);
+        hit_meas(F, sv, ka, ya, za);
+        hit_meas(F, sv, kb, yb, zb);
+        hit_meas(F, sv, 0, yc, zc);
         (void)zb;
         if (!helix_start<double, double>((double)xs[ra], ya, za, (double)xs[rb], yb, (double)xs[rc], yc, zc,
                                          A.kbz, F.max_sin, p))
@@ -440,14 +440,6 @@ __device__ inline void sym_dense(const SymT<double> &C, double M[5][5]) {
     int q = 0;
     for (int r = 0; r < 5; ++r)
         for (int c = 0; c <= r; ++c, ++q) M[r][c] = M[c][r] = v[q];
-}
-
-__device__ inline SymT<double> sym_packed(const double M[5][5]) {
-    SymT<double> C;
-    C.c00 = M[0][0]; C.c10 = M[1][0]; C.c11 = M[1][1]; C.c20 = M[2][0]; C.c21 = M[2][1];
-    C.c22 = M[2][2]; C.c30 = M[3][0]; C.c31 = M[3][1]; C.c32 = M[3][2]; C.c33 = M[3][3];
-    C.c40 = M[4][0]; C.c41 = M[4][1]; C.c42 = M[4][2]; C.c43 = M[4][3]; C.c44 = M[4][4];
-    return C;
 }
 
 // d <- F d for the step Jacobian (identity plus the six off-diagonal terms).
@@ -743,7 +735,7 @@ __global__ void __launch_bounds__(MS_T) smooth_tracks(SmArgs S) {
 MsArgs make_ms_args(const tpc_context *ctx, const tpc_frames *fr, const tpc_seeds *sd, const float *err,
                     const tpc_material *mat, const tpc_tracks *tr, uint8_t *rejected, void *ws, hipStream_t st) {
     MsArgs A;
-    A.F = make_fit_args(ctx, fr, sd, nullptr);
+    A.F = make_fit_args(ctx, sd, nullptr);
     A.F.out = *tr;
     float2 *hyz, *herr;
     fit_ws_layout(ws, sd->cap_seeds, sd->cap_hits, nullptr, &hyz, nullptr, &herr);

@@ -40,8 +40,8 @@ struct FlArgs {
     int32_t n_frames;
     FlIndex X;
     int32_t *rows;                // [cap_seeds][n_rows] cluster per pad row, -1 for none
-    const int32_t *order;         // seeds longest first within each window of FL_WINDOW ...
-    int64_t cap_order;            // ... if there are at most so many (else in their own order)
+    const int32_t *order;         // the seeds' order (fl_order) ...
+    int64_t cap_order;            // ... if there are at most so many (else their own)
     double kbz;                   // -c Bz in double precision
     double gate;
     int32_t max_miss;
@@ -661,7 +661,7 @@ hipError_t launch_follow(const tpc_context *ctx, const tpc_frames *fr, const tpc
     const tpc_config &c = ctx->cfg;
     const int64_t NR = (int64_t)fr->n_frames * c.n_sectors * c.n_rows;
     FlArgs A;
-    A.F = make_fit_args(ctx, fr, sd, nullptr);
+    A.F = make_fit_args(ctx, sd, nullptr);
     A.F.out = *tr;
     A.row_offsets = fr->row_offsets;
     A.frame = sd->frame;

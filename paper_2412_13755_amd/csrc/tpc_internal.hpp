@@ -276,13 +276,6 @@ __device__ inline void order_desc(int n, Key key, int32_t *order, int *start, in
     for (int i = tid; i < n; i += TPC_BLOCK) order[atomicAdd(&start[key(i)], 1)] = i;
 }
 
-// Size key of segment s for order_desc: 1 + its clusters / 128 (capped),
-// 0 if empty.
-__device__ inline int seg_size_key(const int32_t *off, int s) {
-    const int b = (off[s + 1] - off[s]) >> 7;
-    return off[s + 1] == off[s] ? 0 : 1 + (b < TPC_ORDER_BINS - 1 ? b : TPC_ORDER_BINS - 1);
-}
-
 // Minimum over the wavefront, valid in its last lane: six cross-lane operands
 // (DPP) and no LDS round trips.  (row_shr 1, 2, 4, 8 within each row of 16
 // lanes, then row_bcast 15 into rows 1 and 3 and row_bcast 31 into 2 and 3.)

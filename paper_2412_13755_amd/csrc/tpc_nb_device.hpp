@@ -324,17 +324,14 @@ __device__ inline bool better(float q, int32_t u, int32_t d, const Best &b) {
 // paired with that list.  If more down clusters are in the window, each up
 // candidate instead scans the down-row cells that overlap the cut interval
 // around its straight-line prediction c = h - (A / B)(u - h), of half-width
-// A (A + B) / 2 cut.  Without LIST (rows dense enough that the list would
-// overflow anyway) the per-up-candidate scan is used directly; the pairs
-// visited, and so the result, are the same.  Cells scanned are those
-// overlapping the window (or
+// A (A + B) / 2 cut.  Cells scanned are those overlapping the window (or
 // cut) interval widened by a margin m far above the rounding of the
 // predicates and of c; as cell_coord is monotonic, every cluster that can
 // pass the exact predicates is visited.  A cluster h with a non-finite
 // coordinate fails every window, so it is skipped.
 #define TPC_NB_DLIST 8
 
-template <int A = 1, int B = 1, bool LIST = true, class FP, class IP, class CP>
+template <int A = 1, int B = 1, class FP, class IP, class CP>
 __device__ __forceinline__ Best best_pair(float yh, float zh, FP UY, FP UZ, IP UI, CP UCS, const SegGrid &gu,
                                  int32_t ubase, FP DY, FP DZ, IP DI, CP DCS, const SegGrid &gd,
                                  int32_t dbase, float win_y, float win_z, float cut_y, float cut_z) {
@@ -358,7 +355,7 @@ __device__ __forceinline__ Best best_pair(float yh, float zh, FP UY, FP UZ, IP U
 #pragma unroll
     for (int j = 0; j < TPC_NB_DLIST; ++j) { lb[j][0] = 0.f; lb[j][1] = 0.f; ld[j] = -1; }
     int nd = 0;
-    if constexpr (LIST) {
+    {
         const int y0 = cell_coord(yh - wdy, gd.y0, gd.iwy, gd.ny), y1 = cell_coord(yh + wdy, gd.y0, gd.iwy, gd.ny);
         const int z0 = cell_coord(zh - wdz, gd.z0, gd.iwz, gd.nz), z1 = cell_coord(zh + wdz, gd.z0, gd.iwz, gd.nz);
         for (int iy = y0; iy <= y1; ++iy) {
@@ -377,8 +374,8 @@ __device__ __forceinline__ Best best_pair(float yh, float zh, FP UY, FP UZ, IP U
             }
         }
     }
-    if (LIST && nd == 0) return best;
-    const bool listed = LIST && nd <= TPC_NB_DLIST;
+    if (nd == 0) return best;
+    const bool listed = nd <= TPC_NB_DLIST;
     const int yu0 = cell_coord(yh - wuy, gu.y0, gu.iwy, gu.ny), yu1 = cell_coord(yh + wuy, gu.y0, gu.iwy, gu.ny);
     const int zu0 = cell_coord(zh - wuz, gu.z0, gu.iwz, gu.nz), zu1 = cell_coord(zh + wuz, gu.z0, gu.iwz, gu.nz);
     for (int iyu = yu0; iyu <= yu1; ++iyu) {

@@ -396,7 +396,7 @@ hipError_t launch_persistent(const tpc_context *ctx, const tpc_frames *fr, int32
     P.dn = dn;
     P.sd = *sd;
     P.dev_status = dev_status;
-    P.F = make_fit_args(ctx, fr, sd, nullptr);
+    P.F = make_fit_args(ctx, sd, nullptr);
     P.F.out = *tr;
     P.sort_fit = sort_fit;
     persist_ws_layout(ws, fr->n_clusters, P.NR, sd->cap_seeds, sd->cap_hits, &P);

@@ -699,6 +699,7 @@ struct RdArgs {
 #define RD_SLOT_LDS (1 << 14)
 #define RD_SYM_LDS (1 << 13)
 #define RD_T 1024              // threads of a decoding workgroup
+#define RD_SPREAD 2048         // blocks that workgroups of consecutive ones put on 128 CUs
 #define RD_CHUNK 128           // words a wavefront loads at once (4 bytes per lane)
 __device__ inline bool rd_in_lds(int64_t L, int64_t R) { return (1ll << L) <= RD_SLOT_LDS && R <= RD_SYM_LDS; }
 
@@ -945,15 +946,20 @@ __global__ void __launch_bounds__(RD_T, 8) rd_decode(RdArgs A) {
     const bool lds = rd_in_lds(L, R);
     const int lane = threadIdx.x & (TPC_WAVE - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / TPC_WAVE);
-    const int64_t b0 = (int64_t)blockIdx.x * (RD_T / TPC_WAVE);
+    // Consecutive blocks in a workgroup, whose words and table entries then
+    // share caches; in turn over the workgroups where that would leave half
+    // of the CUs or more without one (512 blocks of 2^15, L = 16: 455 -> 256
+    // us; L = 14 208 -> 166; 4 blocks 145, 159 in turn, 16 384 of 2^10 145, 152).
+    constexpr int W = RD_T / TPC_WAVE;
+    const bool spread = nb > W && nb <= RD_SPREAD;
+    const int64_t b0 = spread ? blockIdx.x : (int64_t)blockIdx.x * W, per = spread ? gridDim.x : 1;
     if (b0 >= nb) return;
     if (lds) {
         for (int k = threadIdx.x; k < (1 << L); k += RD_T) S.slot_sym[k] = A.slot_sym[k];
         for (int k = threadIdx.x; k < R; k += RD_T) S.sym_fc[k] = A.sym_fc[k];
         __syncthreads();
     }
-    const int64_t W = (int64_t)gridDim.x * (RD_T / TPC_WAVE);
-    for (int64_t b = b0 + wid; b < nb; b += W) {
+    for (int64_t b = b0 + wid * per; b < nb; b += (int64_t)gridDim.x * W) {
         const bool ok = lds ? decode_block<true>(A, S, S.ring[wid], b, lane)
                             : decode_block<false>(A, S, S.ring[wid], b, lane);
         if (!ok && lane == 0) *A.dev_status = TPC_ERR_ARG;

@@ -15,4 +15,21 @@ pytestmark = pytest.mark.gpu
 def test_blocks(blocks, L):
     rng = np.random.default_rng(blocks + L)
     n = 64 * blocks - (13 if blocks % 2 else 0)
-    check_stream(rng.normal(0, 9.0, n).round().astype(np.int32), L, 64, "%d blocks" % blocks)
+    x = rng.normal(0, 9.0, n).round().astype(np.int32)
+    check_stream(x, L, 64, "%d blocks" % blocks)
+    import torch
+    from paper_2412_13755_amd.reco import rans_encode, rans_decode
+    out, size, status = rans_encode(torch.from_numpy(x).cuda(), L, 64)
+    assert int(status.item()) == 0
+    k = int(size.item())
+    y, count, status = rans_decode(out[:k].clone(), k, n)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0 and int(count.item()) == n
+    assert np.array_equal(y[:n].cpu().numpy(), x)
+    # a word more than the blocks use is found out
+    words = torch.zeros(k // 4 + 2, dtype=torch.int32, device="cuda:0")
+    bad = words.view(torch.uint8)
+    bad[:k] = out[:k]
+    words[10 + (int(words[9].item()) + 3) // 4 + blocks] += 1       # the last block's end
+    _, _, status = rans_decode(bad, k + 2, n)
+    assert int(status.item()) == -1

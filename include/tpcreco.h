@@ -193,7 +193,7 @@ tpc_status tpc_ca_seed(const tpc_context *ctx, const tpc_frames *frames,
  * tpc_create).  Arguments, results and device status as tpc_ca_seed; no
  * workspace argument.  Frames whose seeding workspace
  * (tpc_workspace_bytes with TPC_STAGE_SEED) exceeds the array are refused
- * with TPC_ERR_WORKSPACE before anything is enqueued (128 MiB: about 2.7 M
+ * with TPC_ERR_WORKSPACE before anything is enqueued (128 MiB: about 3.0 M
  * clusters over 36 x 152 segments).  The current device must be the
  * context's.  Every call on a device uses that device's one array, whose
  * contents persist between calls (the kernels initialise every word they

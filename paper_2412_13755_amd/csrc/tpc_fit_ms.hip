@@ -17,10 +17,12 @@
 //                 cluster layout of the seed's (frame, sector) -- a binary
 //                 search for the outermost hit, then a walk down from the
 //                 row above for each next one (at most R + n reads of the
-//                 row offsets per seed, all within the seed's R + 1) -- and
-//                 a seed whose rows do not rise strictly, or with a hit
-//                 outside its (frame, sector), is refused before the fit;
-//                 during the fit each next row is resolved a step ahead.
+//                 row offsets per seed, all within the seed's R + 1, from
+//                 LDS where the wavefront's seeds lie in two neighbouring
+//                 (frame, sector)s) -- and a seed whose rows do not rise
+//                 strictly, or with a hit outside its (frame, sector), is
+//                 refused before the fit; the fit reads the rows found from
+//                 a strip in LDS.
 //                 ERRS: hit h is measured with variances err[h]^2.
 //  smooth_tracks  thread per seed, after the fit over rows: the state at
 //                 every hit's plane from all hits.  The reference starts
@@ -32,11 +34,11 @@
 //                 taken on the reference, diffuse start, the hits the fit
 //                 used; rows as the fit stored them), storing per hit the
 //                 filtered deviation, its covariance, the reference and the
-//                 step that arrived there (Jacobian, noise, energy-loss
-//                 factors; 38 doubles, 16-byte stores); then the
+//                 step that leaves its plane inwards (Jacobian, noise,
+//                 energy-loss factors; 38 doubles, 16-byte stores); then the
 //                 Rauch-Tung-Striebel pass outwards reads them back (no
 //                 step is taken again) and solves with P = F (C + Q) F^T
-//                 by a Cholesky factorisation.
+//                 by its L D L^T.
 #include "tpc_fit_common.hpp"
 #include "tpc_fit_ms.hpp"
 

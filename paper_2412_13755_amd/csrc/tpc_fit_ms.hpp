@@ -16,7 +16,7 @@ hipError_t launch_fit_rows(const tpc_context *ctx, const tpc_frames *fr, const t
 // The fit over rows, then the smoother: the state at every seed hit's plane
 // (hit_par [cap_hits][5], hit_cov [cap_hits][15]); rejected is required.
 // Workspace: smooth_ws_layout bytes (the fit's, then per-seed final states,
-// per-hit filtered deviations and rows).
+// per-hit records of the smoother and rows).
 struct SmWs {
     double *pfin;      // [cap_seeds][5] final states of the fit
     double *wd;        // [cap_hits][38] filtered deviation, covariance, reference, leaving step

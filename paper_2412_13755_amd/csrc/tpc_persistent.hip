@@ -18,8 +18,8 @@
 // copy and the dense h-rows go to two work lists, so that those phases hand
 // out only segments with work; tops and members, whose work is per cluster,
 // stride over the clusters instead of the segments)
-// The fit is not a phase: its ~230 registers per lane would cap the
-// occupancy of every phase at two wavefronts per SIMD.  It runs next, over
+// The fit is not a phase: its 136 registers per lane would cap the
+// occupancy of every phase at three wavefronts per SIMD.  It runs next, over
 // the seeds longest first (with sort_fit), so the lanes of a wavefront carry
 // seeds of similar length (the loop length is the seed length).
 #include "tpc_ca_device.hpp"
